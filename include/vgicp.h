@@ -101,12 +101,13 @@ typedef struct {
     int32_t block_threads;      /* 64, 128, 256 or 512 threads per workgroup; 0 = default */
     int32_t tile_points;        /* source points per work tile, a multiple of 64 up to 32768;
                                    0 = default */
-    int32_t blocks_per_cu;      /* persistent workgroups per compute unit; 0 = default */
+    int32_t blocks_per_cu;      /* checked (0..64) and kept, without effect: every tile is a
+                                   workgroup of its own; 0 = default */
     int32_t lane_kahan;         /* VG_FP32_COMPENSATED only: 1 = Kahan-compensated FP32 sums
                                    inside each lane (sums above a lane are FP64 either way) */
     const char* tune_cache;     /* NULL: no autotuning.  Otherwise a file path: tuned shapes
                                    are read from it, or measured and appended to it */
-    int32_t tile_order;         /* order in which the persistent grid takes tiles: 0 default
+    int32_t tile_order;         /* order in which the tiles' workgroups are dispatched: 0 default
                                    (1), 1 = eight contiguous ranges, one per XCD, 2 = tiles
                                    dealt round-robin to the eight XCDs (all XCDs work in
                                    the same window of factors); results are identical */
@@ -218,7 +219,7 @@ vg_status vg_create_factor_batch(vg_context* ctx, int64_t F, vg_source* const* s
                                  vg_voxelmap* const* tgt, const double* target_viewpoints,
                                  const vg_batch_options* opts, vg_batch** out);
 /* Shape of a batch: total source points, number of work tiles, and the launch
- * shape in use (block threads, tile points, persistent workgroups, tile order).
+ * shape in use (block threads, tile points, workgroups of a launch, tile order).
  * Any output may be NULL. */
 vg_status vg_batch_info(const vg_batch* batch, int64_t* total_points, int64_t* n_tiles,
                         int32_t* block_threads, int32_t* tile_points, int32_t* grid_blocks,
@@ -254,8 +255,8 @@ vg_status vg_evaluate_async(vg_batch* batch, const double* d_poses, double* d_e)
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): the same
  * computation and results as vg_linearize_async, bit for bit, with no
- * allocation, free or allocating library call.  The kernels' scratch (tile
- * counters, staged FP32 poses, one partial row of 40 doubles per tile) lives in
+ * allocation, free or allocating library call.  The kernels' scratch (staged
+ * FP32 poses, one partial row of 40 doubles per tile) lives in
  * a fixed 32 MiB device array, one per device, held until the process ends; a
  * batch needing more (roughly 256 B + 64 B per factor + 320 B per tile, i.e.
  * about 100,000 tiles) fails with VG_ERR_CAPACITY.  Every call on a device
@@ -319,7 +320,7 @@ vg_status vg_lm_step_async(vg_batch* batch, double* d_poses, double* d_lambda, d
 vg_status vg_batch_work(vg_batch* batch, int64_t* walked_points, int64_t* walked_chunks, int64_t* lookups);
 
 /* Autotune the launch shape of a batch at representative poses (host F x 12):
- * every candidate (block threads x tile points x workgroups per CU) is timed
+ * every candidate (block threads x tile points x tile order) is timed
  * with HIP events over `reps` launches of the tile kernel and reduction; the
  * fastest is kept for this batch (candidates are visited in a fixed order of
  * preference and a later one wins only when faster by more than 1.5 %, so the

@@ -16,7 +16,7 @@
 #include "vg_timeline.h"
 
 // Device scratch of the allocation-free linearization (vg_linearize_noalloc):
-// tile counters, staged FP32 poses and tile partial rows.  Every device the
+// staged FP32 poses and tile partial rows.  Every device the
 // library runs on holds its own copy until the process ends; host code reaches
 // it only through the per-device address taken with hipGetSymbolAddress.
 static constexpr size_t kScratchBytes = (size_t)32 << 20;
@@ -693,8 +693,6 @@ vg_status upload_schedule(vg_batch* b) {
     if (nt) VG_HIP(hipMemcpyAsync(b->d_tiles, b->h_tiles.data(), sizeof(Tile) * nt, hipMemcpyHostToDevice, st));
     VG_HIP(hipMemcpyAsync(b->d_tile_first, b->h_tile_first.data(), sizeof(int32_t) * (b->F + 1),
                           hipMemcpyHostToDevice, st));
-    const int64_t want = (int64_t)b->ctx->num_cu * b->blocks_per_cu;
-    b->grid = (int)std::max<int64_t>(1, std::min<int64_t>(want, (int64_t)nt));
     VG_HIP(hipStreamSynchronize(st));
     free_graph(b);
     return VG_OK;
@@ -743,12 +741,12 @@ bool valid_shape(int block, int tile, int bpc) {
 }
 
 // The batch's own buffers for the tile kernel and reduction.
-Workspace batch_ws(vg_batch* b) { return Workspace{b->d_partials, b->d_counter, b->d_posef, b->d_work}; }
+Workspace batch_ws(vg_batch* b) { return Workspace{b->d_partials, b->d_posef, b->d_work}; }
 
 vg_status run_linearize_device(vg_batch* b, const Workspace& ws, const double* d_poses, double* d_out,
                                int64_t* d_inl) {
     const int32_t nt = (int32_t)b->h_tiles.size();
-    VG_TRY(launch_tiles(b, ws, kLin, d_poses, 0, nt, b->grid, nullptr, nullptr, 0, 0, b->F));
+    VG_TRY(launch_tiles(b, ws, kLin, d_poses, 0, nt, nullptr, nullptr, 0, 0, b->F));
     return launch_reduce(b, ws, kLin, d_poses, 0, (int32_t)b->F, d_out, d_inl, nullptr, nullptr, nullptr);
 }
 
@@ -759,7 +757,7 @@ vg_status run_linearize_device(vg_batch* b, const double* d_poses, double* d_out
 vg_status run_evaluate_device(vg_batch* b, const double* d_poses, double* d_e) {
     const int32_t nt = (int32_t)b->h_tiles.size();
     const Workspace ws = batch_ws(b);
-    VG_TRY(launch_tiles(b, ws, kEval, d_poses, 0, nt, b->grid, nullptr, nullptr, 0, 0, b->F));
+    VG_TRY(launch_tiles(b, ws, kEval, d_poses, 0, nt, nullptr, nullptr, 0, 0, b->F));
     return launch_reduce(b, ws, kEval, d_poses, 0, (int32_t)b->F, d_e, nullptr, nullptr, nullptr, nullptr);
 }
 
@@ -807,9 +805,8 @@ vg_status linearize_host(vg_batch* b) {
             VG_HIP(hipMemcpyAsync(b->d_poses + 12 * f, b->h_poses + 12 * f, sizeof(double) * 12,
                                   hipMemcpyHostToDevice, st));
             const int32_t t0 = b->h_tile_first[f], t1 = b->h_tile_first[f + 1];
-            const int grid = std::max(1, std::min(t1 - t0, b->grid));
             const Workspace ws = batch_ws(b);
-            VG_TRY(launch_tiles(b, ws, kLin, b->d_poses, t0, t1, grid, nullptr, nullptr, 0, f, f + 1));
+            VG_TRY(launch_tiles(b, ws, kLin, b->d_poses, t0, t1, nullptr, nullptr, 0, f, f + 1));
             VG_TRY(launch_reduce(b, ws, kLin, b->d_poses, (int32_t)f, (int32_t)f + 1, b->d_out, b->d_inliers,
                                  nullptr, nullptr, nullptr));
             VG_HIP(hipMemcpyAsync(b->h_out + kOutRow * f, b->d_out + kOutRow * f, sizeof(double) * kOutRow,
@@ -840,7 +837,6 @@ void free_batch(vg_batch* b) {
     dfree(b->d_tiles);
     dfree(b->d_tile_first);
     dfree(b->d_partials);
-    dfree(b->d_counter);
     dfree(b->d_poses);
     dfree(b->d_posef);
     dfree(b->d_out);
@@ -977,7 +973,6 @@ extern "C" vg_status vg_create_factor_batch(vg_context* ctx, int64_t F, vg_sourc
     vg_status st = VG_OK;
     do {
         if ((st = dev_alloc(&b->d_fac, F)) != VG_OK) break;
-        if ((st = dev_alloc(&b->d_counter, 64)) != VG_OK) break;
         if ((st = dev_alloc(&b->d_poses, 12 * F)) != VG_OK) break;
         if ((st = dev_alloc(&b->d_posef, 16 * F)) != VG_OK) break;
         if ((st = dev_alloc(&b->d_out, kOutRow * F)) != VG_OK) break;
@@ -1007,7 +1002,6 @@ extern "C" vg_status vg_create_factor_batch(vg_context* ctx, int64_t F, vg_sourc
             st = hip_fail(e, "factor table upload");
             break;
         }
-        if ((st = launch_zero(ctx, b->d_counter, 64 * sizeof(uint32_t))) != VG_OK) break;
         if ((st = launch_zero(ctx, b->d_work, sizeof(int64_t) * kWork * F)) != VG_OK) break;
         st = upload_schedule(b);
     } while (0);
@@ -1034,7 +1028,7 @@ extern "C" vg_status vg_batch_info(const vg_batch* b, int64_t* total_points, int
     if (n_tiles) *n_tiles = (int64_t)b->h_tiles.size();
     if (block_threads) *block_threads = b->block;
     if (tile_points) *tile_points = b->tile_points;
-    if (grid_blocks) *grid_blocks = b->grid;
+    if (grid_blocks) *grid_blocks = kParts * (int32_t)((b->h_tiles.size() + kParts - 1) / kParts);
     if (tile_order) *tile_order = b->tile_order;
     return VG_OK;
 }
@@ -1104,7 +1098,7 @@ extern "C" vg_status vg_overlap(vg_batch* b, const double* poses, double* overla
     VG_HIP(hipMemcpyAsync(b->d_poses, b->h_poses, sizeof(double) * 12 * b->F, hipMemcpyHostToDevice, st));
     const int32_t nt = (int32_t)b->h_tiles.size();
     const Workspace ws = batch_ws(b);
-    VG_TRY(launch_tiles(b, ws, kCount, b->d_poses, 0, nt, b->grid, nullptr, nullptr, 0, 0, b->F));
+    VG_TRY(launch_tiles(b, ws, kCount, b->d_poses, 0, nt, nullptr, nullptr, 0, 0, b->F));
     // the per-level fractions land in d_out (F x L <= F x 43)
     VG_TRY(launch_reduce(b, ws, kCount, b->d_poses, 0, (int32_t)b->F, b->d_out, nullptr, nullptr, nullptr, nullptr));
     VG_HIP(hipMemcpyAsync(b->h_out, b->d_out, sizeof(double) * b->L * b->F, hipMemcpyDeviceToHost, st));
@@ -1134,7 +1128,7 @@ extern "C" vg_status vg_linearize_noalloc(vg_batch* b, const double* d_poses, do
                   (dev < kMaxDevices ? hipGetErrorString(g_scratch_err[dev]) : "device index beyond the table"));
         return VG_ERR_HIP;
     }
-    // layout: counters (256 B), staged poses (F x 16 floats), tile rows (tiles x kRow doubles)
+    // layout: 256 B unused, staged poses (F x 16 floats), tile rows (tiles x kRow doubles)
     auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
     const size_t n_tiles = b->h_tiles.size();
     const size_t off_posef = 256;
@@ -1149,10 +1143,7 @@ extern "C" vg_status vg_linearize_noalloc(vg_batch* b, const double* d_poses, do
         return VG_ERR_CAPACITY;
     }
     unsigned char* base = static_cast<unsigned char*>(b->ctx->scratch);
-    const Workspace ws{reinterpret_cast<double*>(base + off_rows), reinterpret_cast<uint32_t*>(base),
-                       reinterpret_cast<float*>(base + off_posef), nullptr};
-    // the tile counters must start at zero; another call may have left them anywhere
-    VG_TRY(launch_zero(b->ctx, ws.counter, sizeof(uint32_t) * kParts));
+    const Workspace ws{reinterpret_cast<double*>(base + off_rows), reinterpret_cast<float*>(base + off_posef), nullptr};
     return run_linearize_device(b, ws, d_poses, d_out, d_inliers);
 }
 
@@ -1199,7 +1190,7 @@ extern "C" vg_status vg_backward_async(vg_batch* b, const double* d_poses, const
     }
     const int32_t nt = (int32_t)b->h_tiles.size();
     const Workspace ws = batch_ws(b);
-    VG_TRY(launch_tiles(b, ws, kBwd, d_poses, 0, nt, b->grid, d_grad_e, d_grad_points, points_dtype, 0, b->F));
+    VG_TRY(launch_tiles(b, ws, kBwd, d_poses, 0, nt, d_grad_e, d_grad_points, points_dtype, 0, b->F));
     VG_TRY(launch_grad_combine(b, d_grad_points, points_dtype));
     return launch_reduce(b, ws, kBwd, d_poses, 0, (int32_t)b->F, nullptr, nullptr, d_grad_e, d_jr, d_grad_xi);
 }
@@ -1362,7 +1353,7 @@ vg_status time_device(vg_batch* b, int reps, float* ms_tiles, float* ms_reduce) 
     vg_status rc = run_linearize_device(b, b->d_poses, b->d_out, b->d_inliers);   // warm-up
     for (int r = 0; r < reps && rc == VG_OK; ++r) {
         (void)hipEventRecord(ev[3 * r], st);
-        rc = launch_tiles(b, batch_ws(b), kLin, b->d_poses, 0, nt, b->grid, nullptr, nullptr, 0, 0, b->F);
+        rc = launch_tiles(b, batch_ws(b), kLin, b->d_poses, 0, nt, nullptr, nullptr, 0, 0, b->F);
         (void)hipEventRecord(ev[3 * r + 1], st);
         if (rc == VG_OK)
             rc = launch_reduce(b, batch_ws(b), kLin, b->d_poses, 0, (int32_t)b->F, b->d_out, b->d_inliers, nullptr,
@@ -1481,11 +1472,10 @@ extern "C" vg_status vg_batch_tune(vg_batch* b, const double* poses, int32_t rep
     // candidates in order of preference: a later candidate replaces an earlier one
     // only when it is faster by more than 1.5 %, so timing noise does not flip the choice
     const int orders[] = {1, 2};
-    // preference order: larger tiles first (fewer partial rows to reduce, fewer
-    // counter atomics); a later shape replaces the incumbent only if 1.5 % faster
+    // preference order: larger tiles first (fewer partial rows to reduce); a later
+    // shape replaces the incumbent only if 1.5 % faster
     const int tiles[] = {16384, 8192, 32768, 4096, 2048, 1024, 512, 256};
     const int blocks[] = {256, 128, 512};
-    const int occ[] = {2, 1, 4};   // multiples of the full-occupancy workgroup count
     struct Cand {
         int tp, bl, bc, to;
         float ms;
@@ -1500,8 +1490,6 @@ extern "C" vg_status vg_batch_tune(vg_batch* b, const double* poses, int32_t rep
         b->tile_order = c.to;
         b->block = c.bl;
         b->blocks_per_cu = c.bc;
-        b->grid = (int)std::max<int64_t>(
-            1, std::min<int64_t>((int64_t)b->ctx->num_cu * b->blocks_per_cu, (int64_t)b->h_tiles.size()));
         return VG_OK;
     };
     for (int tp : tiles) {
@@ -1509,15 +1497,14 @@ extern "C" vg_status vg_batch_tune(vg_batch* b, const double* poses, int32_t rep
         // a batch that fills the device with 1024-point tiles skips them
         if (tp < 1024 && b->total_points / tp > (int64_t)(1 << 20)) continue;
         for (int to : orders)
-            for (int bl : blocks)
-                for (int oc : occ) {
-                    Cand c{tp, bl, std::max(1, oc * 1024 / bl), to, 0.f};
-                    VG_TRY(apply(c));
-                    float t1 = 0.f, t2 = 0.f;
-                    VG_TRY(time_device(b, reps, &t1, &t2));
-                    c.ms = t1 + t2;
-                    cands.push_back(c);
-                }
+            for (int bl : blocks) {
+                Cand c{tp, bl, default_blocks_per_cu(bl), to, 0.f};
+                VG_TRY(apply(c));
+                float t1 = 0.f, t2 = 0.f;
+                VG_TRY(time_device(b, reps, &t1, &t2));
+                c.ms = t1 + t2;
+                cands.push_back(c);
+            }
     }
     // the sweep's three fastest shapes are timed again, in three interleaved
     // rounds (so drifts of the clock hit all of them), and the choice is made

@@ -6,10 +6,10 @@
 // H = sum J^T W J, b = sum J^T W d.
 //
 // Work decomposition.  A batch is a flat list of tiles (factor, run of 64-point
-// chunks of its source).  A persistent grid pulls tiles from an atomic counter;
-// every tile writes one partial row (28 terms + inlier counts) in FP64 to its own
-// slot, and a second kernel sums each factor's rows in tile order, so results do
-// not depend on which workgroup ran which tile.
+// chunks of its source), one workgroup each; every tile writes one partial row
+// (28 terms + inlier counts) in FP64 to its own slot, and a second kernel sums
+// each factor's rows in tile order, so results do not depend on which workgroup
+// ran which tile.
 //
 // Frames.  The terms are accumulated in the target orientation: with
 // z = R (mu - o_s) the per-point Jacobian is J = [(z)x, -I] Bd G where
@@ -629,6 +629,24 @@ __global__ void k_grad_combine(const SharedSrc* __restrict__ ss, int32_t S, int6
     }
 }
 
+// The work item of this workgroup, of n (n or more: none; the grid is n rounded
+// up to whole rounds of kParts).  Workgroups are dispatched round-robin over the
+// XCDs, so workgroup b runs on XCD b % kParts: the items are dealt to the XCDs in
+// contiguous ranges (each XCD's L2 then serves a narrow window of factors, which
+// share sources and targets) or round-robin (all XCDs in one window, so the
+// last-level cache holds a single working set).  The hardware hands out the
+// workgroups.  A persistent grid that took its tiles from eight counters cost
+// about 12 ns per atomic, serialised across the XCDs on the counters' one cache
+// line, with one atomic per tile and eight more per workgroup to find every
+// partition empty: that was all of the kernel's time below ~8,192-point tiles
+// (575 submap factors, 81M points, 39,900 tiles of 2,048 points: 675 us with the
+// counters, 446 us without; 1,954 FP64 tiles: 237 us, 90 us).
+__device__ __forceinline__ int32_t work_item(int32_t n, int32_t interleave) {
+    const int32_t span = (n + kParts - 1) / kParts;
+    return interleave ? (int32_t)blockIdx.x
+                      : (int32_t)(blockIdx.x % kParts) * span + (int32_t)(blockIdx.x / kParts);
+}
+
 // Pose staging: FP32 copies of every factor's R and t (16 floats per factor),
 // read by the tile kernel through uniform (scalar) loads.
 __global__ void k_stage_poses(int64_t F, const double* __restrict__ poses, float* __restrict__ posef) {
@@ -646,8 +664,8 @@ template <int MODE, int PREC, int BLOCK, bool KH, bool VAL, int LM>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(waves_per_eu<PREC, KH>(), waves_per_eu_max<PREC, KH>()))) void k_tiles(
     const FactorDesc* __restrict__ fac, const Tile* __restrict__ tiles, int32_t t_begin, int32_t t_end,
     const double* __restrict__ poses, const float* __restrict__ posef, double* __restrict__ partials,
-    uint32_t* __restrict__ counter, const double* __restrict__ grad_e,
-    void* __restrict__ grad_points, void* __restrict__ grad_slab, int32_t points_dtype, int32_t interleave) {
+    const double* __restrict__ grad_e, void* __restrict__ grad_points, void* __restrict__ grad_slab,
+    int32_t points_dtype, int32_t interleave) {
     using T = typename PT<PREC>::T;
     constexpr bool validate = VAL;
     constexpr int NW = BLOCK / 64;
@@ -680,649 +698,603 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(waves_per
     using QueueT = typename std::conditional<CMP, HitQueue, int32_t>::type;
     __shared__ QueueT s_q[CMP ? NW : 1];
     __shared__ double s_red[NW][kRow];
-    __shared__ int32_t s_tile;
     const int lane = threadIdx.x & 63;
     // wave index as a uniform (scalar) value, so chunk indices and per-chunk LDS
     // addresses are computed once per wave, not per lane
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    // XCD-aware work distribution: the tiles are split into kParts partitions with
-    // one counter each; workgroups are dispatched round-robin over the XCDs, so
-    // workgroup b starts on partition b % kParts, i.e. on its XCD's partition.
-    // Contiguous partitions give each XCD's L2 a narrow window of factors (which
-    // share sources and targets); interleaved partitions (tile i in partition
-    // i % kParts) keep all XCDs in one window, so the last-level cache holds a
-    // single working set.  A workgroup whose partition is exhausted moves on to
-    // the next one.
-    const int32_t ntiles = t_end - t_begin;
-    const int32_t span = (ntiles + kParts - 1) / kParts;
-    int part = (int)(blockIdx.x % kParts);
-    int tried = 0;
+    const int32_t item = work_item(t_end - t_begin, interleave);
+    if (item >= t_end - t_begin) return;
+    const int32_t t = t_begin + item;
+    const Tile tile = tiles[t];
+    const FactorDesc* __restrict__ Fp = fac + tile.factor;
+    const int64_t n = Fp->n, n_pad = Fp->n_pad;
+    const int L = Fp->L;
+    const double* P = poses + 12 * tile.factor;
+    // pose (uniform): FP32 copies from the staged block, FP64 straight from the poses
+    T R[9], tt[3];
+    if constexpr (PREC == kF64) {
+#pragma unroll
+        for (int k = 0; k < 9; ++k) R[k] = P[k];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) tt[k] = P[9 + k];
+    } else if constexpr (SC) {
+        // R / r (the map's one level), uniform
+        const double ir = Fp->lv[0].inv_r64;
+#pragma unroll
+        for (int k = 0; k < 9; ++k)
+            R[k] = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int((float)(P[k] * ir))));
+#pragma unroll
+        for (int k = 0; k < 3; ++k) tt[k] = 0.0f;
+    } else {
+        const float* Pf = posef + 16 * (int64_t)tile.factor;
+#pragma unroll
+        for (int k = 0; k < 9; ++k) R[k] = Pf[k];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) tt[k] = Pf[9 + k];
+    }
+    // T^-1 c (source frame) for validation, in FP64
+    double cs[3] = {0, 0, 0};
+    if (validate) {
+        const double dc0 = Fp->viewpoint[0] - P[9], dc1 = Fp->viewpoint[1] - P[10], dc2 = Fp->viewpoint[2] - P[11];
+#pragma unroll
+        for (int i = 0; i < 3; ++i) cs[i] = P[i] * dc0 + P[3 + i] * dc1 + P[6 + i] * dc2;
+    }
+    // ---------------------------------------------------------------- per-tile state
+    Acc<T, KAHAN, NT> acc;
+    acc.zero();
+    // points with a voxel and table lookups per level: per lane, or in the
+    // compacted paths wave-uniform totals packed two levels per word (level l
+    // in bits 16 (l % 2) of word l / 2; a tile has fewer than 65536 points);
+    // source points and chunks walked (uniform)
+    int32_t inl[kMaxLevels] = {0, 0, 0, 0};
+    int32_t prb[kMaxLevels] = {0, 0, 0, 0};
+    uint32_t inl2[2] = {0u, 0u}, prb2[2] = {0u, 0u};
+    int32_t walked_pts = 0, walked_chunks = 0;
+    double ge = 0.0;
+    if constexpr (MODE == kBwd) ge = grad_e[tile.factor];
+    const GradOut go{ge, grad_points, grad_slab, points_dtype};
 
-    for (;;) {
-        if (threadIdx.x == 0) {
-            int32_t take = -1;
-            while (tried < kParts) {
-                if (interleave) {
-                    const int32_t cnt = ntiles > part ? (ntiles - part + kParts - 1) / kParts : 0;
-                    if (cnt > 0) {
-                        const uint32_t k = atomicAdd(counter + part, 1u);
-                        if (k < (uint32_t)cnt) {
-                            take = t_begin + part + kParts * (int32_t)k;
-                            break;
-                        }
-                    }
-                } else {
-                    const int32_t lo = t_begin + part * span;
-                    const int32_t hi = min(lo + span, t_end);
-                    if (lo < hi) {
-                        const uint32_t k = atomicAdd(counter + part, 1u);
-                        if (k < (uint32_t)(hi - lo)) {
-                            take = lo + (int32_t)k;
-                            break;
-                        }
-                    }
-                }
-                part = (part + 1) % kParts;
-                ++tried;
-            }
-            s_tile = take;
-        }
-        __syncthreads();
-        const int32_t t = __builtin_amdgcn_readfirstlane(s_tile);
-        if (t < 0) break;
-        const Tile tile = tiles[t];
-        const FactorDesc* __restrict__ Fp = fac + tile.factor;
-        const int64_t n = Fp->n, n_pad = Fp->n_pad;
-        const int L = Fp->L;
-        const double* P = poses + 12 * tile.factor;
-        // pose (uniform): FP32 copies from the staged block, FP64 straight from the poses
-        T R[9], tt[3];
-        if constexpr (PREC == kF64) {
-#pragma unroll
-            for (int k = 0; k < 9; ++k) R[k] = P[k];
-#pragma unroll
-            for (int k = 0; k < 3; ++k) tt[k] = P[9 + k];
-        } else if constexpr (SC) {
-            // R / r (the map's one level), uniform
-            const double ir = Fp->lv[0].inv_r64;
-#pragma unroll
-            for (int k = 0; k < 9; ++k)
-                R[k] = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int((float)(P[k] * ir))));
-#pragma unroll
-            for (int k = 0; k < 3; ++k) tt[k] = 0.0f;
-        } else {
-            const float* Pf = posef + 16 * (int64_t)tile.factor;
-#pragma unroll
-            for (int k = 0; k < 9; ++k) R[k] = Pf[k];
-#pragma unroll
-            for (int k = 0; k < 3; ++k) tt[k] = Pf[9 + k];
-        }
-        // T^-1 c (source frame) for validation, in FP64
-        double cs[3] = {0, 0, 0};
-        if (validate) {
-            const double dc0 = Fp->viewpoint[0] - P[9], dc1 = Fp->viewpoint[1] - P[10], dc2 = Fp->viewpoint[2] - P[11];
-#pragma unroll
-            for (int i = 0; i < 3; ++i) cs[i] = P[i] * dc0 + P[3 + i] * dc1 + P[6 + i] * dc2;
-        }
-        // ---------------------------------------------------------------- per-tile state
-        Acc<T, KAHAN, NT> acc;
-        acc.zero();
-        // points with a voxel and table lookups per level: per lane, or in the
-        // compacted paths wave-uniform totals packed two levels per word (level l
-        // in bits 16 (l % 2) of word l / 2; a tile has fewer than 65536 points);
-        // source points and chunks walked (uniform)
-        int32_t inl[kMaxLevels] = {0, 0, 0, 0};
-        int32_t prb[kMaxLevels] = {0, 0, 0, 0};
-        uint32_t inl2[2] = {0u, 0u}, prb2[2] = {0u, 0u};
-        int32_t walked_pts = 0, walked_chunks = 0;
-        double ge = 0.0;
-        if constexpr (MODE == kBwd) ge = grad_e[tile.factor];
-        const GradOut go{ge, grad_points, grad_slab, points_dtype};
+    // this wave's hit queue (wave-uniform); the head is 0 or 64 (full waves are
+    // drained, and the queue restarts at 0 once a batch's rest is drained), so a
+    // drained wave of entries is head + lane with no wrap
+    int q_head = 0, q_count = 0;
 
-        // this wave's hit queue (wave-uniform); the head is 0 or 64 (full waves are
-        // drained, and the queue restarts at 0 once a batch's rest is drained), so a
-        // drained wave of entries is head + lane with no wrap
-        int q_head = 0, q_count = 0;
-
-        // the first level's probe constants, loaded once per tile (uniform)
-        const ProbeLevel pl0(Fp->lv[0]);
-        // one full wave of queued hits, the oldest 64 (head + lane, no wrap)
-        auto drain_full = [&](const QueueT& Q) {
-            if constexpr (CMP) {
-                if (q_count >= kChunk) {
-                    __builtin_amdgcn_wave_barrier();
-                    drain_hit<MODE, PREC, SC>(acc, Fp, sh, pl0, P, R, tt, n_pad, Q, q_head + lane, go);
-                    q_head = (q_head + kChunk) & (kQueue - 1);
-                    q_count -= kChunk;
-                    __builtin_amdgcn_wave_barrier();
-                }
+    // the first level's probe constants, loaded once per tile (uniform)
+    const ProbeLevel pl0(Fp->lv[0]);
+    // one full wave of queued hits, the oldest 64 (head + lane, no wrap)
+    auto drain_full = [&](const QueueT& Q) {
+        if constexpr (CMP) {
+            if (q_count >= kChunk) {
+                __builtin_amdgcn_wave_barrier();
+                drain_hit<MODE, PREC, SC>(acc, Fp, sh, pl0, P, R, tt, n_pad, Q, q_head + lane, go);
+                q_head = (q_head + kChunk) & (kQueue - 1);
+                q_count -= kChunk;
+                __builtin_amdgcn_wave_barrier();
             }
-        };
-        // the source's positions as a buffer (3 x n_pad floats; sources hold fewer than 2^27 points)
-        const __amdgpu_buffer_rsrc_t xr = raw_rsrc(Fp->dxyz, (uint32_t)(3 * n_pad * (int64_t)sizeof(float)));
-        const int32_t n32 = (int32_t)n;
-        // The tile's chunks are taken in batches of up to kMaxTileChunks (the
-        // per-chunk data held in LDS); the lane sums run on across batches, so a
-        // tile of several batches is reduced once.
-        for (int sb0 = 0; sb0 < tile.nchunks; sb0 += kMaxTileChunks) {
-            const int nch = min(kMaxTileChunks, tile.nchunks - sb0);
-            const int chunk0 = tile.chunk0 + sb0;
-            // ---------------------------------------------------------------- prologue: chunk anchors (kC32)
-            if constexpr (PREC == kC32) {
-                const LevelDesc& top = Fp->lv[L - 1];
-                for (int c = threadIdx.x; c < nch; c += BLOCK) {
-                    const auto a = gbl(Fp->anchor + 3 * (int64_t)(chunk0 + c));
-                    const double a0 = a[0], a1 = a[1], a2 = a[2];
-                    const double o0 = a0 - Fp->src_origin[0], o1 = a1 - Fp->src_origin[1], o2 = a2 - Fp->src_origin[2];
-                    const double av[3] = {a0, a1, a2};
-                    double ya[3];
+        }
+    };
+    // the source's positions as a buffer (3 x n_pad floats; sources hold fewer than 2^27 points)
+    const __amdgpu_buffer_rsrc_t xr = raw_rsrc(Fp->dxyz, (uint32_t)(3 * n_pad * (int64_t)sizeof(float)));
+    const int32_t n32 = (int32_t)n;
+    // The tile's chunks are taken in batches of up to kMaxTileChunks (the
+    // per-chunk data held in LDS); the lane sums run on across batches, so a
+    // tile of several batches is reduced once.
+    for (int sb0 = 0; sb0 < tile.nchunks; sb0 += kMaxTileChunks) {
+        const int nch = min(kMaxTileChunks, tile.nchunks - sb0);
+        const int chunk0 = tile.chunk0 + sb0;
+        // ---------------------------------------------------------------- prologue: chunk anchors (kC32)
+        if constexpr (PREC == kC32) {
+            const LevelDesc& top = Fp->lv[L - 1];
+            for (int c = threadIdx.x; c < nch; c += BLOCK) {
+                const auto a = gbl(Fp->anchor + 3 * (int64_t)(chunk0 + c));
+                const double a0 = a[0], a1 = a[1], a2 = a[2];
+                const double o0 = a0 - Fp->src_origin[0], o1 = a1 - Fp->src_origin[1], o2 = a2 - Fp->src_origin[2];
+                const double av[3] = {a0, a1, a2};
+                double ya[3];
 #pragma unroll
-                    for (int i = 0; i < 3; ++i) {
-                        double fr;
-                        int32_t kb;
-                        ya[i] = anchor_split(P, av, i, top.r64, top.inv_r64, top.K0[i], &fr, &kb);
-                        if constexpr (SC) {
-                            sh.frac[3 * c + i] = fr - 0.5 * top.r64;
-                            sh.cd[c].frac32[i] = (float)(fr * top.inv_r64);
-                        } else {
-                            sh.frac[3 * c + i] = fr;
-                            sh.cd[c].frac32[i] = (float)fr;
-                        }
-                        sh.cd[c].kb[i] = kb + KBB;
-                        sh.cd[c].za[i] = (float)(P[3 * i] * o0 + P[3 * i + 1] * o1 + P[3 * i + 2] * o2);
+                for (int i = 0; i < 3; ++i) {
+                    double fr;
+                    int32_t kb;
+                    ya[i] = anchor_split(P, av, i, top.r64, top.inv_r64, top.K0[i], &fr, &kb);
+                    if constexpr (SC) {
+                        sh.frac[3 * c + i] = fr - 0.5 * top.r64;
+                        sh.cd[c].frac32[i] = (float)(fr * top.inv_r64);
+                    } else {
+                        sh.frac[3 * c + i] = fr;
+                        sh.cd[c].frac32[i] = (float)fr;
                     }
-                    if (validate) {
-                        sh.cd[c].vc[0] = (float)(a0 - cs[0]);
-                        sh.cd[c].vc[1] = (float)(a1 - cs[1]);
-                        sh.cd[c].vc[2] = (float)(a2 - cs[2]);
-                    }
-                    if constexpr (SKIP) sh.reach[c] = (uint8_t)chunk_state(Fp, P, ya, chunk0 + c, L);
+                    sh.cd[c].kb[i] = kb + KBB;
+                    sh.cd[c].za[i] = (float)(P[3 * i] * o0 + P[3 * i + 1] * o1 + P[3 * i + 2] * o2);
                 }
-                __syncthreads();
-            } else if constexpr (SKIP) {
-                for (int c = threadIdx.x; c < nch; c += BLOCK) {
-                    const auto a = gbl(Fp->anchor + 3 * (int64_t)(chunk0 + c));
-                    double ya[3];
-#pragma unroll
-                    for (int i = 0; i < 3; ++i) ya[i] = fma(P[3 * i + 2], a[2], fma(P[3 * i + 1], a[1], P[3 * i] * a[0])) + P[9 + i];
-                    sh.reach[c] = (uint8_t)chunk_state(Fp, P, ya, chunk0 + c, L);
+                if (validate) {
+                    sh.cd[c].vc[0] = (float)(a0 - cs[0]);
+                    sh.cd[c].vc[1] = (float)(a1 - cs[1]);
+                    sh.cd[c].vc[2] = (float)(a2 - cs[2]);
                 }
-                __syncthreads();
-            }
-            // the list of chunks to walk (kept in chunk order)
-            if (wave == 0) {
-                int cnt = 0;
-                int32_t pts = 0;   // per lane: points of the chunks this lane kept
-                for (int base = 0; base < nch; base += 64) {
-                    const int c = base + lane;
-                    bool keep = c < nch;
-                    int flag = 0;
-                    if constexpr (SKIP) {
-                        const int st = keep ? (int)sh.reach[c] : kChunkCulled;
-                        keep = st != kChunkCulled;
-                        flag = st == kChunkInside ? kInsideFlag : 0;
-                    }
-                    const uint64_t m = __ballot(keep);
-                    if (keep) {
-                        sh.live[cnt + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
-                                                                __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u))] = c | flag;
-                        pts += (int32_t)min<int64_t>(kChunk, n - (int64_t)(chunk0 + c) * kChunk);
-                    }
-                    cnt += __popcll(m);
-                }
-                pts = wave_sum(pts);
-                if (lane == 0) {
-                    sh.nlive = cnt;
-                    sh.walked = pts;
-                }
+                if constexpr (SKIP) sh.reach[c] = (uint8_t)chunk_state(Fp, P, ya, chunk0 + c, L);
             }
             __syncthreads();
-            const int nlive = __builtin_amdgcn_readfirstlane(sh.nlive);
-            // this wave walks entries wave, wave + NW, ... of the list; with two or
-            // more waves they are at most 64, held one per lane and read by index
-            int32_t mylive = 0;
-            if constexpr (NW >= 2) {
-                const int jj = wave + NW * lane;
-                mylive = jj < nlive ? sh.live[jj] : 0;
+        } else if constexpr (SKIP) {
+            for (int c = threadIdx.x; c < nch; c += BLOCK) {
+                const auto a = gbl(Fp->anchor + 3 * (int64_t)(chunk0 + c));
+                double ya[3];
+#pragma unroll
+                for (int i = 0; i < 3; ++i) ya[i] = fma(P[3 * i + 2], a[2], fma(P[3 * i + 1], a[1], P[3 * i] * a[0])) + P[9 + i];
+                sh.reach[c] = (uint8_t)chunk_state(Fp, P, ya, chunk0 + c, L);
             }
-            auto live_chunk = [&](int j, int k) -> int {
-                if constexpr (NW >= 2) return __builtin_amdgcn_readlane(mylive, k);
-                else return __builtin_amdgcn_readfirstlane(sh.live[j]);
-            };
-            RawPoint<PREC> nxt;
-            int cnext = 0;
-            if (wave < nlive) {
-                cnext = live_chunk(wave, 0);
+            __syncthreads();
+        }
+        // the list of chunks to walk (kept in chunk order)
+        if (wave == 0) {
+            int cnt = 0;
+            int32_t pts = 0;   // per lane: points of the chunks this lane kept
+            for (int base = 0; base < nch; base += 64) {
+                const int c = base + lane;
+                bool keep = c < nch;
+                int flag = 0;
+                if constexpr (SKIP) {
+                    const int st = keep ? (int)sh.reach[c] : kChunkCulled;
+                    keep = st != kChunkCulled;
+                    flag = st == kChunkInside ? kInsideFlag : 0;
+                }
+                const uint64_t m = __ballot(keep);
+                if (keep) {
+                    sh.live[cnt + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                                            __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u))] = c | flag;
+                    pts += (int32_t)min<int64_t>(kChunk, n - (int64_t)(chunk0 + c) * kChunk);
+                }
+                cnt += __popcll(m);
+            }
+            pts = wave_sum(pts);
+            if (lane == 0) {
+                sh.nlive = cnt;
+                sh.walked = pts;
+            }
+        }
+        __syncthreads();
+        const int nlive = __builtin_amdgcn_readfirstlane(sh.nlive);
+        // this wave walks entries wave, wave + NW, ... of the list; with two or
+        // more waves they are at most 64, held one per lane and read by index
+        int32_t mylive = 0;
+        if constexpr (NW >= 2) {
+            const int jj = wave + NW * lane;
+            mylive = jj < nlive ? sh.live[jj] : 0;
+        }
+        auto live_chunk = [&](int j, int k) -> int {
+            if constexpr (NW >= 2) return __builtin_amdgcn_readlane(mylive, k);
+            else return __builtin_amdgcn_readfirstlane(sh.live[j]);
+        };
+        RawPoint<PREC> nxt;
+        int cnext = 0;
+        if (wave < nlive) {
+            cnext = live_chunk(wave, 0);
+            load_point<PREC>(Fp, xr, (uint32_t)(chunk0 + (cnext & (kInsideFlag - 1))) * kChunk, n_pad,
+                             (uint32_t)lane, nxt);
+        }
+        for (int j = wave, k = 0; j < nlive; j += NW, ++k) {
+            const int c = cnext & (kInsideFlag - 1);
+            // every point of the chunk is inside every level's key box (uniform)
+            const bool inside = (cnext & kInsideFlag) != 0;
+            // point index (sources hold fewer than 2^31 points) and the chunk's
+            // point count (uniform: only a source's last chunk is partial)
+            const uint32_t base = (uint32_t)(chunk0 + c) * kChunk;
+            const int32_t i = (int32_t)(base + (uint32_t)lane);
+            const int32_t npts = min(kChunk, n32 - (int32_t)base);
+            const bool live = lane < npts;
+            const RawPoint<PREC> cur = nxt;
+            if (j + NW < nlive) {
+                cnext = live_chunk(j + NW, k + 1);
                 load_point<PREC>(Fp, xr, (uint32_t)(chunk0 + (cnext & (kInsideFlag - 1))) * kChunk, n_pad,
                                  (uint32_t)lane, nxt);
             }
-            for (int j = wave, k = 0; j < nlive; j += NW, ++k) {
-                const int c = cnext & (kInsideFlag - 1);
-                // every point of the chunk is inside every level's key box (uniform)
-                const bool inside = (cnext & kInsideFlag) != 0;
-                // point index (sources hold fewer than 2^31 points) and the chunk's
-                // point count (uniform: only a source's last chunk is partial)
-                const uint32_t base = (uint32_t)(chunk0 + c) * kChunk;
-                const int32_t i = (int32_t)(base + (uint32_t)lane);
-                const int32_t npts = min(kChunk, n32 - (int32_t)base);
-                const bool live = lane < npts;
-                const RawPoint<PREC> cur = nxt;
-                if (j + NW < nlive) {
-                    cnext = live_chunk(j + NW, k + 1);
-                    load_point<PREC>(Fp, xr, (uint32_t)(chunk0 + (cnext & (kInsideFlag - 1))) * kChunk, n_pad,
-                                     (uint32_t)lane, nxt);
+            if constexpr (CMP && PREC == kF64) {
+                // ---- FP64 mode: probe every point, queue its hits, drain full waves
+                HitQueue& Q = s_q[wave];
+                const double x0 = cur.x[0], x1 = cur.x[1], x2 = cur.x[2];
+                double yl[3];
+#pragma unroll
+                for (int a = 0; a < 3; ++a) yl[a] = (R[3 * a] * x0 + R[3 * a + 1] * x1 + R[3 * a + 2] * x2) + tt[a];
+                bool vis = live;
+                if (live && validate) {
+                    const auto Nv = gbl(Fp->nrm64);
+                    const double sv = (x0 - cs[0]) * Nv[i] + (x1 - cs[1]) * Nv[n_pad + i] + (x2 - cs[2]) * Nv[2 * n_pad + i];
+                    vis = !(sv > 0.0);
                 }
-                if constexpr (CMP && PREC == kF64) {
-                    // ---- FP64 mode: probe every point, queue its hits, drain full waves
-                    HitQueue& Q = s_q[wave];
-                    const double x0 = cur.x[0], x1 = cur.x[1], x2 = cur.x[2];
-                    double yl[3];
-#pragma unroll
-                    for (int a = 0; a < 3; ++a) yl[a] = (R[3 * a] * x0 + R[3 * a + 1] * x1 + R[3 * a + 2] * x2) + tt[a];
-                    bool vis = live;
-                    if (live && validate) {
-                        const auto Nv = gbl(Fp->nrm64);
-                        const double sv = (x0 - cs[0]) * Nv[i] + (x1 - cs[1]) * Nv[n_pad + i] + (x2 - cs[2]) * Nv[2 * n_pad + i];
-                        vis = !(sv > 0.0);
-                    }
-#pragma unroll
-                    for (int l = 0; l < LM; ++l) {
-                        if (l >= L) break;
-                        const LevelDesc& lv = Fp->lv[l];
-                        int32_t kq[3];
-                        bool in = vis;
-#pragma unroll
-                        for (int a = 0; a < 3; ++a) {
-                            const int64_t k = (int64_t)floor(yl[a] * lv.inv_r64) - lv.K0[a];
-                            in &= (k >= lv.kmin[a]) & (k <= lv.kmax[a]);
-                            kq[a] = (int32_t)k;
-                        }
-                        int32_t v = -1;
-                        prb2[l >> 1] += (uint32_t)__popcll(__ballot(in)) << (16 * (l & 1));
-                        // a full wave of earlier hits is processed while the table loads
-                        // are in flight (see the compensated path below)
-                        BlockProbe bp;
-                        if (in)
-                            lookup_issue(lv.slots, lv.log2cap, (uint32_t)(kq[0] + kKeyBias), (uint32_t)(kq[1] + kKeyBias),
-                                         (uint32_t)(kq[2] + kKeyBias), bp);
-                        if constexpr (DRAIN_EARLY) drain_full(Q);
-                        if (in) v = lookup_finish(lv.slots, lv.log2cap, bp);
-                        const bool hit = v >= 0;
-                        const uint64_t mask = __ballot(hit);
-                        inl2[l >> 1] += (uint32_t)__popcll(mask) << (16 * (l & 1));
-                        const int below = __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
-                                                                    __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
-                        if (hit) {
-                            const int e = (q_head + q_count + below) & (kQueue - 1);
-                            Q.pt[e] = (int32_t)i;
-                            Q.rec[e] = v;
-                            Q.cl[e] = (c << 2) | l;
-                        }
-                        q_count += __popcll(mask);
-                        if constexpr (!DRAIN_EARLY) drain_full(Q);
-                    }
-                    continue;
-                } else if constexpr (CMP) {
-                    // ---- probe every point, queue its hits, drain full waves of hits
-                    HitQueue& Q = s_q[wave];
-                    // issue priority up while the chunk's keys are formed and its table
-                    // loads issued (lowered once they are out)
-                    if constexpr (SC) __builtin_amdgcn_s_setprio(1);
-                    const float dx = cur.x[0], dy = cur.x[1], dz = cur.x[2];
-                    float yl[3];
-#pragma unroll
-                    for (int a = 0; a < 3; ++a)
-                        yl[a] = chunk_pos32(sh.cd[c].frac32[a], R[3 * a], R[3 * a + 1], R[3 * a + 2], dx, dy, dz);
-                    bool vis = live;
-                    if (live && validate) {
-                        const auto Nv = gbl(Fp->nrm);
-                        const float sv = (sh.cd[c].vc[0] + dx) * Nv[i] + (sh.cd[c].vc[1] + dy) * Nv[n_pad + i] +
-                                         (sh.cd[c].vc[2] + dz) * Nv[2 * n_pad + i];
-                        vis = !(sv > 0.0f);
-                    }
-#pragma unroll
-                    for (int l = 0; l < LM; ++l) {
-                        if (l >= L) break;
-                        const LevelDesc& lv = Fp->lv[l];
-                        const ProbeLevel pl = l == 0 ? pl0 : ProbeLevel(lv);
-                        int32_t v = -1;
-                        // biased key (coarse anchor key times the level ratio, a shift; a
-                        // one-level kernel's only level is the coarse one) and the
-                        // bounding-box test as one unsigned compare per axis, no branches
-                        uint32_t ku[3];
-                        bool in = vis;
-#pragma unroll
-                        for (int a = 0; a < 3; ++a) {
-                            const uint32_t fl = (uint32_t)floor_i32(SC ? yl[a] : yl[a] * pl.inv_r);
-                            if constexpr (LM == 1) ku[a] = (uint32_t)sh.cd[c].kb[a] + fl;
-                            else ku[a] = (((uint32_t)sh.cd[c].kb[a] + pl.kbias) << pl.log2scale) + fl;
-                        }
-                        // table lookups: inside the key boxes every visible point looks up
-                        // (without validation, every point of the chunk: a uniform count)
-                        uint32_t nlook;
-                        if (inside) {
-                            nlook = validate ? (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(in)) : (uint32_t)npts;
-                        } else {
-#pragma unroll
-                            for (int a = 0; a < 3; ++a) in &= (ku[a] - pl.kbox0u[a]) <= pl.kboxw[a];
-                            nlook = (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(in));
-                        }
-                        prb2[l >> 1] += nlook << (16 * (l & 1));
-                        // the table loads are issued (and the priority lowered), then a
-                        // full wave of earlier hits is processed while they are in flight
-                        // (the queue is FIFO and a drain takes its oldest 64 entries, so
-                        // every drain sees the same hits in the same lanes as draining
-                        // after the push would)
-                        BlockProbe bp;
-                        if (in) lookup_issue(pl.slots, pl.log2cap, ku[0], ku[1], ku[2], bp);
-                        if constexpr (SC) __builtin_amdgcn_s_setprio(0);
-                        if constexpr (DRAIN_EARLY) drain_full(Q);
-                        if (in) v = lookup_finish(pl.slots, pl.log2cap, bp);
-                        const bool hit = v >= 0;
-                        const uint64_t mask = __builtin_amdgcn_ballot_w64(hit);
-                        inl2[l >> 1] += (uint32_t)__popcll(mask) << (16 * (l & 1));
-                        const int below = __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
-                                                                    __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
-                        if (hit) {
-                            const int e = (q_head + q_count + below) & (kQueue - 1);
-                            Q.x[e] = dx;
-                            Q.y[e] = dy;
-                            Q.z[e] = dz;
-                            Q.pt[e] = (int32_t)i;
-                            Q.rec[e] = v;
-                            Q.cl[e] = SC ? c * (int)sizeof(ChunkLds) : (c << 2) | l;
-                        }
-                        q_count += __popcll(mask);
-                        if constexpr (!DRAIN_EARLY) drain_full(Q);
-                    }
-                    continue;
-                }
-                if (!live) continue;
-                // ---- load the point, transform it
-                // yl: transformed position (kC32: relative to the anchor's coarse voxel corner)
-                T x[3], z[3];
-                T yl[3];          // transformed position (kC32: FP32, relative to the anchor's coarse voxel)
-                bool vis = true;
-                if constexpr (PREC == kC32) {
-                    // Keys come from the FP32 position (its ~5e-7 m error only matters
-                    // for points that close to a voxel face, where either voxel is a
-                    // valid answer).  The residual d = mu~ - y cancels metre-scale
-                    // positions down to centimetres, so for hits the offset from the
-                    // anchor is rotated and placed relative to the voxel centre in FP64.
-                    const float dx = cur.x[0], dy = cur.x[1], dz = cur.x[2];
-#pragma unroll
-                    for (int a = 0; a < 3; ++a) {
-                        yl[a] = chunk_pos32(sh.cd[c].frac32[a], R[3 * a], R[3 * a + 1], R[3 * a + 2], dx, dy, dz);
-                        z[a] = sh.cd[c].za[a] + fmaf(R[3 * a + 2], dz, fmaf(R[3 * a + 1], dy, R[3 * a] * dx));
-                    }
-                    x[0] = dx;
-                    x[1] = dy;
-                    x[2] = dz;
-                    if (validate) {
-                        const auto Nv = gbl(Fp->nrm);
-                        const float s = (sh.cd[c].vc[0] + dx) * Nv[i] + (sh.cd[c].vc[1] + dy) * Nv[n_pad + i] +
-                                        (sh.cd[c].vc[2] + dz) * Nv[2 * n_pad + i];
-                        vis = !(s > 0.0f);
-                    }
-                } else if constexpr (PREC == kN32) {
-#pragma unroll
-                    for (int a = 0; a < 3; ++a) x[a] = cur.x[a];
-#pragma unroll
-                    for (int a = 0; a < 3; ++a) {
-                        z[a] = R[3 * a] * x[0] + R[3 * a + 1] * x[1] + R[3 * a + 2] * x[2];
-                        yl[a] = z[a] + tt[a];
-                    }
-                    if (validate) {
-                        const auto Nv = gbl(Fp->nrm);
-                        const float s = (x[0] - (float)cs[0]) * Nv[i] + (x[1] - (float)cs[1]) * Nv[n_pad + i] +
-                                        (x[2] - (float)cs[2]) * Nv[2 * n_pad + i];
-                        vis = !(s > 0.0f);
-                    }
-                } else {
-#pragma unroll
-                    for (int a = 0; a < 3; ++a) x[a] = cur.x[a];
-#pragma unroll
-                    for (int a = 0; a < 3; ++a) {
-                        z[a] = R[3 * a] * x[0] + R[3 * a + 1] * x[1] + R[3 * a + 2] * x[2];
-                        yl[a] = z[a] + tt[a];
-                    }
-                    if (validate) {
-                        const double s = (x[0] - cs[0]) * Fp->nrm64[i] + (x[1] - cs[1]) * Fp->nrm64[n_pad + i] +
-                                         (x[2] - cs[2]) * Fp->nrm64[2 * n_pad + i];
-                        vis = !(s > 0.0);
-                    }
-                }
-                if (!vis) {
-                    if constexpr (MODE == kBwd) {
-                        if (grad_points != nullptr) write_point_grad(Fp, i, grad_points, grad_slab, points_dtype, 0.0, 0.0, 0.0);
-                    }
-                    continue;
-                }
-                // ---- per level: key, probe, terms
-                // S = R C R^T, once per point (FP64 in the compensated mode, where the
-                // fused covariance and its inverse are formed in FP64: both covariances
-                // are near-singular, so FP32 rounding of either one would move W by
-                // ~1e-4 relative along the surface normal)
-                using TS = typename std::conditional<PREC == kC32, double, T>::type;
-                TS S[6];
-                bool haveS = false;
-                T gp[3] = {T(0), T(0), T(0)};
 #pragma unroll
                 for (int l = 0; l < LM; ++l) {
                     if (l >= L) break;
                     const LevelDesc& lv = Fp->lv[l];
-                    // relative key; a key outside the level's key bounding box (which also
-                    // covers keys outside the packable range) has no voxel and is not probed
                     int32_t kq[3];
-                    bool in = true;
-                    int32_t jk[3];
-                    T pc[3];   // absolute position (kN32, kF64)
-                    if constexpr (PREC == kC32) {
+                    bool in = vis;
 #pragma unroll
-                        for (int a = 0; a < 3; ++a) {
-                            jk[a] = floor_i32(yl[a] * lv.inv_r);
-                            kq[a] = (int32_t)((uint32_t)(sh.cd[c].kb[a] - KBB) << lv.log2scale) + jk[a];
-                            in &= (uint32_t)(kq[a] - lv.kbox0[a]) <= lv.kboxw[a];
-                        }
+                    for (int a = 0; a < 3; ++a) {
+                        const int64_t k = (int64_t)floor(yl[a] * lv.inv_r64) - lv.K0[a];
+                        in &= (k >= lv.kmin[a]) & (k <= lv.kmax[a]);
+                        kq[a] = (int32_t)k;
+                    }
+                    int32_t v = -1;
+                    prb2[l >> 1] += (uint32_t)__popcll(__ballot(in)) << (16 * (l & 1));
+                    // a full wave of earlier hits is processed while the table loads
+                    // are in flight (see the compensated path below)
+                    BlockProbe bp;
+                    if (in)
+                        lookup_issue(lv.slots, lv.log2cap, (uint32_t)(kq[0] + kKeyBias), (uint32_t)(kq[1] + kKeyBias),
+                                     (uint32_t)(kq[2] + kKeyBias), bp);
+                    if constexpr (DRAIN_EARLY) drain_full(Q);
+                    if (in) v = lookup_finish(lv.slots, lv.log2cap, bp);
+                    const bool hit = v >= 0;
+                    const uint64_t mask = __ballot(hit);
+                    inl2[l >> 1] += (uint32_t)__popcll(mask) << (16 * (l & 1));
+                    const int below = __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
+                                                                __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+                    if (hit) {
+                        const int e = (q_head + q_count + below) & (kQueue - 1);
+                        Q.pt[e] = (int32_t)i;
+                        Q.rec[e] = v;
+                        Q.cl[e] = (c << 2) | l;
+                    }
+                    q_count += __popcll(mask);
+                    if constexpr (!DRAIN_EARLY) drain_full(Q);
+                }
+                continue;
+            } else if constexpr (CMP) {
+                // ---- probe every point, queue its hits, drain full waves of hits
+                HitQueue& Q = s_q[wave];
+                // issue priority up while the chunk's keys are formed and its table
+                // loads issued (lowered once they are out)
+                if constexpr (SC) __builtin_amdgcn_s_setprio(1);
+                const float dx = cur.x[0], dy = cur.x[1], dz = cur.x[2];
+                float yl[3];
+#pragma unroll
+                for (int a = 0; a < 3; ++a)
+                    yl[a] = chunk_pos32(sh.cd[c].frac32[a], R[3 * a], R[3 * a + 1], R[3 * a + 2], dx, dy, dz);
+                bool vis = live;
+                if (live && validate) {
+                    const auto Nv = gbl(Fp->nrm);
+                    const float sv = (sh.cd[c].vc[0] + dx) * Nv[i] + (sh.cd[c].vc[1] + dy) * Nv[n_pad + i] +
+                                     (sh.cd[c].vc[2] + dz) * Nv[2 * n_pad + i];
+                    vis = !(sv > 0.0f);
+                }
+#pragma unroll
+                for (int l = 0; l < LM; ++l) {
+                    if (l >= L) break;
+                    const LevelDesc& lv = Fp->lv[l];
+                    const ProbeLevel pl = l == 0 ? pl0 : ProbeLevel(lv);
+                    int32_t v = -1;
+                    // biased key (coarse anchor key times the level ratio, a shift; a
+                    // one-level kernel's only level is the coarse one) and the
+                    // bounding-box test as one unsigned compare per axis, no branches
+                    uint32_t ku[3];
+                    bool in = vis;
+#pragma unroll
+                    for (int a = 0; a < 3; ++a) {
+                        const uint32_t fl = (uint32_t)floor_i32(SC ? yl[a] : yl[a] * pl.inv_r);
+                        if constexpr (LM == 1) ku[a] = (uint32_t)sh.cd[c].kb[a] + fl;
+                        else ku[a] = (((uint32_t)sh.cd[c].kb[a] + pl.kbias) << pl.log2scale) + fl;
+                    }
+                    // table lookups: inside the key boxes every visible point looks up
+                    // (without validation, every point of the chunk: a uniform count)
+                    uint32_t nlook;
+                    if (inside) {
+                        nlook = validate ? (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(in)) : (uint32_t)npts;
                     } else {
 #pragma unroll
-                        for (int a = 0; a < 3; ++a) {
-                            int64_t k;
-                            if constexpr (PREC == kN32) k = (int64_t)floorf(yl[a] * lv.inv_r) - lv.K0[a];
-                            else k = (int64_t)floor(yl[a] * lv.inv_r64) - lv.K0[a];
-                            in &= (k >= lv.kmin[a]) & (k <= lv.kmax[a]);
-                            kq[a] = (int32_t)k;
-                            pc[a] = yl[a];
-                        }
+                        for (int a = 0; a < 3; ++a) in &= (ku[a] - pl.kbox0u[a]) <= pl.kboxw[a];
+                        nlook = (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(in));
                     }
-                    if (!in) continue;
-                    prb[l] += 1;
-                    const int32_t v = lookup(lv.slots, lv.log2cap, kq[0], kq[1], kq[2]);
-                    if (v < 0) continue;
-                    inl[l] += 1;
-                    if constexpr (MODE == kCount) continue;
-                    T mv[3];
-                    T W[6];
-                    if constexpr (PREC == kC32) {
-                        // the voxel record's loads are issued before the covariance's (first
-                        // hit only), so the two round trips overlap
-                        const float* rec = lv.rec32 + (int64_t)v * kRec32;
-                        const f32x4 q0 = *gbl(reinterpret_cast<const f32x4*>(rec));
-                        const auto c2 = gbl(reinterpret_cast<const f64x2*>(rec + 4));
-                        const f64x2 cva = c2[0], cvb = c2[1], cvc = c2[2];
-                        if (!haveS) {
-                            point_S<PREC>(Fp, i, n_pad, P, R, S);
-                            haveS = true;
-                        }
-                        mv[0] = q0.x; mv[1] = q0.y; mv[2] = q0.z;
-                        double M[6], W64[6];
-                        M[0] = cva.x + S[0];
-                        M[1] = cva.y + S[1];
-                        M[2] = cvb.x + S[2];
-                        M[3] = cvb.y + S[3];
-                        M[4] = cvc.x + S[4];
-                        M[5] = cvc.y + S[5];
-                        sym3_inverse(M, W64);
-#pragma unroll
-                        for (int k = 0; k < 6; ++k) W[k] = (float)W64[k];
-                    } else {
-                        T cvv[6];
-                        if constexpr (PREC == kN32) {
-                            const auto r4 = gbl(reinterpret_cast<const f32x4*>(lv.recN + (int64_t)v * kRecN));
-                            const f32x4 q0 = r4[0], q1 = r4[1], q2 = r4[2];
-                            mv[0] = q0.x; mv[1] = q0.y; mv[2] = q0.z;
-                            cvv[0] = q0.w; cvv[1] = q1.x; cvv[2] = q1.y; cvv[3] = q1.z; cvv[4] = q1.w; cvv[5] = q2.x;
-                        } else {
-                            const auto r2 = gbl(reinterpret_cast<const f64x2*>(lv.rec64 + (int64_t)v * kRec64));
-                            const f64x2 q0 = r2[0], q1 = r2[1], q2 = r2[2], q3 = r2[3], q4 = r2[4];
-                            mv[0] = q0.x; mv[1] = q0.y; mv[2] = q1.x;
-                            cvv[0] = q1.y; cvv[1] = q2.x; cvv[2] = q2.y; cvv[3] = q3.x; cvv[4] = q3.y; cvv[5] = q4.x;
-                        }
-                        if (!haveS) {
-                            point_S<PREC>(Fp, i, n_pad, P, R, S);
-                            haveS = true;
-                        }
-                        T M[6];
-#pragma unroll
-                        for (int k = 0; k < 6; ++k) M[k] = cvv[k] + S[k];
-                        sym3_inverse(M, W);
+                    prb2[l >> 1] += nlook << (16 * (l & 1));
+                    // the table loads are issued (and the priority lowered), then a
+                    // full wave of earlier hits is processed while they are in flight
+                    // (the queue is FIFO and a drain takes its oldest 64 entries, so
+                    // every drain sees the same hits in the same lanes as draining
+                    // after the push would)
+                    BlockProbe bp;
+                    if (in) lookup_issue(pl.slots, pl.log2cap, ku[0], ku[1], ku[2], bp);
+                    if constexpr (SC) __builtin_amdgcn_s_setprio(0);
+                    if constexpr (DRAIN_EARLY) drain_full(Q);
+                    if (in) v = lookup_finish(pl.slots, pl.log2cap, bp);
+                    const bool hit = v >= 0;
+                    const uint64_t mask = __builtin_amdgcn_ballot_w64(hit);
+                    inl2[l >> 1] += (uint32_t)__popcll(mask) << (16 * (l & 1));
+                    const int below = __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
+                                                                __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+                    if (hit) {
+                        const int e = (q_head + q_count + below) & (kQueue - 1);
+                        Q.x[e] = dx;
+                        Q.y[e] = dy;
+                        Q.z[e] = dz;
+                        Q.pt[e] = (int32_t)i;
+                        Q.rec[e] = v;
+                        Q.cl[e] = SC ? c * (int)sizeof(ChunkLds) : (c << 2) | l;
                     }
-                    T d[3];
-                    if constexpr (PREC == kC32) {
-                        // y relative to the centre of the voxel found above (FP64), then d = mu~ - y
-                        const double ddx = cur.x[0], ddy = cur.x[1], ddz = cur.x[2];
-                        const double half = 0.5 * lv.r64;
-#pragma unroll
-                        for (int a = 0; a < 3; ++a) {
-                            const double t = fma(P[3 * a + 2], ddz,
-                                                 fma(P[3 * a + 1], ddy, fma(P[3 * a], ddx, sh.frac[3 * c + a] - half)));
-                            d[a] = (float)((double)mv[a] - fma(-(double)jk[a], lv.r64, t));
-                        }
-                    } else {
-#pragma unroll
-                        for (int a = 0; a < 3; ++a) d[a] = mv[a] - pc[a];
-                    }
-                    if constexpr (MODE == kLin) {
-                        add_lin_terms(acc, d, W, z);
-                    } else if constexpr (MODE == kEval) {
-                        T u[3];
-                        sym3_mul(W, d, u);
-                        acc.add(0, d[0] * u[0] + d[1] * u[1] + d[2] * u[2]);
-                    } else {
-                        T u[3], Su[3], Sf[6];
-                        sym3_mul(W, d, u);
-#pragma unroll
-                        for (int k = 0; k < 6; ++k) Sf[k] = (T)S[k];
-                        sym3_mul(Sf, u, Su);
-                        const T q0 = z[0] + Su[0], q1 = z[1] + Su[1], q2 = z[2] + Su[2];
-                        acc.add(0, T(2) * (u[1] * q2 - u[2] * q1));
-                        acc.add(1, T(2) * (u[2] * q0 - u[0] * q2));
-                        acc.add(2, T(2) * (u[0] * q1 - u[1] * q0));
-                        acc.add(3, T(-2) * u[0]);
-                        acc.add(4, T(-2) * u[1]);
-                        acc.add(5, T(-2) * u[2]);
-                        // de/dmu = -2 R^T u (source frame)
-                        gp[0] += T(-2) * (R[0] * u[0] + R[3] * u[1] + R[6] * u[2]);
-                        gp[1] += T(-2) * (R[1] * u[0] + R[4] * u[1] + R[7] * u[2]);
-                        gp[2] += T(-2) * (R[2] * u[0] + R[5] * u[1] + R[8] * u[2]);
-                    }
+                    q_count += __popcll(mask);
+                    if constexpr (!DRAIN_EARLY) drain_full(Q);
                 }
-                if constexpr (MODE == kBwd) {
-                    if (grad_points != nullptr)
-                        write_point_grad(Fp, i, grad_points, grad_slab, points_dtype, ge * (double)gp[0],
-                                         ge * (double)gp[1], ge * (double)gp[2]);
-                }
+                continue;
             }
-            if constexpr (CMP) {
-                // the queued hits refer to this batch's chunks: a full wave left by a
-                // probe that drains before pushing, then the partial rest
-                drain_full(s_q[wave]);
-                if (q_count > 0) {
-                    __builtin_amdgcn_wave_barrier();
-                    if (lane < q_count) {
-                        drain_hit<MODE, PREC, SC>(acc, Fp, sh, pl0, P, R, tt, n_pad, s_q[wave], (q_head + lane) & (kQueue - 1), go);
-                    }
-                    __builtin_amdgcn_wave_barrier();
-                    q_head = 0;
-                    q_count = 0;
-                }
-            }
-            walked_pts += __builtin_amdgcn_readfirstlane(sh.walked);
-            walked_chunks += nlive;
-            __syncthreads();   // the next batch's prologue overwrites the chunk data
-        }
-        // ---------------------------------------------------------------- reduction of the tile
-        // lanes -> wave -> tile: FP64 except kN32, which stays FP32 end to end
-        if constexpr (PREC != kN32 && (NT == kTerms || (CMP && MODE == kEval))) {
-            // the 28 terms in one transposed butterfly (value k ends on lanes 2k, 2k + 1);
-            // the compacted evaluate sums its one term the same way, so its e equals
-            // linearize's
-            double v[32];
+            if (!live) continue;
+            // ---- load the point, transform it
+            // yl: transformed position (kC32: relative to the anchor's coarse voxel corner)
+            T x[3], z[3];
+            T yl[3];          // transformed position (kC32: FP32, relative to the anchor's coarse voxel)
+            bool vis = true;
+            if constexpr (PREC == kC32) {
+                // Keys come from the FP32 position (its ~5e-7 m error only matters
+                // for points that close to a voxel face, where either voxel is a
+                // valid answer).  The residual d = mu~ - y cancels metre-scale
+                // positions down to centimetres, so for hits the offset from the
+                // anchor is rotated and placed relative to the voxel centre in FP64.
+                const float dx = cur.x[0], dy = cur.x[1], dz = cur.x[2];
 #pragma unroll
-            for (int k = 0; k < 32; ++k) v[k] = k < NT ? acc.get64(k) : 0.0;
-            const double w = wave_sum_transposed(v, lane);
-            if ((lane & 1) == 0 && (lane >> 1) < NT) s_red[wave][lane >> 1] = w;
-        } else {
-#pragma unroll
-            for (int k = 0; k < NT; ++k) {
-                if constexpr (PREC == kN32) {
-                    const float v = wave_sum(acc.get(k));
-                    if (lane == 0) s_red[wave][k] = (double)v;
-                } else {
-                    const double v = wave_sum(acc.get64(k));
-                    if (lane == 0) s_red[wave][k] = v;
+                for (int a = 0; a < 3; ++a) {
+                    yl[a] = chunk_pos32(sh.cd[c].frac32[a], R[3 * a], R[3 * a + 1], R[3 * a + 2], dx, dy, dz);
+                    z[a] = sh.cd[c].za[a] + fmaf(R[3 * a + 2], dz, fmaf(R[3 * a + 1], dy, R[3 * a] * dx));
                 }
-            }
-        }
-        if constexpr (MODE != kBwd) {
-#pragma unroll
-            for (int l = 0; l < kMaxLevels; ++l) {
-                const int32_t v = CMP ? (int32_t)((inl2[l >> 1] >> (16 * (l & 1))) & 0xFFFFu) : wave_sum(inl[l]);
-                const int32_t p = CMP ? (int32_t)((prb2[l >> 1] >> (16 * (l & 1))) & 0xFFFFu) : wave_sum(prb[l]);
-                if (lane == 0) {
-                    s_red[wave][kRowInl + l] = (double)v;
-                    s_red[wave][kRowProbe + l] = (double)p;
+                x[0] = dx;
+                x[1] = dy;
+                x[2] = dz;
+                if (validate) {
+                    const auto Nv = gbl(Fp->nrm);
+                    const float s = (sh.cd[c].vc[0] + dx) * Nv[i] + (sh.cd[c].vc[1] + dy) * Nv[n_pad + i] +
+                                    (sh.cd[c].vc[2] + dz) * Nv[2 * n_pad + i];
+                    vis = !(s > 0.0f);
                 }
-            }
-        }
-        __syncthreads();
-        if (threadIdx.x < kRow) {
-            const int k = threadIdx.x;
-            double s = 0.0;
-            const bool inl_or_probe = (k >= kRowInl && k < kRowWalk) || (k >= kRowProbe && k < kRowChunks);
-            if (k == kRowWalk) {
-                s = (double)walked_pts;
-            } else if (k == kRowChunks) {
-                s = (double)walked_chunks;
-            } else if (k >= kRowChunks + 1) {
-                s = 0.0;
-            } else if (PREC == kN32 && k < kTerms) {
-                float sf = 0.f;
-                for (int w = 0; w < NW; ++w) sf += (float)s_red[w][k];
-                s = (double)sf;
+            } else if constexpr (PREC == kN32) {
+#pragma unroll
+                for (int a = 0; a < 3; ++a) x[a] = cur.x[a];
+#pragma unroll
+                for (int a = 0; a < 3; ++a) {
+                    z[a] = R[3 * a] * x[0] + R[3 * a + 1] * x[1] + R[3 * a + 2] * x[2];
+                    yl[a] = z[a] + tt[a];
+                }
+                if (validate) {
+                    const auto Nv = gbl(Fp->nrm);
+                    const float s = (x[0] - (float)cs[0]) * Nv[i] + (x[1] - (float)cs[1]) * Nv[n_pad + i] +
+                                    (x[2] - (float)cs[2]) * Nv[2 * n_pad + i];
+                    vis = !(s > 0.0f);
+                }
             } else {
-                for (int w = 0; w < NW; ++w) s += s_red[w][k];
+#pragma unroll
+                for (int a = 0; a < 3; ++a) x[a] = cur.x[a];
+#pragma unroll
+                for (int a = 0; a < 3; ++a) {
+                    z[a] = R[3 * a] * x[0] + R[3 * a + 1] * x[1] + R[3 * a + 2] * x[2];
+                    yl[a] = z[a] + tt[a];
+                }
+                if (validate) {
+                    const double s = (x[0] - cs[0]) * Fp->nrm64[i] + (x[1] - cs[1]) * Fp->nrm64[n_pad + i] +
+                                     (x[2] - cs[2]) * Fp->nrm64[2 * n_pad + i];
+                    vis = !(s > 0.0);
+                }
             }
-            const bool used = (k < NT) || (MODE != kBwd && inl_or_probe) || k == kRowWalk || k == kRowChunks;
-            partials[(int64_t)t * kRow + k] = used ? s : 0.0;
+            if (!vis) {
+                if constexpr (MODE == kBwd) {
+                    if (grad_points != nullptr) write_point_grad(Fp, i, grad_points, grad_slab, points_dtype, 0.0, 0.0, 0.0);
+                }
+                continue;
+            }
+            // ---- per level: key, probe, terms
+            // S = R C R^T, once per point (FP64 in the compensated mode, where the
+            // fused covariance and its inverse are formed in FP64: both covariances
+            // are near-singular, so FP32 rounding of either one would move W by
+            // ~1e-4 relative along the surface normal)
+            using TS = typename std::conditional<PREC == kC32, double, T>::type;
+            TS S[6];
+            bool haveS = false;
+            T gp[3] = {T(0), T(0), T(0)};
+#pragma unroll
+            for (int l = 0; l < LM; ++l) {
+                if (l >= L) break;
+                const LevelDesc& lv = Fp->lv[l];
+                // relative key; a key outside the level's key bounding box (which also
+                // covers keys outside the packable range) has no voxel and is not probed
+                int32_t kq[3];
+                bool in = true;
+                int32_t jk[3];
+                T pc[3];   // absolute position (kN32, kF64)
+                if constexpr (PREC == kC32) {
+#pragma unroll
+                    for (int a = 0; a < 3; ++a) {
+                        jk[a] = floor_i32(yl[a] * lv.inv_r);
+                        kq[a] = (int32_t)((uint32_t)(sh.cd[c].kb[a] - KBB) << lv.log2scale) + jk[a];
+                        in &= (uint32_t)(kq[a] - lv.kbox0[a]) <= lv.kboxw[a];
+                    }
+                } else {
+#pragma unroll
+                    for (int a = 0; a < 3; ++a) {
+                        int64_t k;
+                        if constexpr (PREC == kN32) k = (int64_t)floorf(yl[a] * lv.inv_r) - lv.K0[a];
+                        else k = (int64_t)floor(yl[a] * lv.inv_r64) - lv.K0[a];
+                        in &= (k >= lv.kmin[a]) & (k <= lv.kmax[a]);
+                        kq[a] = (int32_t)k;
+                        pc[a] = yl[a];
+                    }
+                }
+                if (!in) continue;
+                prb[l] += 1;
+                const int32_t v = lookup(lv.slots, lv.log2cap, kq[0], kq[1], kq[2]);
+                if (v < 0) continue;
+                inl[l] += 1;
+                if constexpr (MODE == kCount) continue;
+                T mv[3];
+                T W[6];
+                if constexpr (PREC == kC32) {
+                    // the voxel record's loads are issued before the covariance's (first
+                    // hit only), so the two round trips overlap
+                    const float* rec = lv.rec32 + (int64_t)v * kRec32;
+                    const f32x4 q0 = *gbl(reinterpret_cast<const f32x4*>(rec));
+                    const auto c2 = gbl(reinterpret_cast<const f64x2*>(rec + 4));
+                    const f64x2 cva = c2[0], cvb = c2[1], cvc = c2[2];
+                    if (!haveS) {
+                        point_S<PREC>(Fp, i, n_pad, P, R, S);
+                        haveS = true;
+                    }
+                    mv[0] = q0.x; mv[1] = q0.y; mv[2] = q0.z;
+                    double M[6], W64[6];
+                    M[0] = cva.x + S[0];
+                    M[1] = cva.y + S[1];
+                    M[2] = cvb.x + S[2];
+                    M[3] = cvb.y + S[3];
+                    M[4] = cvc.x + S[4];
+                    M[5] = cvc.y + S[5];
+                    sym3_inverse(M, W64);
+#pragma unroll
+                    for (int k = 0; k < 6; ++k) W[k] = (float)W64[k];
+                } else {
+                    T cvv[6];
+                    if constexpr (PREC == kN32) {
+                        const auto r4 = gbl(reinterpret_cast<const f32x4*>(lv.recN + (int64_t)v * kRecN));
+                        const f32x4 q0 = r4[0], q1 = r4[1], q2 = r4[2];
+                        mv[0] = q0.x; mv[1] = q0.y; mv[2] = q0.z;
+                        cvv[0] = q0.w; cvv[1] = q1.x; cvv[2] = q1.y; cvv[3] = q1.z; cvv[4] = q1.w; cvv[5] = q2.x;
+                    } else {
+                        const auto r2 = gbl(reinterpret_cast<const f64x2*>(lv.rec64 + (int64_t)v * kRec64));
+                        const f64x2 q0 = r2[0], q1 = r2[1], q2 = r2[2], q3 = r2[3], q4 = r2[4];
+                        mv[0] = q0.x; mv[1] = q0.y; mv[2] = q1.x;
+                        cvv[0] = q1.y; cvv[1] = q2.x; cvv[2] = q2.y; cvv[3] = q3.x; cvv[4] = q3.y; cvv[5] = q4.x;
+                    }
+                    if (!haveS) {
+                        point_S<PREC>(Fp, i, n_pad, P, R, S);
+                        haveS = true;
+                    }
+                    T M[6];
+#pragma unroll
+                    for (int k = 0; k < 6; ++k) M[k] = cvv[k] + S[k];
+                    sym3_inverse(M, W);
+                }
+                T d[3];
+                if constexpr (PREC == kC32) {
+                    // y relative to the centre of the voxel found above (FP64), then d = mu~ - y
+                    const double ddx = cur.x[0], ddy = cur.x[1], ddz = cur.x[2];
+                    const double half = 0.5 * lv.r64;
+#pragma unroll
+                    for (int a = 0; a < 3; ++a) {
+                        const double t = fma(P[3 * a + 2], ddz,
+                                             fma(P[3 * a + 1], ddy, fma(P[3 * a], ddx, sh.frac[3 * c + a] - half)));
+                        d[a] = (float)((double)mv[a] - fma(-(double)jk[a], lv.r64, t));
+                    }
+                } else {
+#pragma unroll
+                    for (int a = 0; a < 3; ++a) d[a] = mv[a] - pc[a];
+                }
+                if constexpr (MODE == kLin) {
+                    add_lin_terms(acc, d, W, z);
+                } else if constexpr (MODE == kEval) {
+                    T u[3];
+                    sym3_mul(W, d, u);
+                    acc.add(0, d[0] * u[0] + d[1] * u[1] + d[2] * u[2]);
+                } else {
+                    T u[3], Su[3], Sf[6];
+                    sym3_mul(W, d, u);
+#pragma unroll
+                    for (int k = 0; k < 6; ++k) Sf[k] = (T)S[k];
+                    sym3_mul(Sf, u, Su);
+                    const T q0 = z[0] + Su[0], q1 = z[1] + Su[1], q2 = z[2] + Su[2];
+                    acc.add(0, T(2) * (u[1] * q2 - u[2] * q1));
+                    acc.add(1, T(2) * (u[2] * q0 - u[0] * q2));
+                    acc.add(2, T(2) * (u[0] * q1 - u[1] * q0));
+                    acc.add(3, T(-2) * u[0]);
+                    acc.add(4, T(-2) * u[1]);
+                    acc.add(5, T(-2) * u[2]);
+                    // de/dmu = -2 R^T u (source frame)
+                    gp[0] += T(-2) * (R[0] * u[0] + R[3] * u[1] + R[6] * u[2]);
+                    gp[1] += T(-2) * (R[1] * u[0] + R[4] * u[1] + R[7] * u[2]);
+                    gp[2] += T(-2) * (R[2] * u[0] + R[5] * u[1] + R[8] * u[2]);
+                }
+            }
+            if constexpr (MODE == kBwd) {
+                if (grad_points != nullptr)
+                    write_point_grad(Fp, i, grad_points, grad_slab, points_dtype, ge * (double)gp[0],
+                                     ge * (double)gp[1], ge * (double)gp[2]);
+            }
         }
-        __syncthreads();
+        if constexpr (CMP) {
+            // the queued hits refer to this batch's chunks: a full wave left by a
+            // probe that drains before pushing, then the partial rest
+            drain_full(s_q[wave]);
+            if (q_count > 0) {
+                __builtin_amdgcn_wave_barrier();
+                if (lane < q_count) {
+                    drain_hit<MODE, PREC, SC>(acc, Fp, sh, pl0, P, R, tt, n_pad, s_q[wave], (q_head + lane) & (kQueue - 1), go);
+                }
+                __builtin_amdgcn_wave_barrier();
+                q_head = 0;
+                q_count = 0;
+            }
+        }
+        walked_pts += __builtin_amdgcn_readfirstlane(sh.walked);
+        walked_chunks += nlive;
+        __syncthreads();   // the next batch's prologue overwrites the chunk data
+    }
+    // ---------------------------------------------------------------- reduction of the tile
+    // lanes -> wave -> tile: FP64 except kN32, which stays FP32 end to end
+    if constexpr (PREC != kN32 && (NT == kTerms || (CMP && MODE == kEval))) {
+        // the 28 terms in one transposed butterfly (value k ends on lanes 2k, 2k + 1);
+        // the compacted evaluate sums its one term the same way, so its e equals
+        // linearize's
+        double v[32];
+#pragma unroll
+        for (int k = 0; k < 32; ++k) v[k] = k < NT ? acc.get64(k) : 0.0;
+        const double w = wave_sum_transposed(v, lane);
+        if ((lane & 1) == 0 && (lane >> 1) < NT) s_red[wave][lane >> 1] = w;
+    } else {
+#pragma unroll
+        for (int k = 0; k < NT; ++k) {
+            if constexpr (PREC == kN32) {
+                const float v = wave_sum(acc.get(k));
+                if (lane == 0) s_red[wave][k] = (double)v;
+            } else {
+                const double v = wave_sum(acc.get64(k));
+                if (lane == 0) s_red[wave][k] = v;
+            }
+        }
+    }
+    if constexpr (MODE != kBwd) {
+#pragma unroll
+        for (int l = 0; l < kMaxLevels; ++l) {
+            const int32_t v = CMP ? (int32_t)((inl2[l >> 1] >> (16 * (l & 1))) & 0xFFFFu) : wave_sum(inl[l]);
+            const int32_t p = CMP ? (int32_t)((prb2[l >> 1] >> (16 * (l & 1))) & 0xFFFFu) : wave_sum(prb[l]);
+            if (lane == 0) {
+                s_red[wave][kRowInl + l] = (double)v;
+                s_red[wave][kRowProbe + l] = (double)p;
+            }
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x < kRow) {
+        const int k = threadIdx.x;
+        double s = 0.0;
+        const bool inl_or_probe = (k >= kRowInl && k < kRowWalk) || (k >= kRowProbe && k < kRowChunks);
+        if (k == kRowWalk) {
+            s = (double)walked_pts;
+        } else if (k == kRowChunks) {
+            s = (double)walked_chunks;
+        } else if (k >= kRowChunks + 1) {
+            s = 0.0;
+        } else if (PREC == kN32 && k < kTerms) {
+            float sf = 0.f;
+            for (int w = 0; w < NW; ++w) sf += (float)s_red[w][k];
+            s = (double)sf;
+        } else {
+            for (int w = 0; w < NW; ++w) s += s_red[w][k];
+        }
+        const bool used = (k < NT) || (MODE != kBwd && inl_or_probe) || k == kRowWalk || k == kRowChunks;
+        partials[(int64_t)t * kRow + k] = used ? s : 0.0;
     }
 }
 
 // Per-factor reduction of tile rows in tile order (FP64; FP32 for kN32) and the
 // frame change H = G^T Bd^T H'' Bd G, b = G^T Bd^T b''.  One 64-thread block per
-// factor.  Block 0 also re-arms the tile counter for the next launch.
+// factor.
 template <int MODE, int PREC>
 __global__ __launch_bounds__(64) void k_reduce(const FactorDesc* __restrict__ fac, const int32_t* __restrict__ tile_first,
                                                int32_t f0, const double* __restrict__ partials,
                                                const double* __restrict__ poses, double* __restrict__ out,
-                                               int64_t* __restrict__ inliers, uint32_t* __restrict__ counter,
+                                               int64_t* __restrict__ inliers,
                                                const double* __restrict__ grad_e, const double* __restrict__ jr,
                                                double* __restrict__ grad_xi, int64_t* __restrict__ work) {
     __shared__ double s[kRow];
     const int f = f0 + blockIdx.x;
-    if (blockIdx.x == 0 && threadIdx.x < kParts) counter[threadIdx.x] = 0u;
     const int k = threadIdx.x;
     if (k < kRow) {
         const int32_t a = tile_first[f], bnd = tile_first[f + 1];
@@ -1540,12 +1512,13 @@ __global__ void k_fill_zero(uint32_t* p, int64_t n_words) {
 
 template <int MODE, int PREC, bool KH, bool VAL, int LM>
 static vg_status launch_tiles_v(vg_batch* b, const Workspace& ws, const double* d_poses, int32_t t0, int32_t t1,
-                                int grid, const double* d_grad_e, void* d_grad_points, int points_dtype) {
+                                const double* d_grad_e, void* d_grad_points, int points_dtype) {
     hipStream_t st = b->ctx->stream;
+    const int grid = kParts * ((t1 - t0 + kParts - 1) / kParts);
 #define VG_LAUNCH(BS)                                                                                          \
     k_tiles<MODE, PREC, BS, KH, VAL, LM><<<grid, BS, 0, st>>>(b->d_fac, b->d_tiles, t0, t1, d_poses, ws.posef, \
-                                                              ws.partials, ws.counter, d_grad_e,              \
-                                                              d_grad_points, b->d_gslab, points_dtype,        \
+                                                              ws.partials, d_grad_e, d_grad_points,           \
+                                                              b->d_gslab, points_dtype,                       \
                                                               b->tile_order == 2 ? 1 : 0)
     switch (b->block) {
         case 64: VG_LAUNCH(64); break;
@@ -1560,25 +1533,23 @@ static vg_status launch_tiles_v(vg_batch* b, const Workspace& ws, const double* 
 
 template <int MODE, int PREC, bool KH>
 static vg_status launch_tiles_t(vg_batch* b, const Workspace& ws, const double* d_poses, int32_t t0, int32_t t1,
-                                int grid, const double* d_grad_e, void* d_grad_points, int points_dtype) {
+                                const double* d_grad_e, void* d_grad_points, int points_dtype) {
     if (b->opt.surface_validation)
-        return launch_tiles_v<MODE, PREC, KH, true, kMaxLevels>(b, ws, d_poses, t0, t1, grid, d_grad_e,
-                                                                d_grad_points, points_dtype);
+        return launch_tiles_v<MODE, PREC, KH, true, kMaxLevels>(b, ws, d_poses, t0, t1, d_grad_e, d_grad_points,
+                                                                points_dtype);
     // single-level compensated batches without validation (the submap factors)
     // get a kernel compiled for one level
     if constexpr (PREC == kC32 && !KH) {
         if (b->L == 1)
-            return launch_tiles_v<MODE, PREC, KH, false, 1>(b, ws, d_poses, t0, t1, grid, d_grad_e, d_grad_points,
+            return launch_tiles_v<MODE, PREC, KH, false, 1>(b, ws, d_poses, t0, t1, d_grad_e, d_grad_points,
                                                             points_dtype);
     }
-    return launch_tiles_v<MODE, PREC, KH, false, kMaxLevels>(b, ws, d_poses, t0, t1, grid, d_grad_e,
-                                                             d_grad_points, points_dtype);
+    return launch_tiles_v<MODE, PREC, KH, false, kMaxLevels>(b, ws, d_poses, t0, t1, d_grad_e, d_grad_points,
+                                                             points_dtype);
 }
 
 vg_status launch_tiles(vg_batch* b, const Workspace& ws, int mode, const double* d_poses, int32_t t0, int32_t t1,
-                       int grid, const double* d_grad_e, void* d_grad_points, int points_dtype, int64_t f0,
-                       int64_t f1) {
-    if (grid < 1) grid = 1;
+                       const double* d_grad_e, void* d_grad_points, int points_dtype, int64_t f0, int64_t f1) {
     if (t1 <= t0) return VG_OK;
     // FP32 pose copies for the FP32 kernels; the one-level compensated kernels
     // (linearize, evaluate, backward) form their rotation from the FP64 poses
@@ -1595,12 +1566,12 @@ vg_status launch_tiles(vg_batch* b, const Workspace& ws, int mode, const double*
     const bool kh = b->opt.lane_kahan != 0;
 #define VG_DISPATCH(M)                                                                                  \
     if (p == kC32 && kh)                                                                                \
-        return launch_tiles_t<M, kC32, true>(b, ws, d_poses, t0, t1, grid, d_grad_e, d_grad_points, points_dtype); \
+        return launch_tiles_t<M, kC32, true>(b, ws, d_poses, t0, t1, d_grad_e, d_grad_points, points_dtype); \
     if (p == kC32)                                                                                      \
-        return launch_tiles_t<M, kC32, false>(b, ws, d_poses, t0, t1, grid, d_grad_e, d_grad_points, points_dtype); \
+        return launch_tiles_t<M, kC32, false>(b, ws, d_poses, t0, t1, d_grad_e, d_grad_points, points_dtype); \
     if (p == kN32)                                                                                      \
-        return launch_tiles_t<M, kN32, false>(b, ws, d_poses, t0, t1, grid, d_grad_e, d_grad_points, points_dtype); \
-    return launch_tiles_t<M, kF64, false>(b, ws, d_poses, t0, t1, grid, d_grad_e, d_grad_points, points_dtype);
+        return launch_tiles_t<M, kN32, false>(b, ws, d_poses, t0, t1, d_grad_e, d_grad_points, points_dtype); \
+    return launch_tiles_t<M, kF64, false>(b, ws, d_poses, t0, t1, d_grad_e, d_grad_points, points_dtype);
     if (mode == kLin) { VG_DISPATCH(kLin) }
     if (mode == kEval) { VG_DISPATCH(kEval) }
     if (mode == kCount) { VG_DISPATCH(kCount) }
@@ -1612,7 +1583,7 @@ template <int MODE, int PREC>
 static void reduce_t(vg_batch* b, const Workspace& ws, const double* d_poses, int32_t f0, int32_t f1, double* d_out,
                      int64_t* d_inl, const double* d_grad_e, const double* d_jr, double* d_grad_xi) {
     k_reduce<MODE, PREC><<<f1 - f0, 64, 0, b->ctx->stream>>>(b->d_fac, b->d_tile_first, f0, ws.partials, d_poses,
-                                                             d_out, d_inl, ws.counter, d_grad_e, d_jr, d_grad_xi,
+                                                             d_out, d_inl, d_grad_e, d_jr, d_grad_xi,
                                                              ws.work);
 }
 

@@ -41,7 +41,7 @@ constexpr int kRec32 = 16;              // floats per compensated voxel record (
 constexpr int kRecN = 12;               // floats per absolute-FP32 voxel record
 constexpr int kRec64 = 10;              // doubles per FP64 voxel record
 constexpr int kOutRow = 43;             // e, H (36), b (6)
-constexpr int kParts = 8;               // tile partitions = XCDs of an MI355X
+constexpr int kParts = 8;               // XCDs of an MI355X: workgroups go to them round-robin
 
 enum Mode { kLin = 0, kEval = 1, kBwd = 2, kCount = 3 };
 enum Prec { kN32 = VG_FP32, kC32 = VG_FP32_COMPENSATED, kF64 = VG_FP64 };
@@ -104,7 +104,6 @@ struct SharedSrc {
 // Device buffers one launch of the tile kernel and reduction works in.
 struct Workspace {
     double* partials;        // n_tiles x kRow
-    uint32_t* counter;       // kParts tile counters (zero before the first launch)
     float* posef;            // F x 16 staged FP32 poses
     int64_t* work;           // F x kWork work counts, or nullptr
 };
@@ -208,14 +207,13 @@ struct vg_batch {
     std::vector<int64_t> grad_offsets;   // per unique source
     int64_t total_points = 0;
     int64_t grad_rows = 0;               // rows of the concatenated point gradient
-    int block = 256, tile_points = 2048, grid = 0, blocks_per_cu = 0;
+    int block = 256, tile_points = 2048, blocks_per_cu = 0;
     int tile_order = 1;                  // 1 contiguous per XCD, 2 round-robin over XCDs
     // device buffers
     vg::FactorDesc* d_fac = nullptr;
     vg::Tile* d_tiles = nullptr;
     int32_t* d_tile_first = nullptr;
     double* d_partials = nullptr;
-    uint32_t* d_counter = nullptr;
     double* d_poses = nullptr;
     float* d_posef = nullptr;       // F x 16 staged FP32 poses
     double* d_out = nullptr;        // F x 43
@@ -277,8 +275,7 @@ vg_status set_source_points(vg_context* ctx, vg_source* s, const void* d_xyz, in
 // f0, f1: the factors those tiles belong to (their poses are staged to FP32 first)
 // ws: the buffers of the launch (the batch's own, or a caller-provided scratch)
 vg_status launch_tiles(vg_batch* b, const Workspace& ws, int mode, const double* d_poses, int32_t t0, int32_t t1,
-                       int grid, const double* d_grad_e, void* d_grad_points, int points_dtype, int64_t f0,
-                       int64_t f1);
+                       const double* d_grad_e, void* d_grad_points, int points_dtype, int64_t f0, int64_t f1);
 vg_status launch_reduce(vg_batch* b, const Workspace& ws, int mode, const double* d_poses, int32_t f0, int32_t f1,
                         double* d_out, int64_t* d_inliers, const double* d_grad_e, const double* d_jr,
                         double* d_grad_xi);
