@@ -52,6 +52,16 @@ bool finite_all(const double* p, int64_t n) {
     return true;
 }
 
+// Bounding box (min xyz, max xyz) of n finite points.
+void bounding_box(const double* xyz, int64_t n, double box[6]) {
+    for (int a = 0; a < 3; ++a) box[a] = box[3 + a] = n > 0 ? xyz[a] : 0.0;
+    for (int64_t i = 0; i < n; ++i)
+        for (int a = 0; a < 3; ++a) {
+            box[a] = std::min(box[a], xyz[3 * i + a]);
+            box[3 + a] = std::max(box[3 + a], xyz[3 * i + a]);
+        }
+}
+
 // Leading principal minors of [a b c; b d e; c e f] all positive.
 bool spd6(const double* c) {
     const double a = c[0], b = c[1], cc = c[2], d = c[3], e = c[4], f = c[5];
@@ -204,11 +214,17 @@ extern "C" vg_status vg_context_create(int32_t device, void* hip_stream, vg_cont
     }
     c->arch = arch;
     c->name = prop.name;
+    e = hipHostMalloc((void**)&c->h_small, sizeof(int32_t) * kSmallWords, hipHostMallocDefault);
+    if (e != hipSuccess) {
+        delete c;
+        return hip_fail(e, "hipHostMalloc");
+    }
     if (hip_stream != nullptr) {
         c->stream = (hipStream_t)hip_stream;
     } else {
         e = hipStreamCreateWithFlags(&c->stream, hipStreamNonBlocking);
         if (e != hipSuccess) {
+            (void)hipHostFree(c->h_small);
             delete c;
             return hip_fail(e, "hipStreamCreateWithFlags");
         }
@@ -226,6 +242,7 @@ extern "C" vg_status vg_context_destroy(vg_context* ctx) {
     (void)hipStreamSynchronize(ctx->stream);
     if (ctx->own_stream) (void)hipStreamDestroy(ctx->stream);
     if (ctx->ws) (void)hipFree(ctx->ws);
+    if (ctx->h_small) (void)hipHostFree(ctx->h_small);
     ctx->magic = 0;
     delete ctx;
     return VG_OK;
@@ -233,19 +250,20 @@ extern "C" vg_status vg_context_destroy(vg_context* ctx) {
 
 // ============================================================================ voxel maps
 
-// Voxel map from device FP64 arrays; first = host copy of point 0 (the origin).
-static vg_status make_voxelmap(vg_context* ctx, const double* d_xyz, const double* d_cov, int64_t n,
-                               const double* resolutions, int32_t L, const double* first, vg_voxelmap** out) {
+// Voxel map from device FP64 arrays; first = host copy of point 0 (the origin),
+// box = the points' bounding box.
+static vg_status make_voxelmap(vg_context* ctx, Scratch& sc, const double* d_xyz, const double* d_cov, int64_t n,
+                               const double* resolutions, int32_t L, const double* first, const double box[6],
+                               vg_voxelmap** out) {
     auto* m = new vg_voxelmap();
     m->ctx = ctx;
     m->L = L;
     const double rmax = resolutions[L - 1];
     for (int a = 0; a < 3; ++a) m->origin[a] = (n > 0) ? rmax * std::nearbyint(first[a] / rmax) : 0.0;
-    vg_status st = VG_OK;
-    for (int l = 0; l < L && st == VG_OK; ++l)
-        st = build_level(ctx, d_xyz, d_cov, n, resolutions[l], m->origin, &m->lv[l]);
+    const vg_status st = build_map(ctx, sc, d_xyz, d_cov, n, box, resolutions, L, m);
     if (st != VG_OK) {
-        for (int l = 0; l < kMaxLevels; ++l) free_level(&m->lv[l]);
+        (void)hipStreamSynchronize(ctx->stream);
+        free_map(m);
         delete m;
         return st;
     }
@@ -284,26 +302,17 @@ extern "C" vg_status vg_build_voxelmap(vg_context* ctx, const double* xyz, const
             return VG_ERR_NOT_SPD;
         }
     VG_HIP(hipSetDevice(ctx->device));
+    double box[6];
+    bounding_box(xyz, n, box);
+    Scratch sc(ctx);
     double *d_xyz = nullptr, *d_cov = nullptr;
-    vg_status st = VG_OK;
-    do {
-        if ((st = dev_alloc(&d_xyz, 3 * n)) != VG_OK) break;
-        if ((st = dev_alloc(&d_cov, 6 * n)) != VG_OK) break;
-        hipError_t e = hipSuccess;
-        if (n > 0) {
-            e = hipMemcpyAsync(d_xyz, xyz, sizeof(double) * 3 * n, hipMemcpyHostToDevice, ctx->stream);
-            if (e == hipSuccess)
-                e = hipMemcpyAsync(d_cov, cov, sizeof(double) * 6 * n, hipMemcpyHostToDevice, ctx->stream);
-        }
-        if (e != hipSuccess) {
-            st = hip_fail(e, "voxelmap upload");
-            break;
-        }
-        st = make_voxelmap(ctx, d_xyz, d_cov, n, resolutions, L, xyz, out);
-    } while (0);
-    dfree(d_xyz);
-    dfree(d_cov);
-    return st;
+    VG_HIP(sc.get(&d_xyz, 3 * n));
+    VG_HIP(sc.get(&d_cov, 6 * n));
+    if (n > 0) {
+        VG_HIP(hipMemcpyAsync(d_xyz, xyz, sizeof(double) * 3 * n, hipMemcpyHostToDevice, ctx->stream));
+        VG_HIP(hipMemcpyAsync(d_cov, cov, sizeof(double) * 6 * n, hipMemcpyHostToDevice, ctx->stream));
+    }
+    return make_voxelmap(ctx, sc, d_xyz, d_cov, n, resolutions, L, xyz, box, out);
 }
 
 extern "C" vg_status vg_voxelmap_info(const vg_voxelmap* map, int32_t level, int64_t* n_voxels, int64_t* capacity) {
@@ -337,7 +346,7 @@ extern "C" vg_status vg_voxelmap_destroy(vg_voxelmap* map) {
     if (map->users > 0) return state_err("voxel map is used by a live batch");
     (void)hipSetDevice(map->ctx->device);
     (void)hipStreamSynchronize(map->ctx->stream);
-    for (int l = 0; l < kMaxLevels; ++l) free_level(&map->lv[l]);
+    free_map(map);
     map->magic = 0;
     delete map;
     return VG_OK;
@@ -584,7 +593,8 @@ extern "C" vg_status vg_build_voxelmap_from_cloud(vg_context* ctx, const vg_clou
     *out = nullptr;
     VG_TRY(check_resolutions(resolutions, L));
     VG_HIP(hipSetDevice(ctx->device));
-    return make_voxelmap(ctx, cloud->xyz, cloud->cov, cloud->m, resolutions, L, cloud->first, out);
+    Scratch sc(ctx);
+    return make_voxelmap(ctx, sc, cloud->xyz, cloud->cov, cloud->m, resolutions, L, cloud->first, cloud->box, out);
 }
 
 extern "C" vg_status vg_cloud_destroy(vg_cloud* cloud) {

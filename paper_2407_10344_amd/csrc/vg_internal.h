@@ -127,9 +127,8 @@ struct Level {
     float* rec32 = nullptr;
     float* recN = nullptr;
     double* rec64 = nullptr;
-    uint64_t* keys = nullptr;   // V packed relative keys, ascending (canonical order)
-    int32_t* counts = nullptr;  // V, canonical order
-    int32_t* lex2rec = nullptr; // V: canonical index -> record index (records are block ordered)
+    uint64_t* keys = nullptr;   // V packed relative keys (record order)
+    int32_t* counts = nullptr;  // V points per voxel (record order)
     int32_t kmin[3] = {1, 1, 1}, kmax[3] = {0, 0, 0};   // relative key bounding box
 };
 
@@ -139,8 +138,9 @@ struct vg_context {
     int device = 0;
     hipStream_t stream = nullptr;
     bool own_stream = false;
-    void* ws = nullptr;          // grow-only device workspace of the preprocessing calls
-    size_t ws_bytes = 0;
+    void* ws = nullptr;          // device workspace of the calls that build clouds, maps and sources
+    size_t ws_bytes = 0;         // (grown to the largest such call, up to kKeepWorkspace)
+    int32_t* h_small = nullptr;  // pinned host words that those calls' kernels write their sizes to
     int num_cu = 0;
     void* scratch = nullptr;     // this device's fixed scratch array (device address), or nullptr
     std::string arch;
@@ -153,6 +153,7 @@ struct vg_voxelmap {
     int L = 0;
     double origin[3] = {0, 0, 0};
     vg::Level lv[vg::kMaxLevels];
+    void* blocks[vg::kMaxLevels] = {};   // the allocations that hold every level's arrays
     int users = 0;
     uint32_t magic = 0;
 };
@@ -191,6 +192,7 @@ struct vg_cloud {
     double* d2 = nullptr;       // m x k
     void* block = nullptr;      // one allocation holding every array above
     double first[3] = {0, 0, 0};// host copy of point 0 (origins of sources / maps made from the cloud)
+    double box[6] = {0, 0, 0, 0, 0, 0};   // host copy of the points' bounding box
     uint32_t magic = 0;
 };
 
@@ -254,13 +256,59 @@ vg_status hip_fail(hipError_t e, const char* what);
         if (_e != hipSuccess) return vg::hip_fail(_e, #call);\
     } while (0)
 
+// ---------------------------------------------------------------- scratch
+
+constexpr size_t kKeepWorkspace = (size_t)1 << 30;   // a larger call's temporaries are freed with it
+constexpr int kSmallWords = 1024;                    // pinned words of a context
+
+// Temporaries of one call, carved from the context's workspace (the calls of a
+// context are ordered on its stream, so a later call may write them while the
+// host is ahead of the device); what does not fit is allocated and freed, and the
+// workspace grows to the call's total afterwards, so calls of similar size
+// allocate nothing.
+struct Scratch {
+    vg_context* ctx;
+    size_t off = 0, need = 0;
+    std::vector<void*> ptrs;
+    explicit Scratch(vg_context* c) : ctx(c) {}
+    Scratch(const Scratch&) = delete;
+    Scratch& operator=(const Scratch&) = delete;
+    ~Scratch() {
+        if (!ptrs.empty()) (void)hipStreamSynchronize(ctx->stream);   // also on early error returns
+        for (void* p : ptrs) (void)hipFree(p);
+        if (need > ctx->ws_bytes && need <= kKeepWorkspace) {
+            if (ctx->ws) (void)hipFree(ctx->ws);
+            ctx->ws = nullptr;
+            ctx->ws_bytes = 0;
+            if (hipMalloc(&ctx->ws, need) == hipSuccess) ctx->ws_bytes = need;
+            else (void)hipGetLastError();
+        }
+    }
+    template <typename T>
+    hipError_t get(T** p, size_t count) {
+        const size_t bytes = (sizeof(T) * (count ? count : 1) + 255) & ~(size_t)255;
+        need += bytes;
+        if (ctx->ws && off + bytes <= ctx->ws_bytes) {
+            *p = (T*)((char*)ctx->ws + off);
+            off += bytes;
+            return hipSuccess;
+        }
+        void* q = nullptr;
+        hipError_t e = hipMalloc(&q, bytes);
+        if (e == hipSuccess) ptrs.push_back(q);
+        *p = (T*)q;
+        return e;
+    }
+};
+
 // ---------------------------------------------------------------- launchers (device code)
 
-vg_status build_level(vg_context* ctx, const double* d_xyz, const double* d_cov, int64_t n, double r,
-                      const double origin[3], Level* out);
+// every level of m (its origin is set) from n points; box: their bounding box
+vg_status build_map(vg_context* ctx, Scratch& sc, const double* d_xyz, const double* d_cov, int64_t n,
+                    const double box[6], const double* resolutions, int L, vg_voxelmap* m);
 vg_status export_level(vg_context* ctx, const Level& lv, int64_t* keys, double* means, double* covs,
                        int64_t* counts);
-void free_level(Level* lv);
+void free_map(vg_voxelmap* m);
 
 // frame preprocessing: d_xyz n x 3 FP64 device input; fills every array of *out
 vg_status preprocess_frame(vg_context* ctx, const double* d_xyz, int64_t n, double r, int k, const double sensor[3],

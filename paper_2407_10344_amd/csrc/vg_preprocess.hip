@@ -549,42 +549,41 @@ __global__ void k_cov_normals(const double* __restrict__ xyz, const int32_t* __r
     co[5] = 1.0 - w * nz * nz;
 }
 
-int grid_of(int64_t n, int b = 256) { return (int)((n + b - 1) / b); }
+// Bounding box of the m points (min, max), then point 0; one workgroup (tens of
+// thousands of points), written to pinned host memory.
+__global__ __launch_bounds__(1024) void k_cloud_box(const double* __restrict__ xyz, int64_t m, double* __restrict__ out) {
+    __shared__ double s[16][6];
+    double lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
+    for (int64_t i = threadIdx.x; i < m; i += blockDim.x)
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            lo[a] = fmin(lo[a], xyz[3 * i + a]);
+            hi[a] = fmax(hi[a], xyz[3 * i + a]);
+        }
+#pragma unroll
+    for (int w = 32; w >= 1; w >>= 1)
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            lo[a] = fmin(lo[a], __shfl_xor(lo[a], w));
+            hi[a] = fmax(hi[a], __shfl_xor(hi[a], w));
+        }
+    if ((threadIdx.x & 63) == 0)
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            s[threadIdx.x >> 6][a] = lo[a];
+            s[threadIdx.x >> 6][3 + a] = hi[a];
+        }
+    __syncthreads();
+    if (threadIdx.x < 6) {
+        double v = s[0][threadIdx.x];
+        for (int w = 1; w < 16; ++w) v = threadIdx.x < 3 ? fmin(v, s[w][threadIdx.x]) : fmax(v, s[w][threadIdx.x]);
+        out[threadIdx.x] = v;
+    } else if (threadIdx.x < 9) {
+        out[threadIdx.x] = xyz[threadIdx.x - 6];
+    }
+}
 
-// Temporaries of one preprocessing call, carved from the context's workspace;
-// what does not fit is allocated and freed, and the workspace grows to the
-// call's total afterwards, so frames of similar size allocate nothing.
-struct Scratch {
-    vg_context* ctx;
-    size_t off = 0, need = 0;
-    std::vector<void*> ptrs;
-    explicit Scratch(vg_context* c) : ctx(c) {}
-    ~Scratch() {
-        (void)hipStreamSynchronize(ctx->stream);   // also on early error returns
-        for (void* p : ptrs) (void)hipFree(p);
-        if (need > ctx->ws_bytes) {
-            if (ctx->ws) (void)hipFree(ctx->ws);
-            ctx->ws = nullptr;
-            ctx->ws_bytes = 0;
-            if (hipMalloc(&ctx->ws, need) == hipSuccess) ctx->ws_bytes = need;
-        }
-    }
-    template <typename T>
-    hipError_t get(T** p, size_t count) {
-        const size_t bytes = (sizeof(T) * (count ? count : 1) + 255) & ~(size_t)255;
-        need += bytes;
-        if (ctx->ws && off + bytes <= ctx->ws_bytes) {
-            *p = (T*)((char*)ctx->ws + off);
-            off += bytes;
-            return hipSuccess;
-        }
-        void* q = nullptr;
-        hipError_t e = hipMalloc(&q, bytes);
-        if (e == hipSuccess) ptrs.push_back(q);
-        *p = (T*)q;
-        return e;
-    }
-};
+int grid_of(int64_t n, int b = 256) { return (int)((n + b - 1) / b); }
 
 // every output array of a cloud in one allocation
 hipError_t alloc_cloud(vg_cloud* c, int64_t m, int k) {
@@ -747,8 +746,13 @@ vg_status preprocess_frame(vg_context* ctx, const double* d_xyz, int64_t n, doub
     k_cov_normals<<<grid_of(m), 256, 0, st>>>(out->xyz, out->nbr, m, k, sensor[0], sensor[1], sensor[2], out->cov,
                                                out->cov_raw, out->nrm);
     VG_HIP(hipGetLastError());
-    VG_HIP(hipMemcpyAsync(out->first, out->xyz, sizeof(double) * 3, hipMemcpyDeviceToHost, st));
+    // the points' bounding box and point 0, for the sources and maps made from the cloud
+    double* h_out = reinterpret_cast<double*>(ctx->h_small);
+    k_cloud_box<<<1, 1024, 0, st>>>(out->xyz, m, h_out);
+    VG_HIP(hipGetLastError());
     VG_HIP(hipStreamSynchronize(st));
+    for (int a = 0; a < 6; ++a) out->box[a] = h_out[a];
+    for (int a = 0; a < 3; ++a) out->first[a] = h_out[6 + a];
     return VG_OK;
 }
 

@@ -2,12 +2,19 @@
 // x falls in voxel floor(x / r); a voxel stores the average of its points' means
 // and the average of their covariances.
 //
-// Device pipeline per level: FP64 keys -> stable radix sort of (key, point) ->
-// run-length encoding -> one thread per voxel sums its run in ascending point
-// order in FP64 (deterministic, identical summation order for every build) ->
-// records in three layouts -> open-addressing insert with 64-bit atomicCAS.
+// Device pipeline, all levels of a map together (a level's pass over a submap is
+// a few microseconds of work behind ~25 launches, so the launches are shared):
+// one 64-bit word per (level, point) holding level | block | voxel in block |
+// point -> one sort -> one scan that numbers the voxels and the blocks -> the
+// level sizes go to the host (the build's only synchronization), one allocation
+// -> voxel sums in ascending point order in FP64 (deterministic) -> records in
+// three layouts -> open-addressing insert of the blocks with 64-bit atomicCAS.
+// Bound by launches and their gaps.  A 128-ring sweep (four levels, 40k points)
+// from raw points to its first linearization: 3.91 ms with two sorts, 25 launches,
+// three synchronizations and 18 allocations per level, 2.96 ms with this.
 #include <hipcub/hipcub.hpp>
 
+#include <algorithm>
 #include <climits>
 #include <vector>
 
@@ -15,295 +22,407 @@
 
 namespace vg {
 
-__global__ void k_level_keys(const double* __restrict__ xyz, int64_t n, double r, int64_t K0x, int64_t K0y,
-                             int64_t K0z, uint64_t* __restrict__ keys, int32_t* __restrict__ idx,
-                             int32_t* __restrict__ flag) {
+// One level as the build kernels see it.
+struct BuildLevel {
+    double r;
+    int64_t K0[3];        // absolute key of the map origin
+    int32_t bmin[3];      // first block per axis (biased block coordinates)
+    int32_t wy, wz;       // bits of the block's y and z offsets in a code
+    int32_t v0, b0;       // first voxel / block of the level among all levels'
+    uint32_t log2cap;
+    uint64_t* slots;
+    float* rec32;
+    float* recN;
+    double* rec64;
+    uint64_t* keys;
+    int32_t* counts;
+};
+struct BuildLevels {
+    BuildLevel lv[kMaxLevels];
+    int32_t L;
+    int32_t code_bits;    // a code: level << code_bits | block offsets << 6 | voxel in the block
+    int32_t idx_bits;     // low bits of a sort word that hold the point (0: a separate array)
+};
+
+// Voxel code of a biased voxel key inside a level: (block offsets from the
+// level's first block) << 6 | position in the block.  Ascending codes are
+// ascending blocks (x, y, z), voxels x fastest inside a block: record order.
+__device__ __forceinline__ uint64_t voxel_code(const BuildLevel& b, uint32_t ux, uint32_t uy, uint32_t uz) {
+    const uint64_t x = (ux >> kBlockShift) - (uint32_t)b.bmin[0], y = (uy >> kBlockShift) - (uint32_t)b.bmin[1],
+                   z = (uz >> kBlockShift) - (uint32_t)b.bmin[2];
+    return (((((x << b.wy) | y) << b.wz) | z) << 6) | block_local(ux, uy, uz);
+}
+
+__device__ __forceinline__ void code_key(const BuildLevel& b, uint64_t code, uint32_t u[3]) {
+    const uint32_t local = (uint32_t)code & 63u;
+    const uint64_t blk = code >> 6;
+    const uint32_t z = (uint32_t)(blk & ((1ull << b.wz) - 1)), y = (uint32_t)((blk >> b.wz) & ((1ull << b.wy) - 1)),
+                   x = (uint32_t)(blk >> (b.wz + b.wy));
+    u[0] = ((x + (uint32_t)b.bmin[0]) << kBlockShift) | (local & 3u);
+    u[1] = ((y + (uint32_t)b.bmin[1]) << kBlockShift) | ((local >> 2) & 3u);
+    u[2] = ((z + (uint32_t)b.bmin[2]) << kBlockShift) | (local >> 4);
+}
+
+// Sort word of every (level, point).  Bound by its reads of xyz (24 B per point);
+// the key range was checked on the host from the cloud's bounding box (floor and
+// division are monotone), so nothing is flagged here.
+__global__ void k_map_codes(const double* __restrict__ xyz, int64_t n, BuildLevels B, uint64_t* __restrict__ word,
+                            int32_t* __restrict__ idx) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
-    const int64_t kx = (int64_t)floor(xyz[3 * i + 0] / r) - K0x;
-    const int64_t ky = (int64_t)floor(xyz[3 * i + 1] / r) - K0y;
-    const int64_t kz = (int64_t)floor(xyz[3 * i + 2] / r) - K0z;
-    if (!(key_in_range(kx) && key_in_range(ky) && key_in_range(kz))) {
-        atomicOr(flag, 1);
-        keys[i] = 0;
+    const double x[3] = {xyz[3 * i], xyz[3 * i + 1], xyz[3 * i + 2]};
+    for (int l = 0; l < B.L; ++l) {
+        const BuildLevel& b = B.lv[l];
+        uint32_t u[3];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) u[a] = (uint32_t)((int64_t)floor(x[a] / b.r) - b.K0[a] + kKeyBias);
+        const uint64_t code = ((uint64_t)l << B.code_bits) | voxel_code(b, u[0], u[1], u[2]);
+        word[(int64_t)l * n + i] = (code << B.idx_bits) | (B.idx_bits ? (uint64_t)i : 0ull);
+        if (idx != nullptr) idx[(int64_t)l * n + i] = (int32_t)i;
+    }
+}
+
+// Heads of the sorted words: 1 in the low word where a voxel starts, 1 in the
+// high word where a block starts.
+struct HeadOf {
+    const uint64_t* word;
+    int32_t idx_bits;
+    __host__ __device__ uint64_t operator()(int64_t i) const {
+        if (i == 0) return (1ull << 32) | 1ull;
+        const uint64_t a = word[i - 1] >> idx_bits, b = word[i] >> idx_bits;
+        return (a != b ? 1ull : 0ull) | ((a >> 6) != (b >> 6) ? 1ull << 32 : 0ull);
+    }
+};
+
+// From the scanned heads: code and first element of every voxel, first voxel of
+// every block; the first voxel and block of every level and the totals go to
+// `info` (pinned host memory, read after the build's one synchronization).
+__global__ void k_map_voxels(const uint64_t* __restrict__ word, const uint64_t* __restrict__ scan, int64_t n, int64_t N,
+                             int32_t idx_bits, uint64_t* __restrict__ vcode, int32_t* __restrict__ vstart,
+                             int32_t* __restrict__ bfirst, int32_t* __restrict__ info) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= N) return;
+    const uint64_t s = scan[i], p = i > 0 ? scan[i - 1] : 0ull;
+    const int32_t v = (int32_t)(uint32_t)s - 1, b = (int32_t)(s >> 32) - 1;
+    if ((uint32_t)s != (uint32_t)p) {
+        vcode[v] = word[i] >> idx_bits;
+        vstart[v] = (int32_t)i;
+        if ((s >> 32) != (p >> 32)) bfirst[b] = v;
+    }
+    if (i % n == 0) {
+        info[2 * (i / n)] = v;
+        info[2 * (i / n) + 1] = b;
+    }
+    if (i == N - 1) {
+        vstart[v + 1] = (int32_t)N;
+        bfirst[b + 1] = v + 1;
+        info[2 * (N / n)] = v + 1;
+        info[2 * (N / n) + 1] = b + 1;
+    }
+}
+
+// Per-voxel statistics: FP64 sums of its points in ascending point order, then the
+// average, written as records in record order.  Nine lanes per voxel, one per
+// component (a point's 3 coordinates and 6 covariances are then two contiguous
+// reads, and the serial FP64 chains of a voxel's components run side by side),
+// with the loads of eight points in flight: a voxel's sum is a chain of dependent
+// additions, and one thread per voxel with one load at a time spent it waiting
+// (65-200 us a level for the coarse levels of a 32-ring sweep and for 1M points).
+constexpr int kVoxPerWave = 7;
+__global__ __launch_bounds__(256) void k_map_stats(const double* __restrict__ xyz, const double* __restrict__ cov,
+                                                   const uint64_t* __restrict__ word, const int32_t* __restrict__ idx,
+                                                   const uint64_t* __restrict__ vcode, const int32_t* __restrict__ vstart,
+                                                   int32_t V, BuildLevels B) {
+    const int lane = threadIdx.x & 63, g = lane / 9, k = lane % 9;
+    const int64_t v = ((int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)) * kVoxPerWave + g;
+    if (g >= kVoxPerWave || v >= V) return;
+    const uint64_t code = vcode[v];
+    const int l = (int)(code >> B.code_bits);
+    const BuildLevel& b = B.lv[l];
+    const int32_t j0 = vstart[v], j1 = vstart[v + 1];
+    const uint64_t mask = (1ull << B.idx_bits) - 1ull;
+    const double* src = k < 3 ? xyz + k : cov + (k - 3);
+    const int64_t stride = k < 3 ? 3 : 6;
+    constexpr int kStep = 8;
+    double s = 0.0;
+    int32_t j = j0;
+    for (; j + kStep <= j1; j += kStep) {
+        double x[kStep];
+#pragma unroll
+        for (int q = 0; q < kStep; ++q) {
+            const int64_t i = idx != nullptr ? (int64_t)idx[j + q] : (int64_t)(word[j + q] & mask);
+            x[q] = src[stride * i];
+        }
+#pragma unroll
+        for (int q = 0; q < kStep; ++q) s += x[q];
+    }
+    {
+        double x[kStep - 1];
+        const int rest = j1 - j;
+#pragma unroll
+        for (int q = 0; q < kStep - 1; ++q)
+            if (q < rest) {
+                const int64_t i = idx != nullptr ? (int64_t)idx[j + q] : (int64_t)(word[j + q] & mask);
+                x[q] = src[stride * i];
+            }
+#pragma unroll
+        for (int q = 0; q < kStep - 1; ++q)
+            if (q < rest) s += x[q];
+    }
+    const int32_t cnt = j1 - j0;
+    const double m = s / (double)cnt;
+    uint32_t u[3];
+    code_key(b, code & ((1ull << B.code_bits) - 1ull), u);
+    const int64_t w = v - b.v0;
+    b.rec64[kRec64 * w + k] = m;
+    b.recN[kRecN * w + k] = (float)m;
+    float* r32 = b.rec32 + kRec32 * w;
+    if (k < 3) {
+        const int64_t q = (int64_t)(k == 0 ? u[0] : (k == 1 ? u[1] : u[2])) - kKeyBias + b.K0[k];
+        const double centre = (double)q * b.r + 0.5 * b.r;
+        r32[k] = (float)(m - centre);
+        b.recN[kRecN * w + 9 + k] = 0.f;
     } else {
-        keys[i] = pack_key(kx, ky, kz);
+        reinterpret_cast<double*>(r32 + 4)[k - 3] = m;   // covariance, FP64 (8-byte aligned: records are 64 B)
     }
-    idx[i] = (int32_t)i;
-}
-
-// Per-voxel statistics of voxel v (canonical = ascending-key order): FP64 sums
-// of its points in ascending point order, then the average; records are
-// written at position pos[v] (block order).
-__global__ void k_level_stats(const double* __restrict__ xyz, const double* __restrict__ cov,
-                              const uint64_t* __restrict__ ukeys, const int32_t* __restrict__ counts,
-                              const int32_t* __restrict__ offsets, const int32_t* __restrict__ sorted_idx,
-                              const int32_t* __restrict__ pos, int64_t V, double r, int64_t K0x, int64_t K0y,
-                              int64_t K0z, float* __restrict__ rec32, float* __restrict__ recN,
-                              double* __restrict__ rec64) {
-    const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (v >= V) return;
-    const int32_t off = offsets[v], cnt = counts[v];
-    double s[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
-    for (int32_t j = off; j < off + cnt; ++j) {
-        const int64_t i = sorted_idx[j];
-        s[0] += xyz[3 * i + 0];
-        s[1] += xyz[3 * i + 1];
-        s[2] += xyz[3 * i + 2];
-#pragma unroll
-        for (int k = 0; k < 6; ++k) s[3 + k] += cov[6 * i + k];
+    if (k == 0) {
+        r32[3] = (float)cnt;
+        b.rec64[kRec64 * w + 9] = 0.0;
+        b.keys[w] = pack_key((int64_t)u[0] - kKeyBias, (int64_t)u[1] - kKeyBias, (int64_t)u[2] - kKeyBias);
+        b.counts[w] = cnt;
     }
-    double m[9];
-#pragma unroll
-    for (int k = 0; k < 9; ++k) m[k] = s[k] / (double)cnt;
-    int64_t q[3];
-    unpack_key(ukeys[v], q);
-    q[0] += K0x;
-    q[1] += K0y;
-    q[2] += K0z;
-    const int64_t w = pos[v];
-    double* r64 = rec64 + kRec64 * w;
-    float* r32 = rec32 + kRec32 * w;
-    double* r32c = reinterpret_cast<double*>(r32 + 4);   // 8-byte aligned: records are 64 B
-    float* rN = recN + kRecN * w;
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        const double centre = (double)q[a] * r + 0.5 * r;
-        r64[a] = m[a];
-        r32[a] = (float)(m[a] - centre);
-        rN[a] = (float)m[a];
-    }
-    r32[3] = (float)cnt;
-#pragma unroll
-    for (int k = 0; k < 6; ++k) {
-        r64[3 + k] = m[3 + k];
-        r32c[k] = m[3 + k];                             // covariance, FP64
-        rN[3 + k] = (float)m[3 + k];
-    }
-    r64[9] = 0.0;
-    rN[9] = 0.f;
-    rN[10] = 0.f;
-    rN[11] = 0.f;
-}
-
-// Block-order sort key of voxel v: (block key << 6) | Morton index inside the block.
-__global__ void k_block_codes(const uint64_t* __restrict__ ukeys, int64_t V, uint64_t* __restrict__ codes,
-                              int32_t* __restrict__ idx) {
-    const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (v >= V) return;
-    int64_t q[3];
-    unpack_key(ukeys[v], q);
-    const uint64_t ux = (uint64_t)(q[0] + kKeyBias), uy = (uint64_t)(q[1] + kKeyBias), uz = (uint64_t)(q[2] + kKeyBias);
-    codes[v] = (block_key(ux, uy, uz) << 6) | block_local(ux, uy, uz);
-    idx[v] = (int32_t)v;
-}
-
-// pos[canonical index] = record position, and the block key of every record.
-__global__ void k_block_scatter(const uint64_t* __restrict__ codes_sorted, const int32_t* __restrict__ idx_sorted,
-                                int64_t V, int32_t* __restrict__ pos, uint64_t* __restrict__ bkeys) {
-    const int64_t m = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (m >= V) return;
-    pos[idx_sorted[m]] = (int32_t)m;
-    bkeys[m] = codes_sorted[m] >> 6;
 }
 
 // One thread per occupied block: occupancy mask of its records, then insertion
-// of (block key | first record, mask) into the block table.
-__global__ void k_block_insert(const uint64_t* __restrict__ ublocks, const int32_t* __restrict__ bcounts,
-                               const int32_t* __restrict__ boffsets, const uint64_t* __restrict__ codes_sorted,
-                               int64_t NB, uint64_t* __restrict__ slots, uint32_t log2cap) {
-    const int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= NB) return;
-    const int32_t base = boffsets[b], cnt = bcounts[b];
+// of (block key | first record, mask) into the block table of its level.
+__global__ void k_map_blocks(const uint64_t* __restrict__ vcode, const int32_t* __restrict__ bfirst, int32_t NB,
+                             BuildLevels B) {
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (t >= NB) return;
+    const int32_t v0 = bfirst[t], v1 = bfirst[t + 1];
     uint64_t occ = 0;
-    for (int32_t m = base; m < base + cnt; ++m) occ |= 1ull << (codes_sorted[m] & 63);
-    const uint64_t key = ublocks[b];
-    const uint64_t word = (key << kBaseBits) | (uint64_t)base;
-    const uint32_t mask = (1u << log2cap) - 1u;
-    uint32_t h = slot_of(key, log2cap);
+    for (int32_t v = v0; v < v1; ++v) occ |= 1ull << (vcode[v] & 63);
+    const uint64_t code = vcode[v0];
+    const BuildLevel& b = B.lv[code >> B.code_bits];
+    uint32_t u[3];
+    code_key(b, code & ((1ull << B.code_bits) - 1ull), u);
+    const uint64_t key = block_key(u[0], u[1], u[2]);
+    const uint64_t entry = (key << kBaseBits) | (uint64_t)(v0 - b.v0);
+    const uint32_t mask = (1u << b.log2cap) - 1u;
+    uint32_t h = slot_of(key, b.log2cap);
     for (uint32_t it = 0; it <= mask; ++it) {
-        const unsigned long long prev = atomicCAS((unsigned long long*)(slots + 2 * (uint64_t)h),
-                                                  (unsigned long long)kEmpty, (unsigned long long)word);
+        const unsigned long long prev = atomicCAS((unsigned long long*)(b.slots + 2 * (uint64_t)h),
+                                                  (unsigned long long)kEmpty, (unsigned long long)entry);
         if (prev == (unsigned long long)kEmpty) {
-            slots[2 * (uint64_t)h + 1] = occ;
+            b.slots[2 * (uint64_t)h + 1] = occ;
             return;
         }
         h = (h + 1u) & mask;
     }
 }
 
-// Bounding box of the level's relative keys (box[0..2] = min, box[3..5] = max).
-__global__ void k_level_bbox(const uint64_t* __restrict__ ukeys, int64_t V, int32_t* __restrict__ box) {
-    const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (v >= V) return;
-    int64_t q[3];
-    unpack_key(ukeys[v], q);
-    for (int a = 0; a < 3; ++a) {
-        atomicMin(box + a, (int32_t)q[a]);
-        atomicMax(box + 3 + a, (int32_t)q[a]);
-    }
+// 16-byte fill (table entries).
+__global__ void k_fill_entries(u64x2* p, int64_t n, uint64_t v) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) p[i] = u64x2{v, v};
 }
 
-__global__ void k_fill_u64(uint64_t* p, int64_t n, uint64_t v) {
+__global__ void k_iota(int32_t* p, int64_t n) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = v;
+    if (i < n) p[i] = (int32_t)i;
 }
 
 static int grid_of(int64_t n, int b = 256) { return (int)((n + b - 1) / b); }
 
-namespace {
-// Device scratch owned by one build call.
-struct Scratch {
-    std::vector<void*> ptrs;
-    ~Scratch() {
-        for (void* p : ptrs) (void)hipFree(p);
-    }
-    template <typename T>
-    hipError_t get(T** p, size_t count) {
-        void* q = nullptr;
-        hipError_t e = hipMalloc(&q, sizeof(T) * (count ? count : 1));
-        if (e == hipSuccess) ptrs.push_back(q);
-        *p = (T*)q;
-        return e;
-    }
-};
-}  // namespace
+static int bits_for(uint64_t max_value) {
+    int b = 0;
+    while (b < 64 && (max_value >> b) != 0) ++b;
+    return b;
+}
 
-vg_status build_level(vg_context* ctx, const double* d_xyz, const double* d_cov, int64_t n, double r,
-                      const double origin[3], Level* out) {
+static size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
+
+// Levels [l0, l0 + L) of a map, built together: box is the cloud's bounding box
+// (min xyz, max xyz).  The arrays of these levels are one allocation, *block.
+static vg_status build_levels(vg_context* ctx, Scratch& sc, const double* d_xyz, const double* d_cov, int64_t n,
+                              const double box[6], Level* lv, int L, void** block) {
     hipStream_t st = ctx->stream;
-    out->r = r;
-    for (int a = 0; a < 3; ++a) out->K0[a] = (int64_t)llround(origin[a] / r);
-    out->V = 0;
-    out->n_blocks = 0;
-    Scratch sc;
-    int32_t* d_small = nullptr;   // flag, run counts, bbox
-    VG_HIP(sc.get(&d_small, 64));
-    if (n > 0) {
-        uint64_t *keys_in, *keys_out, *ukeys, *codes, *codes_sorted, *bkeys, *ublocks;
-        int32_t *idx_in, *idx_out, *counts, *offsets, *vidx, *vidx_sorted, *pos, *bcounts, *boffsets;
-        VG_HIP(sc.get(&keys_in, n));
-        VG_HIP(sc.get(&keys_out, n));
-        VG_HIP(sc.get(&idx_in, n));
-        VG_HIP(sc.get(&idx_out, n));
-        VG_HIP(sc.get(&counts, n));
-        VG_HIP(sc.get(&offsets, n));
-        size_t tmp_bytes = 0, b2 = 0, b3 = 0;
-        (void)hipcub::DeviceRadixSort::SortPairs(nullptr, tmp_bytes, keys_in, keys_out, idx_in, idx_out, (int)n, 0,
-                                                 3 * kKeyBits);
-        (void)hipcub::DeviceRunLengthEncode::Encode(nullptr, b2, keys_out, keys_in, counts, d_small, (int)n);
-        (void)hipcub::DeviceScan::ExclusiveSum(nullptr, b3, counts, offsets, (int)n);
-        tmp_bytes = std::max(tmp_bytes, std::max(b2, b3)) + 256;
-        void* tmp = nullptr;
-        VG_HIP(sc.get((char**)&tmp, tmp_bytes));
-        // 1. keys of every point, stable sort by key, runs = voxels
-        VG_HIP(hipMemsetAsync(d_small, 0, sizeof(int32_t), st));
-        k_level_keys<<<grid_of(n), 256, 0, st>>>(d_xyz, n, r, out->K0[0], out->K0[1], out->K0[2], keys_in, idx_in,
-                                                 d_small);
-        VG_HIP(hipGetLastError());
-        int32_t h_flag = 0;
-        VG_HIP(hipMemcpyAsync(&h_flag, d_small, sizeof(int32_t), hipMemcpyDeviceToHost, st));
-        VG_HIP(hipStreamSynchronize(st));
-        if (h_flag) {
-            set_error("voxel key outside the packable range (|q - q_origin| >= 8192 voxels on an axis)");
-            return VG_ERR_KEY_RANGE;
+    BuildLevels B{};
+    B.L = L;
+    int code_bits = 0;
+    for (int l = 0; l < L; ++l) {
+        Level& q = lv[l];
+        BuildLevel& b = B.lv[l];
+        b.r = q.r;
+        int32_t nb[3];
+        for (int a = 0; a < 3; ++a) {
+            b.K0[a] = q.K0[a];
+            const double lo = std::floor(box[a] / q.r), hi = std::floor(box[3 + a] / q.r);
+            // the difference to the origin's key in double first: it may not fit an integer
+            if (!(lo - (double)q.K0[a] >= -(double)kKeyBias && hi - (double)q.K0[a] < (double)kKeyBias)) {
+                set_error("voxel key outside the packable range (|q - q_origin| >= 8192 voxels on an axis)");
+                return VG_ERR_KEY_RANGE;
+            }
+            q.kmin[a] = (int32_t)((int64_t)lo - q.K0[a]);
+            q.kmax[a] = (int32_t)((int64_t)hi - q.K0[a]);
+            b.bmin[a] = (q.kmin[a] + kKeyBias) >> kBlockShift;
+            nb[a] = ((q.kmax[a] + kKeyBias) >> kBlockShift) - b.bmin[a];
         }
-        size_t tb = tmp_bytes;
-        VG_HIP(hipcub::DeviceRadixSort::SortPairs(tmp, tb, keys_in, keys_out, idx_in, idx_out, (int)n, 0,
-                                                  3 * kKeyBits, st));
-        VG_HIP(sc.get(&ukeys, n));
-        tb = tmp_bytes;
-        VG_HIP(hipcub::DeviceRunLengthEncode::Encode(tmp, tb, keys_out, ukeys, counts, d_small + 1, (int)n, st));
-        int32_t V = 0;
-        VG_HIP(hipMemcpyAsync(&V, d_small + 1, sizeof(int32_t), hipMemcpyDeviceToHost, st));
-        VG_HIP(hipStreamSynchronize(st));
-        if (V > kMaxVoxels) {
+        b.wy = bits_for((uint64_t)nb[1]);
+        b.wz = bits_for((uint64_t)nb[2]);
+        code_bits = std::max(code_bits, bits_for((uint64_t)nb[0]) + b.wy + b.wz + 6);
+    }
+    const int64_t N = n * L;
+    B.code_bits = code_bits;
+    const int word_bits = code_bits + bits_for((uint64_t)(L - 1));
+    const int ib = bits_for((uint64_t)(n - 1));
+    // the point rides in the word's low bits where they fit (a stable sort by code
+    // in one array); otherwise words and points are sorted as pairs
+    const bool packed = word_bits + ib <= 64;
+    B.idx_bits = packed ? ib : 0;
+    uint64_t *w0, *w1, *scan, *vcode;
+    int32_t *i0 = nullptr, *i1 = nullptr, *vstart, *bfirst;
+    VG_HIP(sc.get(&w0, N));
+    VG_HIP(sc.get(&w1, N));
+    VG_HIP(sc.get(&scan, N));
+    VG_HIP(sc.get(&vcode, N));
+    VG_HIP(sc.get(&vstart, N + 1));
+    VG_HIP(sc.get(&bfirst, N + 1));
+    if (!packed) {
+        VG_HIP(sc.get(&i0, N));
+        VG_HIP(sc.get(&i1, N));
+    }
+    const int end_bit = std::max(1, word_bits + B.idx_bits);
+    size_t b1 = 0, b2 = 0;
+    const hipcub::CountingInputIterator<int64_t> cnt(0);
+    const hipcub::TransformInputIterator<uint64_t, HeadOf, hipcub::CountingInputIterator<int64_t>> heads(
+        cnt, HeadOf{w1, B.idx_bits});
+    if (packed) (void)hipcub::DeviceRadixSort::SortKeys(nullptr, b1, w0, w1, (int)N, B.idx_bits, end_bit);
+    else (void)hipcub::DeviceRadixSort::SortPairs(nullptr, b1, w0, w1, i0, i1, (int)N, 0, end_bit);
+    (void)hipcub::DeviceScan::InclusiveSum(nullptr, b2, heads, scan, (int)N);
+    size_t tmp_bytes = std::max(b1, b2) + 256;
+    char* tmp = nullptr;
+    VG_HIP(sc.get(&tmp, tmp_bytes));
+    k_map_codes<<<grid_of(n), 256, 0, st>>>(d_xyz, n, B, w0, i0);
+    VG_HIP(hipGetLastError());
+    size_t tb = tmp_bytes;
+    if (packed) VG_HIP(hipcub::DeviceRadixSort::SortKeys(tmp, tb, w0, w1, (int)N, B.idx_bits, end_bit, st));
+    else VG_HIP(hipcub::DeviceRadixSort::SortPairs(tmp, tb, w0, w1, i0, i1, (int)N, 0, end_bit, st));
+    tb = tmp_bytes;
+    VG_HIP(hipcub::DeviceScan::InclusiveSum(tmp, tb, heads, scan, (int)N, st));
+    int32_t* info = ctx->h_small;
+    k_map_voxels<<<grid_of(N), 256, 0, st>>>(w1, scan, n, N, B.idx_bits, vcode, vstart, bfirst, info);
+    VG_HIP(hipGetLastError());
+    VG_HIP(hipStreamSynchronize(st));
+    size_t bytes = 0;
+    const int32_t V_all = info[2 * L], NB_all = info[2 * L + 1];
+    for (int l = 0; l < L; ++l) {
+        Level& q = lv[l];
+        q.V = info[2 * (l + 1)] - info[2 * l];
+        q.n_blocks = info[2 * (l + 1) + 1] - info[2 * l + 1];
+        if (q.V > kMaxVoxels) {
             set_error("too many voxels in one level");
             return VG_ERR_CAPACITY;
         }
-        tb = tmp_bytes;
-        VG_HIP(hipcub::DeviceScan::ExclusiveSum(tmp, tb, counts, offsets, V, st));
-        out->V = V;
-        // 2. block order of the voxels and their record positions
-        VG_HIP(sc.get(&codes, V));
-        VG_HIP(sc.get(&codes_sorted, V));
-        VG_HIP(sc.get(&vidx, V));
-        VG_HIP(sc.get(&vidx_sorted, V));
-        VG_HIP(sc.get(&bkeys, V));
-        VG_HIP(sc.get(&ublocks, V));
-        VG_HIP(sc.get(&bcounts, V));
-        VG_HIP(sc.get(&boffsets, V));
-        VG_HIP(hipMalloc(&out->lex2rec, sizeof(int32_t) * (size_t)V));
-        pos = out->lex2rec;
-        k_block_codes<<<grid_of(V), 256, 0, st>>>(ukeys, V, codes, vidx);
-        VG_HIP(hipGetLastError());
-        tb = tmp_bytes;
-        VG_HIP(hipcub::DeviceRadixSort::SortPairs(tmp, tb, codes, codes_sorted, vidx, vidx_sorted, V, 0,
-                                                  3 * kBlockBits + 6, st));
-        k_block_scatter<<<grid_of(V), 256, 0, st>>>(codes_sorted, vidx_sorted, V, pos, bkeys);
-        VG_HIP(hipGetLastError());
-        tb = tmp_bytes;
-        VG_HIP(hipcub::DeviceRunLengthEncode::Encode(tmp, tb, bkeys, ublocks, bcounts, d_small + 2, V, st));
-        int32_t NB = 0;
-        VG_HIP(hipMemcpyAsync(&NB, d_small + 2, sizeof(int32_t), hipMemcpyDeviceToHost, st));
-        VG_HIP(hipStreamSynchronize(st));
-        tb = tmp_bytes;
-        VG_HIP(hipcub::DeviceScan::ExclusiveSum(tmp, tb, bcounts, boffsets, NB, st));
-        out->n_blocks = NB;
-        // 3. records in block order
-        VG_HIP(hipMalloc(&out->rec32, sizeof(float) * kRec32 * (size_t)V));
-        VG_HIP(hipMalloc(&out->recN, sizeof(float) * kRecN * (size_t)V));
-        VG_HIP(hipMalloc(&out->rec64, sizeof(double) * kRec64 * (size_t)V));
-        VG_HIP(hipMalloc(&out->keys, sizeof(uint64_t) * (size_t)V));
-        VG_HIP(hipMalloc(&out->counts, sizeof(int32_t) * (size_t)V));
-        k_level_stats<<<grid_of(V), 256, 0, st>>>(d_xyz, d_cov, ukeys, counts, offsets, idx_out, pos, V, r,
-                                                  out->K0[0], out->K0[1], out->K0[2], out->rec32, out->recN,
-                                                  out->rec64);
-        VG_HIP(hipGetLastError());
-        VG_HIP(hipMemcpyAsync(out->keys, ukeys, sizeof(uint64_t) * V, hipMemcpyDeviceToDevice, st));
-        VG_HIP(hipMemcpyAsync(out->counts, counts, sizeof(int32_t) * V, hipMemcpyDeviceToDevice, st));
-        // 4. block table: power of two >= 4 x blocks (load factor <= 1/4)
+        B.lv[l].v0 = info[2 * l];
+        B.lv[l].b0 = info[2 * l + 1];
+        // block table: power of two >= 4 x blocks (load factor <= 1/4)
         uint32_t lg = 6;
-        while ((1ull << lg) < 4ull * (uint64_t)NB) ++lg;
-        out->log2cap = lg;
-        const int64_t cap = 1ll << lg;
-        VG_HIP(hipMalloc(&out->slots, sizeof(uint64_t) * 2 * (size_t)cap));
-        k_fill_u64<<<grid_of(2 * cap), 256, 0, st>>>(out->slots, 2 * cap, kEmpty);
-        VG_HIP(hipGetLastError());
-        k_block_insert<<<grid_of(NB), 256, 0, st>>>(ublocks, bcounts, boffsets, codes_sorted, NB, out->slots, lg);
-        VG_HIP(hipGetLastError());
-        // 5. key bounding box
-        int32_t h_box[6] = {INT32_MAX, INT32_MAX, INT32_MAX, INT32_MIN, INT32_MIN, INT32_MIN};
-        VG_HIP(hipMemcpyAsync(d_small + 8, h_box, sizeof(h_box), hipMemcpyHostToDevice, st));
-        k_level_bbox<<<grid_of(V), 256, 0, st>>>(ukeys, V, d_small + 8);
-        VG_HIP(hipGetLastError());
-        VG_HIP(hipMemcpyAsync(h_box, d_small + 8, sizeof(h_box), hipMemcpyDeviceToHost, st));
-        VG_HIP(hipStreamSynchronize(st));
-        for (int a = 0; a < 3; ++a) {
-            out->kmin[a] = h_box[a];
-            out->kmax[a] = h_box[3 + a];
-        }
-    } else {
-        out->log2cap = 6;
-        VG_HIP(hipMalloc(&out->slots, sizeof(uint64_t) * 2 * 64));
-        k_fill_u64<<<1, 128, 0, st>>>(out->slots, 128, kEmpty);
-        VG_HIP(hipGetLastError());
+        while ((1ull << lg) < 4ull * (uint64_t)q.n_blocks) ++lg;
+        q.log2cap = lg;
+        bytes += 16ull << lg;
     }
-    VG_HIP(hipStreamSynchronize(st));
+    const size_t table_bytes = bytes;   // every level's table first, so that one fill covers them
+    for (int l = 0; l < L; ++l)
+        bytes += align256(4 * kRec32 * (size_t)lv[l].V) + align256(4 * kRecN * (size_t)lv[l].V) +
+                 align256(8 * kRec64 * (size_t)lv[l].V) + align256(8 * (size_t)lv[l].V) + align256(4 * (size_t)lv[l].V);
+    VG_HIP(hipMalloc(block, bytes));
+    char* p = (char*)*block;
+    for (int l = 0; l < L; ++l) {
+        lv[l].slots = (uint64_t*)p;
+        p += 16ull << lv[l].log2cap;
+    }
+    for (int l = 0; l < L; ++l) {
+        Level& q = lv[l];
+        const size_t V = (size_t)q.V;
+        auto take = [&](size_t b) { char* r = p; p += align256(b); return r; };
+        q.rec32 = (float*)take(4 * kRec32 * V);
+        q.recN = (float*)take(4 * kRecN * V);
+        q.rec64 = (double*)take(8 * kRec64 * V);
+        q.keys = (uint64_t*)take(8 * V);
+        q.counts = (int32_t*)take(4 * V);
+        BuildLevel& b = B.lv[l];
+        b.log2cap = q.log2cap;
+        b.slots = q.slots;
+        b.rec32 = q.rec32;
+        b.recN = q.recN;
+        b.rec64 = q.rec64;
+        b.keys = q.keys;
+        b.counts = q.counts;
+    }
+    k_fill_entries<<<grid_of((int64_t)(table_bytes / 16)), 256, 0, st>>>((u64x2*)*block, (int64_t)(table_bytes / 16), kEmpty);
+    VG_HIP(hipGetLastError());
+    k_map_stats<<<grid_of(V_all, 4 * kVoxPerWave), 256, 0, st>>>(d_xyz, d_cov, w1, i1, vcode, vstart, V_all, B);
+    VG_HIP(hipGetLastError());
+    k_map_blocks<<<grid_of(NB_all), 256, 0, st>>>(vcode, bfirst, NB_all, B);
+    VG_HIP(hipGetLastError());
     return VG_OK;
 }
 
+vg_status build_map(vg_context* ctx, Scratch& sc, const double* d_xyz, const double* d_cov, int64_t n,
+                    const double box[6], const double* resolutions, int L, vg_voxelmap* m) {
+    for (int l = 0; l < L; ++l) {
+        m->lv[l].r = resolutions[l];
+        for (int a = 0; a < 3; ++a) m->lv[l].K0[a] = (int64_t)llround(m->origin[a] / resolutions[l]);
+    }
+    if (n == 0) {
+        constexpr size_t kTable = 16 * 64;
+        VG_HIP(hipMalloc(&m->blocks[0], kTable * L));
+        k_fill_entries<<<1, 64 * L, 0, ctx->stream>>>((u64x2*)m->blocks[0], 64 * L, kEmpty);
+        VG_HIP(hipGetLastError());
+        for (int l = 0; l < L; ++l) {
+            m->lv[l].log2cap = 6;
+            m->lv[l].slots = (uint64_t*)((char*)m->blocks[0] + kTable * l);
+        }
+        return VG_OK;
+    }
+    // all levels in one go; clouds too large for the library's 32-bit item counts level by level
+    if (n * L < (int64_t)1 << 30) return build_levels(ctx, sc, d_xyz, d_cov, n, box, m->lv, L, &m->blocks[0]);
+    for (int l = 0; l < L; ++l) {
+        Scratch one(ctx);
+        const vg_status rc = build_levels(ctx, one, d_xyz, d_cov, n, box, m->lv + l, 1, &m->blocks[l]);
+        if (rc != VG_OK) return rc;
+    }
+    return VG_OK;
+}
+
+// A level in canonical order (ascending lexicographic key): its records are in
+// block order, and no kernel needs the canonical one, so the rows are ordered here.
 vg_status export_level(vg_context* ctx, const Level& lv, int64_t* keys, double* means, double* covs,
                        int64_t* counts) {
     hipStream_t st = ctx->stream;
     const int64_t V = lv.V;
     if (V == 0) return VG_OK;
+    Scratch sc(ctx);
+    uint64_t* ks = nullptr;
+    int32_t *id = nullptr, *order = nullptr;
+    char* tmp = nullptr;
+    size_t tb = 0;
+    (void)hipcub::DeviceRadixSort::SortPairs(nullptr, tb, lv.keys, ks, id, order, (int)V, 0, 3 * kKeyBits);
+    VG_HIP(sc.get(&ks, V));
+    VG_HIP(sc.get(&id, V));
+    VG_HIP(sc.get(&order, V));
+    VG_HIP(sc.get(&tmp, tb + 256));
+    k_iota<<<grid_of(V), 256, 0, st>>>(id, V);
+    VG_HIP(hipGetLastError());
+    tb += 256;
+    VG_HIP(hipcub::DeviceRadixSort::SortPairs(tmp, tb, lv.keys, ks, id, order, (int)V, 0, 3 * kKeyBits, st));
     std::vector<uint64_t> k((size_t)V);
     std::vector<int32_t> c((size_t)V), l2r((size_t)V);
     std::vector<double> r((size_t)V * kRec64);
-    VG_HIP(hipMemcpyAsync(k.data(), lv.keys, sizeof(uint64_t) * V, hipMemcpyDeviceToHost, st));
+    VG_HIP(hipMemcpyAsync(k.data(), ks, sizeof(uint64_t) * V, hipMemcpyDeviceToHost, st));
     VG_HIP(hipMemcpyAsync(c.data(), lv.counts, sizeof(int32_t) * V, hipMemcpyDeviceToHost, st));
-    VG_HIP(hipMemcpyAsync(l2r.data(), lv.lex2rec, sizeof(int32_t) * V, hipMemcpyDeviceToHost, st));
+    VG_HIP(hipMemcpyAsync(l2r.data(), order, sizeof(int32_t) * V, hipMemcpyDeviceToHost, st));
     VG_HIP(hipMemcpyAsync(r.data(), lv.rec64, sizeof(double) * kRec64 * V, hipMemcpyDeviceToHost, st));
     VG_HIP(hipStreamSynchronize(st));
     for (int64_t v = 0; v < V; ++v) {
@@ -316,20 +435,17 @@ vg_status export_level(vg_context* ctx, const Level& lv, int64_t* keys, double* 
             for (int a = 0; a < 3; ++a) means[3 * v + a] = r[kRec64 * w + a];
         if (covs)
             for (int a = 0; a < 6; ++a) covs[6 * v + a] = r[kRec64 * w + 3 + a];
-        if (counts) counts[v] = c[v];
+        if (counts) counts[v] = c[w];
     }
     return VG_OK;
 }
 
-void free_level(Level* lv) {
-    if (lv->slots) (void)hipFree(lv->slots);
-    if (lv->rec32) (void)hipFree(lv->rec32);
-    if (lv->recN) (void)hipFree(lv->recN);
-    if (lv->rec64) (void)hipFree(lv->rec64);
-    if (lv->keys) (void)hipFree(lv->keys);
-    if (lv->counts) (void)hipFree(lv->counts);
-    if (lv->lex2rec) (void)hipFree(lv->lex2rec);
-    *lv = Level{};
+void free_map(vg_voxelmap* m) {
+    for (int l = 0; l < kMaxLevels; ++l) {
+        if (m->blocks[l]) (void)hipFree(m->blocks[l]);
+        m->blocks[l] = nullptr;
+        m->lv[l] = Level{};
+    }
 }
 
 // ---------------------------------------------------------------- source clouds
