@@ -218,6 +218,12 @@ vg_status vg_cloud_destroy(vg_cloud* cloud);
 vg_status vg_create_factor_batch(vg_context* ctx, int64_t F, vg_source* const* src,
                                  vg_voxelmap* const* tgt, const double* target_viewpoints,
                                  const vg_batch_options* opts, vg_batch** out);
+/* vg_source_set_points_async for every source of a batch at once: d_points holds
+ * the positions of the batch's distinct sources, concatenated in order of first
+ * use (the rows of vg_backward_async's point gradient), each in caller order
+ * (n_total x 3; dtype 0 = float32, 1 = float64).  One launch on the context
+ * stream. */
+vg_status vg_batch_set_points_async(vg_batch* batch, const void* d_points, int32_t dtype);
 /* Shape of a batch: total source points, number of work tiles, and the launch
  * shape in use (block threads, tile points, workgroups of a launch, tile order).
  * Any output may be NULL. */

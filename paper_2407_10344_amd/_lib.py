@@ -78,6 +78,7 @@ SIGNATURES = {
     "vg_build_voxelmap_from_cloud": (C.c_int, [P, P, P, I32, P]),
     "vg_cloud_destroy": (C.c_int, [P]),
     "vg_create_factor_batch": (C.c_int, [P, I64, P, P, P, P, P]),
+    "vg_batch_set_points_async": (C.c_int, [P, P, I32]),
     "vg_batch_info": (C.c_int, [P, P, P, P, P, P, P]),
     "vg_batch_destroy": (C.c_int, [P]),
     "vg_linearize": (C.c_int, [P, P, P, P, P, P]),

@@ -15,16 +15,6 @@ import torch
 from .vgicp import FactorBatch
 
 
-def _set_points(batch: FactorBatch, points: torch.Tensor):
-    seen = set()
-    for s in batch.sources:
-        if id(s) in seen:
-            continue
-        seen.add(id(s))
-        row0, n = batch.source_rows[id(s)]
-        s.set_points(points[row0:row0 + n])
-
-
 class VGICPCost(torch.autograd.Function):
     """e = VGICPCost.apply(xi, points, batch, T0).
 
@@ -38,7 +28,7 @@ class VGICPCost(torch.autograd.Function):
     @staticmethod
     def forward(ctx, xi, points, batch: FactorBatch, T0):
         points = points.contiguous()
-        _set_points(batch, points)
+        batch.set_points(points[:batch.grad_rows])
         T, jr = batch.ctx.se3_retract(T0, xi, jacobian=True)
         e = batch.evaluate_async(T)
         ctx.batch = batch
@@ -49,7 +39,7 @@ class VGICPCost(torch.autograd.Function):
     def backward(ctx, grad_e):
         T, jr, points = ctx.saved_tensors
         batch = ctx.batch
-        _set_points(batch, points)
+        batch.set_points(points[:batch.grad_rows])
         want_pts = ctx.needs_input_grad[1]
         gxi, gp = batch.backward_async(T, grad_e, jr=jr, points_dtype=points.dtype if want_pts else None)
         return (gxi if ctx.needs_input_grad[0] else None), gp, None, None

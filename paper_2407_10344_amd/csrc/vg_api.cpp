@@ -354,39 +354,43 @@ extern "C" vg_status vg_voxelmap_destroy(vg_voxelmap* map) {
 
 // ============================================================================ sources
 
-static void free_source(vg_source* s) {
-    dfree(s->dxyz);
-    dfree(s->cov);
-    dfree(s->nrm);
-    dfree(s->anchor);
-    dfree(s->cbound);
-    dfree(s->axyz);
-    dfree(s->xyz64);
-    dfree(s->cov64);
-    dfree(s->nrm64);
-    dfree(s->perm);
-}
-
-// Upper bound of |mu - origin| over a source's points from its chunk anchors
-// and ball radii (host copy of both; synchronizes the context stream).
-static vg_status source_extent(vg_context* ctx, vg_source* s) {
-    std::vector<double> an(3 * s->n_chunks);
-    std::vector<float> cb(8 * s->n_chunks);
-    VG_HIP(hipMemcpyAsync(an.data(), s->anchor, sizeof(double) * an.size(), hipMemcpyDeviceToHost, ctx->stream));
-    VG_HIP(hipMemcpyAsync(cb.data(), s->cbound, sizeof(float) * cb.size(), hipMemcpyDeviceToHost, ctx->stream));
-    VG_HIP(hipStreamSynchronize(ctx->stream));
-    double ext = 0.0;
-    for (int64_t c = 0; c < s->n_chunks; ++c) {
-        const double dx = an[3 * c] - s->origin[0], dy = an[3 * c + 1] - s->origin[1], dz = an[3 * c + 2] - s->origin[2];
-        ext = std::max(ext, std::sqrt(dx * dx + dy * dy + dz * dz) + (double)cb[8 * c + 3]);
+// Every array of a source is part of one allocation (an allocation and a free
+// cost 2-10 us each, more than a small source's kernels).
+static vg_status alloc_source(vg_source* s) {
+    const size_t np = (size_t)s->n_pad, nc = (size_t)s->n_chunks;
+    auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
+    const size_t nrm = s->has_normals ? up(12 * np) + up(24 * np) : 0;
+    const size_t bytes = up(12 * np) + up(24 * np) + up(24 * nc) + up(32 * nc) + up(12 * np) + up(24 * np) +
+                         up(48 * np) + up(4 * np) + nrm + up(sizeof(PointSrc));
+    unsigned char* p = nullptr;
+    VG_TRY(dev_alloc(&p, bytes));
+    s->block = p;
+    auto take = [&](size_t b) { unsigned char* r = p; p += up(b); return r; };
+    s->dxyz = (float*)take(12 * np);
+    s->cov = (float*)take(24 * np);
+    s->anchor = (double*)take(24 * nc);
+    s->cbound = (float*)take(32 * nc);
+    s->axyz = (float*)take(12 * np);
+    s->xyz64 = (double*)take(24 * np);
+    s->cov64 = (double*)take(48 * np);
+    s->perm = (int32_t*)take(4 * np);
+    if (s->has_normals) {
+        s->nrm = (float*)take(12 * np);
+        s->nrm64 = (double*)take(24 * np);
     }
-    s->extent = ext;
+    s->self = (PointSrc*)take(sizeof(PointSrc));
     return VG_OK;
 }
 
-// Source from device FP64 arrays (caller order); first = host copy of point 0.
-static vg_status make_source(vg_context* ctx, const double* d_xyz, const double* d_cov, const double* d_nrm,
-                             bool has_normals, int64_t n, const double* first, vg_source** out) {
+static PointSrc point_src(const vg_source* s, int64_t row0) {
+    return PointSrc{s->dxyz, s->axyz, s->xyz64, s->perm, s->anchor, s->cbound, s->n, s->n_pad, row0};
+}
+
+// Source from device FP64 arrays (caller order); first = host copy of point 0,
+// box = the points' bounding box.
+static vg_status make_source(vg_context* ctx, Scratch& sc, const double* d_xyz, const double* d_cov,
+                             const double* d_nrm, bool has_normals, int64_t n, const double* first,
+                             const double box[6], vg_source** out) {
     auto* s = new vg_source();
     s->ctx = ctx;
     s->n = n;
@@ -394,27 +398,11 @@ static vg_status make_source(vg_context* ctx, const double* d_xyz, const double*
     s->n_chunks = s->n_pad / kChunk;
     s->has_normals = has_normals;
     for (int a = 0; a < 3; ++a) s->origin[a] = (n > 0) ? std::nearbyint(first[a]) : 0.0;
-    const int64_t np = s->n_pad;
-    vg_status st = VG_OK;
-    do {
-        if ((st = dev_alloc(&s->dxyz, 3 * np)) != VG_OK) break;
-        if ((st = dev_alloc(&s->cov, 6 * np)) != VG_OK) break;
-        if ((st = dev_alloc(&s->anchor, 3 * s->n_chunks)) != VG_OK) break;
-        if ((st = dev_alloc(&s->cbound, 8 * s->n_chunks)) != VG_OK) break;
-        if ((st = dev_alloc(&s->axyz, 3 * np)) != VG_OK) break;
-        if ((st = dev_alloc(&s->xyz64, 3 * np)) != VG_OK) break;
-        if ((st = dev_alloc(&s->cov64, 6 * np)) != VG_OK) break;
-        if ((st = dev_alloc(&s->perm, np)) != VG_OK) break;
-        if (has_normals) {
-            if ((st = dev_alloc(&s->nrm, 3 * np)) != VG_OK) break;
-            if ((st = dev_alloc(&s->nrm64, 3 * np)) != VG_OK) break;
-        }
-        if (n == 0) break;
-        if ((st = layout_source(ctx, s, d_xyz, d_cov, d_nrm)) != VG_OK) break;
-        st = source_extent(ctx, s);
-    } while (0);
+    vg_status st = alloc_source(s);
+    if (st == VG_OK && n > 0) st = layout_source(ctx, sc, s, d_xyz, d_cov, d_nrm, box);
     if (st != VG_OK) {
-        free_source(s);
+        (void)hipStreamSynchronize(ctx->stream);
+        dfree(s->block);
         delete s;
         return st;
     }
@@ -442,30 +430,19 @@ extern "C" vg_status vg_create_source(vg_context* ctx, const double* xyz, const 
             return VG_ERR_NOT_SPD;
         }
     VG_HIP(hipSetDevice(ctx->device));
+    double box[6];
+    bounding_box(xyz, n, box);
+    Scratch sc(ctx);
     double *d_xyz = nullptr, *d_cov = nullptr, *d_nrm = nullptr;
-    vg_status st = VG_OK;
-    do {
-        if (n == 0) {
-            st = make_source(ctx, nullptr, nullptr, nullptr, normals != nullptr, 0, xyz, out);
-            break;
-        }
-        if ((st = dev_alloc(&d_xyz, 3 * n)) != VG_OK) break;
-        if ((st = dev_alloc(&d_cov, 6 * n)) != VG_OK) break;
-        if (normals && (st = dev_alloc(&d_nrm, 3 * n)) != VG_OK) break;
-        hipError_t e = hipMemcpyAsync(d_xyz, xyz, sizeof(double) * 3 * n, hipMemcpyHostToDevice, ctx->stream);
-        if (e == hipSuccess) e = hipMemcpyAsync(d_cov, cov, sizeof(double) * 6 * n, hipMemcpyHostToDevice, ctx->stream);
-        if (e == hipSuccess && normals)
-            e = hipMemcpyAsync(d_nrm, normals, sizeof(double) * 3 * n, hipMemcpyHostToDevice, ctx->stream);
-        if (e != hipSuccess) {
-            st = hip_fail(e, "source upload");
-            break;
-        }
-        st = make_source(ctx, d_xyz, d_cov, d_nrm, normals != nullptr, n, xyz, out);
-    } while (0);
-    dfree(d_xyz);
-    dfree(d_cov);
-    dfree(d_nrm);
-    return st;
+    if (n > 0) {
+        VG_HIP(sc.get(&d_xyz, 3 * n));
+        VG_HIP(sc.get(&d_cov, 6 * n));
+        if (normals) VG_HIP(sc.get(&d_nrm, 3 * n));
+        VG_HIP(hipMemcpyAsync(d_xyz, xyz, sizeof(double) * 3 * n, hipMemcpyHostToDevice, ctx->stream));
+        VG_HIP(hipMemcpyAsync(d_cov, cov, sizeof(double) * 6 * n, hipMemcpyHostToDevice, ctx->stream));
+        if (normals) VG_HIP(hipMemcpyAsync(d_nrm, normals, sizeof(double) * 3 * n, hipMemcpyHostToDevice, ctx->stream));
+    }
+    return make_source(ctx, sc, d_xyz, d_cov, d_nrm, normals != nullptr, n, xyz, box, out);
 }
 
 extern "C" vg_status vg_source_set_points_async(vg_source* src, const void* d_xyz, int32_t dtype) {
@@ -475,7 +452,7 @@ extern "C" vg_status vg_source_set_points_async(vg_source* src, const void* d_xy
     if (dtype != 0 && dtype != 1) return invalid("dtype must be 0 (float32) or 1 (float64)");
     if (src->n > 0 && d_xyz == nullptr) return invalid("d_xyz is NULL");
     VG_HIP(hipSetDevice(src->ctx->device));
-    return set_source_points(src->ctx, src, d_xyz, dtype);
+    return set_points(src->ctx, src->self, 1, src->n_chunks, d_xyz, dtype);
 }
 
 extern "C" vg_status vg_source_destroy(vg_source* src) {
@@ -484,7 +461,7 @@ extern "C" vg_status vg_source_destroy(vg_source* src) {
     if (src->users > 0) return state_err("source is used by a live batch");
     (void)hipSetDevice(src->ctx->device);
     (void)hipStreamSynchronize(src->ctx->stream);
-    free_source(src);
+    dfree(src->block);
     src->magic = 0;
     delete src;
     return VG_OK;
@@ -579,7 +556,8 @@ extern "C" vg_status vg_create_source_from_cloud(vg_context* ctx, const vg_cloud
     *out = nullptr;
     VG_HIP(hipSetDevice(ctx->device));
     if (cloud->m >= (int64_t)1 << 27) return invalid("a source holds fewer than 2^27 points");
-    return make_source(ctx, cloud->xyz, cloud->cov, cloud->nrm, true, cloud->m, cloud->first, out);
+    Scratch sc(ctx);
+    return make_source(ctx, sc, cloud->xyz, cloud->cov, cloud->nrm, true, cloud->m, cloud->first, cloud->box, out);
 }
 
 extern "C" vg_status vg_build_voxelmap_from_cloud(vg_context* ctx, const vg_cloud* cloud, const double* resolutions,
@@ -855,6 +833,7 @@ void free_batch(vg_batch* b) {
     dfree(b->d_e);
     dfree(b->d_lm);
     dfree(b->d_shared);
+    dfree(b->d_points);
     dfree(b->d_slab_off);
     dfree(b->d_gslab);
     hfree(b->h_poses);
@@ -919,11 +898,14 @@ extern "C" vg_status vg_create_factor_batch(vg_context* ctx, int64_t F, vg_sourc
     b->h_fac.resize(F);
     // concatenated point-gradient rows: sources in order of first use
     std::map<const vg_source*, std::pair<int64_t, int>> seen;
+    std::vector<PointSrc> points;
     int64_t rows = 0;
     for (int64_t f = 0; f < F; ++f) {
         auto it = seen.find(src[f]);
         if (it == seen.end()) {
             seen[src[f]] = {rows, 1};
+            points.push_back(point_src(src[f], rows));
+            b->max_chunks = std::max(b->max_chunks, src[f]->n_chunks);
             rows += src[f]->n;
         } else {
             it->second.second += 1;
@@ -931,6 +913,7 @@ extern "C" vg_status vg_create_factor_batch(vg_context* ctx, int64_t F, vg_sourc
         b->total_points += src[f]->n;
     }
     b->grad_rows = rows;
+    b->n_sources = (int64_t)points.size();
     // sources used by several factors: each such factor writes its own point-gradient
     // rows, summed per source in factor order (the sources in order of first use)
     std::map<const vg_source*, size_t> shared_idx;
@@ -1000,6 +983,13 @@ extern "C" vg_status vg_create_factor_batch(vg_context* ctx, int64_t F, vg_sourc
                 st = hip_fail(e1, "shared-source table upload");
                 break;
             }
+        }
+        if ((st = dev_alloc(&b->d_points, points.size())) != VG_OK) break;
+        hipError_t ep = hipMemcpyAsync(b->d_points, points.data(), sizeof(PointSrc) * points.size(),
+                                       hipMemcpyHostToDevice, ctx->stream);
+        if (ep != hipSuccess) {
+            st = hip_fail(ep, "source table upload");
+            break;
         }
         if ((st = dev_alloc(&b->d_e, F)) != VG_OK) break;
         if ((st = dev_alloc(&b->d_lm, 32 * F)) != VG_OK) break;
@@ -1203,6 +1193,16 @@ extern "C" vg_status vg_backward_async(vg_batch* b, const double* d_poses, const
     VG_TRY(launch_tiles(b, ws, kBwd, d_poses, 0, nt, d_grad_e, d_grad_points, points_dtype, 0, b->F));
     VG_TRY(launch_grad_combine(b, d_grad_points, points_dtype));
     return launch_reduce(b, ws, kBwd, d_poses, 0, (int32_t)b->F, nullptr, nullptr, d_grad_e, d_jr, d_grad_xi);
+}
+
+extern "C" vg_status vg_batch_set_points_async(vg_batch* b, const void* d_points, int32_t dtype) {
+    g_err.clear();
+    const TimelineRange range_("vg_batch_set_points_async");
+    if (!bat_ok(b)) return state_err("invalid batch");
+    if (dtype != 0 && dtype != 1) return invalid("dtype must be 0 (float32) or 1 (float64)");
+    if (b->grad_rows > 0 && d_points == nullptr) return invalid("d_points is NULL");
+    VG_HIP(hipSetDevice(b->ctx->device));
+    return set_points(b->ctx, b->d_points, b->n_sources, b->max_chunks, d_points, dtype);
 }
 
 extern "C" vg_status vg_se3_retract_async(vg_context* ctx, int64_t F, const double* d_T0, const double* d_xi,

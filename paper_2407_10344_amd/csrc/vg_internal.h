@@ -92,6 +92,18 @@ struct FactorDesc {
     LevelDesc lv[kMaxLevels];
 };
 
+// One source whose positions are replaced from rows of a device buffer.
+struct PointSrc {
+    float* dxyz;
+    float* axyz;
+    double* xyz64;
+    const int32_t* perm;
+    const double* anchor;
+    float* cbound;
+    int64_t n, n_pad;
+    int64_t row0;            // its first row in the buffer
+};
+
 // A source used by several factors of a batch: its rows of the point gradient
 // are the sum, in factor order, of those factors' rows in the per-factor buffer.
 struct SharedSrc {
@@ -173,6 +185,8 @@ struct vg_source {
     double* cov64 = nullptr;
     double* nrm64 = nullptr;
     int32_t* perm = nullptr;   // internal -> caller
+    void* block = nullptr;     // the allocation that holds every array above and self
+    vg::PointSrc* self = nullptr;   // device table of one entry: this source, rows from 0
     double extent = 0.0;       // upper bound of |mu - origin| over its points (m), from the chunk bounds
     int users = 0;
     uint32_t magic = 0;
@@ -229,6 +243,8 @@ struct vg_batch {
     int64_t slab_rows = 0;
     int64_t shared_rows = 0;
     vg::SharedSrc* d_shared = nullptr;
+    vg::PointSrc* d_points = nullptr;    // its distinct sources in order of first use
+    int64_t n_sources = 0, max_chunks = 0;
     int64_t* d_slab_off = nullptr;
     void* d_gslab = nullptr;             // per-factor point gradients (grown on first use)
     size_t gslab_bytes = 0;
@@ -315,9 +331,12 @@ vg_status preprocess_frame(vg_context* ctx, const double* d_xyz, int64_t n, doub
                            vg_cloud* out);
 void free_cloud(vg_cloud* c);
 
-vg_status layout_source(vg_context* ctx, vg_source* s, const double* d_xyz, const double* d_cov,
-                        const double* d_nrm);
-vg_status set_source_points(vg_context* ctx, vg_source* s, const void* d_xyz, int dtype);
+// every array of s from device FP64 arrays in caller order, and its extent; box: the points' bounding box
+vg_status layout_source(vg_context* ctx, Scratch& sc, vg_source* s, const double* d_xyz, const double* d_cov,
+                        const double* d_nrm, const double box[6]);
+// new positions of n_src sources (device table) from d_xyz, with their chunk bounds
+vg_status set_points(vg_context* ctx, const PointSrc* d_src, int64_t n_src, int64_t max_chunks, const void* d_xyz,
+                     int dtype);
 
 // launch the tile kernel over tiles [t0, t1) and the reduction over factors [f0, f1)
 // f0, f1: the factors those tiles belong to (their poses are staged to FP32 first)

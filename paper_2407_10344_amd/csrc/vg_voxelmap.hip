@@ -460,9 +460,14 @@ __device__ __forceinline__ uint64_t spread21(uint64_t v) {
     return x;
 }
 
-// Morton code of 0.25 m cells around the source origin (21 bits per axis).
-__global__ void k_morton(const double* __restrict__ xyz, int64_t n, double ox, double oy, double oz,
-                         uint64_t* __restrict__ codes, int32_t* __restrict__ idx) {
+// Sort word of a point: the Morton code of its 0.25 m cell around the source
+// origin (21 bits per axis, offset by 2^20), with the point in the low idx_bits.
+// Only `keep` bits per axis and the offset's top bit are interleaved: the bits
+// between are the complement of the top bit for every cell of the cloud, so they
+// never decide between two codes that agree above them, and the order is the full
+// code's.  idx: the points as a separate array where they don't fit the word.
+__global__ void k_morton(const double* __restrict__ xyz, int64_t n, double ox, double oy, double oz, int32_t keep,
+                         int32_t idx_bits, uint64_t* __restrict__ word, int32_t* __restrict__ idx) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     const double o[3] = {ox, oy, oz};
@@ -471,79 +476,12 @@ __global__ void k_morton(const double* __restrict__ xyz, int64_t n, double ox, d
     for (int a = 0; a < 3; ++a) {
         double c = floor((xyz[3 * i + a] - o[a]) * 4.0) + 1048576.0;
         c = fmin(fmax(c, 0.0), 2097151.0);
-        q[a] = (uint64_t)c;
+        const uint64_t u = (uint64_t)c;
+        q[a] = keep >= 20 ? u : ((u >> 20) << keep) | (u & ((1ull << keep) - 1ull));
     }
-    codes[i] = (spread21(q[0]) << 2) | (spread21(q[1]) << 1) | spread21(q[2]);
-    idx[i] = (int32_t)i;
-}
-
-__global__ void k_layout(const double* __restrict__ xyz, const double* __restrict__ cov,
-                         const double* __restrict__ nrm, const int32_t* __restrict__ sorted_idx, int64_t n,
-                         int64_t n_pad, float* __restrict__ dxyz, float* __restrict__ cov32, float* __restrict__ nrm32,
-                         double* __restrict__ anchor, float* __restrict__ axyz, double* __restrict__ xyz64,
-                         double* __restrict__ cov64, double* __restrict__ nrm64, int32_t* __restrict__ perm) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n_pad) return;
-    const int64_t c = i / kChunk;
-    const double an[3] = {anchor[3 * c + 0], anchor[3 * c + 1], anchor[3 * c + 2]};
-    if (i < n) {
-        const int64_t s = sorted_idx[i];
-        perm[i] = (int32_t)s;
-#pragma unroll
-        for (int q = 0; q < 3; ++q) {
-            const double x = xyz[3 * s + q];
-            dxyz[q * n_pad + i] = (float)(x - an[q]);
-            axyz[q * n_pad + i] = (float)x;
-            xyz64[q * n_pad + i] = x;
-            if (nrm) {
-                nrm32[q * n_pad + i] = (float)nrm[3 * s + q];
-                nrm64[q * n_pad + i] = nrm[3 * s + q];
-            }
-        }
-#pragma unroll
-        for (int k = 0; k < 6; ++k) {
-            cov32[k * n_pad + i] = (float)cov[6 * s + k];
-            cov64[k * n_pad + i] = cov[6 * s + k];
-        }
-    } else {
-        perm[i] = -1;
-#pragma unroll
-        for (int q = 0; q < 3; ++q) {
-            dxyz[q * n_pad + i] = 0.f;
-            axyz[q * n_pad + i] = 0.f;
-            xyz64[q * n_pad + i] = 0.0;
-            if (nrm) {
-                nrm32[q * n_pad + i] = 0.f;
-                nrm64[q * n_pad + i] = 0.0;
-            }
-        }
-#pragma unroll
-        for (int k = 0; k < 6; ++k) {
-            cov32[k * n_pad + i] = 0.f;
-            cov64[k * n_pad + i] = 0.0;
-        }
-    }
-}
-
-// Anchor of each 64-point chunk: the centroid of its points (keeps the FP32
-// offsets, and so their rounding, as small as the chunk allows).
-__global__ void k_anchors(const double* __restrict__ xyz, const int32_t* __restrict__ sorted_idx, int64_t n,
-                          int64_t n_chunks, double* __restrict__ anchor) {
-    const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= n_chunks) return;
-    const int64_t i0 = c * kChunk;
-    const int64_t i1 = (i0 + kChunk < n) ? i0 + kChunk : n;
-    double s[3] = {0.0, 0.0, 0.0};
-    for (int64_t i = i0; i < i1; ++i) {
-        const int64_t p = sorted_idx[i];
-        s[0] += xyz[3 * p + 0];
-        s[1] += xyz[3 * p + 1];
-        s[2] += xyz[3 * p + 2];
-    }
-    const double inv = 1.0 / (double)(i1 - i0);
-    anchor[3 * c + 0] = s[0] * inv;
-    anchor[3 * c + 1] = s[1] * inv;
-    anchor[3 * c + 2] = s[2] * inv;
+    const uint64_t code = (spread21(q[0]) << 2) | (spread21(q[1]) << 1) | spread21(q[2]);
+    word[i] = (code << idx_bits) | (idx_bits ? (uint64_t)i : 0ull);
+    if (idx != nullptr) idx[i] = (int32_t)i;
 }
 
 // FP32 value >= x (round up).
@@ -553,106 +491,216 @@ __device__ __forceinline__ float f32_up(double x) {
     return f;
 }
 
-// Per chunk, from the FP32 offsets the kernels read: a ball around the anchor
-// (radius bounds every point's distance) and an axis-aligned box in the source
-// frame (centre offset from the anchor, half extents bounding every point).
-__global__ void k_chunk_bounds(const float* __restrict__ dxyz, int64_t n, int64_t n_pad, int64_t n_chunks,
-                               float* __restrict__ cb) {
-    const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= n_chunks) return;
-    const int64_t i0 = c * kChunk;
-    const int64_t i1 = (i0 + kChunk < n) ? i0 + kChunk : n;
-    double m = 0.0, lo[3] = {0.0, 0.0, 0.0}, hi[3] = {0.0, 0.0, 0.0};
-    for (int64_t i = i0; i < i1; ++i) {
-        const double x[3] = {dxyz[i], dxyz[n_pad + i], dxyz[2 * n_pad + i]};
-        m = fmax(m, x[0] * x[0] + x[1] * x[1] + x[2] * x[2]);
-        for (int a = 0; a < 3; ++a) {
-            lo[a] = (i == i0) ? x[a] : fmin(lo[a], x[a]);
-            hi[a] = (i == i0) ? x[a] : fmax(hi[a], x[a]);
-        }
-    }
-    float* o = cb + 8 * c;
-    for (int a = 0; a < 3; ++a) {
-        const float ctr = (float)(0.5 * (lo[a] + hi[a]));
-        o[a] = ctr;
-        o[4 + a] = f32_up(fmax(hi[a] - (double)ctr, (double)ctr - lo[a]));
-    }
-    o[3] = f32_up(sqrt(m));
-    o[7] = 0.f;
+__device__ __forceinline__ double wave_max(double v) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o));
+    return v;
+}
+__device__ __forceinline__ double wave_min(double v) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v = fmin(v, __shfl_xor(v, o));
+    return v;
 }
 
-vg_status layout_source(vg_context* ctx, vg_source* s, const double* d_xyz, const double* d_cov,
-                        const double* d_nrm) {
+// Bounds of one chunk from the FP32 offsets the kernels read, one point per lane
+// of a wave: a ball around the anchor (radius bounds every point's distance) and
+// an axis-aligned box in the source frame (centre offset from the anchor, half
+// extents bounding every point).  Returns the radius.
+__device__ __forceinline__ float chunk_bounds(const float d[3], bool live, int lane, float* __restrict__ o) {
+    const double x[3] = {d[0], d[1], d[2]};
+    const double m = fmax(0.0, wave_max(live ? x[0] * x[0] + x[1] * x[1] + x[2] * x[2] : 0.0));
+    float ctr[3], half[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        const double lo = wave_min(live ? x[a] : INFINITY), hi = wave_max(live ? x[a] : -INFINITY);
+        ctr[a] = (float)(0.5 * (lo + hi));
+        half[a] = f32_up(fmax(hi - (double)ctr[a], (double)ctr[a] - lo));
+    }
+    const float rad = f32_up(sqrt(m));
+    if (lane < 8) {
+        const float v = lane == 0 ? ctr[0] : lane == 1 ? ctr[1] : lane == 2 ? ctr[2] : lane == 3 ? rad
+                      : lane == 4 ? half[0] : lane == 5 ? half[1] : lane == 6 ? half[2] : 0.f;
+        o[lane] = v;
+    }
+    return rad;
+}
+
+// Value of lane i (uniform).
+__device__ __forceinline__ double lane_value(double v, int i) {
+    const uint64_t u = (uint64_t)__double_as_longlong(v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, i),
+                   hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), i);
+    return __longlong_as_double((int64_t)(((uint64_t)hi << 32) | lo));
+}
+
+// Layout of a source, one wave per 64-point chunk: its points in Morton order
+// (gathered by row), the anchor (the centroid, FP64 sum in that order: keeps the
+// FP32 offsets, and so their rounding, as small as the chunk allows), every array,
+// the chunk's bounds, and an upper bound of its points' distance from the source
+// origin.  Bound by its ~300 B per point of reads and writes.  The anchors and
+// bounds were passes of their own with one thread per chunk, whose serial walk
+// over 64 strided points took 44 and 24 us at any size.
+__global__ __launch_bounds__(256) void k_layout(const double* __restrict__ xyz, const double* __restrict__ cov,
+                                                const double* __restrict__ nrm, const uint64_t* __restrict__ word,
+                                                const int32_t* __restrict__ idx, int32_t idx_bits, int64_t n,
+                                                int64_t n_pad, double ox, double oy, double oz,
+                                                float* __restrict__ dxyz, float* __restrict__ cov32,
+                                                float* __restrict__ nrm32, double* __restrict__ anchor,
+                                                float* __restrict__ cbound, float* __restrict__ axyz,
+                                                double* __restrict__ xyz64, double* __restrict__ cov64,
+                                                double* __restrict__ nrm64, int32_t* __restrict__ perm,
+                                                double* __restrict__ extent, PointSrc* __restrict__ self, PointSrc me) {
+    const int lane = threadIdx.x & 63;
+    const int64_t c = (int64_t)blockIdx.x * (blockDim.x >> 6) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t i = c * kChunk + lane;
+    if (c * kChunk >= n_pad) return;
+    const int npts = (int)min<int64_t>(kChunk, n - c * kChunk);
+    const bool live = lane < npts;
+    int64_t s = 0;
+    double x[3] = {0.0, 0.0, 0.0};
+    if (live) {
+        s = idx != nullptr ? (int64_t)idx[i] : (int64_t)(word[i] & ((1ull << idx_bits) - 1ull));
+#pragma unroll
+        for (int a = 0; a < 3; ++a) x[a] = xyz[3 * s + a];
+    }
+    double an[3] = {0.0, 0.0, 0.0};
+    for (int k = 0; k < npts; ++k) {
+#pragma unroll
+        for (int a = 0; a < 3; ++a) an[a] += lane_value(x[a], k);
+    }
+    const double inv = 1.0 / (double)npts;
+    float d[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        an[a] *= inv;
+        d[a] = live ? (float)(x[a] - an[a]) : 0.f;
+        dxyz[a * n_pad + i] = d[a];
+        axyz[a * n_pad + i] = live ? (float)x[a] : 0.f;
+        xyz64[a * n_pad + i] = x[a];
+    }
+    perm[i] = live ? (int32_t)s : -1;
+#pragma unroll
+    for (int k = 0; k < 6; ++k) {
+        const double v = live ? cov[6 * s + k] : 0.0;
+        cov32[k * n_pad + i] = (float)v;
+        cov64[k * n_pad + i] = v;
+    }
+    if (nrm != nullptr) {
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            const double v = live ? nrm[3 * s + a] : 0.0;
+            nrm32[a * n_pad + i] = (float)v;
+            nrm64[a * n_pad + i] = v;
+        }
+    }
+    const float rad = chunk_bounds(d, live, lane, cbound + 8 * c);
+    if (lane < 3) anchor[3 * c + lane] = lane == 0 ? an[0] : lane == 1 ? an[1] : an[2];
+    if (lane == 0) {
+        const double e0 = an[0] - ox, e1 = an[1] - oy, e2 = an[2] - oz;
+        extent[c] = sqrt(e0 * e0 + e1 * e1 + e2 * e2) + (double)rad;
+        if (c == 0) *self = me;
+    }
+}
+
+// Largest of n values (n >= 1), to pinned host memory; one workgroup.
+__global__ __launch_bounds__(1024) void k_max(const double* __restrict__ v, int64_t n, double* __restrict__ out) {
+    __shared__ double s[16];
+    double m = 0.0;
+    for (int64_t i = threadIdx.x; i < n; i += blockDim.x) m = fmax(m, v[i]);
+    m = wave_max(m);
+    if ((threadIdx.x & 63) == 0) s[threadIdx.x >> 6] = m;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < 16; ++w) m = fmax(m, s[w]);
+        *out = m;
+    }
+}
+
+vg_status layout_source(vg_context* ctx, Scratch& sc, vg_source* s, const double* d_xyz, const double* d_cov,
+                        const double* d_nrm, const double box[6]) {
     hipStream_t st = ctx->stream;
     const int64_t n = s->n, n_pad = s->n_pad;
     if (n == 0) return VG_OK;
-    uint64_t *codes = nullptr, *codes2 = nullptr;
-    int32_t *idx = nullptr, *idx2 = nullptr;
-    void* tmp = nullptr;
-    size_t tb = 0;
-    (void)hipcub::DeviceRadixSort::SortPairs(nullptr, tb, (uint64_t*)nullptr, (uint64_t*)nullptr, (int32_t*)nullptr,
-                                             (int32_t*)nullptr, (int)n, 0, 63);
-    vg_status rc = VG_OK;
-    hipError_t e = hipSuccess;
-    do {
-        if ((e = hipMalloc(&codes, 8 * n)) != hipSuccess) break;
-        if ((e = hipMalloc(&codes2, 8 * n)) != hipSuccess) break;
-        if ((e = hipMalloc(&idx, 4 * n)) != hipSuccess) break;
-        if ((e = hipMalloc(&idx2, 4 * n)) != hipSuccess) break;
-        if ((e = hipMalloc(&tmp, tb + 256)) != hipSuccess) break;
-        k_morton<<<grid_of(n), 256, 0, st>>>(d_xyz, n, s->origin[0], s->origin[1], s->origin[2], codes, idx);
-        if ((e = hipGetLastError()) != hipSuccess) break;
-        size_t tb2 = tb + 256;
-        if ((e = hipcub::DeviceRadixSort::SortPairs(tmp, tb2, codes, codes2, idx, idx2, (int)n, 0, 63, st)) !=
-            hipSuccess)
-            break;
-        k_anchors<<<grid_of(s->n_chunks), 256, 0, st>>>(d_xyz, idx2, n, s->n_chunks, s->anchor);
-        if ((e = hipGetLastError()) != hipSuccess) break;
-        k_layout<<<grid_of(n_pad), 256, 0, st>>>(d_xyz, d_cov, d_nrm, idx2, n, n_pad, s->dxyz, s->cov, s->nrm,
-                                                 s->anchor, s->axyz, s->xyz64, s->cov64, s->nrm64, s->perm);
-        if ((e = hipGetLastError()) != hipSuccess) break;
-        k_chunk_bounds<<<grid_of(s->n_chunks), 256, 0, st>>>(s->dxyz, n, n_pad, s->n_chunks, s->cbound);
-        if ((e = hipGetLastError()) != hipSuccess) break;
-        e = hipStreamSynchronize(st);
-    } while (0);
-    if (e != hipSuccess) rc = hip_fail(e, "source layout");
-    if (codes) (void)hipFree(codes);
-    if (codes2) (void)hipFree(codes2);
-    if (idx) (void)hipFree(idx);
-    if (idx2) (void)hipFree(idx2);
-    if (tmp) (void)hipFree(tmp);
-    return rc;
-}
-
-template <typename S>
-__global__ void k_set_points(const S* __restrict__ in, const int32_t* __restrict__ perm,
-                             const double* __restrict__ anchor, int64_t n, int64_t n_pad, float* __restrict__ dxyz,
-                             float* __restrict__ axyz, double* __restrict__ xyz64) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const int64_t s = perm[i];
-    const int64_t c = i / kChunk;
-#pragma unroll
-    for (int q = 0; q < 3; ++q) {
-        const double x = (double)in[3 * s + q];
-        dxyz[q * n_pad + i] = (float)(x - anchor[3 * c + q]);
-        axyz[q * n_pad + i] = (float)x;
-        xyz64[q * n_pad + i] = x;
+    // low bits per axis that hold every cell's distance from the origin's cell
+    int keep = 0;
+    for (int a = 0; a < 3; ++a) {
+        const double lo = std::floor((box[a] - s->origin[a]) * 4.0), hi = std::floor((box[3 + a] - s->origin[a]) * 4.0);
+        while (keep < 20 && !(lo >= -(double)(1ll << keep) && hi < (double)(1ll << keep))) ++keep;
     }
+    const int code_bits = 3 * (keep + 1), ib = bits_for((uint64_t)(n - 1));
+    const bool packed = code_bits + ib <= 64;
+    const int idx_bits = packed ? ib : 0;
+    uint64_t *w0, *w1;
+    int32_t *i0 = nullptr, *i1 = nullptr;
+    double* ext;
+    VG_HIP(sc.get(&w0, n));
+    VG_HIP(sc.get(&w1, n));
+    VG_HIP(sc.get(&ext, s->n_chunks));
+    if (!packed) {
+        VG_HIP(sc.get(&i0, n));
+        VG_HIP(sc.get(&i1, n));
+    }
+    const int end_bit = code_bits + idx_bits;
+    size_t tb = 0;
+    if (packed) (void)hipcub::DeviceRadixSort::SortKeys(nullptr, tb, w0, w1, (int)n, idx_bits, end_bit);
+    else (void)hipcub::DeviceRadixSort::SortPairs(nullptr, tb, w0, w1, i0, i1, (int)n, 0, end_bit);
+    char* tmp = nullptr;
+    tb += 256;
+    VG_HIP(sc.get(&tmp, tb));
+    k_morton<<<grid_of(n), 256, 0, st>>>(d_xyz, n, s->origin[0], s->origin[1], s->origin[2], keep, idx_bits, w0, i0);
+    VG_HIP(hipGetLastError());
+    if (packed) VG_HIP(hipcub::DeviceRadixSort::SortKeys(tmp, tb, w0, w1, (int)n, idx_bits, end_bit, st));
+    else VG_HIP(hipcub::DeviceRadixSort::SortPairs(tmp, tb, w0, w1, i0, i1, (int)n, 0, end_bit, st));
+    k_layout<<<grid_of(s->n_chunks, 4), 256, 0, st>>>(d_xyz, d_cov, d_nrm, w1, i1, idx_bits, n, n_pad, s->origin[0],
+                                                      s->origin[1], s->origin[2], s->dxyz, s->cov, s->nrm, s->anchor,
+                                                      s->cbound, s->axyz, s->xyz64, s->cov64, s->nrm64, s->perm, ext, s->self,
+                                                      PointSrc{s->dxyz, s->axyz, s->xyz64, s->perm, s->anchor, s->cbound, n, n_pad, 0});
+    VG_HIP(hipGetLastError());
+    double* h = reinterpret_cast<double*>(ctx->h_small);
+    k_max<<<1, 1024, 0, st>>>(ext, s->n_chunks, h);
+    VG_HIP(hipGetLastError());
+    VG_HIP(hipStreamSynchronize(st));
+    s->extent = h[0];
+    return VG_OK;
 }
 
-vg_status set_source_points(vg_context* ctx, vg_source* s, const void* d_xyz, int dtype) {
-    if (s->n == 0) return VG_OK;
-    if (dtype == 0)
-        k_set_points<float><<<grid_of(s->n), 256, 0, ctx->stream>>>((const float*)d_xyz, s->perm, s->anchor, s->n,
-                                                                    s->n_pad, s->dxyz, s->axyz, s->xyz64);
-    else
-        k_set_points<double><<<grid_of(s->n), 256, 0, ctx->stream>>>((const double*)d_xyz, s->perm, s->anchor, s->n,
-                                                                     s->n_pad, s->dxyz, s->axyz, s->xyz64);
-    VG_HIP(hipGetLastError());
-    // the offsets moved: so do the chunk bounds
-    k_chunk_bounds<<<grid_of(s->n_chunks), 256, 0, ctx->stream>>>(s->dxyz, s->n, s->n_pad, s->n_chunks, s->cbound);
-    VG_HIP(hipGetLastError());
+// New positions of a source and its chunk bounds, one wave per chunk: the offsets
+// are taken from the kept anchors, and the bounds from the offsets while they are
+// in registers.  blockIdx.y: the source; its rows start at row0 of `in`.  Bound by
+// its ~70 B per point; one launch for all sources of a batch (64 sources of 100k
+// points: 4.0 ms of launches and of per-chunk serial bounds before).
+template <typename S>
+__global__ __launch_bounds__(256) void k_set_points(const S* __restrict__ in, const PointSrc* __restrict__ src) {
+    const PointSrc q = src[blockIdx.y];
+    const int lane = threadIdx.x & 63;
+    const int64_t c = (int64_t)blockIdx.x * (blockDim.x >> 6) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t i = c * kChunk + lane;
+    if (c * kChunk >= q.n) return;
+    const bool live = i < q.n;
+    float d[3] = {0.f, 0.f, 0.f};
+    if (live) {
+        const int64_t s = q.row0 + q.perm[i];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            const double x = (double)in[3 * s + a];
+            d[a] = (float)(x - q.anchor[3 * c + a]);
+            q.dxyz[a * q.n_pad + i] = d[a];
+            q.axyz[a * q.n_pad + i] = (float)x;
+            q.xyz64[a * q.n_pad + i] = x;
+        }
+    }
+    chunk_bounds(d, live, lane, q.cbound + 8 * c);
+}
+
+vg_status set_points(vg_context* ctx, const PointSrc* d_src, int64_t n_src, int64_t max_chunks, const void* d_xyz,
+                     int dtype) {
+    constexpr int64_t kMaxY = 32768;
+    for (int64_t s0 = 0; s0 < n_src && max_chunks > 0; s0 += kMaxY) {
+        const dim3 grid((unsigned)grid_of(max_chunks, 4), (unsigned)std::min(kMaxY, n_src - s0));
+        if (dtype == 0) k_set_points<float><<<grid, 256, 0, ctx->stream>>>((const float*)d_xyz, d_src + s0);
+        else k_set_points<double><<<grid, 256, 0, ctx->stream>>>((const double*)d_xyz, d_src + s0);
+        VG_HIP(hipGetLastError());
+    }
     return VG_OK;
 }
 

@@ -249,6 +249,19 @@ class FactorBatch:
                 self.source_rows[id(s)] = (self.grad_rows, s.n)
                 self.grad_rows += s.n
 
+    def set_points(self, points: torch.Tensor):
+        """Replace the positions of every distinct source from a device tensor (grad_rows x 3,
+        float32 or float64: sources in order of first use, each in caller order)."""
+        assert points.is_cuda and points.shape == (self.grad_rows, 3)
+        t = points.contiguous()
+        dt = 0 if t.dtype == torch.float32 else 1
+        if t.dtype not in (torch.float32, torch.float64):
+            raise TypeError("points must be float32 or float64")
+        self.ctx.enter()
+        check(load().vg_batch_set_points_async(self.handle, _tp(t), dt))
+        self.ctx.leave()
+        return t
+
     def info(self):
         tp, nt = C.c_int64(), C.c_int64()
         bl, ti, gr, to = C.c_int32(), C.c_int32(), C.c_int32(), C.c_int32()

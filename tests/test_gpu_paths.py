@@ -261,3 +261,38 @@ def test_fd_fp32c_h1e4_within_rounding_bound(vg):
     batch.close()
     src.close()
     m.close()
+
+
+@pytest.mark.parametrize("dtype", ["float32", "float64"])
+def test_batch_set_points_equals_the_sources_one_by_one(vg, dtype):
+    """One launch moves every distinct source of a batch (sizes at the edges of a
+    chunk and of a launch's workgroup, one used twice, one empty) to the same bits
+    as moving each source by itself: same evaluation, same correspondences."""
+    import torch
+    vgicp, ctx = vg
+    cfg = synth.config1(seed=23, n_target=4000, n_source=700)
+    xyz, cov = cfg["sources"][0].xyz64(), cfg["sources"][0].cov64()
+    tgt = cfg["targets"][0]
+    vmap = vgicp.VoxelMap(ctx, tgt.xyz64(), tgt.cov64(), cfg["resolutions"])
+    sizes = [1, 0, 64, 257, 63, 700]
+    srcs = [vgicp.Source(ctx, xyz[:n], cov[:n]) for n in sizes]
+    order = [0, 1, 2, 3, 2, 4, 5]
+    batch = vgicp.FactorBatch(ctx, [srcs[i] for i in order], [vmap] * len(order))
+    poses = np.tile(np.array(cfg["poses"][0])[None], (len(order), 1, 1))
+    moved = torch.tensor(np.concatenate([xyz[:n] for n in sizes]) + 0.05, dtype=getattr(torch, dtype), device="cuda")
+    e0 = batch.evaluate(poses)
+    row = 0
+    for s, n in zip(srcs, sizes):
+        s.set_points(moved[row:row + n])
+        row += n
+    e1 = batch.evaluate(poses)
+    k1 = [batch.correspondences(poses[0], f) for f in range(len(order))]
+    batch.set_points(moved - 0.05)
+    assert not np.array_equal(batch.evaluate(poses), e1)
+    batch.set_points(moved)
+    assert np.array_equal(batch.evaluate(poses), e1) and not np.array_equal(e0, e1)
+    for f in range(len(order)):
+        k2 = batch.correspondences(poses[0], f)
+        assert np.array_equal(k1[f][0], k2[0]) and np.array_equal(k1[f][1], k2[1])
+    for h in [batch, vmap] + srcs:
+        h.close()
