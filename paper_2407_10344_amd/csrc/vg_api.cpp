@@ -487,23 +487,17 @@ extern "C" vg_status vg_preprocess(vg_context* ctx, const double* xyz, int64_t n
     if (sensor == nullptr || !finite_all(sensor, 3)) return invalid("sensor must be 3 finite values");
     if (n > 0 && !finite_all(xyz, 3 * n)) return invalid("xyz has non-finite values");
     VG_HIP(hipSetDevice(ctx->device));
+    double box[6];
+    bounding_box(xyz, n, box);
+    Scratch sc(ctx);
     double* d_xyz = nullptr;
+    VG_HIP(sc.get(&d_xyz, 3 * n));
+    if (n > 0) VG_HIP(hipMemcpyAsync(d_xyz, xyz, sizeof(double) * 3 * n, hipMemcpyHostToDevice, ctx->stream));
     auto* c = new vg_cloud();
     c->ctx = ctx;
-    vg_status st = VG_OK;
-    do {
-        if ((st = dev_alloc(&d_xyz, 3 * n)) != VG_OK) break;
-        if (n > 0) {
-            hipError_t e = hipMemcpyAsync(d_xyz, xyz, sizeof(double) * 3 * n, hipMemcpyHostToDevice, ctx->stream);
-            if (e != hipSuccess) {
-                st = hip_fail(e, "frame upload");
-                break;
-            }
-        }
-        st = preprocess_frame(ctx, d_xyz, n, r, k, sensor, c);
-    } while (0);
-    dfree(d_xyz);
+    const vg_status st = preprocess_frame(ctx, sc, d_xyz, n, box, r, k, sensor, c);
     if (st != VG_OK) {
+        (void)hipStreamSynchronize(ctx->stream);
         free_cloud(c);
         delete c;
         return st;

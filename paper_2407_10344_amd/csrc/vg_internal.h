@@ -326,9 +326,9 @@ vg_status export_level(vg_context* ctx, const Level& lv, int64_t* keys, double* 
                        int64_t* counts);
 void free_map(vg_voxelmap* m);
 
-// frame preprocessing: d_xyz n x 3 FP64 device input; fills every array of *out
-vg_status preprocess_frame(vg_context* ctx, const double* d_xyz, int64_t n, double r, int k, const double sensor[3],
-                           vg_cloud* out);
+// frame preprocessing: d_xyz n x 3 FP64 device input with bounding box `box`; fills every array of *out
+vg_status preprocess_frame(vg_context* ctx, Scratch& sc, const double* d_xyz, int64_t n, const double box[6], double r,
+                           int k, const double sensor[3], vg_cloud* out);
 void free_cloud(vg_cloud* c);
 
 // every array of s from device FP64 arrays in caller order, and its extent; box: the points' bounding box

@@ -3,25 +3,26 @@
 // plane-to-plane regularisation and oriented normals.
 //
 // Device pipeline:
-//   1. FP64 voxel keys -> stable radix sort of (key, point) -> run-length
-//      encoding; one thread per voxel sums its run in input order (FP64).
-//   2. k-NN on a hierarchy of uniform grids (cells of 2r, 4r, ..., 64r):
-//      per grid, points sorted by cell and cells in an open-addressing table.
-//      One thread per query walks cubic shells of cells around its own cell
-//      (radius 0..1 cells) and keeps the k best (distance, index) pairs in
-//      registers, candidates read four at a time and rejected against the
-//      current k-th pair before any insertion work; the walk stops once the k-th distance is below the
-//      distance to the unvisited region (strictly, with a 1e-9 relative
-//      margin), so the result is exact.  A query that is not settled within
-//      two shells starts again on the next coarser grid (sparse regions: few
-//      large cells instead of many empty small ones); on the coarsest grid it
-//      walks on until settled, or scans every point once the next shell would
-//      hold more cells than the grid has occupied cells.
+//   1. one 64-bit word per point (FP64 voxel key | point), sorted; a scan of the
+//      key changes numbers the voxels; three lanes per voxel sum its run in input
+//      order (FP64, one lane per coordinate).
+//   2. k-NN on a hierarchy of six uniform grids (cells of 2r, 4r, ..., 64r).  The
+//      grids are nested, so one sort of the points by the Morton code of their 2r
+//      cell makes every cell of every grid a contiguous range of it, and one hash
+//      table holds the ranges of all six.  Sixteen (or 32) lanes per query look up
+//      the 27 cells around its own, take their points together and keep the k best
+//      (distance, index) pairs sorted across the lanes; the result is final once
+//      the k-th distance is below the distance to the unvisited region (strictly,
+//      with a 1e-9 relative margin), otherwise the k-th pair is an upper bound
+//      that picks the coarser grid to search.  Queries that would read many
+//      candidates, or whose coarsest cells hold too few, go to a pass with a wave
+//      per query.
 //   3. one thread per point: mean and covariance of its neighbours (FP64),
 //      cyclic Jacobi eigen-decomposition, normal = smallest eigenvector,
 //      oriented towards the sensor, C = I - (1 - 1e-3) n n^T.
 #include <hipcub/hipcub.hpp>
 
+#include <algorithm>
 #include <climits>
 #include <cmath>
 #include <vector>
@@ -31,149 +32,165 @@
 namespace vg {
 namespace {
 
-constexpr int kPBits = 21;                       // bits per axis of a packed preprocessing key
+constexpr int kPBits = 21;                       // bits per axis of a preprocessing key
 constexpr int64_t kPBias = 1ll << (kPBits - 1);  // keys live in [-2^20, 2^20)
 constexpr uint64_t kPEmpty = ~0ull;
 constexpr double kEpsReg = 1e-3;
-constexpr int kMaxK = 32;
 
-__device__ __forceinline__ bool pkey_ok(int64_t q) { return q >= -kPBias && q < kPBias; }
+// Voxel keys of the frame relative to its lowest, packed x | y | z (lexicographic).
+struct DsKeys {
+    int64_t q0[3];
+    int32_t wy, wz;
+    int32_t idx_bits;   // low bits of a word that hold the point (0: a separate array)
+};
 
-// lexicographic (x, y, z) order of the packed key equals the order of the integer triple
-__device__ __forceinline__ uint64_t pack21(int64_t x, int64_t y, int64_t z) {
-    return ((uint64_t)(x + kPBias) << (2 * kPBits)) | ((uint64_t)(y + kPBias) << kPBits) | (uint64_t)(z + kPBias);
+__global__ void k_ds_words(const double* __restrict__ xyz, int64_t n, double r, DsKeys K, uint64_t* __restrict__ word,
+                           int32_t* __restrict__ idx) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    uint64_t q[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) q[a] = (uint64_t)((int64_t)floor(xyz[3 * i + a] / r) - K.q0[a]);
+    const uint64_t key = (((q[0] << K.wy) | q[1]) << K.wz) | q[2];
+    word[i] = (key << K.idx_bits) | (K.idx_bits ? (uint64_t)i : 0ull);
+    if (idx != nullptr) idx[i] = (int32_t)i;
 }
 
-__device__ __forceinline__ void unpack21(uint64_t k, int64_t* x, int64_t* y, int64_t* z) {
-    const uint64_t m = (1ull << kPBits) - 1;
-    *x = (int64_t)((k >> (2 * kPBits)) & m) - kPBias;
-    *y = (int64_t)((k >> kPBits) & m) - kPBias;
-    *z = (int64_t)(k & m) - kPBias;
+// 1 where a new voxel starts among the sorted words
+struct KeyChange {
+    const uint64_t* word;
+    int32_t idx_bits;
+    __host__ __device__ int32_t operator()(int64_t i) const {
+        return i == 0 || (word[i - 1] >> idx_bits) != (word[i] >> idx_bits) ? 1 : 0;
+    }
+};
+
+// first element of every voxel; their number goes to pinned host memory
+__global__ void k_ds_starts(const int32_t* __restrict__ scan, int64_t n, int32_t* __restrict__ start,
+                            int32_t* __restrict__ h_count) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    const int32_t v = scan[i];
+    if (i == 0 || scan[i - 1] != v) start[v - 1] = (int32_t)i;
+    if (i == n - 1) {
+        start[v] = (int32_t)n;
+        *h_count = v;
+    }
 }
 
+__device__ __forceinline__ uint64_t spread21(uint64_t v) {
+    uint64_t x = v & 0x1fffffull;
+    x = (x | (x << 32)) & 0x1f00000000ffffull;
+    x = (x | (x << 16)) & 0x1f0000ff0000ffull;
+    x = (x | (x << 8)) & 0x100f00f00f00f00full;
+    x = (x | (x << 4)) & 0x10c30c30c30c30c3ull;
+    x = (x | (x << 2)) & 0x1249249249249249ull;
+    return x;
+}
+
+constexpr int kGrids = 6;       // cell sizes 2r, 4r, ..., 64r
+
+// The nested grids: cells are counted from c0, a multiple of the coarsest cell, so
+// a cell of grid g is a 2r cell's coordinates shifted by g.
+struct Cells {
+    double h;            // finest cell size, 2r
+    int64_t c0[3];
+    int32_t hi[3];       // last 2r cell per axis (the cloud's, with a margin of one cell)
+    int32_t w;           // bits per axis
+    int32_t idx_bits;    // low bits of a sort word that hold the point (0: a separate array)
+    uint32_t lg;         // table entries = 2^lg
+};
+// Table key of a grid's cell: the Morton code under a leading one, shifted, so the
+// grids' keys differ by the place of their highest bit.
+__device__ __forceinline__ uint64_t cell_key(const Cells& C, uint64_t code2r, int g) {
+    return ((1ull << (3 * C.w)) | code2r) >> (3 * g);
+}
 __device__ __forceinline__ uint32_t cell_slot(uint64_t key, uint32_t lg) {
     return (uint32_t)((key * 0x9E3779B97F4A7C15ull) >> (64 - lg));
 }
-
-__global__ void k_ds_keys(const double* __restrict__ xyz, int64_t n, double r, uint64_t* __restrict__ keys,
-                          int32_t* __restrict__ idx, int32_t* __restrict__ flag) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const double qx = floor(xyz[3 * i + 0] / r);
-    const double qy = floor(xyz[3 * i + 1] / r);
-    const double qz = floor(xyz[3 * i + 2] / r);
-    const double lim = (double)kPBias;
-    if (!(qx >= -lim && qx < lim && qy >= -lim && qy < lim && qz >= -lim && qz < lim)) {
-        atomicOr(flag, 1);
-        keys[i] = 0;
-    } else {
-        keys[i] = pack21((int64_t)qx, (int64_t)qy, (int64_t)qz);
-    }
-    idx[i] = (int32_t)i;
+__device__ __forceinline__ int32_t cell_coord(const Cells& C, double x, int a) {
+    return (int32_t)((int64_t)floor(x / C.h) - C.c0[a]);
 }
 
-// one thread per voxel: FP64 sum of its run (input order), then the mean; the
-// point's grid cell for the neighbour search
-__global__ void k_ds_centroids(const double* __restrict__ xyz, const int32_t* __restrict__ sorted_idx,
-                               const int32_t* __restrict__ offsets, const int32_t* __restrict__ counts, int64_t m,
-                               double* __restrict__ out, int32_t* __restrict__ out_counts) {
-    const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (v >= m) return;
-    const int32_t o = offsets[v], c = counts[v];
-    double sx = 0.0, sy = 0.0, sz = 0.0;
-    for (int32_t j = 0; j < c; ++j) {
-        const int32_t p = sorted_idx[o + j];
-        sx += xyz[3 * p + 0];
-        sy += xyz[3 * p + 1];
-        sz += xyz[3 * p + 2];
-    }
-    const double cx = sx / (double)c, cy = sy / (double)c, cz = sz / (double)c;
-    out[3 * v + 0] = cx;
-    out[3 * v + 1] = cy;
-    out[3 * v + 2] = cz;
-    out_counts[v] = c;
-}
-
-// grid cell of every downsampled point (cell size h >= 2r: |c / h| < 2^19, always
-// packable) and the grid's cell bounding box
-__global__ void k_grid_keys(const double* __restrict__ c, int64_t m, double h, uint64_t* __restrict__ cell_keys,
-                            int32_t* __restrict__ cell_idx, int32_t* __restrict__ box) {
-    const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    int32_t lo[3] = {INT32_MAX, INT32_MAX, INT32_MAX}, hi[3] = {INT32_MIN, INT32_MIN, INT32_MIN};
-    if (v < m) {
-        const int64_t gx = (int64_t)floor(c[3 * v] / h), gy = (int64_t)floor(c[3 * v + 1] / h),
-                      gz = (int64_t)floor(c[3 * v + 2] / h);
-        cell_keys[v] = pack21(gx, gy, gz);
-        cell_idx[v] = (int32_t)v;
-        lo[0] = hi[0] = (int32_t)gx;
-        lo[1] = hi[1] = (int32_t)gy;
-        lo[2] = hi[2] = (int32_t)gz;
-    }
-    // the wave's box first, then one atomic per wave and bound
+// Voxel centroids: three lanes per voxel, one per coordinate, eight points in
+// flight: the FP64 sum of its run in input order, then the mean; and the sort word
+// of its 2r cell.  (One thread per voxel with one point in flight: 45 us for 107k
+// raw points, most of it the chain of gathers.)
+constexpr int kCentPerWave = 21;
+__global__ __launch_bounds__(256) void k_ds_centroids(const double* __restrict__ xyz, const uint64_t* __restrict__ word,
+                                                      const int32_t* __restrict__ idx, int32_t ds_bits,
+                                                      const int32_t* __restrict__ start, int64_t m, Cells C,
+                                                      double* __restrict__ out, int32_t* __restrict__ out_counts,
+                                                      uint64_t* __restrict__ cword, int32_t* __restrict__ cidx) {
+    const int lane = threadIdx.x & 63, g = lane / 3, k = lane % 3;
+    const int64_t v = ((int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)) * kCentPerWave + g;
+    if (g >= kCentPerWave || v >= m) return;
+    const int32_t j0 = start[v], j1 = start[v + 1];
+    const uint64_t mask = (1ull << ds_bits) - 1ull;
+    constexpr int kStep = 8;
+    double s = 0.0;
+    for (int32_t j = j0; j < j1; j += kStep) {
+        double x[kStep];
 #pragma unroll
-    for (int w = 32; w >= 1; w >>= 1)
+        for (int q = 0; q < kStep; ++q)
+            if (j + q < j1) {
+                const int64_t p = idx != nullptr ? (int64_t)idx[j + q] : (int64_t)(word[j + q] & mask);
+                x[q] = xyz[3 * p + k];
+            }
 #pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            lo[a] = min(lo[a], __shfl_xor(lo[a], w));
-            hi[a] = max(hi[a], __shfl_xor(hi[a], w));
-        }
-    if ((threadIdx.x & 63) == 0 && lo[0] <= hi[0]) {
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            atomicMin(&box[a], lo[a]);
-            atomicMax(&box[3 + a], hi[a]);
-        }
+        for (int q = 0; q < kStep; ++q)
+            if (j + q < j1) s += x[q];
+    }
+    const double c = s / (double)(j1 - j0);
+    out[3 * v + k] = c;
+    // the three coordinates' cells meet in the first lane of the voxel
+    const uint64_t part = spread21((uint64_t)cell_coord(C, c, k)) << (2 - k);
+    const uint64_t p1 = __shfl_down(part, 1), p2 = __shfl_down(part, 2);
+    if (k == 0) {
+        out_counts[v] = j1 - j0;
+        cword[v] = ((part | p1 | p2) << C.idx_bits) | (C.idx_bits ? (uint64_t)v : 0ull);
+        if (cidx != nullptr) cidx[v] = (int32_t)v;
     }
 }
 
-__global__ void k_fill_i32(int32_t* p, int64_t n, int32_t v) {
+__global__ void k_fill_cells(u64x2* p, int64_t n) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = v;
+    if (i < n) p[i] = u64x2{kPEmpty, 0ull};
 }
 
-__global__ void k_fill_u64p(uint64_t* p, int64_t n, uint64_t v) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = v;
-}
+// A point in cell order.
+struct alignas(32) CellPoint {
+    double x, y, z;
+    int64_t i;           // its index in the cloud
+};
 
-__global__ void k_cells_insert(const uint64_t* __restrict__ ucells, const int32_t* __restrict__ nc,
-                               uint64_t* __restrict__ hkeys, int32_t* __restrict__ hval, uint32_t lg) {
-    const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= *nc) return;
-    const uint64_t key = ucells[c];
-    const uint32_t mask = (1u << lg) - 1;
-    uint32_t s = cell_slot(key, lg);
-    for (;;) {
-        const unsigned long long prev =
-            atomicCAS((unsigned long long*)&hkeys[s], (unsigned long long)kPEmpty, (unsigned long long)key);
-        if (prev == kPEmpty || prev == key) {
-            hval[s] = (int32_t)c;
-            return;
-        }
-        s = (s + 1) & mask;
-    }
-}
-
-// coordinates in cell order (SoA) so that a cell's points are contiguous
-__global__ void k_cells_gather(const double* __restrict__ xyz, const int32_t* __restrict__ cidx, int64_t m,
-                               double* __restrict__ sx, double* __restrict__ sy, double* __restrict__ sz) {
+// Points in cell order, and the range of every cell of every grid: the first
+// point of a range writes its start, the last its end (the low and high halves of
+// the entry's second word), whichever comes first inserts the key.
+__global__ void k_cells(const double* __restrict__ xyz, const uint64_t* __restrict__ cword, const int32_t* __restrict__ cidx,
+                        int64_t m, Cells C, CellPoint* __restrict__ pts, u64x2* __restrict__ table) {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= m) return;
-    const int32_t i = cidx[t];
-    sx[t] = xyz[3 * i + 0];
-    sy[t] = xyz[3 * i + 1];
-    sz[t] = xyz[3 * i + 2];
-}
-
-__device__ __forceinline__ int32_t cell_find(const uint64_t* __restrict__ hkeys, const int32_t* __restrict__ hval,
-                                             uint32_t lg, uint64_t key) {
-    const uint32_t mask = (1u << lg) - 1;
-    uint32_t s = cell_slot(key, lg);
-    for (;;) {
-        const uint64_t k = hkeys[s];
-        if (k == key) return hval[s];
-        if (k == kPEmpty) return -1;
-        s = (s + 1) & mask;
+    const uint64_t w = cword[t], code = w >> C.idx_bits;
+    const int64_t i = cidx != nullptr ? (int64_t)cidx[t] : (int64_t)(w & ((1ull << C.idx_bits) - 1ull));
+    pts[t] = CellPoint{xyz[3 * i], xyz[3 * i + 1], xyz[3 * i + 2], i};
+    const uint64_t prev = t > 0 ? cword[t - 1] >> C.idx_bits : 0ull, next = t + 1 < m ? cword[t + 1] >> C.idx_bits : 0ull;
+    const uint32_t mask = (1u << C.lg) - 1u;
+    for (int g = 0; g < kGrids; ++g) {
+        const bool first = t == 0 || (prev >> (3 * g)) != (code >> (3 * g));
+        const bool last = t + 1 == m || (next >> (3 * g)) != (code >> (3 * g));
+        if (!first && !last) break;   // inside a range of this grid: inside one of every coarser grid too
+        const uint64_t key = cell_key(C, code, g);
+        uint32_t h = cell_slot(key, C.lg);
+        for (;;) {
+            const unsigned long long was = atomicCAS((unsigned long long*)&table[h], (unsigned long long)kPEmpty,
+                                                     (unsigned long long)key);
+            if (was == kPEmpty || was == key) break;
+            h = (h + 1u) & mask;
+        }
+        int32_t* range = reinterpret_cast<int32_t*>(reinterpret_cast<uint64_t*>(&table[h]) + 1);
+        if (first) range[0] = (int32_t)t;
+        if (last) range[1] = (int32_t)(t + 1);
     }
 }
 
@@ -189,254 +206,287 @@ __device__ __forceinline__ bool pair_less(double d, int32_t j, double D, int32_t
     return d < D || (d == D && j < J);
 }
 
-// Insert (d, j) into the list sorted by (distance, index) whose first kk slots
-// are live.  Precondition: (d, j) is below the pair at place kk - 1.  Walking
-// down from that place, each slot either takes its upper neighbour (the new
-// pair goes further up) or the new pair, once; every slot is written once,
-// after the slot below it has been read, so the update is in place.
-template <int KMAX>
-__device__ __forceinline__ void knn_insert(double (&D)[KMAX], int32_t (&I)[KMAX], int kk, double d, int32_t j) {
-    bool placed = false;
+// Compare-exchange of (d, j) with the lane at xor o: the lane keeps the smaller
+// pair if `low`, else the larger.
+__device__ __forceinline__ void exchange(double& d, int32_t& j, int o, bool low) {
+    const double od = __shfl_xor(d, o);
+    const int32_t oj = __shfl_xor(j, o);
+    const bool less = pair_less(od, oj, d, j);
+    if (less == low) {
+        d = od;
+        j = oj;
+    }
+}
+
+// The G smallest pairs seen by a group of G lanes, ascending over the lanes: one
+// new pair per lane is sorted (bitonic) and merged into the kept list.
+template <int G>
+__device__ __forceinline__ void keep_smallest(double& D, int32_t& I, double d, int32_t j, int gl) {
+    // new pairs in descending order
 #pragma unroll
-    for (int s = KMAX - 1; s > 0; --s) {
-        if (s < kk && !placed) {
-            if (pair_less(d, j, D[s - 1], I[s - 1])) {
-                D[s] = D[s - 1];
-                I[s] = I[s - 1];
-            } else {
-                D[s] = d;
-                I[s] = j;
-                placed = true;
+    for (int size = 2; size <= G; size <<= 1)
+#pragma unroll
+        for (int o = size >> 1; o > 0; o >>= 1) {
+            const bool up = (gl & size) != 0 && size < G;   // ascending half of a bitonic run
+            exchange(d, j, o, ((gl & o) == 0) == up);
+        }
+    // the smaller of list[l] and new[l] (ascending against descending) are the G
+    // smallest, and form a bitonic sequence
+    if (pair_less(d, j, D, I)) {
+        D = d;
+        I = j;
+    }
+#pragma unroll
+    for (int o = G >> 1; o > 0; o >>= 1) exchange(D, I, o, (gl & o) == 0);
+}
+
+// Candidates of one query in the (2R + 1)^3 cells of grid g around its own, taken
+// by a group of G lanes: each lane looks up a cell, the cells' ranges are laid end
+// to end, and every lane takes every G-th candidate.  Cells whose box lies beyond
+// the bound are skipped (margin for the rounding of the box and the distances).
+// Returns false, with nothing taken, if more than `most` candidates would be read.
+template <int G>
+struct GroupLds {
+    int32_t start[G], before[G];
+};
+struct Query {
+    double x[3];
+    int32_t c[3];        // its 2r cell
+};
+template <int G, bool LIMITED>
+__device__ __forceinline__ bool scan_cube(const Cells& C, const u64x2* __restrict__ table,
+                                          const CellPoint* __restrict__ pts, const Query& q, int g, int R, double bound,
+                                          int kk, int gl, GroupLds<G>& S, int& budget, double& D, int32_t& I) {
+    const double h = C.h * (double)(1 << g);
+    const int side = 2 * R + 1;
+    const int64_t cells = (int64_t)side * side * side;
+    const uint32_t mask = (1u << C.lg) - 1u;
+    constexpr int PASSES = LIMITED ? (27 + G - 1) / G : 1;   // LIMITED: R = 1, all cells counted before any point is read
+    for (int64_t base = 0; base < cells; base += (int64_t)G * PASSES) {
+        int32_t from[PASSES], cnt[PASSES];
+        int total = 0;
+#pragma unroll
+        for (int p = 0; p < PASSES; ++p) {
+            const int64_t j = base + p * G + gl;
+            from[p] = 0;
+            cnt[p] = 0;
+            if (j < cells) {
+                const int32_t o[3] = {(int32_t)(j / (side * side)) - R, (int32_t)((j / side) % side) - R,
+                                      (int32_t)(j % side) - R};
+                bool in = true;
+                double e2 = 0.0;
+                uint64_t code = 0;
+#pragma unroll
+                for (int a = 0; a < 3; ++a) {
+                    const int32_t x = (q.c[a] >> g) + o[a];
+                    in = in && x >= 0 && x <= (C.hi[a] >> g);
+                    const double lo = (double)((int64_t)x * (1ll << g) + C.c0[a]) * C.h;
+                    const double e = fmax(0.0, fmax(lo - q.x[a], q.x[a] - (lo + h)));
+                    e2 += e * e;
+                    code |= spread21((uint64_t)(uint32_t)x) << (2 - a);
+                }
+                if (in && !(e2 * (1.0 - 1e-9) > bound)) {
+                    const uint64_t key = (1ull << (3 * (C.w - g))) | code;
+                    uint32_t s = cell_slot(key, C.lg);
+                    for (;;) {
+                        const u64x2 t = table[s];
+                        if (t.x == key) {
+                            from[p] = (int32_t)(uint32_t)t.y;
+                            cnt[p] = (int32_t)(uint32_t)(t.y >> 32) - from[p];
+                            break;
+                        }
+                        if (t.x == kPEmpty) break;
+                        s = (s + 1u) & mask;
+                    }
+                }
             }
+            total += cnt[p];
         }
-    }
-    if (!placed) {
-        D[0] = d;
-        I[0] = j;
-    }
-}
-
-// the pair at place kk - 1 (the k-th best so far)
-template <int KMAX>
-__device__ __forceinline__ void kth_pair(const double (&D)[KMAX], const int32_t (&I)[KMAX], int kk, double& wD,
-                                         int32_t& wI) {
-    wD = D[0];
-    wI = I[0];
+        if constexpr (LIMITED) {
+            int all = total;
 #pragma unroll
-    for (int s = 1; s < KMAX; ++s)
-        if (s == kk - 1) {
-            wD = D[s];
-            wI = I[s];
+            for (int o = G >> 1; o > 0; o >>= 1) all += __shfl_xor(all, o);
+            budget -= all;
+            if (budget < 0) return false;
         }
+#pragma unroll
+        for (int p = 0; p < PASSES; ++p) {
+            // exclusive prefix of the lanes' counts, and each cell's start shifted by it
+            int incl = cnt[p];
+#pragma unroll
+            for (int o = 1; o < G; o <<= 1) {
+                const int up = __shfl_up(incl, o, G);
+                if (gl >= o) incl += up;
+            }
+            const int sum = __shfl(incl, G - 1, G);
+            S.before[gl] = incl - cnt[p];
+            S.start[gl] = from[p] - (incl - cnt[p]);
+            __builtin_amdgcn_wave_barrier();
+            for (int c0 = 0; c0 < sum; c0 += G) {
+                const int c = c0 + gl;
+                double d = INFINITY;
+                int32_t j = INT_MAX;
+                if (c < sum) {
+                    int cell = 0;   // the last cell whose candidates start at or before c
+#pragma unroll
+                    for (int o = G >> 1; o > 0; o >>= 1)
+                        if (S.before[cell + o] <= c) cell += o;
+                    const CellPoint pt = pts[S.start[cell] + c];
+                    d = sqdist_rn(q.x[0], q.x[1], q.x[2], pt.x, pt.y, pt.z);
+                    j = (int32_t)pt.i;
+                }
+                // merged only if some lane's candidate beats the group's k-th pair
+                const double kD = __shfl(D, kk - 1, G);
+                const int32_t kI = __shfl(I, kk - 1, G);
+                const bool better = pair_less(d, j, kD, kI);
+                int any = better ? 1 : 0;
+#pragma unroll
+                for (int o = G >> 1; o > 0; o >>= 1) any |= __shfl_xor(any, o);
+                if (any) keep_smallest<G>(D, I, d, j, gl);
+            }
+            __builtin_amdgcn_wave_barrier();
+        }
+    }
+    return true;
 }
 
-constexpr int kGrids = 6;       // cell sizes 2r, 4r, ..., 64r
-constexpr int kShells = 1;      // shells walked on every grid but the coarsest
+// Whether the k-th distance kD is final after the (2R + 1)^3 cells of grid g: the
+// cells cover the cloud, or the distance to the first cell outside is larger.
+__device__ __forceinline__ bool settled(const Cells& C, const Query& q, int g, int R, double kD) {
+    const double h = C.h * (double)(1 << g);
+    bool all = true;
+    double b = INFINITY;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        const int32_t c = q.c[a] >> g;
+        all = all && c - R <= 0 && c + R >= (C.hi[a] >> g);
+        const double lo = (double)((int64_t)(c - R) * (1ll << g) + C.c0[a]) * C.h;
+        b = fmin(b, fmin(q.x[a] - lo, lo + (double)(2 * R + 1) * h - q.x[a]));
+    }
+    return all || (b > 0.0 && kD < b * b * (1.0 - 1e-9));
+}
+
 constexpr int kBudget = 1024;   // candidates a query may scan before it is handed to the wave-wide pass
 
-struct KnnGrid {
-    const double* sx;           // coordinates in cell order
-    const double* sy;
-    const double* sz;
-    const int32_t* cidx;        // cell order -> point index
-    const int32_t* cstart;      // per cell (cell ordinal)
-    const int32_t* ccount;
-    const uint64_t* hkeys;      // cell table
-    const int32_t* hval;
-    const int32_t* box;         // cell bounding box (6)
-    const int32_t* ncells;      // occupied cells (device scalar)
-    uint32_t lg;
-    double h;
-};
-
-struct KnnGrids {
-    KnnGrid g[kGrids];
-};
-
-// Exact k-NN, one thread per query, queries taken in the finest grid's cell order.
+// Exact k-NN, G lanes per query (G >= k), queries in cell order.
 //
 // A pass over grid g lists the k best pairs among the points of the cells it
 // visits.  If it cannot prove them final, its k-th pair P is still an upper
 // bound of the true k-th pair (its points are a subset of the cloud), so the
-// next pass (a) starts on the first coarser grid whose cells are at least
-// sqrt(d(P)) wide, (b) skips cells whose box lies farther than sqrt(d(P)), and
-// (c) keeps only candidates that do not exceed P.  Every point of the true
-// k best lies within sqrt(d(P)), so that pass still finds all of them.
-template <int KMAX>
-__global__ void __launch_bounds__(128) k_knn(const KnnGrid* __restrict__ grids, int64_t m, int k,
-                                             int32_t* __restrict__ nbr, double* __restrict__ nd2,
-                                             int32_t* __restrict__ hard, int32_t* __restrict__ n_hard) {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// next pass starts on the first coarser grid whose cells are at least sqrt(d(P))
+// wide and skips cells whose box lies farther than sqrt(d(P)): every point of the
+// true k best lies within that distance, so the pass still finds all of them.
+//
+// Bound by latency: a query is a chain of table reads, point reads and merges.
+// One thread per query kept 640 waves busy with 27 cells each one after another
+// (40k points, k = 10: 482 us, and 286 us for the queries handed over).
+template <int G>
+__global__ __launch_bounds__(256) void k_knn(Cells C, const u64x2* __restrict__ table, const CellPoint* __restrict__ pts,
+                                             int64_t m, int k, int32_t* __restrict__ nbr, double* __restrict__ nd2,
+                                             int32_t* __restrict__ hard, double* __restrict__ hard_bound,
+                                             int32_t* __restrict__ n_hard) {
+    __shared__ GroupLds<G> s_lds[256 / G];
+    const int gl = threadIdx.x % G;
+    const int64_t t = (int64_t)blockIdx.x * (256 / G) + threadIdx.x / G;
     if (t >= m) return;
-    const double qx = grids[0].sx[t], qy = grids[0].sy[t], qz = grids[0].sz[t];
+    GroupLds<G>& S = s_lds[threadIdx.x / G];
+    const CellPoint me = pts[t];
+    Query q{{me.x, me.y, me.z}, {0, 0, 0}};
+#pragma unroll
+    for (int a = 0; a < 3; ++a) q.c[a] = cell_coord(C, q.x[a], a);
     const int kk = (int)min((int64_t)k, m);
-    double D[KMAX];
-    int32_t I[KMAX];
-    double bD = INFINITY;   // bound carried between passes: the previous pass's k-th pair
-    int32_t bI = INT_MAX;
+    double bound = INFINITY;
+    int budget = kBudget;
     bool done = false;
-    int64_t scanned = 0;    // candidates read; past kBudget the query goes to the wave-wide pass
-#pragma unroll 1
-    for (int gi = 0; gi < kGrids && !done; ++gi) {
-        const KnnGrid g = grids[gi];
-        const double h = g.h;
-        const bool last = (gi == kGrids - 1);
-        if (!last && bD < INFINITY && h * h <= bD) continue;   // cells too small for the bound
-        const int64_t cx = (int64_t)floor(qx / h), cy = (int64_t)floor(qy / h), cz = (int64_t)floor(qz / h);
-        const int32_t bx0 = g.box[0], by0 = g.box[1], bz0 = g.box[2], bx1 = g.box[3], by1 = g.box[4],
-                      bz1 = g.box[5];
-        const int64_t rmax = max(max(max(cx - bx0, bx1 - cx), max(cy - by0, by1 - cy)), max(cz - bz0, bz1 - cz));
-        const int64_t nc = *g.ncells;
-#pragma unroll
-        for (int s = 0; s < KMAX; ++s) {
-            D[s] = INFINITY;
-            I[s] = INT_MAX;
-        }
-        // threshold: a candidate is kept iff it does not exceed (wD, wI); while the
-        // list is not full that is the carried bound, then the list's k-th pair
-        double wD = bD;
-        int32_t wI = bI;
-        int filled = 0;
-        for (int64_t r = 0;; ++r) {
-            if (!last && r > kShells) break;                       // not settled: next grid
-            if (last && r > 0 && (2 * r + 1) * (2 * r + 1) * (2 * r + 1) > 4 * nc + 64) goto handover;
-            for (int64_t dx = -r; dx <= r; ++dx) {
-                const int64_t x = cx + dx;
-                if (x < bx0 || x > bx1) continue;
-                const double ex = fmax(0.0, fmax((double)x * h - qx, qx - (double)(x + 1) * h));
-                for (int64_t dy = -r; dy <= r; ++dy) {
-                    const int64_t y = cy + dy;
-                    if (y < by0 || y > by1) continue;
-                    const double ey = fmax(0.0, fmax((double)y * h - qy, qy - (double)(y + 1) * h));
-                    const bool edge = (dx == -r || dx == r || dy == -r || dy == r);
-                    const int64_t step = (edge || r == 0) ? 1 : 2 * r;
-                    for (int64_t dz = -r; dz <= r; dz += step) {
-                        const int64_t z = cz + dz;
-                        if (z < bz0 || z > bz1) continue;
-                        const double ez = fmax(0.0, fmax((double)z * h - qz, qz - (double)(z + 1) * h));
-                        // the cell's box is farther than the threshold: nothing in it can be kept
-                        // (margin for the rounding of the box and of the distances)
-                        if ((ex * ex + ey * ey + ez * ez) * (1.0 - 1e-9) > wD) continue;
-                        const int32_t c = cell_find(g.hkeys, g.hval, g.lg, pack21(x, y, z));
-                        if (c < 0) continue;
-                        const int32_t p0 = g.cstart[c], p1 = p0 + g.ccount[c];
-                        scanned += p1 - p0;
-                        if (scanned > kBudget) goto handover;
-                        for (int32_t p = p0; p < p1; ++p) {
-                            const double d = sqdist_rn(qx, qy, qz, g.sx[p], g.sy[p], g.sz[p]);
-                            const int32_t j = g.cidx[p];
-                            if (!pair_less(wD, wI, d, j)) {   // (d, j) <= threshold
-                                knn_insert<KMAX>(D, I, kk, d, j);
-                                if (++filled >= kk) kth_pair<KMAX>(D, I, kk, wD, wI);
-                            }
-                        }
-                    }
-                }
-            }
-            if (r >= rmax) {   // every occupied cell of this grid visited
-                done = true;
-                break;
-            }
-            if (filled >= kk) {
-                const double bx = fmin(qx - (double)(cx - r) * h, (double)(cx + r + 1) * h - qx);
-                const double by = fmin(qy - (double)(cy - r) * h, (double)(cy + r + 1) * h - qy);
-                const double bz = fmin(qz - (double)(cz - r) * h, (double)(cz + r + 1) * h - qz);
-                const double b = fmin(bx, fmin(by, bz));
-                if (b > 0.0 && wD < b * b * (1.0 - 1e-9)) {
-                    done = true;
-                    break;
-                }
-            }
-        }
-        if (!done && filled >= kk) {
-            bD = wD;
-            bI = wI;
+    double D = INFINITY;
+    int32_t I = INT_MAX;
+    for (int g = 0; g < kGrids && !done; ++g) {
+        const double h = C.h * (double)(1 << g);
+        if (g < kGrids - 1 && bound < INFINITY && h * h <= bound) continue;   // cells too small for the bound
+        D = INFINITY;
+        I = INT_MAX;
+        if (!scan_cube<G, true>(C, table, pts, q, g, 1, bound, kk, gl, S, budget, D, I)) break;
+        const double kD = __shfl(D, kk - 1, G);
+        if (kD < INFINITY) {
+            done = settled(C, q, g, 1, kD);
+            bound = kD;
         }
     }
-    {
-        const int32_t i = grids[0].cidx[t];
-#pragma unroll
-        for (int s = 0; s < KMAX; ++s) {
-            if (s < k) {
-                const bool ok = s < kk;
-                nbr[(int64_t)i * k + s] = ok ? I[s] : -1;
-                nd2[(int64_t)i * k + s] = ok ? D[s] : INFINITY;
-            }
+    if (done) {
+        if (gl < k) {
+            const bool ok = gl < kk;
+            nbr[me.i * k + gl] = ok ? I : -1;
+            nd2[me.i * k + gl] = ok ? D : INFINITY;
         }
-        return;
+    } else if (gl == 0) {
+        const int32_t s = atomicAdd(n_hard, 1);
+        hard[s] = (int32_t)t;
+        hard_bound[s] = bound;
     }
-handover:
-    hard[atomicAdd(n_hard, 1)] = (int32_t)t;
 }
 
-// The queries the grid walk handed over: one wave per query scans every point
-// (each lane a strided share, its own k best in registers), then the lanes'
-// lists are merged by k rounds of a wave-wide minimum over their heads.
-template <int KMAX>
-__global__ void __launch_bounds__(64) k_knn_wave(const KnnGrid* __restrict__ grids, int64_t m, int k,
-                                                 const int32_t* __restrict__ hard, const int32_t* __restrict__ n_hard,
-                                                 uint32_t* __restrict__ next, int32_t* __restrict__ nbr,
+// The queries handed over, one wave each: the same search without a budget from the
+// first grid that fits the bound, then ever larger cubes of the coarsest cells,
+// and every point once a cube would hold more cells than a quarter of the points.
+__global__ __launch_bounds__(64) void k_knn_wave(Cells C, const u64x2* __restrict__ table,
+                                                 const CellPoint* __restrict__ pts, int64_t m, int k,
+                                                 const int32_t* __restrict__ hard, const double* __restrict__ hard_bound,
+                                                 const int32_t* __restrict__ n_hard, int32_t* __restrict__ nbr,
                                                  double* __restrict__ nd2) {
-    const KnnGrid g = grids[0];
+    __shared__ GroupLds<64> S;
     const int lane = threadIdx.x;
     const int kk = (int)min((int64_t)k, m);
-    for (;;) {
-        int32_t q = 0;
-        if (lane == 0) q = (int32_t)atomicAdd(next, 1u);
-        q = __shfl(q, 0);
-        if (q >= *n_hard) break;
-        const int32_t t = hard[q];
-        const double qx = g.sx[t], qy = g.sy[t], qz = g.sz[t];
-        double D[KMAX];
-        int32_t I[KMAX];
+    const int32_t total = *n_hard;
+    for (int32_t s = blockIdx.x; s < total; s += gridDim.x) {
+        const CellPoint me = pts[hard[s]];
+        Query q{{me.x, me.y, me.z}, {0, 0, 0}};
 #pragma unroll
-        for (int s = 0; s < KMAX; ++s) {
-            D[s] = INFINITY;
-            I[s] = INT_MAX;
-        }
-        double wD = INFINITY;
-        int32_t wI = INT_MAX;
-        int filled = 0;
-        for (int64_t p = lane; p < m; p += 64) {
-            const double d = sqdist_rn(qx, qy, qz, g.sx[p], g.sy[p], g.sz[p]);
-            const int32_t j = g.cidx[p];
-            if (!pair_less(wD, wI, d, j)) {
-                knn_insert<KMAX>(D, I, kk, d, j);
-                if (++filled >= kk) kth_pair<KMAX>(D, I, kk, wD, wI);
+        for (int a = 0; a < 3; ++a) q.c[a] = cell_coord(C, q.x[a], a);
+        double bound = hard_bound[s];
+        double D = INFINITY;
+        int32_t I = INT_MAX;
+        bool done = false;
+        int unused = 0;
+        for (int g = 0, R = 1; !done;) {
+            const double h = C.h * (double)(1 << g);
+            if (g < kGrids - 1 && bound < INFINITY && h * h <= bound) {
+                ++g;
+                continue;
             }
-        }
-        const int32_t i = g.cidx[t];
-        for (int o = 0; o < kk; ++o) {
-            double bd = D[0];
-            int32_t bj = I[0];
-#pragma unroll
-            for (int w = 32; w >= 1; w >>= 1) {
-                const double od = __shfl_xor(bd, w);
-                const int32_t oj = __shfl_xor(bj, w);
-                if (pair_less(od, oj, bd, bj)) {
-                    bd = od;
-                    bj = oj;
+            D = INFINITY;
+            I = INT_MAX;
+            const int64_t side = 2 * R + 1;
+            if (R > 1 && side * side * side > m / 4 + 64) {
+                for (int64_t p0 = 0; p0 < m; p0 += 64) {
+                    const int64_t p = p0 + lane;
+                    double d = INFINITY;
+                    int32_t j = INT_MAX;
+                    if (p < m) {
+                        const CellPoint pt = pts[p];
+                        d = sqdist_rn(q.x[0], q.x[1], q.x[2], pt.x, pt.y, pt.z);
+                        j = (int32_t)pt.i;
+                    }
+                    const double kD = __shfl(D, kk - 1);
+                    const int32_t kI = __shfl(I, kk - 1);
+                    if (__any(pair_less(d, j, kD, kI))) keep_smallest<64>(D, I, d, j, lane);
                 }
-            }
-            if (D[0] == bd && I[0] == bj) {   // this lane's head won: drop it
-#pragma unroll
-                for (int s = 0; s + 1 < KMAX; ++s) {
-                    D[s] = D[s + 1];
-                    I[s] = I[s + 1];
+                done = true;
+            } else {
+                scan_cube<64, false>(C, table, pts, q, g, R, bound, kk, lane, S, unused, D, I);
+                const double kD = __shfl(D, kk - 1);
+                if (kD < INFINITY) {
+                    done = settled(C, q, g, R, kD);
+                    bound = kD;
                 }
-                D[KMAX - 1] = INFINITY;
-                I[KMAX - 1] = INT_MAX;
-            }
-            if (lane == 0) {
-                nbr[(int64_t)i * k + o] = bj;
-                nd2[(int64_t)i * k + o] = bd;
+                if (g < kGrids - 1) ++g;
+                else R *= 2;
             }
         }
-        if (lane == 0)
-            for (int o = kk; o < k; ++o) {
-                nbr[(int64_t)i * k + o] = -1;
-                nd2[(int64_t)i * k + o] = INFINITY;
-            }
+        if (lane < k) {
+            const bool ok = lane < kk;
+            nbr[me.i * k + lane] = ok ? I : -1;
+            nd2[me.i * k + lane] = ok ? D : INFINITY;
+        }
     }
 }
 
@@ -549,12 +599,13 @@ __global__ void k_cov_normals(const double* __restrict__ xyz, const int32_t* __r
     co[5] = 1.0 - w * nz * nz;
 }
 
-// Bounding box of the m points (min, max), then point 0; one workgroup (tens of
-// thousands of points), written to pinned host memory.
-__global__ __launch_bounds__(1024) void k_cloud_box(const double* __restrict__ xyz, int64_t m, double* __restrict__ out) {
-    __shared__ double s[16][6];
+// Bounding boxes (min, max) of kBoxParts shares of the m points, then point 0, to
+// pinned host memory; the host joins the shares.
+constexpr int kBoxParts = 64;
+__global__ __launch_bounds__(256) void k_cloud_box(const double* __restrict__ xyz, int64_t m, double* __restrict__ out) {
+    __shared__ double s[4][6];
     double lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
-    for (int64_t i = threadIdx.x; i < m; i += blockDim.x)
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < m; i += (int64_t)kBoxParts * 256)
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
             lo[a] = fmin(lo[a], xyz[3 * i + a]);
@@ -576,14 +627,30 @@ __global__ __launch_bounds__(1024) void k_cloud_box(const double* __restrict__ x
     __syncthreads();
     if (threadIdx.x < 6) {
         double v = s[0][threadIdx.x];
-        for (int w = 1; w < 16; ++w) v = threadIdx.x < 3 ? fmin(v, s[w][threadIdx.x]) : fmax(v, s[w][threadIdx.x]);
-        out[threadIdx.x] = v;
-    } else if (threadIdx.x < 9) {
-        out[threadIdx.x] = xyz[threadIdx.x - 6];
+        for (int w = 1; w < 4; ++w) v = threadIdx.x < 3 ? fmin(v, s[w][threadIdx.x]) : fmax(v, s[w][threadIdx.x]);
+        out[6 * blockIdx.x + threadIdx.x] = v;
+    } else if (blockIdx.x == 0 && threadIdx.x < 9) {
+        out[6 * kBoxParts + threadIdx.x - 6] = xyz[threadIdx.x - 6];
     }
 }
+static_assert((6 * kBoxParts + 3) * 8 <= kSmallWords * 4, "the boxes fit the pinned words");
 
 int grid_of(int64_t n, int b = 256) { return (int)((n + b - 1) / b); }
+
+int bits_for(uint64_t max_value) {
+    int b = 0;
+    while (b < 64 && (max_value >> b) != 0) ++b;
+    return b;
+}
+
+// Sort of n words by their bits above idx_bits (the points ride in the low bits),
+// or of (word, point) pairs where idx_bits is 0.
+hipError_t sort_words(void* tmp, size_t& bytes, uint64_t* in, uint64_t* out, int32_t* i_in, int32_t* i_out, int64_t n,
+                      int idx_bits, int key_bits, hipStream_t st) {
+    const int end = std::max(1, key_bits + idx_bits);
+    if (i_in == nullptr) return hipcub::DeviceRadixSort::SortKeys(tmp, bytes, in, out, (int)n, idx_bits, std::max(end, idx_bits + 1), st);
+    return hipcub::DeviceRadixSort::SortPairs(tmp, bytes, in, out, i_in, i_out, (int)n, 0, end, st);
+}
 
 // every output array of a cloud in one allocation
 hipError_t alloc_cloud(vg_cloud* c, int64_t m, int k) {
@@ -613,8 +680,8 @@ void free_cloud(vg_cloud* c) {
     c->counts = c->nbr = nullptr;
 }
 
-vg_status preprocess_frame(vg_context* ctx, const double* d_xyz, int64_t n, double r, int k, const double sensor[3],
-                           vg_cloud* out) {
+vg_status preprocess_frame(vg_context* ctx, Scratch& sc, const double* d_xyz, int64_t n, const double box[6], double r,
+                           int k, const double sensor[3], vg_cloud* out) {
     hipStream_t st = ctx->stream;
     out->k = k;
     out->m = 0;
@@ -622,137 +689,122 @@ vg_status preprocess_frame(vg_context* ctx, const double* d_xyz, int64_t n, doub
         VG_HIP(alloc_cloud(out, 0, k));
         return VG_OK;
     }
-    Scratch sc(ctx);
-    int32_t* d_small = nullptr;   // flag, voxel count, hand-over count and cursor
-    VG_HIP(sc.get(&d_small, 16));
-    // 1. downsampling
-    uint64_t *keys, *keys_s, *ukeys;
-    int32_t *idx, *idx_s, *counts, *offsets;
-    VG_HIP(sc.get(&keys, n));
-    VG_HIP(sc.get(&keys_s, n));
-    VG_HIP(sc.get(&ukeys, n));
-    VG_HIP(sc.get(&idx, n));
-    VG_HIP(sc.get(&idx_s, n));
-    VG_HIP(sc.get(&counts, n));
-    VG_HIP(sc.get(&offsets, n));
-    size_t tmp_bytes = 0, b2 = 0, b3 = 0;
-    (void)hipcub::DeviceRadixSort::SortPairs(nullptr, tmp_bytes, keys, keys_s, idx, idx_s, (int)n, 0, 3 * kPBits);
-    (void)hipcub::DeviceRunLengthEncode::Encode(nullptr, b2, keys_s, ukeys, counts, d_small, (int)n);
-    (void)hipcub::DeviceScan::ExclusiveSum(nullptr, b3, counts, offsets, (int)n);
-    tmp_bytes = std::max(tmp_bytes, std::max(b2, b3)) + 256;
-    void* tmp = nullptr;
-    VG_HIP(sc.get((char**)&tmp, tmp_bytes));
-    int32_t h_init[16] = {0, 0, 0, 0, 0, 0, 0, 0, INT32_MAX, INT32_MAX, INT32_MAX, INT32_MIN, INT32_MIN, INT32_MIN, 0, 0};
-    VG_HIP(hipMemcpyAsync(d_small, h_init, sizeof(h_init), hipMemcpyHostToDevice, st));
-    k_ds_keys<<<grid_of(n), 256, 0, st>>>(d_xyz, n, r, keys, idx, d_small);
+    // 1. downsampling.  The key range follows from the frame's bounding box (floor
+    // and division are monotone).
+    DsKeys K{};
+    int64_t span[3];
+    for (int a = 0; a < 3; ++a) {
+        const double lo = std::floor(box[a] / r), hi = std::floor(box[3 + a] / r);
+        if (!(lo >= -(double)kPBias && hi < (double)kPBias)) {
+            set_error("downsampling voxel key outside the packable range (|floor(x / r)| >= 2^20 on an axis)");
+            return VG_ERR_KEY_RANGE;
+        }
+        K.q0[a] = (int64_t)lo;
+        span[a] = (int64_t)hi - (int64_t)lo;
+    }
+    K.wy = bits_for((uint64_t)span[1]);
+    K.wz = bits_for((uint64_t)span[2]);
+    const int ds_bits = bits_for((uint64_t)span[0]) + K.wy + K.wz, ib = bits_for((uint64_t)(n - 1));
+    const bool packed = ds_bits + ib <= 64 && ib > 0;
+    K.idx_bits = packed ? ib : 0;
+    uint64_t *w0, *w1;
+    int32_t *i0 = nullptr, *i1 = nullptr, *scan, *start;
+    VG_HIP(sc.get(&w0, n));
+    VG_HIP(sc.get(&w1, n));
+    VG_HIP(sc.get(&scan, n));
+    VG_HIP(sc.get(&start, n + 1));
+    if (!packed) {
+        VG_HIP(sc.get(&i0, n));
+        VG_HIP(sc.get(&i1, n));
+    }
+    const hipcub::CountingInputIterator<int64_t> cnt(0);
+    const hipcub::TransformInputIterator<int32_t, KeyChange, hipcub::CountingInputIterator<int64_t>> heads(
+        cnt, KeyChange{w1, K.idx_bits});
+    size_t b1 = 0, b2 = 0;
+    (void)sort_words(nullptr, b1, w0, w1, i0, i1, n, K.idx_bits, ds_bits, st);
+    (void)hipcub::DeviceScan::InclusiveSum(nullptr, b2, heads, scan, (int)n);
+    const size_t tmp_bytes = std::max(b1, b2) + 256;
+    char* tmp = nullptr;
+    VG_HIP(sc.get(&tmp, tmp_bytes));
+    k_ds_words<<<grid_of(n), 256, 0, st>>>(d_xyz, n, r, K, w0, i0);
     VG_HIP(hipGetLastError());
     size_t tb = tmp_bytes;
-    VG_HIP(hipcub::DeviceRadixSort::SortPairs(tmp, tb, keys, keys_s, idx, idx_s, (int)n, 0, 3 * kPBits, st));
+    VG_HIP(sort_words(tmp, tb, w0, w1, i0, i1, n, K.idx_bits, ds_bits, st));
     tb = tmp_bytes;
-    VG_HIP(hipcub::DeviceRunLengthEncode::Encode(tmp, tb, keys_s, ukeys, counts, d_small + 1, (int)n, st));
-    int32_t h_small[2] = {0, 0};
-    VG_HIP(hipMemcpyAsync(h_small, d_small, sizeof(h_small), hipMemcpyDeviceToHost, st));
+    VG_HIP(hipcub::DeviceScan::InclusiveSum(tmp, tb, heads, scan, (int)n, st));
+    k_ds_starts<<<grid_of(n), 256, 0, st>>>(scan, n, start, ctx->h_small);
+    VG_HIP(hipGetLastError());
     VG_HIP(hipStreamSynchronize(st));
-    if (h_small[0]) {
-        set_error("downsampling voxel key outside the packable range (|floor(x / r)| >= 2^20 on an axis)");
-        return VG_ERR_KEY_RANGE;
-    }
-    const int64_t m = h_small[1];
-    tb = tmp_bytes;
-    VG_HIP(hipcub::DeviceScan::ExclusiveSum(tmp, tb, counts, offsets, (int)m, st));
+    const int64_t m = ctx->h_small[0];
     VG_HIP(alloc_cloud(out, m, k));
     out->m = m;
-    k_ds_centroids<<<grid_of(m), 256, 0, st>>>(d_xyz, idx_s, offsets, counts, m, out->xyz, out->counts);
+    // 2. cells and the neighbour search (no host round trip)
+    Cells C{};
+    C.h = 2.0 * r;
+    int64_t widest = 0;
+    for (int a = 0; a < 3; ++a) {
+        // a centroid lies in its points' box up to rounding: one cell of margin
+        const int64_t lo = (int64_t)std::floor(box[a] / C.h) - 1, hi = (int64_t)std::floor(box[3 + a] / C.h) + 1;
+        C.c0[a] = (lo >> (kGrids - 1)) << (kGrids - 1);
+        C.hi[a] = (int32_t)(hi - C.c0[a]);
+        widest = std::max<int64_t>(widest, C.hi[a]);
+    }
+    C.w = std::max(bits_for((uint64_t)widest), kGrids);
+    const int cb = bits_for((uint64_t)(m - 1));
+    const bool cpacked = 3 * C.w + cb <= 64 && cb > 0;
+    C.idx_bits = cpacked ? cb : 0;
+    C.lg = 6;   // at most six cells per point: load factor <= 3/4, and mostly below 1/4
+    while ((1ull << C.lg) < 8ull * (uint64_t)m) ++C.lg;
+    uint64_t *cw0, *cw1;
+    int32_t *ci0 = nullptr, *ci1 = nullptr, *hard, *n_hard;
+    CellPoint* pts;
+    u64x2* table;
+    double* hard_bound;
+    VG_HIP(sc.get(&cw0, m));
+    VG_HIP(sc.get(&cw1, m));
+    if (!cpacked) {
+        VG_HIP(sc.get(&ci0, m));
+        VG_HIP(sc.get(&ci1, m));
+    }
+    VG_HIP(sc.get(&pts, m));
+    VG_HIP(sc.get(&table, ((size_t)1 << C.lg) + 1));   // the entry behind the table: the handed-over queries' count
+    VG_HIP(sc.get(&hard, m));
+    VG_HIP(sc.get(&hard_bound, m));
+    char* ctmp = nullptr;
+    size_t ctb = 0;
+    (void)sort_words(nullptr, ctb, cw0, cw1, ci0, ci1, m, C.idx_bits, 3 * C.w, st);
+    ctb += 256;
+    VG_HIP(sc.get(&ctmp, ctb));
+    n_hard = reinterpret_cast<int32_t*>(reinterpret_cast<uint64_t*>(table + ((size_t)1 << C.lg)) + 1);
+    k_fill_cells<<<grid_of(((int64_t)1 << C.lg) + 1), 256, 0, st>>>(table, ((int64_t)1 << C.lg) + 1);
     VG_HIP(hipGetLastError());
-    // 2. grids of cells and the neighbour search (no host round trip: the cell
-    // counts stay on the device, tables are sized for m cells)
-    uint32_t lg = 6;
-    while ((1ull << lg) < 2ull * (uint64_t)m) ++lg;
-    KnnGrids G{};
-    int32_t* d_grid_small = nullptr;   // per grid: box (6), cell count, pad
-    VG_HIP(sc.get(&d_grid_small, 8 * kGrids));
-    {
-        std::vector<int32_t> init(8 * kGrids);
-        for (int gi = 0; gi < kGrids; ++gi) {
-            int32_t* b = init.data() + 8 * gi;
-            b[0] = b[1] = b[2] = INT32_MAX;
-            b[3] = b[4] = b[5] = INT32_MIN;
-            b[6] = b[7] = 0;
-        }
-        VG_HIP(hipMemcpyAsync(d_grid_small, init.data(), sizeof(int32_t) * init.size(), hipMemcpyHostToDevice, st));
-        VG_HIP(hipStreamSynchronize(st));   // init lives on the host stack
-    }
-    uint64_t *ckeys, *ucells;
-    int32_t* cidx;
-    VG_HIP(sc.get(&ckeys, m));
-    VG_HIP(sc.get(&ucells, m));
-    VG_HIP(sc.get(&cidx, m));
-    double h = 2.0 * r;
-    for (int gi = 0; gi < kGrids; ++gi, h *= 2.0) {
-        KnnGrid& g = G.g[gi];
-        uint64_t* ckeys_s;
-        int32_t *cidx_s, *ccount, *cstart, *hval;
-        uint64_t* hkeys;
-        double *sx, *sy, *sz;
-        VG_HIP(sc.get(&ckeys_s, m));
-        VG_HIP(sc.get(&cidx_s, m));
-        VG_HIP(sc.get(&ccount, m));
-        VG_HIP(sc.get(&cstart, m));
-        VG_HIP(sc.get(&hkeys, (size_t)1 << lg));
-        VG_HIP(sc.get(&hval, (size_t)1 << lg));
-        VG_HIP(sc.get(&sx, m));
-        VG_HIP(sc.get(&sy, m));
-        VG_HIP(sc.get(&sz, m));
-        int32_t* box = d_grid_small + 8 * gi;
-        k_grid_keys<<<grid_of(m), 256, 0, st>>>(out->xyz, m, h, ckeys, cidx, box);
-        VG_HIP(hipGetLastError());
-        tb = tmp_bytes;
-        VG_HIP(hipcub::DeviceRadixSort::SortPairs(tmp, tb, ckeys, ckeys_s, cidx, cidx_s, (int)m, 0, 3 * kPBits, st));
-        k_fill_i32<<<grid_of(m), 256, 0, st>>>(ccount, m, 0);
-        VG_HIP(hipGetLastError());
-        tb = tmp_bytes;
-        VG_HIP(hipcub::DeviceRunLengthEncode::Encode(tmp, tb, ckeys_s, ucells, ccount, box + 6, (int)m, st));
-        tb = tmp_bytes;
-        VG_HIP(hipcub::DeviceScan::ExclusiveSum(tmp, tb, ccount, cstart, (int)m, st));
-        k_fill_u64p<<<grid_of((int64_t)1 << lg), 256, 0, st>>>(hkeys, (int64_t)1 << lg, kPEmpty);
-        VG_HIP(hipGetLastError());
-        k_cells_insert<<<grid_of(m), 256, 0, st>>>(ucells, box + 6, hkeys, hval, lg);
-        VG_HIP(hipGetLastError());
-        k_cells_gather<<<grid_of(m), 256, 0, st>>>(out->xyz, cidx_s, m, sx, sy, sz);
-        VG_HIP(hipGetLastError());
-        g = KnnGrid{sx, sy, sz, cidx_s, cstart, ccount, hkeys, hval, box, box + 6, lg, h};
-    }
-    KnnGrid* d_grids = nullptr;
-    VG_HIP(sc.get(&d_grids, kGrids));
-    VG_HIP(hipMemcpyAsync(d_grids, G.g, sizeof(G.g), hipMemcpyHostToDevice, st));
-    int32_t* d_hard = nullptr;
-    VG_HIP(sc.get(&d_hard, m));
-    int32_t* d_nhard = d_small + 4;                      // zeroed with d_small
-    uint32_t* d_next = (uint32_t*)(d_small + 5);
-    const int kb = 128;
-    const int waves = 2048;
-    if (k <= 8) {
-        k_knn<8><<<grid_of(m, kb), kb, 0, st>>>(d_grids, m, k, out->nbr, out->d2, d_hard, d_nhard);
-        k_knn_wave<8><<<waves, 64, 0, st>>>(d_grids, m, k, d_hard, d_nhard, d_next, out->nbr, out->d2);
-    } else if (k <= 16) {
-        k_knn<16><<<grid_of(m, kb), kb, 0, st>>>(d_grids, m, k, out->nbr, out->d2, d_hard, d_nhard);
-        k_knn_wave<16><<<waves, 64, 0, st>>>(d_grids, m, k, d_hard, d_nhard, d_next, out->nbr, out->d2);
-    } else {
-        k_knn<32><<<grid_of(m, kb), kb, 0, st>>>(d_grids, m, k, out->nbr, out->d2, d_hard, d_nhard);
-        k_knn_wave<32><<<waves, 64, 0, st>>>(d_grids, m, k, d_hard, d_nhard, d_next, out->nbr, out->d2);
-    }
+    k_ds_centroids<<<grid_of(m, 4 * kCentPerWave), 256, 0, st>>>(d_xyz, w1, i1, K.idx_bits, start, m, C, out->xyz,
+                                                                out->counts, cw0, ci0);
+    VG_HIP(hipGetLastError());
+    VG_HIP(sort_words(ctmp, ctb, cw0, cw1, ci0, ci1, m, C.idx_bits, 3 * C.w, st));
+    k_cells<<<grid_of(m), 256, 0, st>>>(out->xyz, cw1, ci1, m, C, pts, table);
+    VG_HIP(hipGetLastError());
+    // 16 lanes hold the best 16 pairs, 32 the best 32
+    if (k <= 16) k_knn<16><<<grid_of(m, 16), 256, 0, st>>>(C, table, pts, m, k, out->nbr, out->d2, hard, hard_bound, n_hard);
+    else k_knn<32><<<grid_of(m, 8), 256, 0, st>>>(C, table, pts, m, k, out->nbr, out->d2, hard, hard_bound, n_hard);
+    VG_HIP(hipGetLastError());
+    k_knn_wave<<<4096, 64, 0, st>>>(C, table, pts, m, k, hard, hard_bound, n_hard, out->nbr, out->d2);
     VG_HIP(hipGetLastError());
     // 3. covariances and normals
     k_cov_normals<<<grid_of(m), 256, 0, st>>>(out->xyz, out->nbr, m, k, sensor[0], sensor[1], sensor[2], out->cov,
                                                out->cov_raw, out->nrm);
     VG_HIP(hipGetLastError());
     // the points' bounding box and point 0, for the sources and maps made from the cloud
-    double* h_out = reinterpret_cast<double*>(ctx->h_small);
-    k_cloud_box<<<1, 1024, 0, st>>>(out->xyz, m, h_out);
+    double* h = reinterpret_cast<double*>(ctx->h_small);
+    k_cloud_box<<<kBoxParts, 256, 0, st>>>(out->xyz, m, h);
     VG_HIP(hipGetLastError());
     VG_HIP(hipStreamSynchronize(st));
-    for (int a = 0; a < 6; ++a) out->box[a] = h_out[a];
-    for (int a = 0; a < 3; ++a) out->first[a] = h_out[6 + a];
+    for (int a = 0; a < 6; ++a) {
+        out->box[a] = h[a];
+        for (int p = 1; p < kBoxParts; ++p)
+            out->box[a] = a < 3 ? std::min(out->box[a], h[6 * p + a]) : std::max(out->box[a], h[6 * p + a]);
+    }
+    for (int a = 0; a < 3; ++a) out->first[a] = h[6 * kBoxParts + a];
     return VG_OK;
 }
 

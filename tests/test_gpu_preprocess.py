@@ -252,3 +252,26 @@ def test_preprocessed_clouds_feed_the_factor(vg, frame, validate):
     batch.close()
     src.close()
     vm.close()
+
+
+@pytest.mark.parametrize("n,k,span", [
+    (2, 3, 1.0),         # fewer points than neighbours
+    (15, 16, 2.0),       # all lanes of a query's group, one short
+    (17, 16, 2.0),
+    (33, 32, 2.0),
+    (400, 17, 6.0),      # the first k of the 32-lane groups
+    (300, 10, 100000.0), # a few hundred voxels apart by kilometres: every query ends beyond the coarsest cells
+    (3000, 5, 500000.0), # keys and points need more than 64 bits: sorted as pairs
+])
+def test_edges_of_the_neighbour_groups_and_key_widths(vg, n, k, span):
+    """Against the oracle, bit for bit (points, counts, neighbours, distances)."""
+    vgicp, ctx = vg
+    rng = np.random.default_rng(100 + n)
+    xyz = rng.uniform(-span, span, size=(n, 3))
+    xyz[n // 2:] = xyz[: n - n // 2] + rng.normal(scale=0.4, size=(n - n // 2, 3))   # every point has company
+    s = np.array([0.0, 0.0, 1.0])
+    dev = device(vgicp, ctx, xyz, 0.5, k, s)
+    o = pp.preprocess(xyz, 0.5, k, s)
+    for key in ("xyz", "counts", "d2"):
+        assert np.array_equal(dev[key], o[key]), key
+    assert np.array_equal(dev["nbr"], o["nbr"].astype(np.int32))

@@ -170,3 +170,52 @@ def test_voxel_capacity_per_level(vg):
     with pytest.raises(VGError) as ei:
         vgicp.VoxelMap(ctx, xyz, cov, [1.0])
     assert ei.value.status == -5
+
+
+@pytest.mark.parametrize("n,half,res", [
+    (63, 3.0, [0.25, 0.5, 1.0, 2.0]),            # fewer points than a voxel's load step, all levels
+    (1, 3.0, [0.5]),
+    (1_200_000, 2040.0, [0.25, 1.0]),            # level, voxel and point need more than 64 bits: sorted as pairs
+])
+def test_joint_levels_equal_the_oracle(vg, n, half, res):
+    """Every level of a map built in one go, bit for bit: keys, counts, means, covariances."""
+    vgicp, ctx = vg
+    rng = np.random.default_rng(9)
+    xyz = rng.uniform(-half, half, size=(n, 3))
+    xyz[0] = 0.0
+    cov = _covs(rng, min(n, 1000))[np.arange(n) % 1000]
+    m = vgicp.VoxelMap(ctx, xyz, cov, res)
+    for l, r in enumerate(res):
+        k_o, m_o, c_o, n_o = oracle.voxelize(xyz, cov, r)
+        k_d, m_d, c_d, n_d = m.export(l)
+        assert np.array_equal(k_d, k_o) and np.array_equal(n_d, n_o)
+        assert np.array_equal(m_d, m_o) and np.array_equal(c_d, c_o)
+    m.close()
+
+
+@pytest.mark.parametrize("span", [40.0, 400_000.0])
+def test_source_order_of_wide_clouds(vg, span):
+    """A source whose Morton codes leave no room for the point in the sort word (cells
+    beyond 2^20 per axis) and one that fits: the same factor as the oracle's, and
+    correspondences in caller order."""
+    vgicp, ctx = vg
+    rng = np.random.default_rng(13)
+    near = rng.uniform(-15.0, 15.0, size=(700, 3))
+    far = rng.uniform(-span, span, size=(300, 3))
+    xyz = np.concatenate([[[0.0, 0.0, 0.0]], near, far])
+    cov = _covs(rng, len(xyz))
+    tgt = near + rng.normal(scale=0.01, size=near.shape)
+    tcov = _covs(rng, len(tgt))
+    s, m = vgicp.Source(ctx, xyz, cov), vgicp.VoxelMap(ctx, tgt, tcov, [0.5])
+    batch = vgicp.FactorBatch(ctx, [s], [m], precision="fp64")
+    pose = np.eye(4)
+    pose[:3, 3] = [0.01, -0.02, 0.005]
+    e, H, b, inl = batch.linearize([pose])
+    of = oracle.Factor(xyz, cov, oracle.VoxelMap(tgt, tcov, [0.5])).linearize(pose)
+    assert inl[0, 0] == of["inliers"][0]
+    # FP64 sums of a thousand terms in another order
+    assert abs(e[0] - of["e"]) <= 1e-10 * of["e"] and np.allclose(H[0], of["H"], rtol=0, atol=1e-10 * np.abs(of["H"]).max())
+    keys, _ = batch.correspondences(pose, 0)
+    assert np.array_equal(keys[:, 0], np.floor((xyz + pose[:3, 3]) / 0.5).astype(np.int64))
+    for h in (batch, s, m):
+        h.close()
