@@ -30,9 +30,10 @@
  *
  * Error behaviour: every call returns a vg_status (0 = VG_OK).  No exception
  * crosses the ABI.  On failure vg_last_error() returns a message that stays
- * valid until the next call on the same thread.  Arguments are validated on
- * the host before any device work is queued; a failed call leaves its outputs
- * unspecified and its handles usable.
+ * valid until the next call on the same thread.  Arguments are validated before
+ * any work that uses them is queued (the values of a cloud's arrays on the device,
+ * after their upload); a failed call leaves its outputs unspecified and its
+ * handles usable.
  *
  * Ownership: input arrays are read during the call and never retained;
  * handles are owned by the caller and released with the matching *_destroy.

@@ -52,26 +52,6 @@ bool finite_all(const double* p, int64_t n) {
     return true;
 }
 
-// Bounding box (min xyz, max xyz) of n finite points.
-void bounding_box(const double* xyz, int64_t n, double box[6]) {
-    for (int a = 0; a < 3; ++a) box[a] = box[3 + a] = n > 0 ? xyz[a] : 0.0;
-    for (int64_t i = 0; i < n; ++i)
-        for (int a = 0; a < 3; ++a) {
-            box[a] = std::min(box[a], xyz[3 * i + a]);
-            box[3 + a] = std::max(box[3 + a], xyz[3 * i + a]);
-        }
-}
-
-// Leading principal minors of [a b c; b d e; c e f] all positive.
-bool spd6(const double* c) {
-    const double a = c[0], b = c[1], cc = c[2], d = c[3], e = c[4], f = c[5];
-    if (!(a > 0.0)) return false;
-    const double m2 = a * d - b * b;
-    if (!(m2 > 0.0)) return false;
-    const double det = a * (d * f - e * e) - b * (b * f - cc * e) + cc * (b * e - cc * d);
-    return det > 0.0;
-}
-
 bool is_pow2(double r) {
     int ex = 0;
     const double m = std::frexp(r, &ex);
@@ -248,6 +228,33 @@ extern "C" vg_status vg_context_destroy(vg_context* ctx) {
     return VG_OK;
 }
 
+// Upload of a caller's cloud (covariances and normals may be NULL) and its check
+// on the device: every value finite, every covariance SPD.  box: its bounding box.
+static vg_status upload_cloud(vg_context* ctx, Scratch& sc, const double* xyz, const double* cov, const double* normals,
+                              int64_t n, double** d_xyz, double** d_cov, double** d_nrm, double box[6]) {
+    for (int a = 0; a < 6; ++a) box[a] = 0.0;
+    if (n == 0) return VG_OK;
+    hipStream_t st = ctx->stream;
+    VG_HIP(sc.get(d_xyz, 3 * n));
+    if (cov) VG_HIP(sc.get(d_cov, 6 * n));
+    if (normals) VG_HIP(sc.get(d_nrm, 3 * n));
+    VG_HIP(hipMemcpyAsync(*d_xyz, xyz, sizeof(double) * 3 * n, hipMemcpyHostToDevice, st));
+    if (cov) VG_HIP(hipMemcpyAsync(*d_cov, cov, sizeof(double) * 6 * n, hipMemcpyHostToDevice, st));
+    if (normals) VG_HIP(hipMemcpyAsync(*d_nrm, normals, sizeof(double) * 3 * n, hipMemcpyHostToDevice, st));
+    VG_TRY(launch_check(ctx, *d_xyz, cov ? *d_cov : nullptr, normals ? *d_nrm : nullptr, n));
+    VG_HIP(hipStreamSynchronize(st));
+    const CheckPart c = joined_check(ctx, n);
+    if (c.flags & kBadXyz) return invalid("xyz has non-finite values");
+    if (c.flags & kBadCov) return invalid("cov has non-finite values");
+    if (c.flags & kBadNormal) return invalid("normals have non-finite values");
+    if (c.bad != INT64_MAX) {
+        set_error("covariance of point " + std::to_string(c.bad) + " is not SPD");
+        return VG_ERR_NOT_SPD;
+    }
+    for (int a = 0; a < 6; ++a) box[a] = c.box[a];
+    return VG_OK;
+}
+
 // ============================================================================ voxel maps
 
 // Voxel map from device FP64 arrays; first = host copy of point 0 (the origin),
@@ -294,24 +301,10 @@ extern "C" vg_status vg_build_voxelmap(vg_context* ctx, const double* xyz, const
     if (n > 0 && (xyz == nullptr || cov == nullptr)) return invalid("xyz or cov is NULL");
     if (n >= (int64_t)1 << 31) return invalid("n must be below 2^31");
     VG_TRY(check_resolutions(resolutions, L));
-    if (n > 0 && !finite_all(xyz, 3 * n)) return invalid("xyz has non-finite values");
-    if (n > 0 && !finite_all(cov, 6 * n)) return invalid("cov has non-finite values");
-    for (int64_t i = 0; i < n; ++i)
-        if (!spd6(cov + 6 * i)) {
-            set_error("covariance of point " + std::to_string(i) + " is not SPD");
-            return VG_ERR_NOT_SPD;
-        }
     VG_HIP(hipSetDevice(ctx->device));
-    double box[6];
-    bounding_box(xyz, n, box);
     Scratch sc(ctx);
-    double *d_xyz = nullptr, *d_cov = nullptr;
-    VG_HIP(sc.get(&d_xyz, 3 * n));
-    VG_HIP(sc.get(&d_cov, 6 * n));
-    if (n > 0) {
-        VG_HIP(hipMemcpyAsync(d_xyz, xyz, sizeof(double) * 3 * n, hipMemcpyHostToDevice, ctx->stream));
-        VG_HIP(hipMemcpyAsync(d_cov, cov, sizeof(double) * 6 * n, hipMemcpyHostToDevice, ctx->stream));
-    }
+    double box[6], *d_xyz = nullptr, *d_cov = nullptr;
+    VG_TRY(upload_cloud(ctx, sc, xyz, cov, nullptr, n, &d_xyz, &d_cov, nullptr, box));
     return make_voxelmap(ctx, sc, d_xyz, d_cov, n, resolutions, L, xyz, box, out);
 }
 
@@ -421,27 +414,10 @@ extern "C" vg_status vg_create_source(vg_context* ctx, const double* xyz, const 
     if (n < 0) return invalid("n < 0");
     if (n >= (int64_t)1 << 27) return invalid("n must be below 2^27 (134,217,728 points per source)");
     if (n > 0 && (xyz == nullptr || cov == nullptr)) return invalid("xyz or cov is NULL");
-    if (n > 0 && !finite_all(xyz, 3 * n)) return invalid("xyz has non-finite values");
-    if (n > 0 && !finite_all(cov, 6 * n)) return invalid("cov has non-finite values");
-    if (n > 0 && normals && !finite_all(normals, 3 * n)) return invalid("normals have non-finite values");
-    for (int64_t i = 0; i < n; ++i)
-        if (!spd6(cov + 6 * i)) {
-            set_error("covariance of point " + std::to_string(i) + " is not SPD");
-            return VG_ERR_NOT_SPD;
-        }
     VG_HIP(hipSetDevice(ctx->device));
-    double box[6];
-    bounding_box(xyz, n, box);
     Scratch sc(ctx);
-    double *d_xyz = nullptr, *d_cov = nullptr, *d_nrm = nullptr;
-    if (n > 0) {
-        VG_HIP(sc.get(&d_xyz, 3 * n));
-        VG_HIP(sc.get(&d_cov, 6 * n));
-        if (normals) VG_HIP(sc.get(&d_nrm, 3 * n));
-        VG_HIP(hipMemcpyAsync(d_xyz, xyz, sizeof(double) * 3 * n, hipMemcpyHostToDevice, ctx->stream));
-        VG_HIP(hipMemcpyAsync(d_cov, cov, sizeof(double) * 6 * n, hipMemcpyHostToDevice, ctx->stream));
-        if (normals) VG_HIP(hipMemcpyAsync(d_nrm, normals, sizeof(double) * 3 * n, hipMemcpyHostToDevice, ctx->stream));
-    }
+    double box[6], *d_xyz = nullptr, *d_cov = nullptr, *d_nrm = nullptr;
+    VG_TRY(upload_cloud(ctx, sc, xyz, cov, normals, n, &d_xyz, &d_cov, &d_nrm, box));
     return make_source(ctx, sc, d_xyz, d_cov, d_nrm, normals != nullptr, n, xyz, box, out);
 }
 
@@ -485,14 +461,10 @@ extern "C" vg_status vg_preprocess(vg_context* ctx, const double* xyz, int64_t n
     if (!(std::isfinite(r) && r > 0.0)) return invalid("r must be positive and finite");
     if (k < 1 || k > 32) return invalid("k must be in 1..32");
     if (sensor == nullptr || !finite_all(sensor, 3)) return invalid("sensor must be 3 finite values");
-    if (n > 0 && !finite_all(xyz, 3 * n)) return invalid("xyz has non-finite values");
     VG_HIP(hipSetDevice(ctx->device));
-    double box[6];
-    bounding_box(xyz, n, box);
     Scratch sc(ctx);
-    double* d_xyz = nullptr;
-    VG_HIP(sc.get(&d_xyz, 3 * n));
-    if (n > 0) VG_HIP(hipMemcpyAsync(d_xyz, xyz, sizeof(double) * 3 * n, hipMemcpyHostToDevice, ctx->stream));
+    double box[6], *d_xyz = nullptr;
+    VG_TRY(upload_cloud(ctx, sc, xyz, nullptr, nullptr, n, &d_xyz, nullptr, nullptr, box));
     auto* c = new vg_cloud();
     c->ctx = ctx;
     const vg_status st = preprocess_frame(ctx, sc, d_xyz, n, box, r, k, sensor, c);

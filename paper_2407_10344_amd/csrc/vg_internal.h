@@ -275,7 +275,8 @@ vg_status hip_fail(hipError_t e, const char* what);
 // ---------------------------------------------------------------- scratch
 
 constexpr size_t kKeepWorkspace = (size_t)1 << 30;   // a larger call's temporaries are freed with it
-constexpr int kSmallWords = 1024;                    // pinned words of a context
+constexpr int kCheckParts = 256;                     // workgroups of a cloud's check at most
+constexpr int kSmallWords = 8192;                    // pinned words of a context
 
 // Temporaries of one call, carved from the context's workspace (the calls of a
 // context are ordered on its stream, so a later call may write them while the
@@ -318,6 +319,21 @@ struct Scratch {
 };
 
 // ---------------------------------------------------------------- launchers (device code)
+
+// One workgroup's share of the check of a cloud's arrays, in pinned host memory.
+constexpr int32_t kBadXyz = 1, kBadCov = 2, kBadNormal = 4;   // some value is not finite
+struct CheckPart {
+    double box[6];       // min xyz, max xyz
+    double first[3];     // point 0
+    int64_t bad;         // lowest point whose covariance is not SPD (INT64_MAX: none)
+    int32_t flags;
+    int32_t pad;
+};
+static_assert(sizeof(CheckPart) * kCheckParts <= sizeof(int32_t) * kSmallWords, "the parts fit the pinned words");
+// check n >= 1 points (covariances and normals may be nullptr); the result may be
+// read with joined_check once the stream has been waited for
+vg_status launch_check(vg_context* ctx, const double* d_xyz, const double* d_cov, const double* d_nrm, int64_t n);
+CheckPart joined_check(const vg_context* ctx, int64_t n);
 
 // every level of m (its origin is set) from n points; box: their bounding box
 vg_status build_map(vg_context* ctx, Scratch& sc, const double* d_xyz, const double* d_cov, int64_t n,

@@ -599,41 +599,79 @@ __global__ void k_cov_normals(const double* __restrict__ xyz, const int32_t* __r
     co[5] = 1.0 - w * nz * nz;
 }
 
-// Bounding boxes (min, max) of kBoxParts shares of the m points, then point 0, to
-// pinned host memory; the host joins the shares.
-constexpr int kBoxParts = 64;
-__global__ __launch_bounds__(256) void k_cloud_box(const double* __restrict__ xyz, int64_t m, double* __restrict__ out) {
-    __shared__ double s[4][6];
+// Leading principal minors of [a b c; b d e; c e f] all positive (each operation
+// rounded on its own: this file is compiled without contraction).
+__device__ __forceinline__ bool spd6(const double* c) {
+    const double a = c[0], b = c[1], cc = c[2], d = c[3], e = c[4], f = c[5];
+    const double m2 = a * d - b * b;
+    const double det = a * (d * f - e * e) - b * (b * f - cc * e) + cc * (b * e - cc * d);
+    return a > 0.0 && m2 > 0.0 && det > 0.0;
+}
+
+// Check of a cloud's arrays, and its bounding box: each workgroup takes a share of
+// the points and writes its part to pinned host memory, where the host joins them.
+// Bound by its reads (24 B per point, 72-96 B with covariances and normals).  On the
+// host the same loops took 1.4 ms for a 140k-point submap's source and map, more than
+// the two uploads and builds together.
+__global__ __launch_bounds__(256) void k_check(const double* __restrict__ xyz, const double* __restrict__ cov,
+                                               const double* __restrict__ nrm, int64_t n, CheckPart* __restrict__ out) {
+    __shared__ CheckPart s[4];
     double lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < m; i += (int64_t)kBoxParts * 256)
+    int32_t flags = 0;
+    int64_t bad = INT64_MAX;
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
-            lo[a] = fmin(lo[a], xyz[3 * i + a]);
-            hi[a] = fmax(hi[a], xyz[3 * i + a]);
+            const double x = xyz[3 * i + a];
+            if (!isfinite(x)) flags |= kBadXyz;
+            lo[a] = fmin(lo[a], x);
+            hi[a] = fmax(hi[a], x);
+            if (nrm != nullptr && !isfinite(nrm[3 * i + a])) flags |= kBadNormal;
         }
+        if (cov != nullptr) {
+            double c[6];
 #pragma unroll
-    for (int w = 32; w >= 1; w >>= 1)
+            for (int k = 0; k < 6; ++k) {
+                c[k] = cov[6 * i + k];
+                if (!isfinite(c[k])) flags |= kBadCov;
+            }
+            if (!spd6(c)) bad = min(bad, i);
+        }
+    }
+#pragma unroll
+    for (int w = 32; w >= 1; w >>= 1) {
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
             lo[a] = fmin(lo[a], __shfl_xor(lo[a], w));
             hi[a] = fmax(hi[a], __shfl_xor(hi[a], w));
         }
-    if ((threadIdx.x & 63) == 0)
-#pragma unroll
+        flags |= __shfl_xor(flags, w);
+        bad = min(bad, (int64_t)__shfl_xor((long long)bad, w));
+    }
+    if ((threadIdx.x & 63) == 0) {
+        CheckPart& p = s[threadIdx.x >> 6];
         for (int a = 0; a < 3; ++a) {
-            s[threadIdx.x >> 6][a] = lo[a];
-            s[threadIdx.x >> 6][3 + a] = hi[a];
+            p.box[a] = lo[a];
+            p.box[3 + a] = hi[a];
         }
+        p.bad = bad;
+        p.flags = flags;
+    }
     __syncthreads();
-    if (threadIdx.x < 6) {
-        double v = s[0][threadIdx.x];
-        for (int w = 1; w < 4; ++w) v = threadIdx.x < 3 ? fmin(v, s[w][threadIdx.x]) : fmax(v, s[w][threadIdx.x]);
-        out[6 * blockIdx.x + threadIdx.x] = v;
-    } else if (blockIdx.x == 0 && threadIdx.x < 9) {
-        out[6 * kBoxParts + threadIdx.x - 6] = xyz[threadIdx.x - 6];
+    if (threadIdx.x == 0) {
+        CheckPart p = s[0];
+        for (int w = 1; w < 4; ++w) {
+            for (int a = 0; a < 3; ++a) {
+                p.box[a] = fmin(p.box[a], s[w].box[a]);
+                p.box[3 + a] = fmax(p.box[3 + a], s[w].box[3 + a]);
+            }
+            p.bad = min(p.bad, s[w].bad);
+            p.flags |= s[w].flags;
+        }
+        for (int a = 0; a < 3; ++a) p.first[a] = xyz[a];
+        out[blockIdx.x] = p;
     }
 }
-static_assert((6 * kBoxParts + 3) * 8 <= kSmallWords * 4, "the boxes fit the pinned words");
 
 int grid_of(int64_t n, int b = 256) { return (int)((n + b - 1) / b); }
 
@@ -795,17 +833,35 @@ vg_status preprocess_frame(vg_context* ctx, Scratch& sc, const double* d_xyz, in
                                                out->cov_raw, out->nrm);
     VG_HIP(hipGetLastError());
     // the points' bounding box and point 0, for the sources and maps made from the cloud
-    double* h = reinterpret_cast<double*>(ctx->h_small);
-    k_cloud_box<<<kBoxParts, 256, 0, st>>>(out->xyz, m, h);
-    VG_HIP(hipGetLastError());
+    const vg_status rc = launch_check(ctx, out->xyz, nullptr, nullptr, m);
+    if (rc != VG_OK) return rc;
     VG_HIP(hipStreamSynchronize(st));
-    for (int a = 0; a < 6; ++a) {
-        out->box[a] = h[a];
-        for (int p = 1; p < kBoxParts; ++p)
-            out->box[a] = a < 3 ? std::min(out->box[a], h[6 * p + a]) : std::max(out->box[a], h[6 * p + a]);
-    }
-    for (int a = 0; a < 3; ++a) out->first[a] = h[6 * kBoxParts + a];
+    const CheckPart c = joined_check(ctx, m);
+    for (int a = 0; a < 6; ++a) out->box[a] = c.box[a];
+    for (int a = 0; a < 3; ++a) out->first[a] = c.first[a];
     return VG_OK;
+}
+
+static int check_grid(int64_t n) { return (int)std::min<int64_t>(kCheckParts, (n + 255) / 256); }
+
+vg_status launch_check(vg_context* ctx, const double* d_xyz, const double* d_cov, const double* d_nrm, int64_t n) {
+    k_check<<<check_grid(n), 256, 0, ctx->stream>>>(d_xyz, d_cov, d_nrm, n, reinterpret_cast<CheckPart*>(ctx->h_small));
+    VG_HIP(hipGetLastError());
+    return VG_OK;
+}
+
+CheckPart joined_check(const vg_context* ctx, int64_t n) {
+    const CheckPart* part = reinterpret_cast<const CheckPart*>(ctx->h_small);
+    CheckPart p = part[0];
+    for (int k = 1; k < check_grid(n); ++k) {
+        for (int a = 0; a < 3; ++a) {
+            p.box[a] = std::min(p.box[a], part[k].box[a]);
+            p.box[3 + a] = std::max(p.box[3 + a], part[k].box[3 + a]);
+        }
+        p.bad = std::min(p.bad, part[k].bad);
+        p.flags |= part[k].flags;
+    }
+    return p;
 }
 
 }  // namespace vg

@@ -219,3 +219,32 @@ def test_source_order_of_wide_clouds(vg, span):
     assert np.array_equal(keys[:, 0], np.floor((xyz + pose[:3, 3]) / 0.5).astype(np.int64))
     for h in (batch, s, m):
         h.close()
+
+
+@pytest.mark.parametrize("n", [1, 255, 257, 70_000])
+def test_bad_values_are_refused_wherever_they_are(vg, n):
+    """The check of a cloud's arrays runs on the device: the last point's bad value is
+    found, what is reported is the first in the order positions, covariances, normals,
+    definiteness, and the lowest point that is not SPD is named."""
+    from paper_2407_10344_amd._lib import VGError
+    vgicp, ctx = vg
+    rng = np.random.default_rng(21)
+    xyz = rng.uniform(-5.0, 5.0, size=(n, 3))
+    cov = _covs(rng, min(n, 500))[np.arange(n) % 500]
+    nrm = np.tile([[0.0, 0.0, 1.0]], (n, 1))
+    bad = {"xyz": xyz.copy(), "cov": cov.copy(), "nrm": nrm.copy()}
+    bad["xyz"][-1, 2] = np.inf
+    bad["cov"][-1, 5] = np.nan
+    bad["nrm"][-1, 0] = -np.inf
+    spd = cov.copy()
+    spd[n // 2:, 0] = -1.0
+    for args, text in (((bad["xyz"], bad["cov"], bad["nrm"]), "xyz"), ((xyz, bad["cov"], bad["nrm"]), "cov"),
+                       ((xyz, spd, bad["nrm"]), "normals"), ((xyz, spd, nrm), "point %d " % (n // 2))):
+        with pytest.raises(VGError, match=text):
+            vgicp.Source(ctx, *args)
+    for args, text in (((bad["xyz"], spd), "xyz"), ((xyz, bad["cov"]), "cov"), ((xyz, spd), "point %d " % (n // 2))):
+        with pytest.raises(VGError, match=text):
+            vgicp.VoxelMap(ctx, *args, [0.5])
+    with pytest.raises(VGError, match="xyz"):
+        vgicp.Cloud(ctx, bad["xyz"], 0.5)
+    vgicp.Source(ctx, xyz, cov, nrm).close()
