@@ -1187,17 +1187,28 @@ namespace {
 // One Levenberg-Marquardt iteration for every factor, stream-ordered: linearize
 // at d_poses, propose T Exp(delta) from (H + lambda diag H) delta = -b, evaluate
 // the proposal, accept or reject it (lambda / 10 or x 10).  e at the input poses
-// and the decision go to column `col` of d_e / d_acc (rows of `stride`).
+// and the decision go to column `col` of d_e / d_acc (rows of `stride`).  staged:
+// a previous iteration left the FP32 copies of d_poses.
 vg_status lm_step(vg_batch* b, double* d_poses, double* d_lambda, double* d_e, int32_t* d_acc, int32_t stride,
-                  int32_t col) {
+                  int32_t col, bool staged) {
     const int64_t F = b->F;
-    double* cand = b->d_lm + F;                              // 12 per factor
-    double* e_new = b->d_lm + 13 * F;                        // 1 per factor
-    int32_t* valid = reinterpret_cast<int32_t*>(b->d_lm + 14 * F);
-    VG_TRY(run_linearize_device(b, d_poses, b->d_out, nullptr));
-    VG_TRY(launch_lm_propose(b, b->d_out, d_lambda, d_poses, cand, valid));
-    VG_TRY(run_evaluate_device(b, cand, e_new));
-    return launch_lm_accept(b, b->d_out, e_new, d_lambda, d_poses, cand, valid, d_e, d_acc, stride, col);
+    const int32_t nt = (int32_t)b->h_tiles.size();
+    const Workspace ws = batch_ws(b);
+    LmArgs lm{};
+    lm.lambda = d_lambda;
+    lm.poses = d_poses;
+    lm.cand = b->d_lm + F;                                   // 12 per factor
+    lm.e0 = b->d_lm + 13 * F;                                // 1 per factor
+    lm.valid = reinterpret_cast<int32_t*>(b->d_lm + 14 * F);
+    lm.posef = reads_staged_poses(b, kLin) ? ws.posef : nullptr;   // both modes' kernels read them, or neither
+    lm.e_out = d_e;
+    lm.accepted = d_acc;
+    lm.stride = stride;
+    lm.col = col;
+    VG_TRY(launch_tiles(b, ws, kLin, d_poses, 0, nt, nullptr, nullptr, 0, 0, F, staged));
+    VG_TRY(launch_reduce(b, ws, kLin, d_poses, 0, (int32_t)F, b->d_out, nullptr, nullptr, nullptr, nullptr, lm));
+    VG_TRY(launch_tiles(b, ws, kEval, lm.cand, 0, nt, nullptr, nullptr, 0, 0, F, true));
+    return launch_reduce(b, ws, kEval, lm.cand, 0, (int32_t)F, b->d_e, nullptr, nullptr, nullptr, nullptr, lm);
 }
 
 }  // namespace
@@ -1209,7 +1220,7 @@ extern "C" vg_status vg_lm_step_async(vg_batch* b, double* d_poses, double* d_la
     if (!bat_ok(b)) return state_err("invalid batch");
     if (d_poses == nullptr || d_lambda == nullptr) return invalid("d_poses or d_lambda is NULL");
     VG_HIP(hipSetDevice(b->ctx->device));
-    return lm_step(b, d_poses, d_lambda, d_e, d_accepted, 1, 0);
+    return lm_step(b, d_poses, d_lambda, d_e, d_accepted, 1, 0, false);
 }
 
 extern "C" vg_status vg_lm_run(vg_batch* b, const double* poses_in, int32_t iters, double lambda0, double* poses_out,
@@ -1241,7 +1252,8 @@ extern "C" vg_status vg_lm_run(vg_batch* b, const double* poses_in, int32_t iter
             break;
         }
         if ((rc = launch_fill(b->ctx, lambda, F, lambda0)) != VG_OK) break;
-        for (int32_t it = 0; it < iters && rc == VG_OK; ++it) rc = lm_step(b, b->d_poses, lambda, d_eh, d_acc, iters, it);
+        for (int32_t it = 0; it < iters && rc == VG_OK; ++it) 
+            rc = lm_step(b, b->d_poses, lambda, d_eh, d_acc, iters, it, it > 0);
         if (rc != VG_OK) break;
         std::vector<int32_t> ha((size_t)F * std::max(iters, 1));
         std::vector<double> he((size_t)F * std::max(iters, 1));

@@ -31,6 +31,7 @@
 #include <type_traits>
 
 #include "vg_device.h"
+#include "vg_se3.h"
 
 namespace vg {
 
@@ -1284,146 +1285,152 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(waves_per
 }
 
 // Per-factor reduction of tile rows in tile order (FP64; FP32 for kN32) and the
-// frame change H = G^T Bd^T H'' Bd G, b = G^T Bd^T b''.  One 64-thread block per
-// factor.
+// frame change H = G^T Bd^T H'' Bd G, b = G^T Bd^T b''.  One workgroup per factor.
+// The rows are staged through LDS, kRedRows at a time with the next ones in
+// flight, and one lane per column adds them in tile order; the 6x6 products of the
+// frame change are formed by 36 lanes, one entry each.  Bound by latency (one load
+// round trip per kRedRows rows, then chains of a few dozen FP64 operations): one
+// wave that loaded sixteen rows at a time and one thread for the products took
+// 4.6 us for a factor of one row and 17 us for one of 489 rows.
+constexpr int kRedRows = 64;
+constexpr int kRedThreads = 256;
 template <int MODE, int PREC>
-__global__ __launch_bounds__(64) void k_reduce(const FactorDesc* __restrict__ fac, const int32_t* __restrict__ tile_first,
-                                               int32_t f0, const double* __restrict__ partials,
-                                               const double* __restrict__ poses, double* __restrict__ out,
-                                               int64_t* __restrict__ inliers,
-                                               const double* __restrict__ grad_e, const double* __restrict__ jr,
-                                               double* __restrict__ grad_xi, int64_t* __restrict__ work) {
+__global__ __launch_bounds__(kRedThreads) void k_reduce(
+    const FactorDesc* __restrict__ fac, const int32_t* __restrict__ tile_first, int32_t f0,
+    const double* __restrict__ partials, const double* poses, double* __restrict__ out, int64_t* __restrict__ inliers,
+    const double* __restrict__ grad_e, const double* __restrict__ jr, double* __restrict__ grad_xi,
+    int64_t* __restrict__ work, LmArgs lm) {
+    __shared__ double s_rows[kRedRows * kRow];
     __shared__ double s[kRow];
+    __shared__ double sM[36], sA[36];   // Bd G, then H'' Bd G and the result row
+    __shared__ double sRow[kOutRow];
     const int f = f0 + blockIdx.x;
     const int k = threadIdx.x;
-    if (k < kRow) {
+    const FactorDesc& F = fac[f];
+    const double* R = poses + 12 * f;
+    {
         const int32_t a = tile_first[f], bnd = tile_first[f + 1];
-        // rows are summed in tile order; each step has kStep row loads in flight
-        // before its adds (a factor of a few large sources has hundreds of rows)
-        constexpr int kStep = 16;
-        if constexpr (PREC == kN32) {
-            float sf = 0.f;
-            double si = 0.0;
-            int32_t t = a;
-            for (; t + kStep <= bnd; t += kStep) {
-                double v[kStep];
+        constexpr int kPer = kRedRows * kRow / kRedThreads;
+        static_assert(kPer * kRedThreads == kRedRows * kRow, "whole loads per thread");
+        const double* src = partials + (int64_t)a * kRow;
+        const int64_t total = (int64_t)(bnd - a) * kRow;
+        double v[kPer];
+        auto load = [&](int64_t base) {
 #pragma unroll
-                for (int u = 0; u < kStep; ++u) v[u] = partials[(int64_t)(t + u) * kRow + k];
+            for (int u = 0; u < kPer; ++u) {
+                const int64_t i = base + u * kRedThreads + k;
+                v[u] = i < total ? src[i] : 0.0;
+            }
+        };
+        load(0);
+        float sf = 0.f;
+        double acc = 0.0;
+        for (int64_t base = 0; base < total; base += kRedRows * kRow) {
+            __syncthreads();   // the previous rows have been added
 #pragma unroll
-                for (int u = 0; u < kStep; ++u) {
-                    sf += (float)v[u];
-                    si += v[u];
+            for (int u = 0; u < kPer; ++u) s_rows[u * kRedThreads + k] = v[u];
+            __syncthreads();
+            load(base + kRedRows * kRow);
+            if (k < kRow) {
+                const int rows = (int)min<int64_t>(kRedRows, (total - base) / kRow);
+#pragma unroll 8
+                for (int t = 0; t < rows; ++t) {
+                    const double x = s_rows[t * kRow + k];
+                    acc += x;
+                    if constexpr (PREC == kN32) sf += (float)x;
                 }
             }
-            for (; t < bnd; ++t) {
-                const double v = partials[(int64_t)t * kRow + k];
-                sf += (float)v;
-                si += v;
-            }
-            s[k] = (k >= kTerms) ? si : (double)sf;   // counts are exact integers in FP64
-        } else {
-            double acc = 0.0;
-            int32_t t = a;
-            for (; t + kStep <= bnd; t += kStep) {
-                double v[kStep];
-#pragma unroll
-                for (int u = 0; u < kStep; ++u) v[u] = partials[(int64_t)(t + u) * kRow + k];
-#pragma unroll
-                for (int u = 0; u < kStep; ++u) acc += v[u];
-            }
-            for (; t < bnd; ++t) acc += partials[(int64_t)t * kRow + k];
-            s[k] = acc;
         }
-    }
-    __syncthreads();
-    if (threadIdx.x != 0) return;
-    const FactorDesc& F = fac[f];
-    const double* P = poses + 12 * f;
-    const double* R = P;
-    if (work != nullptr && MODE != kBwd) {
-        int64_t* wr = work + (int64_t)kWork * f;
-        wr[0] = (int64_t)s[kRowWalk];
-        wr[1] = (int64_t)s[kRowChunks];
-        for (int l = 0; l < kMaxLevels; ++l) wr[2 + l] = (int64_t)s[kRowProbe + l];
-        wr[6] = 0;
-        wr[7] = 0;
+        if (k < kRow) s[k] = (PREC == kN32 && k < kTerms) ? (double)sf : acc;   // counts are exact integers in FP64
     }
     const double o[3] = {PREC == kC32 ? F.src_origin[0] : 0.0, PREC == kC32 ? F.src_origin[1] : 0.0,
                          PREC == kC32 ? F.src_origin[2] : 0.0};
-    if constexpr (MODE == kEval) {
-        out[f] = s[0];
-        return;
-    }
-    if constexpr (MODE == kCount) {
-        // overlap rate: fraction of the source points that fall in an occupied voxel
-        for (int l = 0; l < F.L; ++l) out[(int64_t)F.L * f + l] = F.n > 0 ? s[kTerms + l] / (double)F.n : 0.0;
-        return;
-    }
-    if constexpr (MODE == kBwd) {
-        // g' = Bd^T g'' (rotate both halves back to the source frame), g = G^T g'
-        double gw[3], gv[3], g[6];
-        for (int i = 0; i < 3; ++i) {
-            gw[i] = R[i] * s[0] + R[3 + i] * s[1] + R[6 + i] * s[2];
-            gv[i] = R[i] * s[3] + R[3 + i] * s[4] + R[6 + i] * s[5];
+    const int i = (k % 36) / 6, j = k % 6;   // this lane's entry
+    if constexpr (MODE == kLin) {
+        // Bd G (6x6): [[R, 0], [-R (o)x, R]]
+        if (k < 36) {
+            double m = 0.0;
+            if (i < 3 && j < 3) m = R[3 * i + j];
+            else if (i >= 3 && j >= 3) m = R[3 * (i - 3) + j - 3];
+            else if (i >= 3) {
+                const double Ox[9] = {0, -o[2], o[1], o[2], 0, -o[0], -o[1], o[0], 0};
+                double ro = 0.0;
+#pragma unroll
+                for (int q = 0; q < 3; ++q)
+                    ro += R[3 * (i - 3) + q] * (j == 0 ? Ox[3 * q] : (j == 1 ? Ox[3 * q + 1] : Ox[3 * q + 2]));
+                m = -ro;
+            }
+            sM[k] = m;
         }
-        g[0] = gw[0] + (o[1] * gv[2] - o[2] * gv[1]);
-        g[1] = gw[1] + (o[2] * gv[0] - o[0] * gv[2]);
-        g[2] = gw[2] + (o[0] * gv[1] - o[1] * gv[0]);
-        g[3] = gv[0];
-        g[4] = gv[1];
-        g[5] = gv[2];
-        const double ge = grad_e[f];
-        for (int i = 0; i < 6; ++i) {
-            double v = g[i];
+    }
+    __syncthreads();
+    if (work != nullptr && MODE != kBwd && k < kWork) {
+        const double w = k == 0 ? s[kRowWalk] : (k == 1 ? s[kRowChunks] : (k < 2 + kMaxLevels ? s[kRowProbe + k - 2] : 0.0));
+        work[(int64_t)kWork * f + k] = (int64_t)w;
+    }
+    if constexpr (MODE == kEval) {
+        if (k == 0) {
+            out[f] = s[0];
+            if (lm.lambda != nullptr) lm_accept(lm, f, s[0]);
+        }
+    } else if constexpr (MODE == kCount) {
+        // overlap rate: fraction of the source points that fall in an occupied voxel
+        if (k < F.L) out[(int64_t)F.L * f + k] = F.n > 0 ? s[kTerms + k] / (double)F.n : 0.0;
+    } else if constexpr (MODE == kBwd) {
+        // g' = Bd^T g'' (rotate both halves back to the source frame), g = G^T g'
+        if (k < 6) {
+            const int h = k < 3 ? 0 : 3, q = k - h;
+            sA[k] = R[q] * s[h] + R[3 + q] * s[h + 1] + R[6 + q] * s[h + 2];
+        }
+        __syncthreads();
+        if (k == 0) {
+            const double* gw = sA;
+            const double* gv = sA + 3;
+            sRow[0] = gw[0] + (o[1] * gv[2] - o[2] * gv[1]);
+            sRow[1] = gw[1] + (o[2] * gv[0] - o[0] * gv[2]);
+            sRow[2] = gw[2] + (o[0] * gv[1] - o[1] * gv[0]);
+            sRow[3] = gv[0];
+            sRow[4] = gv[1];
+            sRow[5] = gv[2];
+        }
+        __syncthreads();
+        if (k < 6) {
+            double v = sRow[k];
             if (jr != nullptr) {
                 v = 0.0;
-                for (int j = 0; j < 6; ++j) v += jr[36 * (int64_t)f + 6 * j + i] * g[j];
+#pragma unroll
+                for (int q = 0; q < 6; ++q) v += jr[36 * (int64_t)f + 6 * q + k] * sRow[q];
             }
-            grad_xi[6 * (int64_t)f + i] = ge * v;
+            grad_xi[6 * (int64_t)f + k] = grad_e[f] * v;
         }
-        return;
-    }
-    // unpack H'' (symmetric) and b''
-    double Hs[36];
-    for (int i = 0; i < 6; ++i)
-        for (int j = i; j < 6; ++j) {
-            Hs[6 * i + j] = s[1 + tri(i, j)];
-            Hs[6 * j + i] = s[1 + tri(i, j)];
-        }
-    // M = Bd G (6x6): [[R, 0], [-R (o)x, R]]
-    double M[36] = {0};
-    double Ox[9] = {0, -o[2], o[1], o[2], 0, -o[0], -o[1], o[0], 0};
-    for (int i = 0; i < 3; ++i)
-        for (int j = 0; j < 3; ++j) {
-            M[6 * i + j] = R[3 * i + j];
-            M[6 * (3 + i) + 3 + j] = R[3 * i + j];
-            double ro = 0.0;
-            for (int q = 0; q < 3; ++q) ro += R[3 * i + q] * Ox[3 * q + j];
-            M[6 * (3 + i) + j] = -ro;
-        }
-    double HM[36];
-    for (int i = 0; i < 6; ++i)
-        for (int j = 0; j < 6; ++j) {
+    } else {
+        // H'' (symmetric, upper triangle in s[1..21]) times Bd G
+        if (k < 36) {
             double acc = 0.0;
-            for (int q = 0; q < 6; ++q) acc += Hs[6 * i + q] * M[6 * q + j];
-            HM[6 * i + j] = acc;
+#pragma unroll
+            for (int q = 0; q < 6; ++q) acc += s[1 + (i <= q ? tri(i, q) : tri(q, i))] * sM[6 * q + j];
+            sA[k] = acc;
         }
-    double* o_row = out + (int64_t)kOutRow * f;
-    o_row[0] = s[0];
-    for (int i = 0; i < 6; ++i)
-        for (int j = i; j < 6; ++j) {
+        __syncthreads();
+        if (k < 36) {
+            const int r = min(i, j), c = max(i, j);   // both triangles from the upper one's formula
             double acc = 0.0;
-            for (int q = 0; q < 6; ++q) acc += M[6 * q + i] * HM[6 * q + j];
-            o_row[1 + 6 * i + j] = acc;
-            o_row[1 + 6 * j + i] = acc;
+#pragma unroll
+            for (int q = 0; q < 6; ++q) acc += sM[6 * q + r] * sA[6 * q + c];
+            sRow[1 + k] = acc;
+        } else if (k < 42) {
+            double acc = 0.0;
+#pragma unroll
+            for (int q = 0; q < 6; ++q) acc += sM[6 * q + k - 36] * s[22 + q];
+            sRow[1 + k] = acc;
+        } else if (k == 42) {
+            sRow[0] = s[0];
         }
-    for (int i = 0; i < 6; ++i) {
-        double acc = 0.0;
-        for (int q = 0; q < 6; ++q) acc += M[6 * q + i] * s[22 + q];
-        o_row[37 + i] = acc;
+        __syncthreads();
+        if (k < kOutRow) out[(int64_t)kOutRow * f + k] = sRow[k];
+        if (inliers != nullptr && k < F.L) inliers[(int64_t)F.L * f + k] = (int64_t)s[kTerms + k];
+        if (k == 0 && lm.lambda != nullptr) lm_propose(lm, f, sRow);
     }
-    if (inliers != nullptr)
-        for (int l = 0; l < F.L; ++l) inliers[(int64_t)F.L * f + l] = (int64_t)s[kTerms + l];
 }
 
 // Correspondences of one factor (keys and found flags in caller order).
@@ -1548,15 +1555,20 @@ static vg_status launch_tiles_t(vg_batch* b, const Workspace& ws, const double* 
                                                              points_dtype);
 }
 
-vg_status launch_tiles(vg_batch* b, const Workspace& ws, int mode, const double* d_poses, int32_t t0, int32_t t1,
-                       const double* d_grad_e, void* d_grad_points, int points_dtype, int64_t f0, int64_t f1) {
-    if (t1 <= t0) return VG_OK;
-    // FP32 pose copies for the FP32 kernels; the one-level compensated kernels
-    // (linearize, evaluate, backward) form their rotation from the FP64 poses
-    // and read none
+// FP32 pose copies for the FP32 kernels; the one-level compensated kernels
+// (linearize, evaluate, backward) form their rotation from the FP64 poses and
+// read none
+bool reads_staged_poses(const vg_batch* b, int mode) {
     const bool one_level_cmp = mode != kCount && b->opt.precision == kC32 && !b->opt.lane_kahan &&
                                !b->opt.surface_validation && b->L == 1;
-    if (b->opt.precision != kF64 && f1 > f0 && !one_level_cmp) {
+    return b->opt.precision != kF64 && !one_level_cmp;
+}
+
+vg_status launch_tiles(vg_batch* b, const Workspace& ws, int mode, const double* d_poses, int32_t t0, int32_t t1,
+                       const double* d_grad_e, void* d_grad_points, int points_dtype, int64_t f0, int64_t f1,
+                       bool staged) {
+    if (t1 <= t0) return VG_OK;
+    if (!staged && f1 > f0 && reads_staged_poses(b, mode)) {
         const int64_t nf = (f1 - f0) * 16;
         k_stage_poses<<<(int)((nf + 255) / 256), 256, 0, b->ctx->stream>>>(f1 - f0, d_poses + 12 * f0,
                                                                           ws.posef + 16 * f0);
@@ -1581,21 +1593,22 @@ vg_status launch_tiles(vg_batch* b, const Workspace& ws, int mode, const double*
 
 template <int MODE, int PREC>
 static void reduce_t(vg_batch* b, const Workspace& ws, const double* d_poses, int32_t f0, int32_t f1, double* d_out,
-                     int64_t* d_inl, const double* d_grad_e, const double* d_jr, double* d_grad_xi) {
-    k_reduce<MODE, PREC><<<f1 - f0, 64, 0, b->ctx->stream>>>(b->d_fac, b->d_tile_first, f0, ws.partials, d_poses,
-                                                             d_out, d_inl, d_grad_e, d_jr, d_grad_xi,
-                                                             ws.work);
+                     int64_t* d_inl, const double* d_grad_e, const double* d_jr, double* d_grad_xi,
+                     const LmArgs& lm) {
+    k_reduce<MODE, PREC><<<f1 - f0, kRedThreads, 0, b->ctx->stream>>>(b->d_fac, b->d_tile_first, f0, ws.partials,
+                                                                      d_poses, d_out, d_inl, d_grad_e, d_jr,
+                                                                      d_grad_xi, ws.work, lm);
 }
 
 vg_status launch_reduce(vg_batch* b, const Workspace& ws, int mode, const double* d_poses, int32_t f0, int32_t f1,
                         double* d_out, int64_t* d_inliers, const double* d_grad_e, const double* d_jr,
-                        double* d_grad_xi) {
+                        double* d_grad_xi, const LmArgs& lm) {
     if (f1 <= f0) return VG_OK;
     const int p = b->opt.precision;
 #define VG_R(M)                                                                               \
-    if (p == kC32) reduce_t<M, kC32>(b, ws, d_poses, f0, f1, d_out, d_inliers, d_grad_e, d_jr, d_grad_xi); \
-    else if (p == kN32) reduce_t<M, kN32>(b, ws, d_poses, f0, f1, d_out, d_inliers, d_grad_e, d_jr, d_grad_xi); \
-    else reduce_t<M, kF64>(b, ws, d_poses, f0, f1, d_out, d_inliers, d_grad_e, d_jr, d_grad_xi);
+    if (p == kC32) reduce_t<M, kC32>(b, ws, d_poses, f0, f1, d_out, d_inliers, d_grad_e, d_jr, d_grad_xi, lm); \
+    else if (p == kN32) reduce_t<M, kN32>(b, ws, d_poses, f0, f1, d_out, d_inliers, d_grad_e, d_jr, d_grad_xi, lm); \
+    else reduce_t<M, kF64>(b, ws, d_poses, f0, f1, d_out, d_inliers, d_grad_e, d_jr, d_grad_xi, lm);
     if (mode == kLin) { VG_R(kLin) }
     else if (mode == kEval) { VG_R(kEval) }
     else if (mode == kCount) { VG_R(kCount) }

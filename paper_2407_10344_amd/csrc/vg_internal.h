@@ -120,6 +120,22 @@ struct Workspace {
     int64_t* work;           // F x kWork work counts, or nullptr
 };
 
+// One Levenberg-Marquardt iteration (every pointer on the device; lambda nullptr:
+// none).  The reduction of a linearization ends with the proposal of every factor
+// and that of the evaluation of the candidates with accepting or rejecting it, so
+// an iteration is two tile launches and two reductions.
+struct LmArgs {
+    double* lambda;          // F damping factors
+    double* poses;           // F x 12 poses T
+    double* cand;            // F x 12 candidates T Exp(delta)
+    int32_t* valid;          // F: the damped matrix was SPD
+    double* e0;              // F errors at T
+    float* posef;            // F x 16 FP32 poses for the next tile launch, or nullptr
+    double* e_out;           // error at T and decision, at column `col` of rows of `stride`, or nullptr
+    int32_t* accepted;
+    int32_t stride, col;
+};
+
 struct Tile {
     int32_t factor;
     int32_t chunk0;          // first chunk of the factor's source
@@ -355,13 +371,17 @@ vg_status set_points(vg_context* ctx, const PointSrc* d_src, int64_t n_src, int6
                      int dtype);
 
 // launch the tile kernel over tiles [t0, t1) and the reduction over factors [f0, f1)
-// f0, f1: the factors those tiles belong to (their poses are staged to FP32 first)
+// f0, f1: the factors those tiles belong to (their poses are staged to FP32 first where the kernel reads
+// them so, unless `staged` says that they are)
 // ws: the buffers of the launch (the batch's own, or a caller-provided scratch)
 vg_status launch_tiles(vg_batch* b, const Workspace& ws, int mode, const double* d_poses, int32_t t0, int32_t t1,
-                       const double* d_grad_e, void* d_grad_points, int points_dtype, int64_t f0, int64_t f1);
+                       const double* d_grad_e, void* d_grad_points, int points_dtype, int64_t f0, int64_t f1,
+                       bool staged = false);
+// whether the batch's kernels of a mode read FP32 poses staged in ws.posef
+bool reads_staged_poses(const vg_batch* b, int mode);
 vg_status launch_reduce(vg_batch* b, const Workspace& ws, int mode, const double* d_poses, int32_t f0, int32_t f1,
                         double* d_out, int64_t* d_inliers, const double* d_grad_e, const double* d_jr,
-                        double* d_grad_xi);
+                        double* d_grad_xi, const LmArgs& lm = LmArgs{});
 // rows of shared sources: sum of their factors' per-factor rows in factor order
 vg_status launch_grad_combine(vg_batch* b, void* d_grad_points, int points_dtype);
 vg_status launch_correspondences(vg_batch* b, const double* d_pose, int64_t factor, int64_t* d_keys,
@@ -369,17 +389,6 @@ vg_status launch_correspondences(vg_batch* b, const double* d_pose, int64_t fact
 vg_status launch_zero(vg_context* ctx, void* d_ptr, size_t bytes);
 vg_status launch_se3_retract(vg_context* ctx, int64_t F, const double* d_T0, const double* d_xi, double* d_T,
                              double* d_jr);
-// LM on the device: propose solves (H + lambda diag H) delta = -b from the
-// linearization rows d_out and writes T Exp(delta) to d_cand (d_valid = 0 and
-// d_cand = T where the damped matrix is not SPD); accept keeps the candidate
-// iff it is valid and e decreases (lambda / 10), else keeps T (lambda x 10),
-// writing e at T and the decision to d_e / d_accepted at column `col` of rows
-// of length `stride` (either may be nullptr).
-vg_status launch_lm_propose(vg_batch* b, const double* d_out, const double* d_lambda, const double* d_poses,
-                            double* d_cand, int32_t* d_valid);
-vg_status launch_lm_accept(vg_batch* b, const double* d_out, const double* d_e_new, double* d_lambda,
-                           double* d_poses, const double* d_cand, const int32_t* d_valid, double* d_e,
-                           int32_t* d_accepted, int32_t stride, int32_t col);
 vg_status launch_fill(vg_context* ctx, double* d_ptr, int64_t n, double v);
 
 }  // namespace vg
