@@ -95,7 +95,8 @@ typedef struct {
     int32_t surface_validation; /* 1: discard a point when (mu - T^-1 c) . n > 0 (Sec. III-C,
                                    Correspondence search); sources need normals, c is the
                                    target viewpoint of the factor */
-    int32_t use_graph;          /* 1: replay a captured hipGraph [H2D, kernels, D2H] */
+    int32_t use_graph;          /* kept, without effect: a host call's kernels read the poses
+                                   from and write the results to pinned memory themselves */
     int32_t plain_per_factor;   /* 1: one launch, one upload, one download and one host
                                    synchronization per factor (the per-factor loop the
                                    batched mechanism replaces) */

@@ -625,13 +625,6 @@ void build_tiles(vg_batch* b) {
     b->h_tile_first[b->F] = (int32_t)b->h_tiles.size();
 }
 
-void free_graph(vg_batch* b) {
-    if (b->exec) (void)hipGraphExecDestroy(b->exec);
-    if (b->graph) (void)hipGraphDestroy(b->graph);
-    b->exec = nullptr;
-    b->graph = nullptr;
-}
-
 vg_status upload_schedule(vg_batch* b) {
     hipStream_t st = b->ctx->stream;
     dfree(b->d_tiles);
@@ -648,7 +641,6 @@ vg_status upload_schedule(vg_batch* b) {
     VG_HIP(hipMemcpyAsync(b->d_tile_first, b->h_tile_first.data(), sizeof(int32_t) * (b->F + 1),
                           hipMemcpyHostToDevice, st));
     VG_HIP(hipStreamSynchronize(st));
-    free_graph(b);
     return VG_OK;
 }
 
@@ -715,39 +707,34 @@ vg_status run_evaluate_device(vg_batch* b, const double* d_poses, double* d_e) {
     return launch_reduce(b, ws, kEval, d_poses, 0, (int32_t)b->F, d_e, nullptr, nullptr, nullptr, nullptr);
 }
 
-// Capture [H2D poses, tile kernel, reduction, D2H results] once; replayed per call.
-vg_status ensure_graph(vg_batch* b) {
-    if (b->exec) return VG_OK;
-    hipStream_t cs = nullptr;
-    VG_HIP(hipStreamCreateWithFlags(&cs, hipStreamNonBlocking));
-    hipStream_t saved = b->ctx->stream;
-    b->ctx->stream = cs;
-    vg_status st = VG_OK;
-    hipError_t e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
-    if (e == hipSuccess) {
-        e = hipMemcpyAsync(b->d_poses, b->h_poses, sizeof(double) * 12 * b->F, hipMemcpyHostToDevice, cs);
-        if (e == hipSuccess) st = run_linearize_device(b, b->d_poses, b->d_out, b->d_inliers);
-        if (e == hipSuccess && st == VG_OK)
-            e = hipMemcpyAsync(b->h_out, b->d_out, sizeof(double) * kOutRow * b->F, hipMemcpyDeviceToHost, cs);
-        if (e == hipSuccess && st == VG_OK)
-            e = hipMemcpyAsync(b->h_inliers, b->d_inliers, sizeof(int64_t) * b->L * b->F, hipMemcpyDeviceToHost, cs);
-        hipGraph_t g = nullptr;
-        hipError_t e2 = hipStreamEndCapture(cs, &g);
-        if (e == hipSuccess) e = e2;
-        b->graph = g;
-        if (e == hipSuccess && st == VG_OK) e = hipGraphInstantiate(&b->exec, b->graph, nullptr, nullptr, 0);
-    }
-    b->ctx->stream = saved;
-    (void)hipStreamDestroy(cs);
-    if (st != VG_OK) {
-        free_graph(b);
-        return st;
-    }
-    if (e != hipSuccess) {
-        free_graph(b);
-        return hip_fail(e, "graph capture");
-    }
+// Host calls move their poses and results by kernels that read and write the
+// batch's pinned buffers: the staging kernel every launch of a multi-level batch
+// starts with takes the poses from there, and the reduction writes its rows there
+// (a factor's row is one coalesced write of 344 bytes).  A copy before and one or
+// two after the kernels cost more than the kernels of a small batch (one factor
+// of 5,000 points: 45 us a call with the copies in a replayed graph, 39 us with
+// the results copied, 35 us without).  Beyond kDirectFactors factors the rows go
+// through one copy (1,000 factors: 68 us direct, 76 us copied; 4,000: 203 and 199).
+constexpr int64_t kDirectFactors = 2048;
+constexpr size_t kDirectHistory = (size_t)4 << 20;
+
+double* host_out(vg_batch* b, double* device) { return b->F <= kDirectFactors ? b->h_out : device; }
+
+// fetch `count` doubles of a result that was not written to h_out directly, and wait for it
+vg_status finish_host(vg_batch* b, const double* device, size_t count) {
+    hipStream_t st = b->ctx->stream;
+    if (b->F > kDirectFactors)
+        VG_HIP(hipMemcpyAsync(b->h_out, device, sizeof(double) * count, hipMemcpyDeviceToHost, st));
+    VG_HIP(hipStreamSynchronize(st));
     return VG_OK;
+}
+
+vg_status run_host(vg_batch* b, int mode, double* d_out, int64_t* d_inl) {
+    const int32_t nt = (int32_t)b->h_tiles.size();
+    const Workspace ws = batch_ws(b);
+    VG_TRY(launch_pose_upload(b, ws, mode, b->h_poses));
+    VG_TRY(launch_tiles(b, ws, mode, b->d_poses, 0, nt, nullptr, nullptr, 0, 0, b->F, true));
+    return launch_reduce(b, ws, mode, b->d_poses, 0, (int32_t)b->F, d_out, d_inl, nullptr, nullptr, nullptr);
 }
 
 // The whole host-side linearize: stage poses, run, fetch results (pinned buffers).
@@ -771,22 +758,14 @@ vg_status linearize_host(vg_batch* b) {
         }
         return VG_OK;
     }
-    if (b->opt.use_graph) {
-        VG_TRY(ensure_graph(b));
-        VG_HIP(hipGraphLaunch(b->exec, st));
-        VG_HIP(hipStreamSynchronize(st));
-        return VG_OK;
-    }
-    VG_HIP(hipMemcpyAsync(b->d_poses, b->h_poses, sizeof(double) * 12 * F, hipMemcpyHostToDevice, st));
-    VG_TRY(run_linearize_device(b, b->d_poses, b->d_out, b->d_inliers));
-    VG_HIP(hipMemcpyAsync(b->h_out, b->d_out, sizeof(double) * kOutRow * F, hipMemcpyDeviceToHost, st));
-    VG_HIP(hipMemcpyAsync(b->h_inliers, b->d_inliers, sizeof(int64_t) * b->L * F, hipMemcpyDeviceToHost, st));
-    VG_HIP(hipStreamSynchronize(st));
-    return VG_OK;
+    const bool direct = F <= kDirectFactors;
+    VG_TRY(run_host(b, kLin, host_out(b, b->d_out), direct ? b->h_inliers : b->d_inliers));
+    if (!direct)
+        VG_HIP(hipMemcpyAsync(b->h_inliers, b->d_inliers, sizeof(int64_t) * b->L * F, hipMemcpyDeviceToHost, st));
+    return finish_host(b, b->d_out, (size_t)kOutRow * F);
 }
 
 void free_batch(vg_batch* b) {
-    free_graph(b);
     dfree(b->d_fac);
     dfree(b->d_tiles);
     dfree(b->d_tile_first);
@@ -805,6 +784,7 @@ void free_batch(vg_batch* b) {
     hfree(b->h_poses);
     hfree(b->h_out);
     hfree(b->h_inliers);
+    hfree(b->h_lm);
 }
 
 }  // namespace
@@ -1042,12 +1022,9 @@ extern "C" vg_status vg_evaluate(vg_batch* b, const double* poses, double* e) {
     if (e == nullptr) return invalid("e is NULL");
     VG_TRY(check_poses(poses, b->F));
     VG_HIP(hipSetDevice(b->ctx->device));
-    hipStream_t st = b->ctx->stream;
     std::memcpy(b->h_poses, poses, sizeof(double) * 12 * b->F);
-    VG_HIP(hipMemcpyAsync(b->d_poses, b->h_poses, sizeof(double) * 12 * b->F, hipMemcpyHostToDevice, st));
-    VG_TRY(run_evaluate_device(b, b->d_poses, b->d_e));
-    VG_HIP(hipMemcpyAsync(b->h_out, b->d_e, sizeof(double) * b->F, hipMemcpyDeviceToHost, st));
-    VG_HIP(hipStreamSynchronize(st));
+    VG_TRY(run_host(b, kEval, host_out(b, b->d_e), nullptr));
+    VG_TRY(finish_host(b, b->d_e, (size_t)b->F));
     std::memcpy(e, b->h_out, sizeof(double) * b->F);
     return VG_OK;
 }
@@ -1059,16 +1036,10 @@ extern "C" vg_status vg_overlap(vg_batch* b, const double* poses, double* overla
     if (overlap == nullptr) return invalid("overlap is NULL");
     VG_TRY(check_poses(poses, b->F));
     VG_HIP(hipSetDevice(b->ctx->device));
-    hipStream_t st = b->ctx->stream;
     std::memcpy(b->h_poses, poses, sizeof(double) * 12 * b->F);
-    VG_HIP(hipMemcpyAsync(b->d_poses, b->h_poses, sizeof(double) * 12 * b->F, hipMemcpyHostToDevice, st));
-    const int32_t nt = (int32_t)b->h_tiles.size();
-    const Workspace ws = batch_ws(b);
-    VG_TRY(launch_tiles(b, ws, kCount, b->d_poses, 0, nt, nullptr, nullptr, 0, 0, b->F));
     // the per-level fractions land in d_out (F x L <= F x 43)
-    VG_TRY(launch_reduce(b, ws, kCount, b->d_poses, 0, (int32_t)b->F, b->d_out, nullptr, nullptr, nullptr, nullptr));
-    VG_HIP(hipMemcpyAsync(b->h_out, b->d_out, sizeof(double) * b->L * b->F, hipMemcpyDeviceToHost, st));
-    VG_HIP(hipStreamSynchronize(st));
+    VG_TRY(run_host(b, kCount, host_out(b, b->d_out), nullptr));
+    VG_TRY(finish_host(b, b->d_out, (size_t)b->L * b->F));
     std::memcpy(overlap, b->h_out, sizeof(double) * b->L * b->F);
     return VG_OK;
 }
@@ -1236,43 +1207,55 @@ extern "C" vg_status vg_lm_run(vg_batch* b, const double* poses_in, int32_t iter
     hipStream_t st = b->ctx->stream;
     const int64_t F = b->F;
     double* lambda = b->d_lm;                // 1 per factor
-    int32_t* d_acc = nullptr;
-    double* d_eh = nullptr;
-    VG_TRY(dev_alloc(&d_acc, (size_t)F * std::max(iters, 1)));
-    vg_status rc = dev_alloc(&d_eh, (size_t)F * std::max(iters, 1));
-    if (rc != VG_OK) {
-        dfree(d_acc);
-        return rc;
+    // histories: in pinned memory kept with the batch, which the kernels write, up
+    // to kDirectHistory bytes; longer ones in device memory of this call
+    const size_t items = (size_t)F * std::max(iters, 1), bytes = items * (sizeof(double) + sizeof(int32_t));
+    const bool direct = bytes <= kDirectHistory;
+    unsigned char* hist = nullptr;
+    if (direct) {
+        if (b->h_lm_bytes < bytes) {
+            VG_HIP(hipStreamSynchronize(st));
+            hfree(b->h_lm);
+            b->h_lm = nullptr;
+            b->h_lm_bytes = 0;
+            VG_TRY(host_alloc(&b->h_lm, bytes));
+            b->h_lm_bytes = bytes;
+        }
+        hist = b->h_lm;
+    } else {
+        VG_TRY(dev_alloc(&hist, bytes));
     }
+    double* eh = reinterpret_cast<double*>(hist);
+    int32_t* acc = reinterpret_cast<int32_t*>(hist + items * sizeof(double));
+    std::vector<unsigned char> copy;
+    vg_status rc = VG_OK;
     do {
         std::memcpy(b->h_poses, poses_in, sizeof(double) * 12 * F);
-        hipError_t e = hipMemcpyAsync(b->d_poses, b->h_poses, sizeof(double) * 12 * F, hipMemcpyHostToDevice, st);
-        if (e != hipSuccess) {
-            rc = hip_fail(e, "pose upload");
-            break;
-        }
+        if ((rc = launch_pose_upload(b, batch_ws(b), kLin, b->h_poses)) != VG_OK) break;
         if ((rc = launch_fill(b->ctx, lambda, F, lambda0)) != VG_OK) break;
-        for (int32_t it = 0; it < iters && rc == VG_OK; ++it) 
-            rc = lm_step(b, b->d_poses, lambda, d_eh, d_acc, iters, it, it > 0);
+        for (int32_t it = 0; it < iters && rc == VG_OK; ++it)
+            rc = lm_step(b, b->d_poses, lambda, eh, acc, iters, it, true);
         if (rc != VG_OK) break;
-        std::vector<int32_t> ha((size_t)F * std::max(iters, 1));
-        std::vector<double> he((size_t)F * std::max(iters, 1));
-        e = hipMemcpyAsync(b->h_poses, b->d_poses, sizeof(double) * 12 * F, hipMemcpyDeviceToHost, st);
-        if (e == hipSuccess && iters > 0)
-            e = hipMemcpyAsync(ha.data(), d_acc, sizeof(int32_t) * F * iters, hipMemcpyDeviceToHost, st);
-        if (e == hipSuccess && iters > 0)
-            e = hipMemcpyAsync(he.data(), d_eh, sizeof(double) * F * iters, hipMemcpyDeviceToHost, st);
+        if ((rc = launch_copy(b->ctx, b->d_poses, b->h_poses, sizeof(double) * 12 * F)) != VG_OK) break;
+        hipError_t e = hipSuccess;
+        if (!direct) {
+            copy.resize(bytes);
+            e = hipMemcpyAsync(copy.data(), hist, bytes, hipMemcpyDeviceToHost, st);
+        }
         if (e == hipSuccess) e = hipStreamSynchronize(st);
         if (e != hipSuccess) {
             rc = hip_fail(e, "LM download");
             break;
         }
+        const unsigned char* h = direct ? hist : copy.data();
         std::memcpy(poses_out, b->h_poses, sizeof(double) * 12 * F);
-        if (accepted && iters > 0) std::memcpy(accepted, ha.data(), sizeof(int32_t) * F * iters);
-        if (e_hist && iters > 0) std::memcpy(e_hist, he.data(), sizeof(double) * F * iters);
+        if (e_hist && iters > 0) std::memcpy(e_hist, h, sizeof(double) * items);
+        if (accepted && iters > 0) std::memcpy(accepted, h + sizeof(double) * items, sizeof(int32_t) * items);
     } while (0);
-    dfree(d_acc);
-    dfree(d_eh);
+    if (!direct) {
+        if (rc != VG_OK) (void)hipStreamSynchronize(st);
+        dfree(hist);
+    }
     return rc;
 }
 
@@ -1380,7 +1363,7 @@ extern "C" vg_status vg_batch_time_kernels(vg_batch* b, const double* poses, int
     std::memcpy(b->h_poses, poses, sizeof(double) * 12 * b->F);
     VG_HIP(hipMemcpyAsync(b->d_poses, b->h_poses, sizeof(double) * 12 * b->F, hipMemcpyHostToDevice, st));
     VG_TRY(time_device(b, reps, &ms[0], &ms[1]));
-    VG_TRY(linearize_host(b));   // warm-up (captures the graph if enabled)
+    VG_TRY(linearize_host(b));   // warm-up
     const auto t0 = std::chrono::steady_clock::now();
     for (int r = 0; r < reps; ++r) VG_TRY(linearize_host(b));
     const auto t1 = std::chrono::steady_clock::now();

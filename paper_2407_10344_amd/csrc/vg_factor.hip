@@ -648,13 +648,22 @@ __device__ __forceinline__ int32_t work_item(int32_t n, int32_t interleave) {
                       : (int32_t)(blockIdx.x % kParts) * span + (int32_t)(blockIdx.x / kParts);
 }
 
-// Pose staging: FP32 copies of every factor's R and t (16 floats per factor),
-// read by the tile kernel through uniform (scalar) loads.
-__global__ void k_stage_poses(int64_t F, const double* __restrict__ poses, float* __restrict__ posef) {
+// Pose staging: FP32 copies of every factor's R and t (16 floats per factor), read
+// by the tile kernel through uniform (scalar) loads, and, where the poses come
+// from pinned host memory, their FP64 copy on the device (either may be nullptr).
+__global__ void k_stage_poses(int64_t F, const double* __restrict__ poses, double* __restrict__ pose64,
+                              float* __restrict__ posef) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= F * 16) return;
     const int64_t f = i / 16, k = i % 16;
-    posef[i] = (k < 12) ? (float)poses[12 * f + k] : 0.0f;
+    const double v = (k < 12) ? poses[12 * f + k] : 0.0;
+    if (posef != nullptr) posef[i] = (float)v;
+    if (pose64 != nullptr && k < 12) pose64[12 * f + k] = v;
+}
+
+__global__ void k_copy_words(const uint64_t* __restrict__ in, uint64_t* __restrict__ out, int64_t n) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) out[i] = in[i];
 }
 
 // VAL: surface validation (a compile-time switch, so that batches without it
@@ -1571,7 +1580,7 @@ vg_status launch_tiles(vg_batch* b, const Workspace& ws, int mode, const double*
     if (!staged && f1 > f0 && reads_staged_poses(b, mode)) {
         const int64_t nf = (f1 - f0) * 16;
         k_stage_poses<<<(int)((nf + 255) / 256), 256, 0, b->ctx->stream>>>(f1 - f0, d_poses + 12 * f0,
-                                                                          ws.posef + 16 * f0);
+                                                                          nullptr, ws.posef + 16 * f0);
         VG_HIP(hipGetLastError());
     }
     const int p = b->opt.precision;
@@ -1614,6 +1623,21 @@ vg_status launch_reduce(vg_batch* b, const Workspace& ws, int mode, const double
     else if (mode == kCount) { VG_R(kCount) }
     else { VG_R(kBwd) }
 #undef VG_R
+    VG_HIP(hipGetLastError());
+    return VG_OK;
+}
+
+vg_status launch_pose_upload(vg_batch* b, const Workspace& ws, int mode, const double* h_poses) {
+    float* posef = reads_staged_poses(b, mode) ? ws.posef : nullptr;
+    k_stage_poses<<<(int)((b->F * 16 + 255) / 256), 256, 0, b->ctx->stream>>>(b->F, h_poses, b->d_poses, posef);
+    VG_HIP(hipGetLastError());
+    return VG_OK;
+}
+
+vg_status launch_copy(vg_context* ctx, const void* src, void* dst, size_t bytes) {
+    const int64_t n = (int64_t)(bytes / 8);
+    if (n == 0) return VG_OK;
+    k_copy_words<<<(int)((n + 255) / 256), 256, 0, ctx->stream>>>((const uint64_t*)src, (uint64_t*)dst, n);
     VG_HIP(hipGetLastError());
     return VG_OK;
 }

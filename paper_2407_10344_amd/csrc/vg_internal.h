@@ -269,8 +269,8 @@ struct vg_batch {
     double* h_poses = nullptr;
     double* h_out = nullptr;
     int64_t* h_inliers = nullptr;
-    hipGraph_t graph = nullptr;
-    hipGraphExec_t exec = nullptr;
+    unsigned char* h_lm = nullptr;  // error and decision histories of short LM runs
+    size_t h_lm_bytes = 0;
     uint32_t magic = 0;
 };
 
@@ -382,6 +382,11 @@ bool reads_staged_poses(const vg_batch* b, int mode);
 vg_status launch_reduce(vg_batch* b, const Workspace& ws, int mode, const double* d_poses, int32_t f0, int32_t f1,
                         double* d_out, int64_t* d_inliers, const double* d_grad_e, const double* d_jr,
                         double* d_grad_xi, const LmArgs& lm = LmArgs{});
+// the batch's poses from pinned host memory to b->d_poses, and to ws.posef where a mode's kernels read
+// them so (the tile launch that follows is then `staged`)
+vg_status launch_pose_upload(vg_batch* b, const Workspace& ws, int mode, const double* h_poses);
+// copy of a multiple of 8 bytes between device and pinned host memory by a kernel
+vg_status launch_copy(vg_context* ctx, const void* src, void* dst, size_t bytes);
 // rows of shared sources: sum of their factors' per-factor rows in factor order
 vg_status launch_grad_combine(vg_batch* b, void* d_grad_points, int points_dtype);
 vg_status launch_correspondences(vg_batch* b, const double* d_pose, int64_t factor, int64_t* d_keys,

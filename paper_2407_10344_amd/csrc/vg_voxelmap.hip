@@ -573,6 +573,7 @@ __global__ __launch_bounds__(256) void k_layout(const double* __restrict__ xyz, 
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
         an[a] *= inv;
+        asm("" : "+v"(an[a]));   // the offsets are taken from the rounded anchor, not from a fused product
         d[a] = live ? (float)(x[a] - an[a]) : 0.f;
         dxyz[a * n_pad + i] = d[a];
         axyz[a * n_pad + i] = live ? (float)x[a] : 0.f;
