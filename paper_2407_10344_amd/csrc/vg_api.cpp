@@ -1169,15 +1169,16 @@ vg_status lm_step(vg_batch* b, double* d_poses, double* d_lambda, double* d_e, i
     lm.lambda = d_lambda;
     lm.poses = d_poses;
     lm.cand = b->d_lm + F;                                   // 12 per factor
-    lm.e0 = b->d_lm + 13 * F;                                // 1 per factor
-    lm.valid = reinterpret_cast<int32_t*>(b->d_lm + 14 * F);
+    lm.lin = b->d_out;
+    lm.valid = reinterpret_cast<int32_t*>(b->d_lm + 13 * F);
     lm.posef = reads_staged_poses(b, kLin) ? ws.posef : nullptr;   // both modes' kernels read them, or neither
     lm.e_out = d_e;
     lm.accepted = d_acc;
     lm.stride = stride;
     lm.col = col;
     VG_TRY(launch_tiles(b, ws, kLin, d_poses, 0, nt, nullptr, nullptr, 0, 0, F, staged));
-    VG_TRY(launch_reduce(b, ws, kLin, d_poses, 0, (int32_t)F, b->d_out, nullptr, nullptr, nullptr, nullptr, lm));
+    VG_TRY(launch_reduce(b, ws, kLin, d_poses, 0, (int32_t)F, b->d_out, nullptr, nullptr, nullptr, nullptr));
+    VG_TRY(launch_lm_propose(b, b->d_out, lm));
     VG_TRY(launch_tiles(b, ws, kEval, lm.cand, 0, nt, nullptr, nullptr, 0, 0, F, true));
     return launch_reduce(b, ws, kEval, lm.cand, 0, (int32_t)F, b->d_e, nullptr, nullptr, nullptr, nullptr, lm);
 }

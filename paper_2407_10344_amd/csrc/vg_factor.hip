@@ -1438,7 +1438,6 @@ __global__ __launch_bounds__(kRedThreads) void k_reduce(
         __syncthreads();
         if (k < kOutRow) out[(int64_t)kOutRow * f + k] = sRow[k];
         if (inliers != nullptr && k < F.L) inliers[(int64_t)F.L * f + k] = (int64_t)s[kTerms + k];
-        if (k == 0 && lm.lambda != nullptr) lm_propose(lm, f, sRow);
     }
 }
 

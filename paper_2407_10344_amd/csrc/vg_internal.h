@@ -121,15 +121,15 @@ struct Workspace {
 };
 
 // One Levenberg-Marquardt iteration (every pointer on the device; lambda nullptr:
-// none).  The reduction of a linearization ends with the proposal of every factor
-// and that of the evaluation of the candidates with accepting or rejecting it, so
-// an iteration is two tile launches and two reductions.
+// none).  The proposal and the acceptance leave the FP32 poses of the tile launch
+// that follows, and the reduction of the evaluation of the candidates ends with
+// accepting or rejecting them.
 struct LmArgs {
     double* lambda;          // F damping factors
     double* poses;           // F x 12 poses T
     double* cand;            // F x 12 candidates T Exp(delta)
     int32_t* valid;          // F: the damped matrix was SPD
-    double* e0;              // F errors at T
+    const double* lin;       // F x kOutRow linearization rows at T
     float* posef;            // F x 16 FP32 poses for the next tile launch, or nullptr
     double* e_out;           // error at T and decision, at column `col` of rows of `stride`, or nullptr
     int32_t* accepted;
@@ -394,6 +394,8 @@ vg_status launch_correspondences(vg_batch* b, const double* d_pose, int64_t fact
 vg_status launch_zero(vg_context* ctx, void* d_ptr, size_t bytes);
 vg_status launch_se3_retract(vg_context* ctx, int64_t F, const double* d_T0, const double* d_xi, double* d_T,
                              double* d_jr);
+// candidates of every factor from its linearization row
+vg_status launch_lm_propose(vg_batch* b, const double* d_out, const LmArgs& lm);
 vg_status launch_fill(vg_context* ctx, double* d_ptr, int64_t n, double v);
 
 }  // namespace vg

@@ -1,4 +1,6 @@
-// FP64 pose kernels: SE(3) retraction with its right Jacobian.
+// FP64 pose kernels: SE(3) retraction with its right Jacobian, and the proposal of
+// a Levenberg-Marquardt step (one thread per factor; 6x6 systems are tiny, so the
+// point is to stay on the device).
 #include "vg_se3.h"
 
 namespace vg {
@@ -56,6 +58,61 @@ __global__ void k_se3_retract(int64_t F, const double* __restrict__ T0, const do
     }
 }
 
+// Solve (H + lambda diag(H)) delta = -b by Cholesky; returns false if not SPD.
+__device__ bool lm_solve(const double* row, double lambda, double delta[6]) {
+    double A[36], L[36] = {0};
+    for (int i = 0; i < 6; ++i)
+        for (int j = 0; j < 6; ++j) A[6 * i + j] = row[1 + 6 * i + j] + (i == j ? lambda * row[1 + 7 * i] : 0.0);
+    for (int j = 0; j < 6; ++j) {
+        double s = A[7 * j];
+        for (int k = 0; k < j; ++k) s -= L[6 * j + k] * L[6 * j + k];
+        if (!(s > 0.0)) return false;
+        L[7 * j] = sqrt(s);
+        for (int i = j + 1; i < 6; ++i) {
+            double u = A[6 * i + j];
+            for (int k = 0; k < j; ++k) u -= L[6 * i + k] * L[6 * j + k];
+            L[6 * i + j] = u / L[7 * j];
+        }
+    }
+    double z[6];
+    for (int i = 0; i < 6; ++i) {
+        double s = -row[37 + i];
+        for (int k = 0; k < i; ++k) s -= L[6 * i + k] * z[k];
+        z[i] = s / L[7 * i];
+    }
+    for (int i = 5; i >= 0; --i) {
+        double s = z[i];
+        for (int k = i + 1; k < 6; ++k) s -= L[6 * k + i] * delta[k];
+        delta[i] = s / L[7 * i];
+    }
+    return true;
+}
+
+// Proposal of one damped step per factor: delta from (H + lambda diag H) delta = -b
+// (FP64 Cholesky) at the linearization rows, candidate T Exp(delta).  A matrix
+// that is not SPD leaves the candidate at T and marks it invalid.  A kernel of its
+// own: inside the reduction the compiler fuses the exponential's sums in another
+// order, and a step's last bit decides later accepts near convergence.
+__global__ void k_lm_propose(int64_t F, const double* __restrict__ out, const double* __restrict__ lambda,
+                             const double* __restrict__ poses, double* __restrict__ cand, int32_t* __restrict__ valid,
+                             float* __restrict__ posef) {
+    const int64_t f = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (f >= F) return;
+    const double* row = out + (int64_t)kOutRow * f;
+    double delta[6], T[12], E[12], C[12];
+    for (int k = 0; k < 12; ++k) T[k] = poses[12 * f + k];
+    const bool ok = lm_solve(row, lambda[f], delta);
+    if (ok) {
+        se3_exp(delta, E);
+        pose_mul(T, E, C);
+    } else {
+        for (int k = 0; k < 12; ++k) C[k] = T[k];
+    }
+    for (int k = 0; k < 12; ++k) cand[12 * f + k] = C[k];
+    valid[f] = ok ? 1 : 0;
+    stage_pose(posef, f, cand + 12 * f);
+}
+
 __global__ void k_fill(double* __restrict__ p, int64_t n, double v) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) p[i] = v;
@@ -65,6 +122,13 @@ vg_status launch_se3_retract(vg_context* ctx, int64_t F, const double* d_T0, con
                              double* d_jr) {
     if (F == 0) return VG_OK;
     k_se3_retract<<<(int)((F + 63) / 64), 64, 0, ctx->stream>>>(F, d_T0, d_xi, d_T, d_jr);
+    VG_HIP(hipGetLastError());
+    return VG_OK;
+}
+
+vg_status launch_lm_propose(vg_batch* b, const double* d_out, const LmArgs& lm) {
+    k_lm_propose<<<(int)((b->F + 63) / 64), 64, 0, b->ctx->stream>>>(b->F, d_out, lm.lambda, lm.poses, lm.cand, lm.valid,
+                                                                     lm.posef);
     VG_HIP(hipGetLastError());
     return VG_OK;
 }

@@ -1,5 +1,5 @@
-// Device helpers on SE(3) in FP64 (retraction, composition) and the damped step
-// of a Levenberg-Marquardt iteration, which the reduction kernels end with.
+// Device helpers on SE(3) in FP64 (retraction, composition) and the end of a
+// Levenberg-Marquardt iteration, which the candidates' reduction does.
 #pragma once
 
 #include "vg_device.h"
@@ -59,78 +59,30 @@ __device__ inline void pose_mul(const double A[12], const double B[12], double C
     for (int k = 0; k < 9; ++k) C[k] = Rm[k];
 }
 
-// Solve (H + lambda diag(H)) delta = -b by Cholesky; returns false if not SPD.
-__device__ inline bool lm_solve(const double* row, double lambda, double delta[6]) {
-    double A[36], L[36] = {0};
-    for (int i = 0; i < 6; ++i)
-        for (int j = 0; j < 6; ++j) A[6 * i + j] = row[1 + 6 * i + j] + (i == j ? lambda * row[1 + 7 * i] : 0.0);
-    for (int j = 0; j < 6; ++j) {
-        double s = A[7 * j];
-        for (int k = 0; k < j; ++k) s -= L[6 * j + k] * L[6 * j + k];
-        if (!(s > 0.0)) return false;
-        L[7 * j] = sqrt(s);
-        for (int i = j + 1; i < 6; ++i) {
-            double u = A[6 * i + j];
-            for (int k = 0; k < j; ++k) u -= L[6 * i + k] * L[6 * j + k];
-            L[6 * i + j] = u / L[7 * j];
-        }
-    }
-    double z[6];
-    for (int i = 0; i < 6; ++i) {
-        double s = -row[37 + i];
-        for (int k = 0; k < i; ++k) s -= L[6 * i + k] * z[k];
-        z[i] = s / L[7 * i];
-    }
-    for (int i = 5; i >= 0; --i) {
-        double s = z[i];
-        for (int k = i + 1; k < 6; ++k) s -= L[6 * k + i] * delta[k];
-        delta[i] = s / L[7 * i];
-    }
-    return true;
-}
-
-// FP32 copy of a pose (16 floats), as the multi-level FP32 kernels read it.
-__device__ __forceinline__ void stage_pose(float* __restrict__ posef, int64_t f, const double P[12]) {
+// FP32 copy of a pose (16 floats) as the multi-level FP32 kernels read it, taken
+// from where the pose was stored: as further uses of the values themselves the
+// conversions change the order in which the compiler fuses the sums that form them,
+// and the last bit of a step decides accepts near convergence.
+__device__ __forceinline__ void stage_pose(float* __restrict__ posef, int64_t f, const volatile double* P) {
     if (posef == nullptr) return;
     for (int k = 0; k < 16; ++k) posef[16 * f + k] = k < 12 ? (float)P[k] : 0.0f;
-}
-
-// Proposal of one damped step of factor f: delta from (H + lambda diag H) delta =
-// -b (FP64 Cholesky) at its linearization row, candidate T Exp(delta).  A matrix
-// that is not SPD leaves the candidate at T and marks it invalid.
-__device__ inline void lm_propose(const LmArgs& lm, int64_t f, const double* row) {
-    double delta[6], T[12], E[12], C[12];
-    for (int k = 0; k < 12; ++k) T[k] = lm.poses[12 * f + k];
-    const bool ok = lm_solve(row, lm.lambda[f], delta);
-    if (ok) {
-        se3_exp(delta, E);
-        pose_mul(T, E, C);
-    } else {
-        for (int k = 0; k < 12; ++k) C[k] = T[k];
-    }
-    for (int k = 0; k < 12; ++k) lm.cand[12 * f + k] = C[k];
-    lm.valid[f] = ok ? 1 : 0;
-    lm.e0[f] = row[0];
-    stage_pose(lm.posef, f, C);
 }
 
 // Accept the candidate of factor f iff it is valid and its error e_new is below the
 // error at T (then lambda / 10), else keep T (lambda x 10).  Records e at T and the
 // decision.
 __device__ inline void lm_accept(const LmArgs& lm, int64_t f, double e_new) {
-    const double e0 = lm.e0[f];
+    const double e0 = lm.lin[(int64_t)kOutRow * f];
     const bool acc = (lm.valid[f] != 0) && (e_new < e0);
-    double T[12];
-    for (int k = 0; k < 12; ++k) T[k] = acc ? lm.cand[12 * f + k] : lm.poses[12 * f + k];
     if (acc) {
-        for (int k = 0; k < 12; ++k) lm.poses[12 * f + k] = T[k];
+        for (int k = 0; k < 12; ++k) lm.poses[12 * f + k] = lm.cand[12 * f + k];
         lm.lambda[f] /= 10.0;
     } else {
         lm.lambda[f] *= 10.0;
     }
     if (lm.accepted != nullptr) lm.accepted[(int64_t)lm.stride * f + lm.col] = acc ? 1 : 0;
     if (lm.e_out != nullptr) lm.e_out[(int64_t)lm.stride * f + lm.col] = e0;
-    stage_pose(lm.posef, f, T);
+    stage_pose(lm.posef, f, lm.poses + 12 * f);
 }
 
 }  // namespace vg
