@@ -619,25 +619,46 @@ void build_tiles(vg_batch* b) {
             t.factor = (int32_t)f;
             t.chunk0 = (int32_t)c;
             t.nchunks = (int32_t)std::min<int64_t>(tc, nch - c);
+            t.row0 = (int32_t)b->h_tiles.size();
             b->h_tiles.push_back(t);
         }
     }
     b->h_tile_first[b->F] = (int32_t)b->h_tiles.size();
+    // units: up to kGroup tiles (one batch of kMaxTileChunks chunks) that share a
+    // prologue where the batch still has four units for every workgroup that fits
+    // the device at once (1024 threads per compute unit); else single tiles: fewer
+    // units than that leave compute units idle at the end of the launch, which costs
+    // more than the prologue saved
+    const int64_t fit = (int64_t)b->ctx->num_cu * std::max(1, 1024 / b->block);
+    int g = std::min(kGroup, std::max(1, kMaxTileChunks / tc));
+    while (g > 1 && (int64_t)b->h_tiles.size() < 4 * fit * g) --g;
+    b->h_units.clear();
+    b->h_unit_first.assign(b->F + 1, 0);
+    for (int64_t f = 0; f < b->F; ++f) {
+        b->h_unit_first[f] = (int32_t)b->h_units.size();
+        for (int32_t t = b->h_tile_first[f]; t < b->h_tile_first[f + 1]; t += g) {
+            Tile u = b->h_tiles[t];
+            for (int32_t k = t + 1; k < std::min(t + g, b->h_tile_first[f + 1]); ++k) u.nchunks += b->h_tiles[k].nchunks;
+            b->h_units.push_back(u);
+        }
+    }
+    b->h_unit_first[b->F] = (int32_t)b->h_units.size();
 }
 
 vg_status upload_schedule(vg_batch* b) {
     hipStream_t st = b->ctx->stream;
-    dfree(b->d_tiles);
+    dfree(b->d_units);
     dfree(b->d_tile_first);
     dfree(b->d_partials);
-    b->d_tiles = nullptr;
+    b->d_units = nullptr;
     b->d_tile_first = nullptr;
     b->d_partials = nullptr;
     const size_t nt = b->h_tiles.size();
-    VG_TRY(dev_alloc(&b->d_tiles, nt));
+    VG_TRY(dev_alloc(&b->d_units, b->h_units.size()));
     VG_TRY(dev_alloc(&b->d_tile_first, b->F + 1));
     VG_TRY(dev_alloc(&b->d_partials, (size_t)kRow * std::max<size_t>(nt, 1)));
-    if (nt) VG_HIP(hipMemcpyAsync(b->d_tiles, b->h_tiles.data(), sizeof(Tile) * nt, hipMemcpyHostToDevice, st));
+    if (nt)
+        VG_HIP(hipMemcpyAsync(b->d_units, b->h_units.data(), sizeof(Tile) * b->h_units.size(), hipMemcpyHostToDevice, st));
     VG_HIP(hipMemcpyAsync(b->d_tile_first, b->h_tile_first.data(), sizeof(int32_t) * (b->F + 1),
                           hipMemcpyHostToDevice, st));
     VG_HIP(hipStreamSynchronize(st));
@@ -691,8 +712,7 @@ Workspace batch_ws(vg_batch* b) { return Workspace{b->d_partials, b->d_posef, b-
 
 vg_status run_linearize_device(vg_batch* b, const Workspace& ws, const double* d_poses, double* d_out,
                                int64_t* d_inl) {
-    const int32_t nt = (int32_t)b->h_tiles.size();
-    VG_TRY(launch_tiles(b, ws, kLin, d_poses, 0, nt, nullptr, nullptr, 0, 0, b->F));
+    VG_TRY(launch_tiles(b, ws, kLin, d_poses, nullptr, nullptr, 0, 0, b->F));
     return launch_reduce(b, ws, kLin, d_poses, 0, (int32_t)b->F, d_out, d_inl, nullptr, nullptr, nullptr);
 }
 
@@ -701,9 +721,8 @@ vg_status run_linearize_device(vg_batch* b, const double* d_poses, double* d_out
 }
 
 vg_status run_evaluate_device(vg_batch* b, const double* d_poses, double* d_e) {
-    const int32_t nt = (int32_t)b->h_tiles.size();
     const Workspace ws = batch_ws(b);
-    VG_TRY(launch_tiles(b, ws, kEval, d_poses, 0, nt, nullptr, nullptr, 0, 0, b->F));
+    VG_TRY(launch_tiles(b, ws, kEval, d_poses, nullptr, nullptr, 0, 0, b->F));
     return launch_reduce(b, ws, kEval, d_poses, 0, (int32_t)b->F, d_e, nullptr, nullptr, nullptr, nullptr);
 }
 
@@ -730,10 +749,9 @@ vg_status finish_host(vg_batch* b, const double* device, size_t count) {
 }
 
 vg_status run_host(vg_batch* b, int mode, double* d_out, int64_t* d_inl) {
-    const int32_t nt = (int32_t)b->h_tiles.size();
     const Workspace ws = batch_ws(b);
     VG_TRY(launch_pose_upload(b, ws, mode, b->h_poses));
-    VG_TRY(launch_tiles(b, ws, mode, b->d_poses, 0, nt, nullptr, nullptr, 0, 0, b->F, true));
+    VG_TRY(launch_tiles(b, ws, mode, b->d_poses, nullptr, nullptr, 0, 0, b->F, true));
     return launch_reduce(b, ws, mode, b->d_poses, 0, (int32_t)b->F, d_out, d_inl, nullptr, nullptr, nullptr);
 }
 
@@ -745,9 +763,8 @@ vg_status linearize_host(vg_batch* b) {
         for (int64_t f = 0; f < F; ++f) {
             VG_HIP(hipMemcpyAsync(b->d_poses + 12 * f, b->h_poses + 12 * f, sizeof(double) * 12,
                                   hipMemcpyHostToDevice, st));
-            const int32_t t0 = b->h_tile_first[f], t1 = b->h_tile_first[f + 1];
             const Workspace ws = batch_ws(b);
-            VG_TRY(launch_tiles(b, ws, kLin, b->d_poses, t0, t1, nullptr, nullptr, 0, f, f + 1));
+            VG_TRY(launch_tiles(b, ws, kLin, b->d_poses, nullptr, nullptr, 0, f, f + 1));
             VG_TRY(launch_reduce(b, ws, kLin, b->d_poses, (int32_t)f, (int32_t)f + 1, b->d_out, b->d_inliers,
                                  nullptr, nullptr, nullptr));
             VG_HIP(hipMemcpyAsync(b->h_out + kOutRow * f, b->d_out + kOutRow * f, sizeof(double) * kOutRow,
@@ -767,7 +784,7 @@ vg_status linearize_host(vg_batch* b) {
 
 void free_batch(vg_batch* b) {
     dfree(b->d_fac);
-    dfree(b->d_tiles);
+    dfree(b->d_units);
     dfree(b->d_tile_first);
     dfree(b->d_partials);
     dfree(b->d_poses);
@@ -974,7 +991,7 @@ extern "C" vg_status vg_batch_info(const vg_batch* b, int64_t* total_points, int
     if (n_tiles) *n_tiles = (int64_t)b->h_tiles.size();
     if (block_threads) *block_threads = b->block;
     if (tile_points) *tile_points = b->tile_points;
-    if (grid_blocks) *grid_blocks = kParts * (int32_t)((b->h_tiles.size() + kParts - 1) / kParts);
+    if (grid_blocks) *grid_blocks = kParts * (int32_t)((b->h_units.size() + kParts - 1) / kParts);
     if (tile_order) *tile_order = b->tile_order;
     return VG_OK;
 }
@@ -1125,9 +1142,8 @@ extern "C" vg_status vg_backward_async(vg_batch* b, const double* d_poses, const
         if (compacted && b->slab_rows > 0)
             VG_TRY(launch_zero(b->ctx, b->d_gslab, (size_t)b->slab_rows * 3 * (points_dtype ? 8 : 4)));
     }
-    const int32_t nt = (int32_t)b->h_tiles.size();
     const Workspace ws = batch_ws(b);
-    VG_TRY(launch_tiles(b, ws, kBwd, d_poses, 0, nt, d_grad_e, d_grad_points, points_dtype, 0, b->F));
+    VG_TRY(launch_tiles(b, ws, kBwd, d_poses, d_grad_e, d_grad_points, points_dtype, 0, b->F));
     VG_TRY(launch_grad_combine(b, d_grad_points, points_dtype));
     return launch_reduce(b, ws, kBwd, d_poses, 0, (int32_t)b->F, nullptr, nullptr, d_grad_e, d_jr, d_grad_xi);
 }
@@ -1163,7 +1179,6 @@ namespace {
 vg_status lm_step(vg_batch* b, double* d_poses, double* d_lambda, double* d_e, int32_t* d_acc, int32_t stride,
                   int32_t col, bool staged) {
     const int64_t F = b->F;
-    const int32_t nt = (int32_t)b->h_tiles.size();
     const Workspace ws = batch_ws(b);
     LmArgs lm{};
     lm.lambda = d_lambda;
@@ -1176,10 +1191,10 @@ vg_status lm_step(vg_batch* b, double* d_poses, double* d_lambda, double* d_e, i
     lm.accepted = d_acc;
     lm.stride = stride;
     lm.col = col;
-    VG_TRY(launch_tiles(b, ws, kLin, d_poses, 0, nt, nullptr, nullptr, 0, 0, F, staged));
+    VG_TRY(launch_tiles(b, ws, kLin, d_poses, nullptr, nullptr, 0, 0, F, staged));
     VG_TRY(launch_reduce(b, ws, kLin, d_poses, 0, (int32_t)F, b->d_out, nullptr, nullptr, nullptr, nullptr));
     VG_TRY(launch_lm_propose(b, b->d_out, lm));
-    VG_TRY(launch_tiles(b, ws, kEval, lm.cand, 0, nt, nullptr, nullptr, 0, 0, F, true));
+    VG_TRY(launch_tiles(b, ws, kEval, lm.cand, nullptr, nullptr, 0, 0, F, true));
     return launch_reduce(b, ws, kEval, lm.cand, 0, (int32_t)F, b->d_e, nullptr, nullptr, nullptr, nullptr, lm);
 }
 
@@ -1319,13 +1334,12 @@ namespace {
 // Average device time of the tile kernel and the reduction over `reps` launches.
 vg_status time_device(vg_batch* b, int reps, float* ms_tiles, float* ms_reduce) {
     hipStream_t st = b->ctx->stream;
-    const int32_t nt = (int32_t)b->h_tiles.size();
     std::vector<hipEvent_t> ev(3 * reps);
     for (auto& x : ev) VG_HIP(hipEventCreate(&x));
     vg_status rc = run_linearize_device(b, b->d_poses, b->d_out, b->d_inliers);   // warm-up
     for (int r = 0; r < reps && rc == VG_OK; ++r) {
         (void)hipEventRecord(ev[3 * r], st);
-        rc = launch_tiles(b, batch_ws(b), kLin, b->d_poses, 0, nt, nullptr, nullptr, 0, 0, b->F);
+        rc = launch_tiles(b, batch_ws(b), kLin, b->d_poses, nullptr, nullptr, 0, 0, b->F);
         (void)hipEventRecord(ev[3 * r + 1], st);
         if (rc == VG_OK)
             rc = launch_reduce(b, batch_ws(b), kLin, b->d_poses, 0, (int32_t)b->F, b->d_out, b->d_inliers, nullptr,

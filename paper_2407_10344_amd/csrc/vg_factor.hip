@@ -28,6 +28,7 @@
 //        FP32 (optionally Kahan-compensated), everything above a lane in FP64.
 //  kN32: absolute FP32 coordinates and FP32 sums everywhere.
 //  kF64: absolute FP64 coordinates and arithmetic.
+#include <algorithm>
 #include <type_traits>
 
 #include "vg_device.h"
@@ -56,6 +57,12 @@ struct Acc {
         for (int k = 0; k < N; ++k) {
             s[k] = T(0);
             if constexpr (KAHAN) c[k] = T(0);
+            // opaque: sums known to be zero after a tile are otherwise kept apart
+            // from running ones and copied on every path between them (224 moves
+            // and 38 VGPRs in the FP64 kernel: 178 us against 128 us over 190
+            // submap factors)
+            asm("" : "+v"(s[k]));
+            if constexpr (KAHAN) asm("" : "+v"(c[k]));
         }
     }
     __device__ __forceinline__ void add(int k, T v) {
@@ -238,13 +245,20 @@ struct ChunkLds {
     float za[3];       // R (anchor - o_s)
     float vc[3];       // anchor - T^-1 c (surface validation)
 };
+// What the hit terms of a multi-level batch read of each level (a lane's level is
+// its hit's: from LDS the record gather waits on one LDS read, not on a descriptor
+// load from memory).
+struct HitLevel {
+    const void* rec;   // rec32 (compensated) or rec64 (FP64)
+    double r64;
+    float inv_r;
+    float pad_;
+};
 struct TileShared {
     double frac[kMaxTileChunks * 3];   // anchor position inside its coarse voxel, FP64 (kC32; minus r/2 in
                                        // one-level compacted kernels)
     ChunkLds cd[kMaxTileChunks];
-    int32_t live[kMaxTileChunks];      // the chunks the waves walk, in chunk order
-    int32_t nlive;
-    int32_t walked;                    // source points in those chunks
+    HitLevel lvl[kMaxLevels];
     uint8_t reach[kMaxTileChunks];     // kChunkCulled / kChunkStraddles / kChunkInside
 };
 
@@ -452,17 +466,10 @@ __device__ __forceinline__ void cmp_hit_terms(A& acc, const FactorDesc* __restri
         return;
     }
     const int c = cl >> 2, l = cl & 3;
-    // the level's record array, 1/r and r: the first level's come from scalar
-    // registers, so its record gather does not wait on a descriptor load
-    const float* rec_base = pl0.rec32;
-    float inv_r = pl0.inv_r;
-    double r64 = pl0.r64;
-    if (l != 0) {
-        const LevelDesc& lv = Fp->lv[l];
-        rec_base = lv.rec32;
-        inv_r = lv.inv_r;
-        r64 = lv.r64;
-    }
+    const HitLevel lv = sh.lvl[l];
+    const void* rec_base = lv.rec;
+    const float inv_r = lv.inv_r;
+    const double r64 = lv.r64;
     const uint32_t ro = (uint32_t)v * (uint32_t)(kRec32 * sizeof(float));
     const f32x4 q0 = load_off<f32x4>(rec_base, ro);
     const f64x2 cva = load_off<f64x2>(rec_base, ro + 16u), cvb = load_off<f64x2>(rec_base, ro + 32u),
@@ -504,13 +511,12 @@ __device__ __forceinline__ void cmp_hit_terms(A& acc, const FactorDesc* __restri
 // FP64 positions (it was read one drain ago, so the load hits the caches) and
 // the arithmetic is the uncompacted FP64 path's.
 template <int MODE, typename A>
-__device__ __forceinline__ void cmp_hit_terms64(A& acc, const FactorDesc* __restrict__ Fp, const double* P,
-                                                const double* R, const double* tt, int64_t n_pad, int32_t i,
-                                                int32_t v, int32_t cl) {
-    const LevelDesc& lv = Fp->lv[cl & 3];
+__device__ __forceinline__ void cmp_hit_terms64(A& acc, const FactorDesc* __restrict__ Fp, const TileShared& sh,
+                                                const double* P, const double* R, const double* tt, int64_t n_pad,
+                                                int32_t i, int32_t v, int32_t cl) {
     const auto X = gbl(Fp->xyz64);
     const double x[3] = {X[i], X[n_pad + i], X[2 * n_pad + i]};
-    const auto r2 = gbl(reinterpret_cast<const f64x2*>(lv.rec64 + (int64_t)v * kRec64));
+    const auto r2 = gbl(reinterpret_cast<const f64x2*>(static_cast<const double*>(sh.lvl[cl & 3].rec) + (int64_t)v * kRec64));
     const f64x2 q0 = r2[0], q1 = r2[1], q2 = r2[2], q3 = r2[3], q4 = r2[4];
     double S[6];
     point_S<kF64>(Fp, (int64_t)i, n_pad, P, R, S);
@@ -534,18 +540,25 @@ __device__ __forceinline__ void drain_hit(A& acc, const FactorDesc* __restrict__
     if constexpr (PREC == kC32)
         cmp_hit_terms<MODE, SC>(acc, Fp, sh, pl0, P, R, n_pad, Q.x[e], Q.y[e], Q.z[e], Q.pt[e], Q.rec[e], Q.cl[e], go);
     else
-        cmp_hit_terms64<MODE>(acc, Fp, P, R, tt, n_pad, Q.pt[e], Q.rec[e], Q.cl[e]);
+        cmp_hit_terms64<MODE>(acc, Fp, sh, P, R, tt, n_pad, Q.pt[e], Q.rec[e], Q.cl[e]);
 }
 
-// Register budget: 4 waves per SIMD (<= 128 VGPRs) for the FP32 modes; the
-// FP64 mode needs more and runs at what its register count allows.
-template <int PREC, bool KH>
-constexpr int waves_per_eu() { return (PREC == kF64 || KH) ? 1 : 4; }
-// the FP32 kernels are held at exactly four (the scheduler then keeps loads in
-// flight instead of saving registers for a fifth); the others may run up to the
-// eight a SIMD holds, so their scheduler still works for occupancy
-template <int PREC, bool KH>
-constexpr int waves_per_eu_max() { return waves_per_eu<PREC, KH>() == 4 ? 4 : 8; }
+// Register budget, in waves per SIMD.  The FP32 linearize and backward kernels are
+// held at exactly four (<= 128 VGPRs): the scheduler then keeps loads in flight
+// instead of saving registers for a fifth (five spill: 580 us against 395 us for
+// the 500-submap linearize).  Evaluate and the counts have few live sums and wait
+// on probe loads, so they run more waves (500 submaps: evaluate 331 us at six
+// against 364 us at four; overlap 153 us at eight, 166 us at six, 231 us at four).
+// FP64 and Kahan kernels take what their register count allows (FP64: three; four
+// spill and take 150 us against 128 us over 190 factors).
+template <int MODE, int PREC, bool KH>
+constexpr int waves_per_eu() {
+    return MODE == kCount ? 8 : (PREC == kF64 || KH) ? 1 : MODE == kEval ? 6 : 4;
+}
+template <int MODE, int PREC, bool KH>
+constexpr int waves_per_eu_max() {
+    return waves_per_eu<MODE, PREC, KH>() == 4 ? 4 : 8;
+}
 
 // Every point of chunk cg lies in a ball around the anchor and in a box of
 // the source frame, both stored with the chunk.  In the target frame (anchor
@@ -556,7 +569,13 @@ constexpr int waves_per_eu_max() { return waves_per_eu<PREC, KH>() == 4 ? 4 : 8;
 // per-point box test.  The margins (1e-3 m + 1e-5 relative) cover FP32 key
 // positions and the FP32 rounding of the stored offsets.
 constexpr int kChunkCulled = 0, kChunkStraddles = 1, kChunkInside = 2;
-constexpr int kInsideFlag = 1 << 16;   // in a live-list entry: the chunk is inside every key box
+
+// In a wave's list of chunks: the chunk is inside every key box; the list's end.
+constexpr int kInsideFlag = 0x100, kListEnd = 0x80;
+__device__ __forceinline__ uint64_t bits_below(int k) {   // k clamped to 0..64
+    return k >= 64 ? ~0ull : (k <= 0 ? 0ull : (1ull << k) - 1ull);
+}
+
 __device__ __forceinline__ int chunk_state(const FactorDesc* __restrict__ Fp, const double* P, const double ya[3],
                                            int64_t cg, int L) {
     const auto cb = gbl(Fp->cbound + 8 * cg);
@@ -670,9 +689,18 @@ __global__ void k_copy_words(const uint64_t* __restrict__ in, uint64_t* __restri
 // carry none of its state through the point loop).  LM: the most levels the
 // point loop is compiled for (1 for single-level batches, whose kernel then
 // holds no state of the other levels; else kMaxLevels).
+// Tiles are taken in units of up to kGroup whole tiles of one factor (tc chunks
+// each), one workgroup per unit: they share the chunk prologue and its barriers.
+// A tile of 2,048 points is 32 chunks dealt to four waves and half of them are
+// culled in a submap batch, so what a tile costs besides its points (descriptors,
+// anchors, barriers: 43 % of a wave's time there) was as much as the points.  Each
+// wave picks its chunks from the ballots of the whole unit, without a list that one
+// wave writes and a barrier around it.  500 submaps: linearize 439 -> 364 us,
+// overlap 278 -> 232 us (both with one tile per unit: 447 and 297 us).  The rows stay one per tile and a wave's share of a tile is the same in any unit, so
+// results do not depend on it.
 template <int MODE, int PREC, int BLOCK, bool KH, bool VAL, int LM>
-__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(waves_per_eu<PREC, KH>(), waves_per_eu_max<PREC, KH>()))) void k_tiles(
-    const FactorDesc* __restrict__ fac, const Tile* __restrict__ tiles, int32_t t_begin, int32_t t_end,
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(waves_per_eu<MODE, PREC, KH>(), waves_per_eu_max<MODE, PREC, KH>()))) void k_tiles(
+    const FactorDesc* __restrict__ fac, const Tile* __restrict__ units, int32_t u_begin, int32_t n_units, int32_t tc,
     const double* __restrict__ poses, const float* __restrict__ posef, double* __restrict__ partials,
     const double* __restrict__ grad_e, void* __restrict__ grad_points, void* __restrict__ grad_slab,
     int32_t points_dtype, int32_t interleave) {
@@ -707,15 +735,15 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(waves_per
     __shared__ TileShared sh;
     using QueueT = typename std::conditional<CMP, HitQueue, int32_t>::type;
     __shared__ QueueT s_q[CMP ? NW : 1];
-    __shared__ double s_red[NW][kRow];
+    __shared__ double s_red[kGroup][NW][kRow];
+    __shared__ uint16_t s_list[NW][kMaxTileChunks];   // each wave's chunks, in order
     const int lane = threadIdx.x & 63;
     // wave index as a uniform (scalar) value, so chunk indices and per-chunk LDS
     // addresses are computed once per wave, not per lane
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int32_t item = work_item(t_end - t_begin, interleave);
-    if (item >= t_end - t_begin) return;
-    const int32_t t = t_begin + item;
-    const Tile tile = tiles[t];
+    const int32_t item = work_item(n_units, interleave);
+    if (item >= n_units) return;
+    const Tile tile = units[u_begin + item];
     const FactorDesc* __restrict__ Fp = fac + tile.factor;
     const int64_t n = Fp->n, n_pad = Fp->n_pad;
     const int L = Fp->L;
@@ -749,6 +777,10 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(waves_per
 #pragma unroll
         for (int i = 0; i < 3; ++i) cs[i] = P[i] * dc0 + P[3 + i] * dc1 + P[6 + i] * dc2;
     }
+    if (CMP && !SC && threadIdx.x < L) {
+        const LevelDesc& lv = Fp->lv[threadIdx.x];
+        sh.lvl[threadIdx.x] = HitLevel{PREC == kF64 ? (const void*)lv.rec64 : (const void*)lv.rec32, lv.r64, lv.inv_r, 0.f};
+    }
     // ---------------------------------------------------------------- per-tile state
     Acc<T, KAHAN, NT> acc;
     acc.zero();
@@ -759,7 +791,8 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(waves_per
     int32_t inl[kMaxLevels] = {0, 0, 0, 0};
     int32_t prb[kMaxLevels] = {0, 0, 0, 0};
     uint32_t inl2[2] = {0u, 0u}, prb2[2] = {0u, 0u};
-    int32_t walked_pts = 0, walked_chunks = 0;
+    bool any_hit = false;   // some hit of the tile was processed by this wave (compacted paths)
+    int sub = 0;            // tile within the unit
     double ge = 0.0;
     if constexpr (MODE == kBwd) ge = grad_e[tile.factor];
     const GradOut go{ge, grad_points, grad_slab, points_dtype};
@@ -779,6 +812,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(waves_per
                 drain_hit<MODE, PREC, SC>(acc, Fp, sh, pl0, P, R, tt, n_pad, Q, q_head + lane, go);
                 q_head = (q_head + kChunk) & (kQueue - 1);
                 q_count -= kChunk;
+                any_hit = true;
                 __builtin_amdgcn_wave_barrier();
             }
         }
@@ -786,9 +820,9 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(waves_per
     // the source's positions as a buffer (3 x n_pad floats; sources hold fewer than 2^27 points)
     const __amdgpu_buffer_rsrc_t xr = raw_rsrc(Fp->dxyz, (uint32_t)(3 * n_pad * (int64_t)sizeof(float)));
     const int32_t n32 = (int32_t)n;
-    // The tile's chunks are taken in batches of up to kMaxTileChunks (the
-    // per-chunk data held in LDS); the lane sums run on across batches, so a
-    // tile of several batches is reduced once.
+    // The unit's chunks are taken in batches of up to kMaxTileChunks (the per-chunk
+    // data held in LDS).  A unit of several tiles is one batch; the lane sums of a
+    // larger tile run on across its batches, so it is reduced once.
     for (int sb0 = 0; sb0 < tile.nchunks; sb0 += kMaxTileChunks) {
         const int nch = min(kMaxTileChunks, tile.nchunks - sb0);
         const int chunk0 = tile.chunk0 + sb0;
@@ -834,55 +868,66 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(waves_per
             }
             __syncthreads();
         }
-        // the list of chunks to walk (kept in chunk order)
-        if (wave == 0) {
-            int cnt = 0;
-            int32_t pts = 0;   // per lane: points of the chunks this lane kept
-            for (int base = 0; base < nch; base += 64) {
-                const int c = base + lane;
-                bool keep = c < nch;
-                int flag = 0;
-                if constexpr (SKIP) {
-                    const int st = keep ? (int)sh.reach[c] : kChunkCulled;
-                    keep = st != kChunkCulled;
-                    flag = st == kChunkInside ? kInsideFlag : 0;
-                }
-                const uint64_t m = __ballot(keep);
-                if (keep) {
-                    sh.live[cnt + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
-                                                            __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u))] = c | flag;
-                    pts += (int32_t)min<int64_t>(kChunk, n - (int64_t)(chunk0 + c) * kChunk);
-                }
-                cnt += __popcll(m);
+        // the chunks to walk, a bit each: this wave takes those whose rank among their
+        // tile's is wave, wave + NW, ... (uniform)
+        int nown;            // chunks of this wave's list
+        {
+            int ln = lane, tx = threadIdx.x;   // opaque, or the masks below are hoisted out of the loop and held
+            asm volatile("" : "+v"(ln), "+v"(tx));
+            uint64_t walk[2], own[2];
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                const int c = 64 * q + ln;
+                walk[q] = __ballot(c < nch && (!SKIP || sh.reach[c] != kChunkCulled));
             }
-            pts = wave_sum(pts);
-            if (lane == 0) {
-                sh.nlive = cnt;
-                sh.walked = pts;
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                const int c = 64 * q + ln;
+                const int first = c >= 2 * tc ? (c >= 3 * tc ? 3 * tc : 2 * tc) : (c >= tc ? tc : 0);   // of the chunk's tile
+                const int rank = __popcll(walk[0] & bits_below(c) & ~bits_below(first)) +
+                                 __popcll(walk[1] & bits_below(c - 64) & ~bits_below(first - 64));
+                own[q] = walk[q] & __ballot((rank & (NW - 1)) == wave);
+            }
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                const int c = 64 * q + ln;
+                if ((own[q] >> ln) & 1)
+                    s_list[wave][__popcll(own[0] & bits_below(c)) + __popcll(own[1] & bits_below(c - 64))] =
+                        (uint16_t)(c | (SKIP && sh.reach[c] == kChunkInside ? kInsideFlag : 0));
+            }
+            nown = __popcll(own[0]) + __popcll(own[1]);
+            if (tx < kGroup && tx * tc < nch) {   // thread r: the walked chunks and points of tile r
+                const int c0 = tx * tc, c1 = min(nch, c0 + tc);
+                const uint64_t w0 = walk[0] & bits_below(c1) & ~bits_below(c0);
+                const uint64_t w1 = walk[1] & bits_below(c1 - 64) & ~bits_below(c0 - 64);
+                const int cnt = __popcll(w0) + __popcll(w1);
+                const int last = (int)(n_pad / kChunk) - 1 - chunk0;   // the source's last chunk may be partial
+                const bool part = last >= c0 && last < c1 && (((last < 64 ? w0 : w1) >> (last & 63)) & 1) != 0;
+                const int pts = cnt * kChunk - (part ? (int)(n_pad - n) : 0);
+                double* red = s_red[tx][0];
+                red[kRowWalk] = (sb0 ? red[kRowWalk] : 0.0) + (double)pts;
+                red[kRowChunks] = (sb0 ? red[kRowChunks] : 0.0) + (double)cnt;
             }
         }
-        __syncthreads();
-        const int nlive = __builtin_amdgcn_readfirstlane(sh.nlive);
-        // this wave walks entries wave, wave + NW, ... of the list; with two or
-        // more waves they are at most 64, held one per lane and read by index
-        int32_t mylive = 0;
-        if constexpr (NW >= 2) {
-            const int jj = wave + NW * lane;
-            mylive = jj < nlive ? sh.live[jj] : 0;
-        }
-        auto live_chunk = [&](int j, int k) -> int {
-            if constexpr (NW >= 2) return __builtin_amdgcn_readlane(mylive, k);
-            else return __builtin_amdgcn_readfirstlane(sh.live[j]);
-        };
         RawPoint<PREC> nxt;
-        int cnext = 0;
-        if (wave < nlive) {
-            cnext = live_chunk(wave, 0);
-            load_point<PREC>(Fp, xr, (uint32_t)(chunk0 + (cnext & (kInsideFlag - 1))) * kChunk, n_pad,
-                             (uint32_t)lane, nxt);
-        }
-        for (int j = wave, k = 0; j < nlive; j += NW, ++k) {
-            const int c = cnext & (kInsideFlag - 1);
+        __builtin_amdgcn_wave_barrier();
+        // with two or more waves the list has at most 64 entries, held one per lane
+        // and read by index: no wait on LDS per chunk
+        int32_t mine = 0;
+        if constexpr (NW >= 2) mine = lane < nown ? (int)s_list[wave][lane] : 0;
+        int k = 0;
+        auto next_chunk = [&]() -> int {
+            if (k >= nown) return kListEnd;
+            if constexpr (NW >= 2) return __builtin_amdgcn_readlane(mine, k++);
+            else return __builtin_amdgcn_readfirstlane((int)s_list[wave][k++]);
+        };
+        int cnext = next_chunk();
+        if ((cnext & kListEnd) == 0)
+            load_point<PREC>(Fp, xr, (uint32_t)(chunk0 + (cnext & 127)) * kChunk, n_pad, (uint32_t)lane, nxt);
+        for (int c0 = 0; c0 < nch; c0 += tc) {
+        const int c1 = min(nch, c0 + tc);
+        while ((cnext & 255) < c1) {
+            const int c = cnext & 127;
             // every point of the chunk is inside every level's key box (uniform)
             const bool inside = (cnext & kInsideFlag) != 0;
             // point index (sources hold fewer than 2^31 points) and the chunk's
@@ -892,11 +937,9 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(waves_per
             const int32_t npts = min(kChunk, n32 - (int32_t)base);
             const bool live = lane < npts;
             const RawPoint<PREC> cur = nxt;
-            if (j + NW < nlive) {
-                cnext = live_chunk(j + NW, k + 1);
-                load_point<PREC>(Fp, xr, (uint32_t)(chunk0 + (cnext & (kInsideFlag - 1))) * kChunk, n_pad,
-                                 (uint32_t)lane, nxt);
-            }
+            cnext = next_chunk();
+            if ((cnext & kListEnd) == 0)
+                load_point<PREC>(Fp, xr, (uint32_t)(chunk0 + (cnext & 127)) * kChunk, n_pad, (uint32_t)lane, nxt);
             if constexpr (CMP && PREC == kF64) {
                 // ---- FP64 mode: probe every point, queue its hits, drain full waves
                 HitQueue& Q = s_q[wave];
@@ -1219,7 +1262,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(waves_per
             }
         }
         if constexpr (CMP) {
-            // the queued hits refer to this batch's chunks: a full wave left by a
+            // the tile's hits (and this batch's chunks) end here: a full wave left by a
             // probe that drains before pushing, then the partial rest
             drain_full(s_q[wave]);
             if (q_count > 0) {
@@ -1228,68 +1271,77 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(waves_per
                     drain_hit<MODE, PREC, SC>(acc, Fp, sh, pl0, P, R, tt, n_pad, s_q[wave], (q_head + lane) & (kQueue - 1), go);
                 }
                 __builtin_amdgcn_wave_barrier();
-                q_head = 0;
-                q_count = 0;
+                any_hit = true;
+            }
+            q_head = 0;
+            q_count = 0;
+        }
+        if (sb0 + nch < tile.nchunks) continue;   // a tile of several batches goes on
+        // ---------------------------------------------------------------- the tile's sums over the wave
+        // lanes -> wave: FP64 except kN32, which stays FP32 end to end; a wave
+        // without a hit has zero sums
+        // (the lane and wave are made opaque here: else their masks and addresses are
+        // hoisted out of the tile loop and held in registers through it)
+        int ln = lane, wv = wave;
+        asm volatile("" : "+v"(ln), "+s"(wv));
+        double* red = s_red[sub][wv];
+        if constexpr (PREC != kN32 && (NT == kTerms || (CMP && MODE == kEval))) {
+            // the 28 terms in one transposed butterfly (value k ends on lanes 2k, 2k + 1);
+            // the compacted evaluate sums its one term the same way, so its e equals
+            // linearize's
+            double w = 0.0;
+            if (!CMP || any_hit) {
+                double v[32];
+#pragma unroll
+                for (int k = 0; k < 32; ++k) v[k] = k < NT ? acc.get64(k) : 0.0;
+                w = wave_sum_transposed(v, ln);
+            }
+            if ((ln & 1) == 0 && (ln >> 1) < NT) red[ln >> 1] = w;
+        } else if constexpr (MODE != kCount) {
+#pragma unroll
+            for (int k = 0; k < NT; ++k) {
+                if constexpr (PREC == kN32) {
+                    const float v = wave_sum(acc.get(k));
+                    if (ln == 0) red[k] = (double)v;
+                } else {
+                    const double v = wave_sum(acc.get64(k));
+                    if (ln == 0) red[k] = v;
+                }
             }
         }
-        walked_pts += __builtin_amdgcn_readfirstlane(sh.walked);
-        walked_chunks += nlive;
-        __syncthreads();   // the next batch's prologue overwrites the chunk data
-    }
-    // ---------------------------------------------------------------- reduction of the tile
-    // lanes -> wave -> tile: FP64 except kN32, which stays FP32 end to end
-    if constexpr (PREC != kN32 && (NT == kTerms || (CMP && MODE == kEval))) {
-        // the 28 terms in one transposed butterfly (value k ends on lanes 2k, 2k + 1);
-        // the compacted evaluate sums its one term the same way, so its e equals
-        // linearize's
-        double v[32];
+        if constexpr (MODE != kBwd) {
 #pragma unroll
-        for (int k = 0; k < 32; ++k) v[k] = k < NT ? acc.get64(k) : 0.0;
-        const double w = wave_sum_transposed(v, lane);
-        if ((lane & 1) == 0 && (lane >> 1) < NT) s_red[wave][lane >> 1] = w;
-    } else {
-#pragma unroll
-        for (int k = 0; k < NT; ++k) {
-            if constexpr (PREC == kN32) {
-                const float v = wave_sum(acc.get(k));
-                if (lane == 0) s_red[wave][k] = (double)v;
-            } else {
-                const double v = wave_sum(acc.get64(k));
-                if (lane == 0) s_red[wave][k] = v;
+            for (int l = 0; l < kMaxLevels; ++l) {
+                const int32_t v = CMP ? (int32_t)((inl2[l >> 1] >> (16 * (l & 1))) & 0xFFFFu) : wave_sum(inl[l]);
+                const int32_t p = CMP ? (int32_t)((prb2[l >> 1] >> (16 * (l & 1))) & 0xFFFFu) : wave_sum(prb[l]);
+                if (ln == 0) {
+                    red[kRowInl + l] = (double)v;
+                    red[kRowProbe + l] = (double)p;
+                }
+                inl[l] = prb[l] = 0;
             }
+            inl2[0] = inl2[1] = prb2[0] = prb2[1] = 0u;
         }
-    }
-    if constexpr (MODE != kBwd) {
-#pragma unroll
-        for (int l = 0; l < kMaxLevels; ++l) {
-            const int32_t v = CMP ? (int32_t)((inl2[l >> 1] >> (16 * (l & 1))) & 0xFFFFu) : wave_sum(inl[l]);
-            const int32_t p = CMP ? (int32_t)((prb2[l >> 1] >> (16 * (l & 1))) & 0xFFFFu) : wave_sum(prb[l]);
-            if (lane == 0) {
-                s_red[wave][kRowInl + l] = (double)v;
-                s_red[wave][kRowProbe + l] = (double)p;
-            }
+        if constexpr (MODE != kCount) acc.zero();
+        any_hit = false;
+        ++sub;
         }
+        __syncthreads();   // the next batch's prologue overwrites the chunk data; the tiles' sums are read
     }
-    __syncthreads();
-    if (threadIdx.x < kRow) {
-        const int k = threadIdx.x;
+    // ---------------------------------------------------------------- rows: the waves' sums in wave order
+    for (int j = threadIdx.x; j < sub * kRow; j += BLOCK) {
+        const int r = j / kRow, k = j % kRow;
         double s = 0.0;
-        const bool inl_or_probe = (k >= kRowInl && k < kRowWalk) || (k >= kRowProbe && k < kRowChunks);
-        if (k == kRowWalk) {
-            s = (double)walked_pts;
-        } else if (k == kRowChunks) {
-            s = (double)walked_chunks;
-        } else if (k >= kRowChunks + 1) {
-            s = 0.0;
-        } else if (PREC == kN32 && k < kTerms) {
+        if (k == kRowWalk || k == kRowChunks) {
+            s = s_red[r][0][k];
+        } else if (PREC == kN32 && MODE != kCount && k < NT) {
             float sf = 0.f;
-            for (int w = 0; w < NW; ++w) sf += (float)s_red[w][k];
+            for (int w = 0; w < NW; ++w) sf += (float)s_red[r][w][k];
             s = (double)sf;
-        } else {
-            for (int w = 0; w < NW; ++w) s += s_red[w][k];
+        } else if ((MODE != kCount && k < NT) || (MODE != kBwd && k >= kRowInl && k < kRowChunks)) {
+            for (int w = 0; w < NW; ++w) s += s_red[r][w][k];
         }
-        const bool used = (k < NT) || (MODE != kBwd && inl_or_probe) || k == kRowWalk || k == kRowChunks;
-        partials[(int64_t)t * kRow + k] = used ? s : 0.0;
+        partials[((int64_t)tile.row0 + r) * kRow + k] = s;
     }
 }
 
@@ -1526,12 +1578,13 @@ __global__ void k_fill_zero(uint32_t* p, int64_t n_words) {
 // ---------------------------------------------------------------- host launchers
 
 template <int MODE, int PREC, bool KH, bool VAL, int LM>
-static vg_status launch_tiles_v(vg_batch* b, const Workspace& ws, const double* d_poses, int32_t t0, int32_t t1,
+static vg_status launch_tiles_v(vg_batch* b, const Workspace& ws, const double* d_poses, int32_t u0, int32_t u1,
                                 const double* d_grad_e, void* d_grad_points, int points_dtype) {
     hipStream_t st = b->ctx->stream;
-    const int grid = kParts * ((t1 - t0 + kParts - 1) / kParts);
+    const int32_t nu = u1 - u0, tc = std::max(1, b->tile_points / kChunk);
+    const int grid = kParts * ((nu + kParts - 1) / kParts);
 #define VG_LAUNCH(BS)                                                                                          \
-    k_tiles<MODE, PREC, BS, KH, VAL, LM><<<grid, BS, 0, st>>>(b->d_fac, b->d_tiles, t0, t1, d_poses, ws.posef, \
+    k_tiles<MODE, PREC, BS, KH, VAL, LM><<<grid, BS, 0, st>>>(b->d_fac, b->d_units, u0, nu, tc, d_poses, ws.posef, \
                                                               ws.partials, d_grad_e, d_grad_points,           \
                                                               b->d_gslab, points_dtype,                       \
                                                               b->tile_order == 2 ? 1 : 0)
@@ -1547,19 +1600,19 @@ static vg_status launch_tiles_v(vg_batch* b, const Workspace& ws, const double* 
 }
 
 template <int MODE, int PREC, bool KH>
-static vg_status launch_tiles_t(vg_batch* b, const Workspace& ws, const double* d_poses, int32_t t0, int32_t t1,
+static vg_status launch_tiles_t(vg_batch* b, const Workspace& ws, const double* d_poses, int32_t u0, int32_t u1,
                                 const double* d_grad_e, void* d_grad_points, int points_dtype) {
     if (b->opt.surface_validation)
-        return launch_tiles_v<MODE, PREC, KH, true, kMaxLevels>(b, ws, d_poses, t0, t1, d_grad_e, d_grad_points,
+        return launch_tiles_v<MODE, PREC, KH, true, kMaxLevels>(b, ws, d_poses, u0, u1, d_grad_e, d_grad_points,
                                                                 points_dtype);
     // single-level compensated batches without validation (the submap factors)
     // get a kernel compiled for one level
     if constexpr (PREC == kC32 && !KH) {
         if (b->L == 1)
-            return launch_tiles_v<MODE, PREC, KH, false, 1>(b, ws, d_poses, t0, t1, d_grad_e, d_grad_points,
+            return launch_tiles_v<MODE, PREC, KH, false, 1>(b, ws, d_poses, u0, u1, d_grad_e, d_grad_points,
                                                             points_dtype);
     }
-    return launch_tiles_v<MODE, PREC, KH, false, kMaxLevels>(b, ws, d_poses, t0, t1, d_grad_e, d_grad_points,
+    return launch_tiles_v<MODE, PREC, KH, false, kMaxLevels>(b, ws, d_poses, u0, u1, d_grad_e, d_grad_points,
                                                              points_dtype);
 }
 
@@ -1572,10 +1625,11 @@ bool reads_staged_poses(const vg_batch* b, int mode) {
     return b->opt.precision != kF64 && !one_level_cmp;
 }
 
-vg_status launch_tiles(vg_batch* b, const Workspace& ws, int mode, const double* d_poses, int32_t t0, int32_t t1,
-                       const double* d_grad_e, void* d_grad_points, int points_dtype, int64_t f0, int64_t f1,
+vg_status launch_tiles(vg_batch* b, const Workspace& ws, int mode, const double* d_poses, const double* d_grad_e,
+                       void* d_grad_points, int points_dtype, int64_t f0, int64_t f1,
                        bool staged) {
-    if (t1 <= t0) return VG_OK;
+    const int32_t u0 = b->h_unit_first[f0], u1 = b->h_unit_first[f1];
+    if (u1 <= u0) return VG_OK;
     if (!staged && f1 > f0 && reads_staged_poses(b, mode)) {
         const int64_t nf = (f1 - f0) * 16;
         k_stage_poses<<<(int)((nf + 255) / 256), 256, 0, b->ctx->stream>>>(f1 - f0, d_poses + 12 * f0,
@@ -1586,12 +1640,12 @@ vg_status launch_tiles(vg_batch* b, const Workspace& ws, int mode, const double*
     const bool kh = b->opt.lane_kahan != 0;
 #define VG_DISPATCH(M)                                                                                  \
     if (p == kC32 && kh)                                                                                \
-        return launch_tiles_t<M, kC32, true>(b, ws, d_poses, t0, t1, d_grad_e, d_grad_points, points_dtype); \
+        return launch_tiles_t<M, kC32, true>(b, ws, d_poses, u0, u1, d_grad_e, d_grad_points, points_dtype); \
     if (p == kC32)                                                                                      \
-        return launch_tiles_t<M, kC32, false>(b, ws, d_poses, t0, t1, d_grad_e, d_grad_points, points_dtype); \
+        return launch_tiles_t<M, kC32, false>(b, ws, d_poses, u0, u1, d_grad_e, d_grad_points, points_dtype); \
     if (p == kN32)                                                                                      \
-        return launch_tiles_t<M, kN32, false>(b, ws, d_poses, t0, t1, d_grad_e, d_grad_points, points_dtype); \
-    return launch_tiles_t<M, kF64, false>(b, ws, d_poses, t0, t1, d_grad_e, d_grad_points, points_dtype);
+        return launch_tiles_t<M, kN32, false>(b, ws, d_poses, u0, u1, d_grad_e, d_grad_points, points_dtype); \
+    return launch_tiles_t<M, kF64, false>(b, ws, d_poses, u0, u1, d_grad_e, d_grad_points, points_dtype);
     if (mode == kLin) { VG_DISPATCH(kLin) }
     if (mode == kEval) { VG_DISPATCH(kEval) }
     if (mode == kCount) { VG_DISPATCH(kCount) }

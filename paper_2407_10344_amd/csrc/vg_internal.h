@@ -37,6 +37,7 @@ constexpr int kRow = 40;
 constexpr int kWork = 8;                // per-factor work counts: walked points, walked chunks, lookups (4), 0, 0
 constexpr int kMaxTileChunks = 128;     // chunks whose data a tile holds in LDS at once
 constexpr int kMaxTilePoints = 32768;   // points per tile (taken in batches of kMaxTileChunks chunks)
+constexpr int kGroup = 4;               // tiles per unit (workgroup) at most
 constexpr int kRec32 = 16;              // floats per compensated voxel record (64 B: 4 FP32 + 6 FP64)
 constexpr int kRecN = 12;               // floats per absolute-FP32 voxel record
 constexpr int kRec64 = 10;              // doubles per FP64 voxel record
@@ -140,7 +141,7 @@ struct Tile {
     int32_t factor;
     int32_t chunk0;          // first chunk of the factor's source
     int32_t nchunks;
-    int32_t pad;
+    int32_t row0;            // its partial row (a unit of tiles: that of its first tile)
 };
 
 // ---------------------------------------------------------------- host objects
@@ -236,6 +237,8 @@ struct vg_batch {
     std::vector<vg::FactorDesc> h_fac;
     std::vector<vg::Tile> h_tiles;
     std::vector<int32_t> h_tile_first;   // F + 1
+    std::vector<vg::Tile> h_units;       // units: runs of whole tiles of one factor
+    std::vector<int32_t> h_unit_first;   // F + 1
     std::vector<int64_t> grad_offsets;   // per unique source
     int64_t total_points = 0;
     int64_t grad_rows = 0;               // rows of the concatenated point gradient
@@ -243,7 +246,7 @@ struct vg_batch {
     int tile_order = 1;                  // 1 contiguous per XCD, 2 round-robin over XCDs
     // device buffers
     vg::FactorDesc* d_fac = nullptr;
-    vg::Tile* d_tiles = nullptr;
+    vg::Tile* d_units = nullptr;
     int32_t* d_tile_first = nullptr;
     double* d_partials = nullptr;
     double* d_poses = nullptr;
@@ -370,13 +373,11 @@ vg_status layout_source(vg_context* ctx, Scratch& sc, vg_source* s, const double
 vg_status set_points(vg_context* ctx, const PointSrc* d_src, int64_t n_src, int64_t max_chunks, const void* d_xyz,
                      int dtype);
 
-// launch the tile kernel over tiles [t0, t1) and the reduction over factors [f0, f1)
-// f0, f1: the factors those tiles belong to (their poses are staged to FP32 first where the kernel reads
-// them so, unless `staged` says that they are)
+// launch the tile kernel of a mode over the tiles of factors [f0, f1) (their poses are staged to FP32
+// first where the kernel reads them so, unless `staged` says that they are)
 // ws: the buffers of the launch (the batch's own, or a caller-provided scratch)
-vg_status launch_tiles(vg_batch* b, const Workspace& ws, int mode, const double* d_poses, int32_t t0, int32_t t1,
-                       const double* d_grad_e, void* d_grad_points, int points_dtype, int64_t f0, int64_t f1,
-                       bool staged = false);
+vg_status launch_tiles(vg_batch* b, const Workspace& ws, int mode, const double* d_poses, const double* d_grad_e,
+                       void* d_grad_points, int points_dtype, int64_t f0, int64_t f1, bool staged = false);
 // whether the batch's kernels of a mode read FP32 poses staged in ws.posef
 bool reads_staged_poses(const vg_batch* b, int mode);
 vg_status launch_reduce(vg_batch* b, const Workspace& ws, int mode, const double* d_poses, int32_t f0, int32_t f1,

@@ -296,3 +296,39 @@ def test_batch_set_points_equals_the_sources_one_by_one(vg, dtype):
         assert np.array_equal(k1[f][0], k2[0]) and np.array_equal(k1[f][1], k2[1])
     for h in [batch, vmap] + srcs:
         h.close()
+
+
+@pytest.mark.parametrize("precision,block,tile,F,group", [
+    ("fp32c", 512, 64, 400, 2), ("fp32c", 512, 64, 560, 3), ("fp64", 512, 64, 700, 4), ("fp32c", 256, 128, 2400, 4)])
+def test_units_of_several_tiles_equal_each_factor_alone(vg, precision, block, tile, F, group):
+    """A batch with many tiles takes several of a factor's tiles per workgroup: the
+    results of every factor (tile counts that leave every remainder) stay the bits
+    of a batch of that factor alone, in every mode."""
+    vgicp, ctx = vg
+    cfg = synth.config1(seed=29, n_target=6000, n_source=4000)
+    xyz, cov = cfg["sources"][0].xyz64(), cfg["sources"][0].cov64()
+    tgt = cfg["targets"][0]
+    vmap = vgicp.VoxelMap(ctx, tgt.xyz64(), tgt.cov64(), cfg["resolutions"])
+    sizes = [1, tile, tile + 1, 2 * tile + 2, 5 * tile - 1, min(4000, 63 * tile)]
+    srcs = [vgicp.Source(ctx, xyz[:n], cov[:n]) for n in sizes]
+    opts = dict(precision=precision, block=block, tile=tile)
+    pose = np.array(cfg["poses"][0])
+    batch = vgicp.FactorBatch(ctx, [srcs[f % 6] for f in range(F)], [vmap] * F, **opts)
+    info = batch.info()
+    n_tiles = sum(-(-sizes[f % 6] // tile) for f in range(F))
+    n_units = sum(-(-(-(-sizes[f % 6] // tile)) // group) for f in range(F))
+    assert info["n_tiles"] == n_tiles and info["grid_blocks"] == 8 * (-(-n_units // 8))
+    poses = np.tile(pose[None], (F, 1, 1))
+    got = [batch.linearize(poses), (batch.evaluate(poses),), (batch.overlap(poses),)]
+    for k in range(6):
+        one = vgicp.FactorBatch(ctx, [srcs[k]], [vmap], **opts)
+        want = [one.linearize([pose]), (one.evaluate([pose]),), (one.overlap([pose]),)]
+        for g, w in zip(got, want):
+            for a, b in zip(g, w):
+                a, b = np.asarray(a), np.asarray(b)
+                assert all(np.array_equal(a[f], b[0]) for f in range(k, F, 6)), (k, a.shape)
+        one.close()
+    batch.close()
+    vmap.close()
+    for s in srcs:
+        s.close()
