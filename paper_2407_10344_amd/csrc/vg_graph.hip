@@ -7,9 +7,10 @@
 // xi = xi_i - Ad(T^-1) xi_j to first order, so with A = Ad(T^-1):
 //   H_ii = H, H_ij = -H A, H_ji = H_ij^T, H_jj = A^T H A, b_i = b, b_j = -A^T b.
 //
-// Assembly is deterministic: every block of the BSR matrix and every node of
-// the right-hand side has a fixed list of contributions (built on the host,
-// in factor order), summed in that order in FP64.
+// Assembly is deterministic: every block of the BSR matrix has a fixed list of
+// contributions (built on the host, in factor order), summed in that order in
+// FP64.  A node's diagonal block has one contribution per factor of the node, so
+// the node's entries of the right-hand side are summed along with it.
 #include <algorithm>
 #include <map>
 
@@ -23,92 +24,107 @@ struct vg_graph {
     // contributions: per block slot, a list of (factor, kind); kind 0 ii, 1 ij, 2 ji, 3 jj
     int32_t* d_blk_ptr = nullptr;   // nnzb + 1
     int32_t* d_blk_item = nullptr;  // packed (factor << 2 | kind)
-    int32_t* d_rhs_ptr = nullptr;   // N + 1
-    int32_t* d_rhs_item = nullptr;  // packed (factor << 1 | side), side 0 = i, 1 = j
-    double* d_adj = nullptr;        // F x 36: Ad(T^-1) per factor
+    int32_t* d_blk_node = nullptr;  // nnzb: the node of a diagonal block, else -1
     uint32_t magic = 0;
 };
 
 namespace vg {
 
-// Ad(T^-1) for T = (R, t): T^-1 = (R^T, -R^T t) and Ad(R', t') = [[R', 0], [(t')x R', R']].
-__global__ void k_graph_adjoint(int64_t F, const double* __restrict__ poses, double* __restrict__ adj) {
-    const int64_t f = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (f >= F) return;
-    const double* P = poses + 12 * f;
-    double Rt[9], tp[3];
-    for (int i = 0; i < 3; ++i)
-        for (int j = 0; j < 3; ++j) Rt[3 * i + j] = P[3 * j + i];
-    for (int i = 0; i < 3; ++i) tp[i] = -(Rt[3 * i] * P[9] + Rt[3 * i + 1] * P[10] + Rt[3 * i + 2] * P[11]);
-    const double tx[9] = {0, -tp[2], tp[1], tp[2], 0, -tp[0], -tp[1], tp[0], 0};
-    double* A = adj + 36 * f;
-    for (int i = 0; i < 6; ++i)
-        for (int j = 0; j < 6; ++j) A[6 * i + j] = 0.0;
-    for (int i = 0; i < 3; ++i)
-        for (int j = 0; j < 3; ++j) {
-            A[6 * i + j] = Rt[3 * i + j];
-            A[6 * (3 + i) + 3 + j] = Rt[3 * i + j];
-            double s = 0.0;
-            for (int q = 0; q < 3; ++q) s += tx[3 * i + q] * Rt[3 * q + j];
-            A[6 * (3 + i) + j] = s;
-        }
+constexpr int kAsmWaves = 4;
+
+// Entry (i, j) of A = Ad(T^-1) for T = (R, t): T^-1 = (R', t') = (R^T, -R^T t) and
+// Ad = [[R', 0], [(t')x R', R']].  P (uniform): R row-major, t.
+__device__ __forceinline__ double adjoint_entry(const double* __restrict__ P, int i, int j) {
+    const int i3 = i % 3, j3 = j % 3;
+    // column j3 of R' is row j3 of R
+    const double c0 = j3 == 0 ? P[0] : (j3 == 1 ? P[3] : P[6]);
+    const double c1 = j3 == 0 ? P[1] : (j3 == 1 ? P[4] : P[7]);
+    const double c2 = j3 == 0 ? P[2] : (j3 == 1 ? P[5] : P[8]);
+    double tp[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) tp[a] = -(P[a] * P[9] + P[3 + a] * P[10] + P[6 + a] * P[11]);
+    const double x0 = i3 == 0 ? 0.0 : (i3 == 1 ? tp[2] : -tp[1]);
+    const double x1 = i3 == 0 ? -tp[2] : (i3 == 1 ? 0.0 : tp[0]);
+    const double x2 = i3 == 0 ? tp[1] : (i3 == 1 ? -tp[0] : 0.0);
+    const double low = (x0 * c0 + x1 * c1) + x2 * c2;
+    const double rot = i3 == 0 ? c0 : (i3 == 1 ? c1 : c2);
+    return (i < 3) == (j < 3) ? rot : (i < 3 ? 0.0 : low);
 }
 
-// One 64-thread block per BSR block; thread k < 36 owns entry (r, c) = (k / 6, k % 6).
-__global__ void k_graph_blocks(const int32_t* __restrict__ blk_ptr, const int32_t* __restrict__ blk_item,
-                               const double* __restrict__ lin, const double* __restrict__ adj,
-                               double* __restrict__ values) {
+// One workgroup per BSR block: its contributions are dealt to the waves in rounds of
+// kAsmWaves, lane k < 36 of a wave making entry (k / 6, k % 6) of one contribution
+// and, for a diagonal block, lanes 36..41 the node's right-hand side; the workgroup
+// adds a round's contributions in list order.  Bound by the chain of dependent
+// loads (list, factor row, pose) of the longest list, so the list is read once by
+// the lanes and the rounds are few: a node of 20 factors takes five.  Making A in
+// place (a few selects and nine multiply-adds per lane) leaves no launch and no
+// buffer for it.  500 nodes, 5,000 factors: 55 us a call
+// with separate kernels for A, blocks and right-hand side, 45 us so, most of it the
+// host ordering the two streams.
+__global__ __launch_bounds__(64 * kAsmWaves) void k_graph_assemble(
+    const int32_t* __restrict__ blk_ptr, const int32_t* __restrict__ blk_item, const int32_t* __restrict__ blk_node,
+    const double* __restrict__ poses, const double* __restrict__ lin, double* __restrict__ values,
+    double* __restrict__ rhs) {
+    __shared__ double sH[kAsmWaves][36], sA[kAsmWaves][36], sHA[kAsmWaves][36], sB[kAsmWaves][6], sV[2][kAsmWaves][42];
     const int64_t s = blockIdx.x;
-    const int k = threadIdx.x;
-    if (k >= 36) return;
-    const int r = k / 6, c = k % 6;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int r = lane / 6, c = lane % 6;   // of lanes 0..35; r == 6: the right-hand side
+    const int32_t i0 = blk_ptr[s], i1 = blk_ptr[s + 1];
+    const int32_t node = blk_node[s];
     double acc = 0.0;
-    for (int32_t it = blk_ptr[s]; it < blk_ptr[s + 1]; ++it) {
-        const int32_t item = blk_item[it];
-        const int64_t f = item >> 2;
-        const int kind = item & 3;
-        const double* H = lin + (int64_t)kOutRow * f + 1;
-        const double* A = adj + 36 * f;
-        double v = 0.0;
-        if (kind == 0) {
-            v = H[6 * r + c];
-        } else if (kind == 1) {   // -(H A)_{rc}
-            for (int q = 0; q < 6; ++q) v -= H[6 * r + q] * A[6 * q + c];
-        } else if (kind == 2) {   // (H_ij)^T_{rc} = -(H A)_{cr}
-            for (int q = 0; q < 6; ++q) v -= H[6 * c + q] * A[6 * q + r];
-        } else {                  // (A^T H A)_{rc}
-            for (int p = 0; p < 6; ++p) {
-                double hq = 0.0;
-                for (int q = 0; q < 6; ++q) hq += H[6 * p + q] * A[6 * q + c];
-                v += A[6 * p + r] * hq;
+    int buf = 0;
+    for (int32_t base = i0; base < i1; base += 64) {
+        const int32_t mine = base + lane < i1 ? blk_item[base + lane] : 0;
+        const int cnt = min(64, i1 - base);
+        for (int k0 = 0; k0 < cnt; k0 += kAsmWaves, buf ^= 1) {
+            const int k = k0 + wave;
+            if (k < cnt) {   // uniform per wave
+                const int32_t item = __builtin_amdgcn_readlane(mine, k);
+                const int64_t f = item >> 2;
+                const int kind = item & 3;
+                const double* row = lin + (int64_t)kOutRow * f + 1;   // H (36), b (6)
+                const double h = lane < 42 ? row[lane] : 0.0;
+                double v = h;   // kind 0: H and b
+                if (kind != 0) {
+                    if (lane < 36) {
+                        sA[wave][lane] = adjoint_entry(poses + 12 * f, r, c);
+                        sH[wave][lane] = h;
+                    } else if (lane < 42) {
+                        sB[wave][c] = h;
+                    }
+                    __builtin_amdgcn_wave_barrier();
+                    if (lane < 36) {   // H A
+                        double x = 0.0;
+#pragma unroll
+                        for (int q = 0; q < 6; ++q) x += sH[wave][6 * r + q] * sA[wave][6 * q + c];
+                        sHA[wave][lane] = x;
+                    }
+                    __builtin_amdgcn_wave_barrier();
+                    if (lane < 36) {
+                        if (kind == 3) {          // A^T (H A)
+                            v = 0.0;
+#pragma unroll
+                            for (int p = 0; p < 6; ++p) v += sA[wave][6 * p + r] * sHA[wave][6 * p + c];
+                        } else {                  // -H A or its transpose
+                            v = -sHA[wave][kind == 1 ? lane : 6 * c + r];
+                        }
+                    } else if (lane < 42) {       // -A^T b (used for kind 3)
+                        double x = 0.0;
+#pragma unroll
+                        for (int q = 0; q < 6; ++q) x += sA[wave][6 * q + c] * sB[wave][q];
+                        v = -x;
+                    }
+                }
+                if (lane < 42) sV[buf][wave][lane] = v;
+            }
+            __syncthreads();   // (the sums of the round before last are done with this half of sV)
+            if (threadIdx.x < 42) {
+                for (int w = 0; w < min(kAsmWaves, cnt - k0); ++w) acc += sV[buf][w][threadIdx.x];
             }
         }
-        acc += v;
     }
-    values[36 * s + k] = acc;
-}
-
-// One 64-thread block per node; thread r < 6 owns rhs entry r; thread 6 sums e.
-__global__ void k_graph_rhs(const int32_t* __restrict__ rhs_ptr, const int32_t* __restrict__ rhs_item,
-                            const double* __restrict__ lin, const double* __restrict__ adj, double* __restrict__ rhs) {
-    const int64_t node = blockIdx.x;
-    const int r = threadIdx.x;
-    if (r >= 6) return;
-    double acc = 0.0;
-    for (int32_t it = rhs_ptr[node]; it < rhs_ptr[node + 1]; ++it) {
-        const int32_t item = rhs_item[it];
-        const int64_t f = item >> 1;
-        const double* b = lin + (int64_t)kOutRow * f + 37;
-        if ((item & 1) == 0) {
-            acc += b[r];
-        } else {                   // -(A^T b)_r
-            const double* A = adj + 36 * f;
-            double v = 0.0;
-            for (int q = 0; q < 6; ++q) v += A[6 * q + r] * b[q];
-            acc -= v;
-        }
-    }
-    rhs[6 * node + r] = acc;
+    if (threadIdx.x < 36) values[36 * s + threadIdx.x] = acc;
+    else if (threadIdx.x < 42 && node >= 0) rhs[6 * (int64_t)node + threadIdx.x - 36] = acc;
 }
 
 }  // namespace vg
@@ -125,9 +141,7 @@ vg_status g_invalid(const char* m) {
 void graph_free(vg_graph* g) {
     if (g->d_blk_ptr) (void)hipFree(g->d_blk_ptr);
     if (g->d_blk_item) (void)hipFree(g->d_blk_item);
-    if (g->d_rhs_ptr) (void)hipFree(g->d_rhs_ptr);
-    if (g->d_rhs_item) (void)hipFree(g->d_rhs_item);
-    if (g->d_adj) (void)hipFree(g->d_adj);
+    if (g->d_blk_node) (void)hipFree(g->d_blk_node);
 }
 template <typename T>
 hipError_t up(T** d, const std::vector<T>& h) {
@@ -153,15 +167,12 @@ extern "C" vg_status vg_create_graph(vg_context* ctx, int64_t N, int64_t F, cons
             return g_invalid("factor nodes must be distinct and in [0, N)");
     // blocks: (r, c) -> ordered contribution list
     std::map<std::pair<int64_t, int64_t>, std::vector<int32_t>> blocks;
-    std::vector<std::vector<int32_t>> rhs((size_t)N);
     for (int64_t f = 0; f < F; ++f) {
         const int64_t i = node_i[f], j = node_j[f];
         blocks[{i, i}].push_back((int32_t)(f << 2 | 0));
         blocks[{i, j}].push_back((int32_t)(f << 2 | 1));
         blocks[{j, i}].push_back((int32_t)(f << 2 | 2));
         blocks[{j, j}].push_back((int32_t)(f << 2 | 3));
-        rhs[i].push_back((int32_t)(f << 1 | 0));
-        rhs[j].push_back((int32_t)(f << 1 | 1));
     }
     for (int64_t n = 0; n < N; ++n) blocks[{n, n}];   // every node has a diagonal block
     auto* g = new vg_graph();
@@ -169,27 +180,21 @@ extern "C" vg_status vg_create_graph(vg_context* ctx, int64_t N, int64_t F, cons
     g->N = N;
     g->F = F;
     g->row_ptr.assign(N + 1, 0);
-    std::vector<int32_t> bptr, bitem, rptr, ritem;
+    std::vector<int32_t> bptr, bitem, bnode;
     bptr.push_back(0);
     for (auto& kv : blocks) {
         g->row_ptr[kv.first.first + 1] += 1;
         g->col_idx.push_back(kv.first.second);
         for (int32_t it : kv.second) bitem.push_back(it);
         bptr.push_back((int32_t)bitem.size());
+        bnode.push_back(kv.first.first == kv.first.second ? (int32_t)kv.first.first : -1);
     }
     for (int64_t n = 0; n < N; ++n) g->row_ptr[n + 1] += g->row_ptr[n];
     g->nnzb = (int64_t)g->col_idx.size();
-    rptr.push_back(0);
-    for (int64_t n = 0; n < N; ++n) {
-        for (int32_t it : rhs[n]) ritem.push_back(it);
-        rptr.push_back((int32_t)ritem.size());
-    }
     hipError_t e = hipSetDevice(ctx->device);
     if (e == hipSuccess) e = up(&g->d_blk_ptr, bptr);
     if (e == hipSuccess) e = up(&g->d_blk_item, bitem);
-    if (e == hipSuccess) e = up(&g->d_rhs_ptr, rptr);
-    if (e == hipSuccess) e = up(&g->d_rhs_item, ritem);
-    if (e == hipSuccess) e = hipMalloc(&g->d_adj, sizeof(double) * 36 * std::max<int64_t>(F, 1));
+    if (e == hipSuccess) e = up(&g->d_blk_node, bnode);
     if (e != hipSuccess) {
         graph_free(g);
         delete g;
@@ -224,13 +229,8 @@ extern "C" vg_status vg_graph_assemble_async(vg_graph* g, const double* d_poses,
         return g_invalid("NULL device pointer");
     VG_HIP(hipSetDevice(g->ctx->device));
     hipStream_t st = g->ctx->stream;
-    if (g->F > 0) {
-        k_graph_adjoint<<<(int)((g->F + 63) / 64), 64, 0, st>>>(g->F, d_poses, g->d_adj);
-        VG_HIP(hipGetLastError());
-    }
-    k_graph_blocks<<<(int)g->nnzb, 64, 0, st>>>(g->d_blk_ptr, g->d_blk_item, d_lin, g->d_adj, d_values);
-    VG_HIP(hipGetLastError());
-    k_graph_rhs<<<(int)g->N, 64, 0, st>>>(g->d_rhs_ptr, g->d_rhs_item, d_lin, g->d_adj, d_rhs);
+    k_graph_assemble<<<(int)g->nnzb, 64 * kAsmWaves, 0, st>>>(g->d_blk_ptr, g->d_blk_item, g->d_blk_node, d_poses, d_lin,
+                                                              d_values, d_rhs);
     VG_HIP(hipGetLastError());
     return VG_OK;
 }
