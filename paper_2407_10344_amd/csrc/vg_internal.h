@@ -244,7 +244,9 @@ struct vg_batch {
     int64_t grad_rows = 0;               // rows of the concatenated point gradient
     int block = 256, tile_points = 2048, blocks_per_cu = 0;
     int tile_order = 1;                  // 1 contiguous per XCD, 2 round-robin over XCDs
-    // device buffers
+    // device buffers, carved from one block
+    char* dblock = nullptr;
+    char* sched = nullptr;          // tables and rows of a launch shape set after creation
     vg::FactorDesc* d_fac = nullptr;
     vg::Tile* d_units = nullptr;
     int32_t* d_tile_first = nullptr;
@@ -268,7 +270,8 @@ struct vg_batch {
     void* d_gslab = nullptr;             // per-factor point gradients (grown on first use)
     size_t gslab_bytes = 0;
     double max_source_extent = 0.0;      // largest |mu - o_s| over the batch's sources (m)
-    // pinned host staging (one upload, one download)
+    // pinned host staging (one upload, one download), carved from one block
+    char* hblock = nullptr;
     double* h_poses = nullptr;
     double* h_out = nullptr;
     int64_t* h_inliers = nullptr;
