@@ -59,8 +59,8 @@ struct Acc {
             if constexpr (KAHAN) c[k] = T(0);
             // opaque: sums known to be zero after a tile are otherwise kept apart
             // from running ones and copied on every path between them (224 moves
-            // and 38 VGPRs in the FP64 kernel: 178 us against 128 us over 190
-            // submap factors)
+            // and 38 VGPRs in the FP64 kernel: 178 us against 128 us over the
+            // factors of 20 submaps)
             asm("" : "+v"(s[k]));
             if constexpr (KAHAN) asm("" : "+v"(c[k]));
         }
@@ -546,11 +546,11 @@ __device__ __forceinline__ void drain_hit(A& acc, const FactorDesc* __restrict__
 // Register budget, in waves per SIMD.  The FP32 linearize and backward kernels are
 // held at exactly four (<= 128 VGPRs): the scheduler then keeps loads in flight
 // instead of saving registers for a fifth (five spill: 580 us against 395 us for
-// the 500-submap linearize).  Evaluate and the counts have few live sums and wait
-// on probe loads, so they run more waves (500 submaps: evaluate 331 us at six
+// 575 submap factors).  Evaluate and the counts have few live sums and wait
+// on probe loads, so they run more waves (the same batch: evaluate 331 us at six
 // against 364 us at four; overlap 153 us at eight, 166 us at six, 231 us at four).
 // FP64 and Kahan kernels take what their register count allows (FP64: three; four
-// spill and take 150 us against 128 us over 190 factors).
+// spill and take 150 us against 128 us over the factors of 20 submaps).
 template <int MODE, int PREC, bool KH>
 constexpr int waves_per_eu() {
     return MODE == kCount ? 8 : (PREC == kF64 || KH) ? 1 : MODE == kEval ? 6 : 4;
@@ -695,9 +695,10 @@ __global__ void k_copy_words(const uint64_t* __restrict__ in, uint64_t* __restri
 // culled in a submap batch, so what a tile costs besides its points (descriptors,
 // anchors, barriers: 43 % of a wave's time there) was as much as the points.  Each
 // wave picks its chunks from the ballots of the whole unit, without a list that one
-// wave writes and a barrier around it.  500 submaps: linearize 439 -> 364 us,
-// overlap 278 -> 232 us (both with one tile per unit: 447 and 297 us).  The rows stay one per tile and a wave's share of a tile is the same in any unit, so
-// results do not depend on it.
+// wave writes and a barrier around it.  575 submap factors: linearize 439 -> 364
+// us, overlap 278 -> 232 us (with one tile per unit 447 and 297 us).  The rows stay
+// one per tile and a wave's share of a tile is the same in any unit, so results do
+// not depend on it.
 template <int MODE, int PREC, int BLOCK, bool KH, bool VAL, int LM>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(waves_per_eu<MODE, PREC, KH>(), waves_per_eu_max<MODE, PREC, KH>()))) void k_tiles(
     const FactorDesc* __restrict__ fac, const Tile* __restrict__ units, int32_t u_begin, int32_t n_units, int32_t tc,
@@ -1581,21 +1582,25 @@ template <int MODE, int PREC, bool KH, bool VAL, int LM>
 static vg_status launch_tiles_v(vg_batch* b, const Workspace& ws, const double* d_poses, int32_t u0, int32_t u1,
                                 const double* d_grad_e, void* d_grad_points, int points_dtype) {
     hipStream_t st = b->ctx->stream;
-    const int32_t nu = u1 - u0, tc = std::max(1, b->tile_points / kChunk);
-    const int grid = kParts * ((nu + kParts - 1) / kParts);
+    const int32_t tc = std::max(1, b->tile_points / kChunk);
+    constexpr int32_t kMaxUnits = 1 << 22;   // a launch holds fewer than 2^32 threads
+    for (; u0 < u1; u0 += kMaxUnits) {
+        const int32_t nu = std::min(kMaxUnits, u1 - u0);
+        const int grid = kParts * ((nu + kParts - 1) / kParts);
 #define VG_LAUNCH(BS)                                                                                          \
-    k_tiles<MODE, PREC, BS, KH, VAL, LM><<<grid, BS, 0, st>>>(b->d_fac, b->d_units, u0, nu, tc, d_poses, ws.posef, \
-                                                              ws.partials, d_grad_e, d_grad_points,           \
-                                                              b->d_gslab, points_dtype,                       \
-                                                              b->tile_order == 2 ? 1 : 0)
-    switch (b->block) {
-        case 64: VG_LAUNCH(64); break;
-        case 128: VG_LAUNCH(128); break;
-        case 512: VG_LAUNCH(512); break;
-        default: VG_LAUNCH(256); break;
-    }
+        k_tiles<MODE, PREC, BS, KH, VAL, LM><<<grid, BS, 0, st>>>(b->d_fac, b->d_units, u0, nu, tc, d_poses, ws.posef, \
+                                                                  ws.partials, d_grad_e, d_grad_points,           \
+                                                                  b->d_gslab, points_dtype,                       \
+                                                                  b->tile_order == 2 ? 1 : 0)
+        switch (b->block) {
+            case 64: VG_LAUNCH(64); break;
+            case 128: VG_LAUNCH(128); break;
+            case 512: VG_LAUNCH(512); break;
+            default: VG_LAUNCH(256); break;
+        }
 #undef VG_LAUNCH
-    VG_HIP(hipGetLastError());
+        VG_HIP(hipGetLastError());
+    }
     return VG_OK;
 }
 

@@ -64,67 +64,69 @@ __device__ __forceinline__ double adjoint_entry(const double* __restrict__ P, in
 __global__ __launch_bounds__(64 * kAsmWaves) void k_graph_assemble(
     const int32_t* __restrict__ blk_ptr, const int32_t* __restrict__ blk_item, const int32_t* __restrict__ blk_node,
     const double* __restrict__ poses, const double* __restrict__ lin, double* __restrict__ values,
-    double* __restrict__ rhs) {
+    double* __restrict__ rhs, int64_t n_blocks) {
     __shared__ double sH[kAsmWaves][36], sA[kAsmWaves][36], sHA[kAsmWaves][36], sB[kAsmWaves][6], sV[2][kAsmWaves][42];
-    const int64_t s = blockIdx.x;
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int r = lane / 6, c = lane % 6;   // of lanes 0..35; r == 6: the right-hand side
-    const int32_t i0 = blk_ptr[s], i1 = blk_ptr[s + 1];
-    const int32_t node = blk_node[s];
-    double acc = 0.0;
-    int buf = 0;
-    for (int32_t base = i0; base < i1; base += 64) {
-        const int32_t mine = base + lane < i1 ? blk_item[base + lane] : 0;
-        const int cnt = min(64, i1 - base);
-        for (int k0 = 0; k0 < cnt; k0 += kAsmWaves, buf ^= 1) {
-            const int k = k0 + wave;
-            if (k < cnt) {   // uniform per wave
-                const int32_t item = __builtin_amdgcn_readlane(mine, k);
-                const int64_t f = item >> 2;
-                const int kind = item & 3;
-                const double* row = lin + (int64_t)kOutRow * f + 1;   // H (36), b (6)
-                const double h = lane < 42 ? row[lane] : 0.0;
-                double v = h;   // kind 0: H and b
-                if (kind != 0) {
-                    if (lane < 36) {
-                        sA[wave][lane] = adjoint_entry(poses + 12 * f, r, c);
-                        sH[wave][lane] = h;
-                    } else if (lane < 42) {
-                        sB[wave][c] = h;
-                    }
-                    __builtin_amdgcn_wave_barrier();
-                    if (lane < 36) {   // H A
-                        double x = 0.0;
-#pragma unroll
-                        for (int q = 0; q < 6; ++q) x += sH[wave][6 * r + q] * sA[wave][6 * q + c];
-                        sHA[wave][lane] = x;
-                    }
-                    __builtin_amdgcn_wave_barrier();
-                    if (lane < 36) {
-                        if (kind == 3) {          // A^T (H A)
-                            v = 0.0;
-#pragma unroll
-                            for (int p = 0; p < 6; ++p) v += sA[wave][6 * p + r] * sHA[wave][6 * p + c];
-                        } else {                  // -H A or its transpose
-                            v = -sHA[wave][kind == 1 ? lane : 6 * c + r];
+    for (int64_t s = blockIdx.x; s < n_blocks; s += gridDim.x) {
+        const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        const int r = lane / 6, c = lane % 6;   // of lanes 0..35; r == 6: the right-hand side
+        const int32_t i0 = blk_ptr[s], i1 = blk_ptr[s + 1];
+        const int32_t node = blk_node[s];
+        double acc = 0.0;
+        int buf = 0;
+        for (int32_t base = i0; base < i1; base += 64) {
+            const int32_t mine = base + lane < i1 ? blk_item[base + lane] : 0;
+            const int cnt = min(64, i1 - base);
+            for (int k0 = 0; k0 < cnt; k0 += kAsmWaves, buf ^= 1) {
+                const int k = k0 + wave;
+                if (k < cnt) {   // uniform per wave
+                    const int32_t item = __builtin_amdgcn_readlane(mine, k);
+                    const int64_t f = item >> 2;
+                    const int kind = item & 3;
+                    const double* row = lin + (int64_t)kOutRow * f + 1;   // H (36), b (6)
+                    const double h = lane < 42 ? row[lane] : 0.0;
+                    double v = h;   // kind 0: H and b
+                    if (kind != 0) {
+                        if (lane < 36) {
+                            sA[wave][lane] = adjoint_entry(poses + 12 * f, r, c);
+                            sH[wave][lane] = h;
+                        } else if (lane < 42) {
+                            sB[wave][c] = h;
                         }
-                    } else if (lane < 42) {       // -A^T b (used for kind 3)
-                        double x = 0.0;
-#pragma unroll
-                        for (int q = 0; q < 6; ++q) x += sA[wave][6 * q + c] * sB[wave][q];
-                        v = -x;
+                        __builtin_amdgcn_wave_barrier();
+                        if (lane < 36) {   // H A
+                            double x = 0.0;
+    #pragma unroll
+                            for (int q = 0; q < 6; ++q) x += sH[wave][6 * r + q] * sA[wave][6 * q + c];
+                            sHA[wave][lane] = x;
+                        }
+                        __builtin_amdgcn_wave_barrier();
+                        if (lane < 36) {
+                            if (kind == 3) {          // A^T (H A)
+                                v = 0.0;
+    #pragma unroll
+                                for (int p = 0; p < 6; ++p) v += sA[wave][6 * p + r] * sHA[wave][6 * p + c];
+                            } else {                  // -H A or its transpose
+                                v = -sHA[wave][kind == 1 ? lane : 6 * c + r];
+                            }
+                        } else if (lane < 42) {       // -A^T b (used for kind 3)
+                            double x = 0.0;
+    #pragma unroll
+                            for (int q = 0; q < 6; ++q) x += sA[wave][6 * q + c] * sB[wave][q];
+                            v = -x;
+                        }
                     }
+                    if (lane < 42) sV[buf][wave][lane] = v;
                 }
-                if (lane < 42) sV[buf][wave][lane] = v;
-            }
-            __syncthreads();   // (the sums of the round before last are done with this half of sV)
-            if (threadIdx.x < 42) {
-                for (int w = 0; w < min(kAsmWaves, cnt - k0); ++w) acc += sV[buf][w][threadIdx.x];
+                __syncthreads();   // (the sums of the round before last are done with this half of sV)
+                if (threadIdx.x < 42) {
+                    for (int w = 0; w < min(kAsmWaves, cnt - k0); ++w) acc += sV[buf][w][threadIdx.x];
+                }
             }
         }
+        if (threadIdx.x < 36) values[36 * s + threadIdx.x] = acc;
+        else if (threadIdx.x < 42 && node >= 0) rhs[6 * (int64_t)node + threadIdx.x - 36] = acc;
+        __syncthreads();   // the next block's rounds start on the same half of sV
     }
-    if (threadIdx.x < 36) values[36 * s + threadIdx.x] = acc;
-    else if (threadIdx.x < 42 && node >= 0) rhs[6 * (int64_t)node + threadIdx.x - 36] = acc;
 }
 
 }  // namespace vg
@@ -229,8 +231,8 @@ extern "C" vg_status vg_graph_assemble_async(vg_graph* g, const double* d_poses,
         return g_invalid("NULL device pointer");
     VG_HIP(hipSetDevice(g->ctx->device));
     hipStream_t st = g->ctx->stream;
-    k_graph_assemble<<<(int)g->nnzb, 64 * kAsmWaves, 0, st>>>(g->d_blk_ptr, g->d_blk_item, g->d_blk_node, d_poses, d_lin,
-                                                              d_values, d_rhs);
+    k_graph_assemble<<<(int)std::min<int64_t>(g->nnzb, 1 << 22), 64 * kAsmWaves, 0, st>>>(g->d_blk_ptr, g->d_blk_item, g->d_blk_node, d_poses, d_lin,
+                                                              d_values, d_rhs, g->nnzb);
     VG_HIP(hipGetLastError());
     return VG_OK;
 }

@@ -1,6 +1,8 @@
 // FP64 pose kernels: SE(3) retraction with its right Jacobian, and the proposal of
 // a Levenberg-Marquardt step (one thread per factor; 6x6 systems are tiny, so the
 // point is to stay on the device).
+#include <algorithm>
+
 #include "vg_se3.h"
 
 namespace vg {
@@ -14,41 +16,42 @@ __global__ __launch_bounds__(64) void k_se3_retract(int64_t F, const double* __r
                                                     const double* __restrict__ xi, double* __restrict__ T,
                                                     double* __restrict__ jr) {
     __shared__ double s_term[36];
-    const int64_t f = blockIdx.x;
     const int lane = threadIdx.x;
-    double x[6], E[12], A[12], C[12];
-    for (int k = 0; k < 6; ++k) x[k] = xi[6 * f + k];
-    for (int k = 0; k < 12; ++k) A[k] = T0[12 * f + k];
-    se3_exp(x, E);
-    pose_mul(A, E, C);
-    for (int k = 0; k < 12; ++k)
-        if (lane == k) T[12 * f + k] = C[k];
-    if (jr == nullptr) return;
-    const int i = min(lane, 35) / 6, j = min(lane, 35) % 6;
-    // column j of -ad: rows of -(omega)x, -(v)x
-    double W[9], V[9], ad[6];
-    hat3(x, W);
-    hat3(x + 3, V);
+    for (int64_t f = blockIdx.x; f < F; f += gridDim.x) {
+        double x[6], E[12], A[12], C[12];
+        for (int k = 0; k < 6; ++k) x[k] = xi[6 * f + k];
+        for (int k = 0; k < 12; ++k) A[k] = T0[12 * f + k];
+        se3_exp(x, E);
+        pose_mul(A, E, C);
+        for (int k = 0; k < 12; ++k)
+            if (lane == k) T[12 * f + k] = C[k];
+        if (jr == nullptr) continue;
+        const int i = min(lane, 35) / 6, j = min(lane, 35) % 6;
+        // column j of -ad: rows of -(omega)x, -(v)x
+        double W[9], V[9], ad[6];
+        hat3(x, W);
+        hat3(x + 3, V);
 #pragma unroll
-    for (int q = 0; q < 6; ++q) {
-        const int a = q % 3;
-        const double w = j % 3 == 0 ? W[3 * a] : (j % 3 == 1 ? W[3 * a + 1] : W[3 * a + 2]);
-        const double v = j % 3 == 0 ? V[3 * a] : (j % 3 == 1 ? V[3 * a + 1] : V[3 * a + 2]);
-        ad[q] = (q < 3) == (j < 3) ? -w : (q < 3 ? 0.0 : -v);
-    }
-    double term = i == j ? 1.0 : 0.0, J = term;
-    for (int n = 1; n < 60; ++n) {
-        __syncthreads();
-        if (lane < 36) s_term[lane] = term;
-        __syncthreads();
-        double s = 0.0;
+        for (int q = 0; q < 6; ++q) {
+            const int a = q % 3;
+            const double w = j % 3 == 0 ? W[3 * a] : (j % 3 == 1 ? W[3 * a + 1] : W[3 * a + 2]);
+            const double v = j % 3 == 0 ? V[3 * a] : (j % 3 == 1 ? V[3 * a + 1] : V[3 * a + 2]);
+            ad[q] = (q < 3) == (j < 3) ? -w : (q < 3 ? 0.0 : -v);
+        }
+        double term = i == j ? 1.0 : 0.0, J = term;
+        for (int n = 1; n < 60; ++n) {
+            __syncthreads();
+            if (lane < 36) s_term[lane] = term;
+            __syncthreads();
+            double s = 0.0;
 #pragma unroll
-        for (int q = 0; q < 6; ++q) s += s_term[6 * i + q] * ad[q];
-        term = s / (double)(n + 1);
-        J += term;
-        if (!__any(fabs(term) >= 1e-18)) break;   // uniform
+            for (int q = 0; q < 6; ++q) s += s_term[6 * i + q] * ad[q];
+            term = s / (double)(n + 1);
+            J += term;
+            if (!__any(fabs(term) >= 1e-18)) break;   // uniform
+        }
+        if (lane < 36) jr[36 * f + lane] = J;
     }
-    if (lane < 36) jr[36 * f + lane] = J;
 }
 
 // Solve (H + lambda diag(H)) delta = -b by Cholesky; returns false if not SPD.
@@ -114,7 +117,7 @@ __global__ void k_fill(double* __restrict__ p, int64_t n, double v) {
 vg_status launch_se3_retract(vg_context* ctx, int64_t F, const double* d_T0, const double* d_xi, double* d_T,
                              double* d_jr) {
     if (F == 0) return VG_OK;
-    k_se3_retract<<<(unsigned)F, 64, 0, ctx->stream>>>(F, d_T0, d_xi, d_T, d_jr);
+    k_se3_retract<<<(unsigned)std::min<int64_t>(F, 1 << 22), 64, 0, ctx->stream>>>(F, d_T0, d_xi, d_T, d_jr);
     VG_HIP(hipGetLastError());
     return VG_OK;
 }
