@@ -106,6 +106,15 @@ vg_status dev_alloc(T** p, size_t count) {
     return VG_OK;
 }
 
+vg_status pool_alloc(vg::BlockPool* pool, void** p, size_t bytes) {
+    const hipError_t e = pool->get(p, bytes);
+    if (e != hipSuccess) {
+        vg::set_error(std::string("hipMalloc failed: ") + hipGetErrorString(e));
+        return VG_ERR_OOM;
+    }
+    return VG_OK;
+}
+
 template <typename T>
 vg_status host_alloc(T** p, size_t count) {
     *p = nullptr;
@@ -133,6 +142,100 @@ void hfree(void* p) {
 }
 
 }  // namespace
+
+namespace vg {
+
+hipError_t BlockPool::get(void** p, size_t bytes) {
+    *p = nullptr;
+    if (bytes < kPooled) return hipMalloc(p, bytes);
+    size_t step = 1;
+    while (step * 16 <= bytes) step *= 2;   // bytes / 16 < step <= bytes / 8 at most
+    const size_t size = (bytes + step - 1) / step * step;
+    std::lock_guard<std::mutex> lock(mu);
+    size_t best = idle.size();
+    for (size_t k = 0; k < idle.size(); ++k)
+        if (idle[k].second >= bytes && idle[k].second <= size + size / 2 &&
+            (best == idle.size() || idle[k].second < idle[best].second))
+            best = k;
+    try {
+        live.reserve(live.size() + 1);
+        if (best < idle.size()) {
+            const auto blk = idle[best];
+            live.emplace(blk.first, blk.second);
+            idle.erase(idle.begin() + (std::ptrdiff_t)best);
+            kept -= blk.second;
+            *p = blk.first;
+            return hipSuccess;
+        }
+        size_t got = size;
+        hipError_t e = hipMalloc(p, size);
+        if (e != hipSuccess) {
+            (void)hipGetLastError();
+            release_locked(0);
+            got = bytes;
+            e = hipMalloc(p, bytes);
+        }
+        if (e != hipSuccess) {
+            (void)hipGetLastError();
+            *p = nullptr;
+            return e;
+        }
+        try {
+            live.emplace(*p, got);
+        } catch (...) {
+            (void)hipFree(*p);
+            *p = nullptr;
+            return hipErrorOutOfMemory;
+        }
+        return hipSuccess;
+    } catch (...) {
+        return hipErrorOutOfMemory;
+    }
+}
+
+void BlockPool::put(void* p) {
+    if (p == nullptr) return;
+    std::unique_lock<std::mutex> lock(mu);
+    const auto it = live.find(p);
+    const size_t size = it == live.end() ? 0 : it->second;
+    if (it != live.end()) live.erase(it);
+    if (size == 0 || size > kKeepBlocks || closed) {
+        lock.unlock();
+        (void)hipFree(p);
+        return;
+    }
+    lock.unlock();
+    const bool quiet = hipDeviceSynchronize() == hipSuccess;
+    lock.lock();
+    bool keep = quiet && !closed;
+    if (keep) {
+        try {
+            idle.emplace_back(p, size);
+            kept += size;
+        } catch (...) {
+            keep = false;
+        }
+    }
+    if (!keep) (void)hipFree(p);
+    release_locked(kKeepBlocks);
+}
+
+void BlockPool::release_locked(size_t limit) {
+    size_t k = 0;
+    for (; k < idle.size() && kept > limit; ++k) {
+        (void)hipFree(idle[k].first);
+        kept -= idle[k].second;
+    }
+    idle.erase(idle.begin(), idle.begin() + (std::ptrdiff_t)k);
+}
+
+void BlockPool::close() {
+    std::lock_guard<std::mutex> lock(mu);
+    closed = true;
+    release_locked(0);
+}
+
+}  // namespace vg
 
 namespace vg {
 
@@ -221,6 +324,7 @@ extern "C" vg_status vg_context_destroy(vg_context* ctx) {
     (void)hipSetDevice(ctx->device);
     (void)hipStreamSynchronize(ctx->stream);
     if (ctx->own_stream) (void)hipStreamDestroy(ctx->stream);
+    ctx->pool->close();
     if (ctx->ws) (void)hipFree(ctx->ws);
     if (ctx->h_small) (void)hipHostFree(ctx->h_small);
     ctx->magic = 0;
@@ -264,6 +368,7 @@ static vg_status make_voxelmap(vg_context* ctx, Scratch& sc, const double* d_xyz
                                vg_voxelmap** out) {
     auto* m = new vg_voxelmap();
     m->ctx = ctx;
+    m->pool = ctx->pool;
     m->L = L;
     const double rmax = resolutions[L - 1];
     for (int a = 0; a < 3; ++a) m->origin[a] = (n > 0) ? rmax * std::nearbyint(first[a] / rmax) : 0.0;
@@ -355,9 +460,8 @@ static vg_status alloc_source(vg_source* s) {
     const size_t nrm = s->has_normals ? up(12 * np) + up(24 * np) : 0;
     const size_t bytes = up(12 * np) + up(24 * np) + up(24 * nc) + up(32 * nc) + up(12 * np) + up(24 * np) +
                          up(48 * np) + up(4 * np) + nrm + up(sizeof(PointSrc));
-    unsigned char* p = nullptr;
-    VG_TRY(dev_alloc(&p, bytes));
-    s->block = p;
+    VG_TRY(pool_alloc(s->pool.get(), (void**)&s->block, bytes));
+    unsigned char* p = (unsigned char*)s->block;
     auto take = [&](size_t b) { unsigned char* r = p; p += up(b); return r; };
     s->dxyz = (float*)take(12 * np);
     s->cov = (float*)take(24 * np);
@@ -386,6 +490,7 @@ static vg_status make_source(vg_context* ctx, Scratch& sc, const double* d_xyz, 
                              const double box[6], vg_source** out) {
     auto* s = new vg_source();
     s->ctx = ctx;
+    s->pool = ctx->pool;
     s->n = n;
     s->n_pad = ((n + kChunk - 1) / kChunk) * kChunk;
     s->n_chunks = s->n_pad / kChunk;
@@ -395,7 +500,7 @@ static vg_status make_source(vg_context* ctx, Scratch& sc, const double* d_xyz, 
     if (st == VG_OK && n > 0) st = layout_source(ctx, sc, s, d_xyz, d_cov, d_nrm, box);
     if (st != VG_OK) {
         (void)hipStreamSynchronize(ctx->stream);
-        dfree(s->block);
+        s->pool->put(s->block);
         delete s;
         return st;
     }
@@ -437,7 +542,7 @@ extern "C" vg_status vg_source_destroy(vg_source* src) {
     if (src->users > 0) return state_err("source is used by a live batch");
     (void)hipSetDevice(src->ctx->device);
     (void)hipStreamSynchronize(src->ctx->stream);
-    dfree(src->block);
+    src->pool->put(src->block);
     src->magic = 0;
     delete src;
     return VG_OK;
@@ -467,6 +572,7 @@ extern "C" vg_status vg_preprocess(vg_context* ctx, const double* xyz, int64_t n
     VG_TRY(upload_cloud(ctx, sc, xyz, nullptr, nullptr, n, &d_xyz, nullptr, nullptr, box));
     auto* c = new vg_cloud();
     c->ctx = ctx;
+    c->pool = ctx->pool;
     const vg_status st = preprocess_frame(ctx, sc, d_xyz, n, box, r, k, sensor, c);
     if (st != VG_OK) {
         (void)hipStreamSynchronize(ctx->stream);
@@ -687,11 +793,11 @@ vg_status upload_schedule(vg_batch* b) {
 // A batch's device memory is one block and its pinned memory another: an allocation
 // and its release cost the host about 10 us each, and a batch that lives for one
 // call (an odometry frame's) had twelve and three of them and five small uploads
-// from pageable memory: 101 us to create and 30 us more to close than now, 48 us to
-// create with the two blocks (21 factors).  The
-// tables are written to the pinned block, which later holds poses and results, and
-// copied by one launch; a batch whose tables exceed kStagedTables is uploaded by a
-// copy from ordinary memory (pinning pages costs more than it saves there).
+// from pageable memory: 101 us to create and 97 us to close with its frame's other
+// objects, 48 us and 65 us with the two blocks (21 factors).  The tables are written
+// to the pinned block, which later holds poses and results, and copied by one
+// launch; a batch whose tables exceed kStagedTables is uploaded by a copy from
+// ordinary memory (pinning pages costs more than it saves there).
 constexpr size_t kStagedTables = (size_t)1 << 20;
 
 vg_status alloc_batch(vg_batch* b, const std::vector<PointSrc>& points) {
@@ -716,7 +822,7 @@ vg_status alloc_batch(vg_batch* b, const std::vector<PointSrc>& points) {
     };
     Carve c{nullptr};
     carve(c);
-    VG_TRY(dev_alloc(&b->dblock, c.off));
+    VG_TRY(pool_alloc(b->pool.get(), (void**)&b->dblock, c.off));
     c = Carve{b->dblock};
     carve(c);
     const bool staged = tables <= kStagedTables;
@@ -866,7 +972,7 @@ vg_status linearize_host(vg_batch* b) {
 }
 
 void free_batch(vg_batch* b) {
-    dfree(b->dblock);
+    b->pool->put(b->dblock);
     dfree(b->sched);
     dfree(b->d_gslab);
     hfree(b->hblock);
@@ -921,6 +1027,7 @@ extern "C" vg_status vg_create_factor_batch(vg_context* ctx, int64_t F, vg_sourc
     VG_HIP(hipSetDevice(ctx->device));
     auto* b = new vg_batch();
     b->ctx = ctx;
+    b->pool = ctx->pool;
     b->F = F;
     b->L = L;
     b->opt = o;

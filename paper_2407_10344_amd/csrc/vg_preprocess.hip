@@ -694,7 +694,7 @@ hipError_t sort_words(void* tmp, size_t& bytes, uint64_t* in, uint64_t* out, int
 hipError_t alloc_cloud(vg_cloud* c, int64_t m, int k) {
     const size_t nd = (size_t)m * (3 + 6 + 6 + 3 + k), ni = (size_t)m * (1 + k);
     void* b = nullptr;
-    hipError_t e = hipMalloc(&b, sizeof(double) * (nd ? nd : 1) + sizeof(int32_t) * (ni ? ni : 1));
+    hipError_t e = c->pool->get(&b, sizeof(double) * (nd ? nd : 1) + sizeof(int32_t) * (ni ? ni : 1));
     if (e != hipSuccess) return e;
     c->block = b;
     double* d = (double*)b;
@@ -712,7 +712,7 @@ hipError_t alloc_cloud(vg_cloud* c, int64_t m, int k) {
 }  // namespace
 
 void free_cloud(vg_cloud* c) {
-    if (c->block) (void)hipFree(c->block);
+    if (c->block) c->pool->put(c->block);
     c->block = nullptr;
     c->xyz = c->cov = c->cov_raw = c->nrm = c->d2 = nullptr;
     c->counts = c->nbr = nullptr;

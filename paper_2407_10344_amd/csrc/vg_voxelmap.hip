@@ -336,7 +336,7 @@ static vg_status build_levels(vg_context* ctx, Scratch& sc, const double* d_xyz,
     for (int l = 0; l < L; ++l)
         bytes += align256(4 * kRec32 * (size_t)lv[l].V) + align256(4 * kRecN * (size_t)lv[l].V) +
                  align256(8 * kRec64 * (size_t)lv[l].V) + align256(8 * (size_t)lv[l].V) + align256(4 * (size_t)lv[l].V);
-    VG_HIP(hipMalloc(block, bytes));
+    VG_HIP(ctx->pool->get(block, bytes));
     char* p = (char*)*block;
     for (int l = 0; l < L; ++l) {
         lv[l].slots = (uint64_t*)p;
@@ -377,7 +377,7 @@ vg_status build_map(vg_context* ctx, Scratch& sc, const double* d_xyz, const dou
     }
     if (n == 0) {
         constexpr size_t kTable = 16 * 64;
-        VG_HIP(hipMalloc(&m->blocks[0], kTable * L));
+        VG_HIP(ctx->pool->get(&m->blocks[0], kTable * L));
         k_fill_entries<<<1, 64 * L, 0, ctx->stream>>>((u64x2*)m->blocks[0], 64 * L, kEmpty);
         VG_HIP(hipGetLastError());
         for (int l = 0; l < L; ++l) {
@@ -442,7 +442,7 @@ vg_status export_level(vg_context* ctx, const Level& lv, int64_t* keys, double* 
 
 void free_map(vg_voxelmap* m) {
     for (int l = 0; l < kMaxLevels; ++l) {
-        if (m->blocks[l]) (void)hipFree(m->blocks[l]);
+        if (m->blocks[l]) m->pool->put(m->blocks[l]);
         m->blocks[l] = nullptr;
         m->lv[l] = Level{};
     }
@@ -706,7 +706,7 @@ vg_status set_points(vg_context* ctx, const PointSrc* d_src, int64_t n_src, int6
                      int dtype) {
     if (max_chunks <= 0) return VG_OK;
     const int64_t nb = (max_chunks + 3) / 4;   // workgroups per source
-    const int64_t step = std::max<int64_t>(1, (1ll << 24) / nb);
+    const int64_t step = std::max<int64_t>(1, (1ll << 22) / nb);
     for (int64_t s0 = 0; s0 < n_src; s0 += step) {
         const uint32_t items = (uint32_t)(nb * std::min(step, n_src - s0));
         const unsigned grid = (unsigned)(kParts * ((items + kParts - 1) / kParts));

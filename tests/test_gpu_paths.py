@@ -332,3 +332,81 @@ def test_units_of_several_tiles_equal_each_factor_alone(vg, precision, block, ti
     vmap.close()
     for s in srcs:
         s.close()
+
+
+def test_row_counts_at_the_edges_of_the_reduction(vg):
+    """Factors of 0, 1, 63, 64, 65 and 129 tile rows (the reduction brings 64 rows at
+    a time) against the oracle, FP64 sums of at most 8,256 points."""
+    vgicp, ctx = vg
+    cfg = synth.config1(seed=31, n_target=6000, n_source=8300)
+    xyz, cov = cfg["sources"][0].xyz64(), cfg["sources"][0].cov64()
+    tgt = cfg["targets"][0]
+    vmap = vgicp.VoxelMap(ctx, tgt.xyz64(), tgt.cov64(), cfg["resolutions"])
+    omap = oracle.VoxelMap(tgt.xyz64(), tgt.cov64(), cfg["resolutions"])
+    pose = np.array(cfg["poses"][0])
+    rows = [0, 1, 63, 64, 65, 129]
+    sizes = [max(0, 64 * r - 5) for r in rows]
+    srcs = [vgicp.Source(ctx, xyz[:n], cov[:n]) for n in sizes]
+    batch = vgicp.FactorBatch(ctx, srcs, [vmap] * len(rows), precision="fp64", block=256, tile=64)
+    e, H, b, inl = batch.linearize(np.tile(pose[None], (len(rows), 1, 1)))
+    assert batch.info()["n_tiles"] == sum(rows)
+    assert e[0] == 0 and not H[0].any() and not b[0].any() and not inl[0].any()
+    for f in range(1, len(rows)):
+        of = oracle.Factor(xyz[:sizes[f]], cov[:sizes[f]], omap)
+        check_factor(batch, f, pose, of, e[f], H[f], b[f], rel=1e-9)
+    for h in [batch, vmap] + srcs:
+        h.close()
+
+
+def test_long_lm_histories_equal_short_ones(vg):
+    """An LM run whose histories exceed 4 MiB (kept in device memory, copied at the
+    end) gives every factor the bits of a run of that factor alone."""
+    vgicp, ctx = vg
+    cfg = synth.config1(seed=37, n_target=3000, n_source=300)
+    xyz, cov = cfg["sources"][0].xyz64(), cfg["sources"][0].cov64()
+    tgt = cfg["targets"][0]
+    vmap = vgicp.VoxelMap(ctx, tgt.xyz64(), tgt.cov64(), cfg["resolutions"])
+    srcs = [vgicp.Source(ctx, xyz[:n], cov[:n]) for n in (70, 300)]
+    F, iters = 4000, 90
+    assert F * iters * 12 > 4 << 20
+    pose = np.array(cfg["poses"][0])
+    batch = vgicp.FactorBatch(ctx, [srcs[f % 2] for f in range(F)], [vmap] * F)
+    T, acc, eh = batch.lm(np.tile(pose[None], (F, 1, 1)), iters=iters)
+    for k in range(2):
+        one = vgicp.FactorBatch(ctx, [srcs[k]], [vmap])
+        T1, acc1, eh1 = one.lm([pose], iters=iters)
+        assert np.array_equal(T[k::2], np.repeat(T1, F // 2, 0))
+        assert np.array_equal(acc[k::2], np.repeat(acc1, F // 2, 0))
+        assert np.array_equal(eh[k::2], np.repeat(eh1, F // 2, 0))
+        one.close()
+    batch.close()
+    vmap.close()
+    for s in srcs:
+        s.close()
+
+
+def test_kept_blocks_give_the_bits_of_fresh_ones(vg):
+    """Clouds, maps, sources and batches of sizes that shrink and grow, each built in
+    memory that an earlier object of the context left behind, equal those of a
+    context of their own."""
+    vgicp, ctx = vg
+    cfg = synth.config1(seed=41, n_target=60000, n_source=50000)
+    src, tgt = cfg["sources"][0], cfg["targets"][0]
+    pose = np.array(cfg["poses"][0])
+
+    def run(c, n, m):
+        s = vgicp.Source(c, src.xyz64()[:n], src.cov64()[:n])
+        cl = vgicp.Cloud(c, tgt.xyz64()[:m], 0.25, 10)
+        v = vgicp.VoxelMap.from_cloud(c, cl, cfg["resolutions"])
+        b = vgicp.FactorBatch(c, [s, s], [v, v])
+        out = b.linearize(np.tile(pose[None], (2, 1, 1)))
+        for h in (b, v, cl, s):
+            h.close()
+        return out
+
+    for n, m in [(50000, 30000), (21000, 60000), (49990, 20000), (333, 59000), (30000, 60000)]:
+        own = vgicp.Context(0)
+        want = run(own, n, m)
+        own.close()
+        for a, b in zip(run(ctx, n, m), want):
+            assert np.array_equal(np.asarray(a), np.asarray(b)), (n, m)
