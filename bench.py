@@ -752,7 +752,7 @@ def main():
     ap.add_argument("--no-tune-cache", action="store_true", help="autotune from scratch (ignore the tuned shapes)")
     ap.add_argument("--block", type=int, default=0, help="threads per workgroup (0: library default / tuned)")
     ap.add_argument("--tile", type=int, default=0, help="source points per tile (0: default / tuned)")
-    ap.add_argument("--bpc", type=int, default=0, help="persistent workgroups per CU (0: default / tuned)")
+    ap.add_argument("--bpc", type=int, default=0, help="accepted for older command lines; one workgroup takes one unit of tiles")
     ap.add_argument("--tile-order", type=int, default=0,
                     help="1: contiguous tile range per XCD, 2: tiles dealt round-robin to XCDs (0: default / tuned)")
     ap.add_argument("--lane-kahan", action="store_true", help="Kahan-compensated FP32 sums inside each lane")
