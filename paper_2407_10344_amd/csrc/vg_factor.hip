@@ -576,6 +576,10 @@ __device__ __forceinline__ uint64_t bits_below(int k) {   // k clamped to 0..64
     return k >= 64 ? ~0ull : (k <= 0 ? 0ull : (1ull << k) - 1ull);
 }
 
+__device__ __forceinline__ int lanes_below(uint64_t m) {   // set bits of m below this lane's
+    return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
+
 __device__ __forceinline__ int chunk_state(const FactorDesc* __restrict__ Fp, const double* P, const double ya[3],
                                            int64_t cg, int L) {
     const auto cb = gbl(Fp->cbound + 8 * cg);
@@ -881,33 +885,43 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(waves_per
                 const int c = 64 * q + ln;
                 walk[q] = __ballot(c < nch && (!SKIP || sh.reach[c] != kChunkCulled));
             }
+            int before[kGroup + 1];   // walked chunks before each tile (uniform)
+#pragma unroll
+            for (int r = 0; r <= kGroup; ++r) {
+                const int c0 = min(nch, r * tc);
+                before[r] = __popcll(walk[0] & bits_below(c0)) + __popcll(walk[1] & bits_below(c0 - 64));
+            }
+            const int walk0 = __popcll(walk[0]);
 #pragma unroll
             for (int q = 0; q < 2; ++q) {
                 const int c = 64 * q + ln;
-                const int first = c >= 2 * tc ? (c >= 3 * tc ? 3 * tc : 2 * tc) : (c >= tc ? tc : 0);   // of the chunk's tile
-                const int rank = __popcll(walk[0] & bits_below(c) & ~bits_below(first)) +
-                                 __popcll(walk[1] & bits_below(c - 64) & ~bits_below(first - 64));
+                const int below = c >= 2 * tc ? (c >= 3 * tc ? before[3] : before[2]) : (c >= tc ? before[1] : 0);
+                const int rank = (q ? walk0 : 0) - below + lanes_below(walk[q]);
                 own[q] = walk[q] & __ballot((rank & (NW - 1)) == wave);
             }
+            const int own0 = __popcll(own[0]);
 #pragma unroll
             for (int q = 0; q < 2; ++q) {
                 const int c = 64 * q + ln;
                 if ((own[q] >> ln) & 1)
-                    s_list[wave][__popcll(own[0] & bits_below(c)) + __popcll(own[1] & bits_below(c - 64))] =
+                    s_list[wave][(q ? own0 : 0) + lanes_below(own[q])] =
                         (uint16_t)(c | (SKIP && sh.reach[c] == kChunkInside ? kInsideFlag : 0));
             }
-            nown = __popcll(own[0]) + __popcll(own[1]);
-            if (tx < kGroup && tx * tc < nch) {   // thread r: the walked chunks and points of tile r
-                const int c0 = tx * tc, c1 = min(nch, c0 + tc);
-                const uint64_t w0 = walk[0] & bits_below(c1) & ~bits_below(c0);
-                const uint64_t w1 = walk[1] & bits_below(c1 - 64) & ~bits_below(c0 - 64);
-                const int cnt = __popcll(w0) + __popcll(w1);
+            nown = own0 + __popcll(own[1]);
+            if (wave == 0) {   // the walked chunks and points of each tile
                 const int last = (int)(n_pad / kChunk) - 1 - chunk0;   // the source's last chunk may be partial
-                const bool part = last >= c0 && last < c1 && (((last < 64 ? w0 : w1) >> (last & 63)) & 1) != 0;
-                const int pts = cnt * kChunk - (part ? (int)(n_pad - n) : 0);
-                double* red = s_red[tx][0];
-                red[kRowWalk] = (sb0 ? red[kRowWalk] : 0.0) + (double)pts;
-                red[kRowChunks] = (sb0 ? red[kRowChunks] : 0.0) + (double)cnt;
+#pragma unroll
+                for (int r = 0; r < kGroup; ++r) {
+                    if (r * tc >= nch) break;
+                    const int cnt = before[r + 1] - before[r];
+                    const bool part = last >= r * tc && last < min(nch, r * tc + tc) &&
+                                      (((last < 64 ? walk[0] : walk[1]) >> (last & 63)) & 1) != 0;
+                    if (tx == r) {
+                        double* red = s_red[r][0];
+                        red[kRowWalk] = (sb0 ? red[kRowWalk] : 0.0) + (double)(cnt * kChunk - (part ? (int)(n_pad - n) : 0));
+                        red[kRowChunks] = (sb0 ? red[kRowChunks] : 0.0) + (double)cnt;
+                    }
+                }
             }
         }
         RawPoint<PREC> nxt;
