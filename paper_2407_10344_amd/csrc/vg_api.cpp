@@ -769,25 +769,69 @@ void carve_schedule(vg_batch* b, Carve& c) {
 }
 void carve_rows(vg_batch* b, Carve& c) { b->d_partials = c.take<double>((size_t)kRow * b->h_tiles.size()); }
 
-// A new launch shape's schedule: tables and rows in a block of their own (the ones
-// the batch was created with lie in its block).
+// The schedule of the batch's launch shape on the device, tables and rows in a block
+// of their own (the ones the batch was created with lie in its block).  A failure
+// leaves the previous block in place.
 vg_status upload_schedule(vg_batch* b) {
     hipStream_t st = b->ctx->stream;
-    dfree(b->sched);
-    b->sched = nullptr;
+    Tile* const units = b->d_units;
+    int32_t* const tile_first = b->d_tile_first;
+    double* const partials = b->d_partials;
+    auto carve = [&](Carve& c) {
+        carve_schedule(b, c);
+        carve_rows(b, c);
+    };
     Carve c{nullptr};
-    carve_schedule(b, c);
-    carve_rows(b, c);
-    VG_TRY(dev_alloc(&b->sched, c.off));
-    c = Carve{b->sched};
-    carve_schedule(b, c);
-    carve_rows(b, c);
-    if (!b->h_units.empty())
-        VG_HIP(hipMemcpyAsync(b->d_units, b->h_units.data(), sizeof(Tile) * b->h_units.size(), hipMemcpyHostToDevice, st));
-    VG_HIP(hipMemcpyAsync(b->d_tile_first, b->h_tile_first.data(), sizeof(int32_t) * (b->F + 1),
-                          hipMemcpyHostToDevice, st));
-    VG_HIP(hipStreamSynchronize(st));
+    carve(c);
+    char* block = nullptr;
+    vg_status rc = dev_alloc(&block, c.off);
+    if (rc == VG_OK) {
+        c = Carve{block};
+        carve(c);
+        hipError_t e = hipSuccess;
+        if (!b->h_units.empty())
+            e = hipMemcpyAsync(b->d_units, b->h_units.data(), sizeof(Tile) * b->h_units.size(), hipMemcpyHostToDevice, st);
+        if (e == hipSuccess)
+            e = hipMemcpyAsync(b->d_tile_first, b->h_tile_first.data(), sizeof(int32_t) * (b->F + 1),
+                               hipMemcpyHostToDevice, st);
+        if (e == hipSuccess) e = hipStreamSynchronize(st);
+        if (e != hipSuccess) rc = hip_fail(e, "schedule upload");
+    }
+    if (rc != VG_OK) {
+        dfree(block);
+        b->d_units = units;
+        b->d_tile_first = tile_first;
+        b->d_partials = partials;
+        return rc;
+    }
+    dfree(b->sched);
+    b->sched = block;
     return VG_OK;
+}
+
+// Another launch shape for a batch; a failure leaves it with the shape and schedule
+// that it had.
+vg_status set_shape(vg_batch* b, int block, int tile_points, int blocks_per_cu, int tile_order) {
+    std::vector<Tile> tiles = b->h_tiles, units = b->h_units;
+    std::vector<int32_t> tile_first = b->h_tile_first, unit_first = b->h_unit_first;
+    const int was[4] = {b->block, b->tile_points, b->blocks_per_cu, b->tile_order};
+    b->block = block;
+    b->tile_points = tile_points;
+    b->blocks_per_cu = blocks_per_cu;
+    b->tile_order = tile_order;
+    build_tiles(b);
+    const vg_status rc = upload_schedule(b);
+    if (rc != VG_OK) {
+        b->h_tiles.swap(tiles);
+        b->h_units.swap(units);
+        b->h_tile_first.swap(tile_first);
+        b->h_unit_first.swap(unit_first);
+        b->block = was[0];
+        b->tile_points = was[1];
+        b->blocks_per_cu = was[2];
+        b->tile_order = was[3];
+    }
+    return rc;
 }
 
 // A batch's device memory is one block and its pinned memory another: an allocation
@@ -1536,12 +1580,7 @@ extern "C" vg_status vg_batch_tune(vg_batch* b, const double* poses, int32_t rep
         int bl = 0, tp = 0, bc = 0, to = 0;
         if (!b->opt.plain_per_factor && tune_lookup(b, &bl, &tp, &bc, &to) && valid_shape(bl, tp, bc) &&
             (to == 1 || to == 2)) {
-            b->block = bl;
-            b->tile_points = tp;
-            b->blocks_per_cu = bc;
-            b->tile_order = to;
-            build_tiles(b);
-            VG_TRY(upload_schedule(b));
+            VG_TRY(set_shape(b, bl, tp, bc, to));
             if (chosen) {
                 chosen[0] = bl;
                 chosen[1] = tp;
@@ -1561,11 +1600,7 @@ extern "C" vg_status vg_batch_tune(vg_batch* b, const double* poses, int32_t rep
         int bb = b->block, bt = b->tile_points;
         for (int tp : ptiles)
             for (int bl : pblocks) {
-                b->tile_points = tp;
-                b->block = bl;
-                b->blocks_per_cu = default_blocks_per_cu(bl);
-                build_tiles(b);
-                VG_TRY(upload_schedule(b));
+                VG_TRY(set_shape(b, bl, tp, default_blocks_per_cu(bl), b->tile_order));
                 VG_TRY(linearize_host(b));   // warm-up
                 const auto t0 = std::chrono::steady_clock::now();
                 for (int r = 0; r < reps; ++r) VG_TRY(linearize_host(b));
@@ -1577,11 +1612,7 @@ extern "C" vg_status vg_batch_tune(vg_batch* b, const double* poses, int32_t rep
                     bt = tp;
                 }
             }
-        b->block = bb;
-        b->tile_points = bt;
-        b->blocks_per_cu = default_blocks_per_cu(bb);
-        build_tiles(b);
-        VG_TRY(upload_schedule(b));
+        VG_TRY(set_shape(b, bb, bt, default_blocks_per_cu(bb), b->tile_order));
         if (chosen) {
             chosen[0] = bb;
             chosen[1] = bt;
@@ -1603,11 +1634,7 @@ extern "C" vg_status vg_batch_tune(vg_batch* b, const double* poses, int32_t rep
     };
     std::vector<Cand> cands;   // in preference order
     auto apply = [&](const Cand& c) -> vg_status {
-        if (b->tile_points != c.tp || b->h_tiles.empty()) {
-            b->tile_points = c.tp;
-            build_tiles(b);
-            VG_TRY(upload_schedule(b));
-        }
+        if (b->tile_points != c.tp) VG_TRY(set_shape(b, b->block, c.tp, b->blocks_per_cu, b->tile_order));
         b->tile_order = c.to;
         b->block = c.bl;
         b->blocks_per_cu = c.bc;
@@ -1658,12 +1685,7 @@ extern "C" vg_status vg_batch_tune(vg_batch* b, const double* poses, int32_t rep
             bo = c.to;
         }
     }
-    b->tile_order = bo;
-    b->block = bb;
-    b->tile_points = bt;
-    b->blocks_per_cu = bc;
-    build_tiles(b);
-    VG_TRY(upload_schedule(b));
+    VG_TRY(set_shape(b, bb, bt, bc, bo));
     if (chosen) {
         chosen[0] = bb;
         chosen[1] = bt;
