@@ -60,7 +60,8 @@ typedef enum {
     VG_ERR_HIP = -2,         /* a HIP runtime call failed (message has the HIP string) */
     VG_ERR_OOM = -3,         /* device or pinned host allocation failed */
     VG_ERR_KEY_RANGE = -4,   /* a target voxel key lies outside the packable range */
-    VG_ERR_CAPACITY = -5,    /* too many voxels in one level */
+    VG_ERR_CAPACITY = -5,    /* too many voxels in one level, downsampled points in a frame or
+                                tiles for the fixed scratch */
     VG_ERR_NOT_SPD = -6,     /* an input covariance is not symmetric positive definite */
     VG_ERR_STATE = -7        /* handle in use, destroyed, or from another context */
 } vg_status;
@@ -192,7 +193,8 @@ typedef struct vg_cloud vg_cloud;
  *      so that n . (sensor - p) >= 0.
  * xyz: n x 3 host FP64 (n >= 0, finite); r > 0; 1 <= k <= 32; sensor: 3 host
  * doubles (the frame's sensor position).  Synchronous (the output size is read
- * back).  Errors: VG_ERR_INVALID_ARG, VG_ERR_KEY_RANGE, VG_ERR_OOM, VG_ERR_HIP. */
+ * back).  At most 715,827,882 downsampled points (else VG_ERR_CAPACITY).  Errors:
+ * VG_ERR_INVALID_ARG, VG_ERR_KEY_RANGE, VG_ERR_CAPACITY, VG_ERR_OOM, VG_ERR_HIP. */
 vg_status vg_preprocess(vg_context* ctx, const double* xyz, int64_t n, double r, int32_t k, const double* sensor,
                         vg_cloud** out);
 /* Number of downsampled points and the neighbour count k of a cloud. */

@@ -25,6 +25,7 @@
 #include <algorithm>
 #include <climits>
 #include <cmath>
+#include <string>
 #include <vector>
 
 #include "vg_device.h"
@@ -89,6 +90,14 @@ __device__ __forceinline__ uint64_t spread21(uint64_t v) {
 }
 
 constexpr int kGrids = 6;       // cell sizes 2r, 4r, ..., 64r
+// Workgroups of a launch at most: a launch holds fewer than 2^32 threads, and frames
+// of 2^27 points and more with 16 or 32 lanes a point would not.  4 M queries of 16
+// lanes take milliseconds, so a launch per range costs them nothing.
+constexpr int64_t kMaxGroups = 1 << 18;
+// Slots of the cell table are 32-bit numbers, and a point has up to kGrids cells: one
+// entry has to stay empty, or a search for a missing cell would not end.
+constexpr uint32_t kMaxTableBits = 32;
+constexpr int64_t kMaxCellPoints = ((1ll << kMaxTableBits) - 1) / kGrids;
 
 // The nested grids: cells are counted from c0, a multiple of the coarsest cell, so
 // a cell of grid g is a 2r cell's coordinates shifted by g.
@@ -98,8 +107,9 @@ struct Cells {
     int32_t hi[3];       // last 2r cell per axis (the cloud's, with a margin of one cell)
     int32_t w;           // bits per axis
     int32_t idx_bits;    // low bits of a sort word that hold the point (0: a separate array)
-    uint32_t lg;         // table entries = 2^lg
+    uint32_t lg;         // table entries = 2^lg, lg <= 32
 };
+__device__ __forceinline__ uint32_t slot_mask(const Cells& C) { return (uint32_t)((1ull << C.lg) - 1ull); }
 // Table key of a grid's cell: the Morton code under a leading one, shifted, so the
 // grids' keys differ by the place of their highest bit.
 __device__ __forceinline__ uint64_t cell_key(const Cells& C, uint64_t code2r, int g) {
@@ -154,8 +164,8 @@ __global__ __launch_bounds__(256) void k_ds_centroids(const double* __restrict__
 }
 
 __global__ void k_fill_cells(u64x2* p, int64_t n) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = u64x2{kPEmpty, 0ull};
+    const int64_t step = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += step) p[i] = u64x2{kPEmpty, 0ull};
 }
 
 // A point in cell order.
@@ -175,7 +185,7 @@ __global__ void k_cells(const double* __restrict__ xyz, const uint64_t* __restri
     const int64_t i = cidx != nullptr ? (int64_t)cidx[t] : (int64_t)(w & ((1ull << C.idx_bits) - 1ull));
     pts[t] = CellPoint{xyz[3 * i], xyz[3 * i + 1], xyz[3 * i + 2], i};
     const uint64_t prev = t > 0 ? cword[t - 1] >> C.idx_bits : 0ull, next = t + 1 < m ? cword[t + 1] >> C.idx_bits : 0ull;
-    const uint32_t mask = (1u << C.lg) - 1u;
+    const uint32_t mask = slot_mask(C);
     for (int g = 0; g < kGrids; ++g) {
         const bool first = t == 0 || (prev >> (3 * g)) != (code >> (3 * g));
         const bool last = t + 1 == m || (next >> (3 * g)) != (code >> (3 * g));
@@ -260,7 +270,7 @@ __device__ __forceinline__ bool scan_cube(const Cells& C, const u64x2* __restric
     const double h = C.h * (double)(1 << g);
     const int side = 2 * R + 1;
     const int64_t cells = (int64_t)side * side * side;
-    const uint32_t mask = (1u << C.lg) - 1u;
+    const uint32_t mask = slot_mask(C);
     constexpr int PASSES = LIMITED ? (27 + G - 1) / G : 1;   // LIMITED: R = 1, all cells counted before any point is read
     for (int64_t base = 0; base < cells; base += (int64_t)G * PASSES) {
         int32_t from[PASSES], cnt[PASSES];
@@ -368,7 +378,7 @@ __device__ __forceinline__ bool settled(const Cells& C, const Query& q, int g, i
 
 constexpr int kBudget = 1024;   // candidates a query may scan before it is handed to the wave-wide pass
 
-// Exact k-NN, G lanes per query (G >= k), queries in cell order.
+// Exact k-NN, G lanes per query (G >= k), queries from t0 on in cell order.
 //
 // A pass over grid g lists the k best pairs among the points of the cells it
 // visits.  If it cannot prove them final, its k-th pair P is still an upper
@@ -382,12 +392,12 @@ constexpr int kBudget = 1024;   // candidates a query may scan before it is hand
 // (40k points, k = 10: 482 us, and 286 us for the queries handed over).
 template <int G>
 __global__ __launch_bounds__(256) void k_knn(Cells C, const u64x2* __restrict__ table, const CellPoint* __restrict__ pts,
-                                             int64_t m, int k, int32_t* __restrict__ nbr, double* __restrict__ nd2,
-                                             int32_t* __restrict__ hard, double* __restrict__ hard_bound,
-                                             int32_t* __restrict__ n_hard) {
+                                             int64_t t0, int64_t m, int k, int32_t* __restrict__ nbr,
+                                             double* __restrict__ nd2, int32_t* __restrict__ hard,
+                                             double* __restrict__ hard_bound, int32_t* __restrict__ n_hard) {
     __shared__ GroupLds<G> s_lds[256 / G];
     const int gl = threadIdx.x % G;
-    const int64_t t = (int64_t)blockIdx.x * (256 / G) + threadIdx.x / G;
+    const int64_t t = t0 + (int64_t)blockIdx.x * (256 / G) + threadIdx.x / G;
     if (t >= m) return;
     GroupLds<G>& S = s_lds[threadIdx.x / G];
     const CellPoint me = pts[t];
@@ -774,6 +784,10 @@ vg_status preprocess_frame(vg_context* ctx, Scratch& sc, const double* d_xyz, in
     VG_HIP(hipGetLastError());
     VG_HIP(hipStreamSynchronize(st));
     const int64_t m = ctx->h_small[0];
+    if (m > kMaxCellPoints) {
+        set_error("too many downsampled points (" + std::to_string(m) + "; at most " + std::to_string(kMaxCellPoints) + ")");
+        return VG_ERR_CAPACITY;
+    }
     VG_HIP(alloc_cloud(out, m, k));
     out->m = m;
     // 2. cells and the neighbour search (no host round trip)
@@ -791,8 +805,8 @@ vg_status preprocess_frame(vg_context* ctx, Scratch& sc, const double* d_xyz, in
     const int cb = bits_for((uint64_t)(m - 1));
     const bool cpacked = 3 * C.w + cb <= 64 && cb > 0;
     C.idx_bits = cpacked ? cb : 0;
-    C.lg = 6;   // at most six cells per point: load factor <= 3/4, and mostly below 1/4
-    while ((1ull << C.lg) < 8ull * (uint64_t)m) ++C.lg;
+    C.lg = 6;   // at most six cells per point: load factor <= 3/4 (up to 2^29 points), and mostly below 1/4
+    while (C.lg < kMaxTableBits && (1ull << C.lg) < 8ull * (uint64_t)m) ++C.lg;
     uint64_t *cw0, *cw1;
     int32_t *ci0 = nullptr, *ci1 = nullptr, *hard, *n_hard;
     CellPoint* pts;
@@ -814,7 +828,8 @@ vg_status preprocess_frame(vg_context* ctx, Scratch& sc, const double* d_xyz, in
     ctb += 256;
     VG_HIP(sc.get(&ctmp, ctb));
     n_hard = reinterpret_cast<int32_t*>(reinterpret_cast<uint64_t*>(table + ((size_t)1 << C.lg)) + 1);
-    k_fill_cells<<<grid_of(((int64_t)1 << C.lg) + 1), 256, 0, st>>>(table, ((int64_t)1 << C.lg) + 1);
+    const int64_t entries = ((int64_t)1 << C.lg) + 1;
+    k_fill_cells<<<(int)std::min<int64_t>((entries + 255) / 256, 1 << 22), 256, 0, st>>>(table, entries);
     VG_HIP(hipGetLastError());
     k_ds_centroids<<<grid_of(m, 4 * kCentPerWave), 256, 0, st>>>(d_xyz, w1, i1, K.idx_bits, start, m, C, out->xyz,
                                                                 out->counts, cw0, ci0);
@@ -823,9 +838,13 @@ vg_status preprocess_frame(vg_context* ctx, Scratch& sc, const double* d_xyz, in
     k_cells<<<grid_of(m), 256, 0, st>>>(out->xyz, cw1, ci1, m, C, pts, table);
     VG_HIP(hipGetLastError());
     // 16 lanes hold the best 16 pairs, 32 the best 32
-    if (k <= 16) k_knn<16><<<grid_of(m, 16), 256, 0, st>>>(C, table, pts, m, k, out->nbr, out->d2, hard, hard_bound, n_hard);
-    else k_knn<32><<<grid_of(m, 8), 256, 0, st>>>(C, table, pts, m, k, out->nbr, out->d2, hard, hard_bound, n_hard);
-    VG_HIP(hipGetLastError());
+    const int per = k <= 16 ? 16 : 8;   // queries a workgroup
+    for (int64_t t0 = 0; t0 < m; t0 += kMaxGroups * per) {
+        const int grid = (int)std::min<int64_t>(kMaxGroups, (m - t0 + per - 1) / per);
+        if (k <= 16) k_knn<16><<<grid, 256, 0, st>>>(C, table, pts, t0, m, k, out->nbr, out->d2, hard, hard_bound, n_hard);
+        else k_knn<32><<<grid, 256, 0, st>>>(C, table, pts, t0, m, k, out->nbr, out->d2, hard, hard_bound, n_hard);
+        VG_HIP(hipGetLastError());
+    }
     k_knn_wave<<<4096, 64, 0, st>>>(C, table, pts, m, k, hard, hard_bound, n_hard, out->nbr, out->d2);
     VG_HIP(hipGetLastError());
     // 3. covariances and normals

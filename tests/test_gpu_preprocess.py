@@ -275,3 +275,25 @@ def test_edges_of_the_neighbour_groups_and_key_widths(vg, n, k, span):
     for key in ("xyz", "counts", "d2"):
         assert np.array_equal(dev[key], o[key]), key
     assert np.array_equal(dev["nbr"], o["nbr"].astype(np.int32))
+
+
+def test_searches_of_more_than_one_launch(vg):
+    """2.2 million points with 17 neighbours (32 lanes a query): more than one launch's
+    2^18 workgroups of 8 queries.  Every point finds itself first; the corners of the
+    lattice, first and last in search order, agree with brute force bit for bit."""
+    vgicp, ctx = vg
+    rng = np.random.default_rng(5)
+    side, k = 130, 17
+    cell = np.stack(np.meshgrid(*[np.arange(side)] * 3, indexing="ij"), axis=-1).reshape(-1, 3)
+    xyz = cell + 0.5 + rng.uniform(-0.4, 0.4, size=(side ** 3, 3))
+    assert 8 << 18 < len(xyz)
+    dev = device(vgicp, ctx, xyz[::-1], 1.0, k, np.zeros(3))
+    assert np.array_equal(dev["xyz"], xyz) and np.all(dev["counts"] == 1)
+    assert np.array_equal(dev["nbr"][:, 0], np.arange(len(xyz))) and np.all(dev["d2"][:, 0] == 0.0)
+    assert dev["nbr"].min() >= 0
+    for lo, hi in ((0, 6), (60, 66), (side - 6, side)):
+        # a cube of 15 cells around holds the 17 nearest of its inner points
+        near = np.flatnonzero(np.all((cell >= lo - 8) & (cell < hi + 8), axis=1))
+        own = np.flatnonzero(np.all((cell[near] >= lo) & (cell[near] < hi), axis=1))
+        nbr, d2 = pp.knn(xyz[near], k, own)[:2]
+        assert np.array_equal(dev["nbr"][near[own]], near[nbr]) and np.array_equal(dev["d2"][near[own]], d2)

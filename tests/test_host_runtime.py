@@ -43,3 +43,36 @@ def shape_survives_failed_tuning(h):
 
 def test_batch_survives_a_tuner_out_of_memory(run):
     run("shape_survives_failed_tuning")
+
+
+def preprocessing_launches_fit_the_device(h):
+    """Sizes around the powers of two at which 16 or 32 lanes a point, or the cell table's
+    entries, reach 2^32 threads; beyond the cell table's reach the call is refused."""
+    xyz, sensor = (C.c_double * 16)(), (C.c_double * 3)()
+    h.watch("k_knnILi", 4)
+    for m, k in ((1, 1), (1000, 10), ((1 << 27) + 77, 10), ((1 << 27) + 77, 17), ((1 << 28) + 77, 16),
+                 ((1 << 28) + 77, 32), ((1 << 29) + 77, 1), (715_000_000, 1)):
+        h.fake.fake_reset()
+        h.set("downsampled", m)
+        cloud = h.make("vg_preprocess", h.ctx, xyz, m, C.c_double(0.5), k, sensor)
+        for name, grid, block, _ in h.launches():
+            assert 0 < grid * block < 1 << 32, (name, grid, block)
+        # the searches take every query once
+        lanes = 16 if k <= 16 else 32
+        done = 0
+        for name, grid, block, args in h.launches("k_knnILi"):
+            assert "k_knnILi%dE" % lanes in name
+            assert args[3] == done
+            done += grid * block // lanes
+        assert m <= done < m + 256 // lanes
+        h.check("vg_cloud_destroy", cloud)
+    h.fake.fake_reset()
+    h.set("downsampled", 720_000_000)
+    out = C.c_void_p()
+    assert h.call("vg_preprocess", h.ctx, xyz, 720_000_000, C.c_double(0.5), 1, sensor, C.byref(out)) == -5
+    assert out.value is None and not h.launches("k_knn")
+    assert h.fake.fake_bad_frees() == 0
+
+
+def test_preprocessing_launches_at_the_largest_frames(run):
+    run("preprocessing_launches_fit_the_device")
