@@ -676,12 +676,13 @@ __device__ __forceinline__ int32_t work_item(int32_t n, int32_t interleave) {
 // from pinned host memory, their FP64 copy on the device (either may be nullptr).
 __global__ void k_stage_poses(int64_t F, const double* __restrict__ poses, double* __restrict__ pose64,
                               float* __restrict__ posef) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= F * 16) return;
-    const int64_t f = i / 16, k = i % 16;
-    const double v = (k < 12) ? poses[12 * f + k] : 0.0;
-    if (posef != nullptr) posef[i] = (float)v;
-    if (pose64 != nullptr && k < 12) pose64[12 * f + k] = v;
+    const int64_t step = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < F * 16; i += step) {
+        const int64_t f = i / 16, k = i % 16;
+        const double v = (k < 12) ? poses[12 * f + k] : 0.0;
+        if (posef != nullptr) posef[i] = (float)v;
+        if (pose64 != nullptr && k < 12) pose64[12 * f + k] = v;
+    }
 }
 
 __global__ void k_copy_words(const uint64_t* __restrict__ in, uint64_t* __restrict__ out, int64_t n) {
@@ -1592,6 +1593,13 @@ __global__ void k_fill_zero(uint32_t* p, int64_t n_words) {
 
 // ---------------------------------------------------------------- host launchers
 
+// A launch holds fewer than 2^32 threads.  Poses are staged by strides; a reduction
+// takes 256 threads a factor and goes in ranges of factors (a million factors take it
+// milliseconds, so a launch per range costs nothing).
+constexpr int kMaxStageGroups = 1 << 22;
+constexpr int32_t kMaxReduceFactors = 1 << 20;
+static int stage_grid(int64_t factors) { return (int)std::min<int64_t>((factors * 16 + 255) / 256, kMaxStageGroups); }
+
 template <int MODE, int PREC, bool KH, bool VAL, int LM>
 static vg_status launch_tiles_v(vg_batch* b, const Workspace& ws, const double* d_poses, int32_t u0, int32_t u1,
                                 const double* d_grad_e, void* d_grad_points, int points_dtype) {
@@ -1650,9 +1658,8 @@ vg_status launch_tiles(vg_batch* b, const Workspace& ws, int mode, const double*
     const int32_t u0 = b->h_unit_first[f0], u1 = b->h_unit_first[f1];
     if (u1 <= u0) return VG_OK;
     if (!staged && f1 > f0 && reads_staged_poses(b, mode)) {
-        const int64_t nf = (f1 - f0) * 16;
-        k_stage_poses<<<(int)((nf + 255) / 256), 256, 0, b->ctx->stream>>>(f1 - f0, d_poses + 12 * f0,
-                                                                          nullptr, ws.posef + 16 * f0);
+        k_stage_poses<<<stage_grid(f1 - f0), 256, 0, b->ctx->stream>>>(f1 - f0, d_poses + 12 * f0, nullptr,
+                                                                       ws.posef + 16 * f0);
         VG_HIP(hipGetLastError());
     }
     const int p = b->opt.precision;
@@ -1676,9 +1683,9 @@ template <int MODE, int PREC>
 static void reduce_t(vg_batch* b, const Workspace& ws, const double* d_poses, int32_t f0, int32_t f1, double* d_out,
                      int64_t* d_inl, const double* d_grad_e, const double* d_jr, double* d_grad_xi,
                      const LmArgs& lm) {
-    k_reduce<MODE, PREC><<<f1 - f0, kRedThreads, 0, b->ctx->stream>>>(b->d_fac, b->d_tile_first, f0, ws.partials,
-                                                                      d_poses, d_out, d_inl, d_grad_e, d_jr,
-                                                                      d_grad_xi, ws.work, lm);
+    for (int32_t a = f0; a < f1; a += kMaxReduceFactors)
+        k_reduce<MODE, PREC><<<std::min(kMaxReduceFactors, f1 - a), kRedThreads, 0, b->ctx->stream>>>(
+            b->d_fac, b->d_tile_first, a, ws.partials, d_poses, d_out, d_inl, d_grad_e, d_jr, d_grad_xi, ws.work, lm);
 }
 
 vg_status launch_reduce(vg_batch* b, const Workspace& ws, int mode, const double* d_poses, int32_t f0, int32_t f1,
@@ -1701,7 +1708,7 @@ vg_status launch_reduce(vg_batch* b, const Workspace& ws, int mode, const double
 
 vg_status launch_pose_upload(vg_batch* b, const Workspace& ws, int mode, const double* h_poses) {
     float* posef = reads_staged_poses(b, mode) ? ws.posef : nullptr;
-    k_stage_poses<<<(int)((b->F * 16 + 255) / 256), 256, 0, b->ctx->stream>>>(b->F, h_poses, b->d_poses, posef);
+    k_stage_poses<<<stage_grid(b->F), 256, 0, b->ctx->stream>>>(b->F, h_poses, b->d_poses, posef);
     VG_HIP(hipGetLastError());
     return VG_OK;
 }

@@ -410,3 +410,29 @@ def test_kept_blocks_give_the_bits_of_fresh_ones(vg):
         own.close()
         for a, b in zip(run(ctx, n, m), want):
             assert np.array_equal(np.asarray(a), np.asarray(b)), (n, m)
+
+
+# ----------------------------------------------------------------- very many factors
+
+def test_factors_of_more_than_one_reduction_launch(vg, c1):
+    """2^20 + 3 factors are reduced in two launches: every row equals that of a small
+    batch at the same pose, bit for bit (linearize, evaluate, LM)."""
+    vgicp, ctx = vg
+    t, s = c1["targets"][0], c1["sources"][0]
+    m = vgicp.VoxelMap(ctx, t.xyz64(), t.cov64(), c1["resolutions"])
+    src = vgicp.Source(ctx, s.xyz64()[:100], s.cov64()[:100])
+    F = (1 << 20) + 3
+    five = np.repeat(vgicp.poses12(c1["poses_true"][0]), 5, axis=0)
+    five[:, 9:] += np.random.default_rng(3).normal(scale=0.05, size=(5, 3))
+    pick = np.arange(F) % 5
+    few = vgicp.FactorBatch(ctx, [src] * 5, [m] * 5)
+    many = vgicp.FactorBatch(ctx, [src] * F, [m] * F)
+    for a, b in zip(few.linearize(five), many.linearize(five[pick])):
+        assert np.array_equal(a[pick], b)
+    assert np.array_equal(few.evaluate(five)[pick], many.evaluate(five[pick]))
+    for a, b in zip(few.lm(five, iters=2), many.lm(five[pick], iters=2)):
+        assert np.array_equal(a[pick], b)
+    few.close()
+    many.close()
+    src.close()
+    m.close()

@@ -76,3 +76,28 @@ def preprocessing_launches_fit_the_device(h):
 
 def test_preprocessing_launches_at_the_largest_frames(run):
     run("preprocessing_launches_fit_the_device")
+
+
+def launches_per_factor_stay_bounded(h):
+    """2^20 + 3 factors (2^30 are accepted): no launch grows with the factors beyond 2^28
+    threads, and the reductions take every factor once."""
+    F = (1 << 20) + 3
+    h.watch("k_reduce", 3)
+    s, m = h.source(0), h.map(0)
+    b = h.batch([s] * F, [m] * F)
+    d = C.c_void_p(1 << 45)
+    for name, args in (("vg_linearize_async", (d, d, None)), ("vg_evaluate_async", (d, d)),
+                       ("vg_backward_async", (d, d, None, d, None, 0)), ("vg_lm_step_async", (d, d, d, d))):
+        h.fake.fake_reset()
+        h.check(name, b, *args)
+        for kernel, grid, block, _ in h.launches():
+            assert 0 < grid * block <= 1 << 28, (kernel, grid, block)
+        done = 0
+        for kernel, grid, block, (_, _, f0) in h.launches("k_reduce"):
+            assert f0 & 0xFFFFFFFF == done % F
+            done += grid
+        assert done == (2 * F if name == "vg_lm_step_async" else F)
+
+
+def test_launches_of_very_many_factors(run):
+    run("launches_per_factor_stay_bounded")
