@@ -1634,9 +1634,9 @@ extern "C" vg_status vg_batch_tune(vg_batch* b, const double* poses, int32_t rep
     };
     std::vector<Cand> cands;   // in preference order
     auto apply = [&](const Cand& c) -> vg_status {
-        if (b->tile_points != c.tp) VG_TRY(set_shape(b, b->block, c.tp, b->blocks_per_cu, b->tile_order));
+        // units depend on the block size too: a shape is timed with its own
+        if (b->tile_points != c.tp || b->block != c.bl) return set_shape(b, c.bl, c.tp, c.bc, c.to);
         b->tile_order = c.to;
-        b->block = c.bl;
         b->blocks_per_cu = c.bc;
         return VG_OK;
     };

@@ -101,3 +101,43 @@ def launches_per_factor_stay_bounded(h):
 
 def test_launches_of_very_many_factors(run):
     run("launches_per_factor_stay_bounded")
+
+
+def tuner_times_what_it_installs(h):
+    """Every shape that the tuner times is launched with the workgroups of a batch created
+    with that shape, and so is the shape that it leaves."""
+    h.watch("k_tiles", 13)
+    s, m = h.source(200_000), h.map(1000)
+    expect = {}
+
+    def launched():
+        out = set()
+        for _, grid, block, args in h.launches("k_tiles"):
+            n_units, tc, interleave = (args[k] & 0xFFFFFFFF for k in (3, 4, 12))
+            out.add((block, 64 * tc, 2 if interleave else 1, n_units, grid))
+        return out
+
+    for plain in (0, 1):
+        F = 1 if plain else 50
+        b = h.batch([s] * F, [m] * F, plain_per_factor=plain)
+        chosen = (C.c_int32 * 4)()
+        h.fake.fake_reset()
+        h.check("vg_batch_tune", b, h.poses(F), 1, chosen)
+        timed = launched()
+        assert len({t[:3] for t in timed}) == (10 if plain else 48)
+        for block, tile, order, n_units, grid in timed:
+            key = (F, block, tile, order)
+            if key not in expect:
+                fresh = h.batch([s] * F, [m] * F, block_threads=block, tile_points=tile, tile_order=order)
+                expect[key] = h.info(fresh)["grid"]
+                h.check("vg_batch_destroy", fresh)
+            assert grid == expect[key], (key, grid, expect[key])
+        h.fake.fake_reset()
+        d = C.c_void_p(1 << 45)
+        h.check("vg_linearize_async", b, d, d, None)
+        (block, tile, order, _, grid), = launched()
+        assert [block, tile, order] == [chosen[0], chosen[1], chosen[3]] and grid == expect[(F, block, tile, order)]
+
+
+def test_tuner_times_the_schedules_it_installs(run):
+    run("tuner_times_what_it_installs")
