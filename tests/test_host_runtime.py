@@ -141,3 +141,27 @@ def tuner_times_what_it_installs(h):
 
 def test_tuner_times_the_schedules_it_installs(run):
     run("tuner_times_what_it_installs")
+
+
+def plain_factors_are_not_grouped(h):
+    """The per-factor loop launches one factor at a time: as many workgroups as the factor has
+    tiles, however many factors the batch has."""
+    h.watch("k_tiles", 5)
+    s, m = h.source(200_000), h.map(1000)
+    F = 100
+    b = h.batch([s] * F, [m] * F, plain_per_factor=1)
+    h.fake.fake_reset()
+    e, H, g = (C.c_double * F)(), (C.c_double * (36 * F))(), (C.c_double * (6 * F))()
+    h.check("vg_linearize", b, h.poses(F), e, H, g, None)
+    units = [args[3] & 0xFFFFFFFF for _, _, _, args in h.launches("k_tiles")]
+    assert units == [-(-200_000 // h.info(b)["tile"])] * F
+    # the same factors in one launch share prologues
+    c = h.batch([s] * F, [m] * F)
+    h.fake.fake_reset()
+    h.check("vg_linearize", c, h.poses(F), e, H, g, None)
+    (_, _, _, args), = h.launches("k_tiles")
+    assert args[3] & 0xFFFFFFFF < sum(units)
+
+
+def test_plain_factors_are_not_grouped(run):
+    run("plain_factors_are_not_grouped")
