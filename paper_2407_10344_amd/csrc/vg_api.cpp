@@ -97,9 +97,8 @@ template <typename T>
 vg_status dev_alloc(T** p, size_t count) {
     *p = nullptr;
     if (count == 0) count = 1;
-    hipError_t e = hipMalloc((void**)p, sizeof(T) * count);
+    const hipError_t e = vg::device_alloc((void**)p, sizeof(T) * count);
     if (e != hipSuccess) {
-        (void)hipGetLastError();
         vg::set_error(std::string("hipMalloc failed: ") + hipGetErrorString(e));
         return VG_ERR_OOM;
     }
@@ -145,50 +144,84 @@ void hfree(void* p) {
 
 namespace vg {
 
+// Every live pool; never destroyed, as contexts may outlive the library's statics.
+struct Pools {
+    std::mutex mu;
+    std::vector<BlockPool*> all;
+};
+static Pools& pools() {
+    static Pools* p = new Pools;
+    return *p;
+}
+
+hipError_t device_alloc(void** p, size_t bytes) {
+    *p = nullptr;
+    hipError_t e = hipMalloc(p, bytes);
+    if (e == hipSuccess) return e;
+    (void)hipGetLastError();
+    int device = 0;
+    if (e == hipErrorOutOfMemory && hipGetDevice(&device) == hipSuccess) {
+        {
+            std::lock_guard<std::mutex> lock(pools().mu);
+            for (BlockPool* q : pools().all)
+                if (q->device == device) q->give_back();
+        }
+        e = hipMalloc(p, bytes);
+        if (e == hipSuccess) return e;
+        (void)hipGetLastError();
+    }
+    *p = nullptr;
+    return e;
+}
+
+BlockPool::BlockPool(int d) : device(d) {
+    std::lock_guard<std::mutex> lock(pools().mu);
+    pools().all.push_back(this);
+}
+
+BlockPool::~BlockPool() {
+    std::lock_guard<std::mutex> lock(pools().mu);
+    auto& all = pools().all;
+    all.erase(std::remove(all.begin(), all.end(), this), all.end());
+}
+
+// (the pool's lock is not held while it allocates: a failing allocation takes the
+// locks of all pools)
 hipError_t BlockPool::get(void** p, size_t bytes) {
     *p = nullptr;
-    if (bytes < kPooled) return hipMalloc(p, bytes);
+    if (bytes < kPooled) return device_alloc(p, bytes);
     size_t step = 1;
     while (step * 16 <= bytes) step *= 2;   // bytes / 16 < step <= bytes / 8 at most
-    const size_t size = (bytes + step - 1) / step * step;
-    std::lock_guard<std::mutex> lock(mu);
-    size_t best = idle.size();
-    for (size_t k = 0; k < idle.size(); ++k)
-        if (idle[k].second >= bytes && idle[k].second <= size + size / 2 &&
-            (best == idle.size() || idle[k].second < idle[best].second))
-            best = k;
+    size_t size = (bytes + step - 1) / step * step;
     try {
-        live.reserve(live.size() + 1);
-        if (best < idle.size()) {
-            const auto blk = idle[best];
-            live.emplace(blk.first, blk.second);
-            idle.erase(idle.begin() + (std::ptrdiff_t)best);
-            kept -= blk.second;
-            *p = blk.first;
-            return hipSuccess;
+        {
+            std::lock_guard<std::mutex> lock(mu);
+            size_t best = idle.size();
+            for (size_t k = 0; k < idle.size(); ++k)
+                if (idle[k].second >= bytes && idle[k].second <= size + size / 2 &&
+                    (best == idle.size() || idle[k].second < idle[best].second))
+                    best = k;
+            if (best < idle.size()) {
+                const auto blk = idle[best];
+                live.emplace(blk.first, blk.second);
+                idle.erase(idle.begin() + (std::ptrdiff_t)best);
+                kept -= blk.second;
+                *p = blk.first;
+                return hipSuccess;
+            }
         }
-        size_t got = size;
-        hipError_t e = hipMalloc(p, size);
-        if (e != hipSuccess) {
-            (void)hipGetLastError();
-            release_locked(0);
-            got = bytes;
-            e = hipMalloc(p, bytes);
+        hipError_t e = device_alloc(p, size);
+        if (e != hipSuccess && size != bytes) {
+            size = bytes;
+            e = device_alloc(p, size);
         }
-        if (e != hipSuccess) {
-            (void)hipGetLastError();
-            *p = nullptr;
-            return e;
-        }
-        try {
-            live.emplace(*p, got);
-        } catch (...) {
-            (void)hipFree(*p);
-            *p = nullptr;
-            return hipErrorOutOfMemory;
-        }
+        if (e != hipSuccess) return e;
+        std::lock_guard<std::mutex> lock(mu);
+        live.emplace(*p, size);
         return hipSuccess;
     } catch (...) {
+        if (*p) (void)hipFree(*p);
+        *p = nullptr;
         return hipErrorOutOfMemory;
     }
 }
@@ -229,10 +262,50 @@ void BlockPool::release_locked(size_t limit) {
     idle.erase(idle.begin(), idle.begin() + (std::ptrdiff_t)k);
 }
 
+void BlockPool::give_back() {
+    std::lock_guard<std::mutex> lock(mu);
+    release_locked(0);
+    if (ws_users == 0) {
+        if (ws) (void)hipFree(ws);
+        ws = nullptr;
+        ws_bytes = 0;
+    }
+}
+
 void BlockPool::close() {
+    give_back();
     std::lock_guard<std::mutex> lock(mu);
     closed = true;
     release_locked(0);
+}
+
+void* BlockPool::workspace(size_t* bytes) {
+    std::lock_guard<std::mutex> lock(mu);
+    ++ws_users;
+    *bytes = ws_bytes;
+    return ws;
+}
+
+void BlockPool::end_workspace(size_t need) {
+    std::lock_guard<std::mutex> lock(mu);
+    if (--ws_users > 0 || closed || need <= ws_bytes) return;
+    if (ws) (void)hipFree(ws);
+    ws = nullptr;
+    ws_bytes = 0;
+    if (hipMalloc(&ws, need) == hipSuccess) {
+        ws_bytes = need;
+    } else {
+        (void)hipGetLastError();
+        ws = nullptr;
+    }
+}
+
+void BlockPool::drop_workspace() {
+    std::lock_guard<std::mutex> lock(mu);
+    if (ws_users != 1) return;
+    if (ws) (void)hipFree(ws);
+    ws = nullptr;
+    ws_bytes = 0;
 }
 
 }  // namespace vg
@@ -280,6 +353,7 @@ extern "C" vg_status vg_context_create(int32_t device, void* hip_stream, vg_cont
     }
     auto* c = new vg_context();
     c->device = device;
+    c->pool = std::make_shared<BlockPool>(device);
     c->num_cu = prop.multiProcessorCount;
     if (device < kMaxDevices) {
         // this device's copy of the fixed scratch (device current); a failure only
@@ -325,7 +399,6 @@ extern "C" vg_status vg_context_destroy(vg_context* ctx) {
     (void)hipStreamSynchronize(ctx->stream);
     if (ctx->own_stream) (void)hipStreamDestroy(ctx->stream);
     ctx->pool->close();
-    if (ctx->ws) (void)hipFree(ctx->ws);
     if (ctx->h_small) (void)hipHostFree(ctx->h_small);
     ctx->magic = 0;
     delete ctx;

@@ -147,7 +147,7 @@ void graph_free(vg_graph* g) {
 }
 template <typename T>
 hipError_t up(T** d, const std::vector<T>& h) {
-    hipError_t e = hipMalloc((void**)d, sizeof(T) * std::max<size_t>(h.size(), 1));
+    hipError_t e = device_alloc((void**)d, sizeof(T) * std::max<size_t>(h.size(), 1));
     if (e == hipSuccess && !h.empty()) e = hipMemcpy(*d, h.data(), sizeof(T) * h.size(), hipMemcpyHostToDevice);
     return e;
 }

@@ -169,20 +169,37 @@ struct Level {
 
 namespace vg {
 
-// Device blocks of a context's clouds, maps, sources and batches, kept for the next
-// ones.  The runtime hands out memory of 2 MiB and more by mapping it, unless a
-// block of that very size was freed just before: 290 us against 12 us.  128-ring
-// frames of differing sizes: 1,515 us each, 735 us with kept blocks.
+// hipMalloc on the current device.  Out of memory, it gives back what every context
+// there keeps idle and tries again.  Leaves no error in the runtime when it fails.
+hipError_t device_alloc(void** p, size_t bytes);
+
+// Device memory that a context keeps: blocks of its clouds, maps, sources and batches
+// for the next ones, and a workspace for the calls that build them.  The runtime
+// hands out memory of 2 MiB and more by mapping it, unless a block of that very size
+// was freed just before: 290 us against 12 us.  128-ring frames of differing sizes:
+// 1,515 us each, 735 us with kept blocks.
 // Blocks from kPooled on are rounded up by at most an eighth and kept when their
-// object is destroyed, up to kKeepBlocks in all (the oldest are freed first); they
-// are given back with the context, or when an allocation fails.  A block is taken
-// back once the device is idle, as hipFree would wait, so no stream of any user
-// still reads it.  Objects share the pool, which any thread may call.
+// object is destroyed, up to kKeepBlocks in all (the oldest are freed first); an idle
+// block of up to one and a half times the rounded size is taken again.  They are
+// given back with the context, or when any allocation of the library on the device
+// fails (so is the workspace, unless a call is using it).  A block is taken back once
+// the device is idle, as hipFree would wait, so no stream of any user still reads
+// it.  Objects share the pool, which any thread may call.
 struct BlockPool {
     static constexpr size_t kPooled = (size_t)2 << 20, kKeepBlocks = (size_t)256 << 20;
+    explicit BlockPool(int device);
+    ~BlockPool();
+    BlockPool(const BlockPool&) = delete;
+    BlockPool& operator=(const BlockPool&) = delete;
     hipError_t get(void** p, size_t bytes);
     void put(void* p);
-    void close();   // frees what is kept; blocks put later are freed at once
+    void close();     // frees what is kept; blocks put later are freed at once
+    void give_back(); // frees what is idle
+    // the workspace for one call, grown to `need` (0: as it is) when the call ends
+    void* workspace(size_t* bytes);
+    void end_workspace(size_t need);
+    void drop_workspace();   // by the call that holds it
+    const int device;
 private:
     void release_locked(size_t limit);
     std::mutex mu;
@@ -190,17 +207,18 @@ private:
     size_t kept = 0;
     std::vector<std::pair<void*, size_t>> idle;   // oldest first
     std::unordered_map<void*, size_t> live;
+    void* ws = nullptr;
+    size_t ws_bytes = 0;
+    int ws_users = 0;
 };
 
 }  // namespace vg
 
 struct vg_context {
     int device = 0;
-    std::shared_ptr<vg::BlockPool> pool = std::make_shared<vg::BlockPool>();
+    std::shared_ptr<vg::BlockPool> pool;
     hipStream_t stream = nullptr;
     bool own_stream = false;
-    void* ws = nullptr;          // device workspace of the calls that build clouds, maps and sources
-    size_t ws_bytes = 0;         // (grown to the largest such call, up to kKeepWorkspace)
     int32_t* h_small = nullptr;  // pinned host words that those calls' kernels write their sizes to
     int num_cu = 0;
     void* scratch = nullptr;     // this device's fixed scratch array (device address), or nullptr
@@ -339,37 +357,38 @@ constexpr int kSmallWords = 8192;                    // pinned words of a contex
 // Temporaries of one call, carved from the context's workspace (the calls of a
 // context are ordered on its stream, so a later call may write them while the
 // host is ahead of the device); what does not fit is allocated and freed, and the
-// workspace grows to the call's total afterwards, so calls of similar size
-// allocate nothing.
+// workspace grows to the call's total afterwards, up to kKeepWorkspace, so calls of
+// similar size allocate nothing.
 struct Scratch {
     vg_context* ctx;
-    size_t off = 0, need = 0;
+    char* ws;
+    size_t ws_bytes = 0, off = 0, need = 0;
     std::vector<void*> ptrs;
-    explicit Scratch(vg_context* c) : ctx(c) {}
+    explicit Scratch(vg_context* c) : ctx(c), ws((char*)c->pool->workspace(&ws_bytes)) {}
     Scratch(const Scratch&) = delete;
     Scratch& operator=(const Scratch&) = delete;
     ~Scratch() {
         if (!ptrs.empty()) (void)hipStreamSynchronize(ctx->stream);   // also on early error returns
         for (void* p : ptrs) (void)hipFree(p);
-        if (need > ctx->ws_bytes && need <= kKeepWorkspace) {
-            if (ctx->ws) (void)hipFree(ctx->ws);
-            ctx->ws = nullptr;
-            ctx->ws_bytes = 0;
-            if (hipMalloc(&ctx->ws, need) == hipSuccess) ctx->ws_bytes = need;
-            else (void)hipGetLastError();
-        }
+        ctx->pool->end_workspace(need <= kKeepWorkspace ? need : 0);
     }
     template <typename T>
     hipError_t get(T** p, size_t count) {
         const size_t bytes = (sizeof(T) * (count ? count : 1) + 255) & ~(size_t)255;
         need += bytes;
-        if (ctx->ws && off + bytes <= ctx->ws_bytes) {
-            *p = (T*)((char*)ctx->ws + off);
+        *p = nullptr;
+        if (ws && off + bytes <= ws_bytes) {
+            *p = (T*)(ws + off);
             off += bytes;
             return hipSuccess;
         }
         void* q = nullptr;
-        hipError_t e = hipMalloc(&q, bytes);
+        hipError_t e = device_alloc(&q, bytes);
+        if (e != hipSuccess && ws && off == 0) {   // too small for this call, and in its way
+            ctx->pool->drop_workspace();
+            ws = nullptr;
+            e = device_alloc(&q, bytes);
+        }
         if (e == hipSuccess) ptrs.push_back(q);
         *p = (T*)q;
         return e;

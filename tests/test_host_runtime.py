@@ -165,3 +165,72 @@ def plain_factors_are_not_grouped(h):
 
 def test_plain_factors_are_not_grouped(run):
     run("plain_factors_are_not_grouped")
+
+
+def kept_memory_is_given_back(h):
+    """Blocks and workspaces kept idle, of any context on the device, never make a call fail
+    for want of memory; a call that does fail leaves no error behind in the runtime."""
+    m, s = h.map(1000), h.source(30_000)
+    b = h.batch([s] * 40, [m] * 40)
+    d = C.c_void_p(1 << 45)
+    F, iters = 40, 10_000
+    ni, nj = (C.c_int64 * 2000)(*range(2000)), (C.c_int64 * 2000)(*range(1, 2001))
+    keys, found = (C.c_int64 * (3 * 30_000))(), (C.c_int32 * 30_000)()
+    out, acc, eh = (C.c_double * (12 * F))(), (C.c_int32 * (F * iters))(), (C.c_double * (F * iters))()
+    chosen = (C.c_int32 * 4)()
+    cloud_xyz, sensor = (C.c_double * 16)(), (C.c_double * 3)()
+    other = h.make("vg_context_create", 0, None)
+    calls = {
+        "graph": lambda: h.call("vg_create_graph", h.ctx, 2001, 2000, ni, nj, C.byref(C.c_void_p())),
+        "gradients": lambda: h.call("vg_backward_async", b, d, d, None, d, d, 1),
+        "correspondences": lambda: h.call("vg_correspondences", b, h.poses(1), 3, keys, found),
+        "histories": lambda: h.call("vg_lm_run", b, h.poses(F), iters, C.c_double(1e-4), out, acc, eh),
+        "tuner": lambda: h.call("vg_batch_tune", b, h.poses(F), 1, chosen),
+        "small source": lambda: h.call("vg_create_source", other, cloud_xyz, cloud_xyz, None, 100, C.byref(C.c_void_p())),
+        "large source": lambda: h.call("vg_create_source", other, cloud_xyz, cloud_xyz, None, 900_000,
+                                       C.byref(C.c_void_p())),
+        "frame": lambda: h.call("vg_preprocess", other, cloud_xyz, 100_000, C.c_double(0.5), 10, sensor,
+                                C.byref(C.c_void_p())),
+    }
+    for keeper in (h.ctx, h.make("vg_context_create", 0, None)):
+        for name, call in calls.items():
+            # a source of a million points leaves 160 MB of blocks and 90 MB of workspace
+            src = h.make("vg_create_source", keeper, cloud_xyz, cloud_xyz, None, 1_000_000)
+            before = h.fake.fake_used()
+            h.check("vg_source_destroy", src)
+            assert h.fake.fake_used() == before
+            h.fake.fake_reset()
+            h.fake.fake_budget(h.fake.fake_used() + 512)
+            rc = call()
+            assert rc == 0, (name, rc, h.lib.vg_last_error())
+            assert h.fake.fake_last_error() == 0
+            # nothing left to give back: the call fails, and leaves no error behind
+            h.fake.fake_budget(0)
+            assert h.call("vg_create_source", other, cloud_xyz, cloud_xyz, None, 50_000_000, C.byref(C.c_void_p())) == h.OOM
+            assert h.call("vg_create_graph", h.ctx, 2001, 2000, ni, nj, C.byref(C.c_void_p())) == h.OOM
+            assert h.fake.fake_last_error() == 0
+            h.fake.fake_budget(-1)
+    assert h.fake.fake_bad_frees() == 0
+
+
+def test_kept_memory_never_fails_a_call(run):
+    run("kept_memory_is_given_back")
+
+
+def everything_is_freed(h):
+    """A context gives back all that it kept."""
+    base = h.fake.fake_used()
+    for _ in range(2):
+        h.ctx = h.make("vg_context_create", 0, None)
+        m, s = h.map(100_000, (0.5, 1.0)), h.source(300_000)
+        b = h.batch([s] * 40, [m] * 40)
+        h.check("vg_batch_tune", b, h.poses(40), 1, None)
+        h.check("vg_batch_destroy", b)
+        for call in (("vg_source_destroy", s), ("vg_voxelmap_destroy", m)):
+            h.check(*call)
+        h.check("vg_context_destroy", h.ctx)
+        assert h.fake.fake_used() == base and h.fake.fake_bad_frees() == 0
+
+
+def test_contexts_give_back_what_they_kept(run):
+    run("everything_is_freed")
