@@ -851,8 +851,8 @@ void carve_schedule(vg_batch* b, Carve& c) {
 void carve_rows(vg_batch* b, Carve& c) { b->d_partials = c.take<double>((size_t)kRow * b->h_tiles.size()); }
 
 // The schedule of the batch's launch shape on the device, tables and rows in a block
-// of their own (the ones the batch was created with lie in its block).  A failure
-// leaves the previous block in place.
+// of their own (the tables the batch was created with, and rows of less than
+// kOwnRows, lie in its block).  A failure leaves the previous block in place.
 vg_status upload_schedule(vg_batch* b) {
     hipStream_t st = b->ctx->stream;
     Tile* const units = b->d_units;
@@ -865,7 +865,7 @@ vg_status upload_schedule(vg_batch* b) {
     Carve c{nullptr};
     carve(c);
     char* block = nullptr;
-    vg_status rc = dev_alloc(&block, c.off);
+    vg_status rc = pool_alloc(b->pool.get(), (void**)&block, c.off);
     if (rc == VG_OK) {
         c = Carve{block};
         carve(c);
@@ -879,13 +879,13 @@ vg_status upload_schedule(vg_batch* b) {
         if (e != hipSuccess) rc = hip_fail(e, "schedule upload");
     }
     if (rc != VG_OK) {
-        dfree(block);
+        b->pool->put(block);
         b->d_units = units;
         b->d_tile_first = tile_first;
         b->d_partials = partials;
         return rc;
     }
-    dfree(b->sched);
+    b->pool->put(b->sched);
     b->sched = block;
     return VG_OK;
 }
@@ -924,11 +924,22 @@ vg_status set_shape(vg_batch* b, int block, int tile_points, int blocks_per_cu, 
 // launch; a batch whose tables exceed kStagedTables is uploaded by a copy from
 // ordinary memory (pinning pages costs more than it saves there).
 constexpr size_t kStagedTables = (size_t)1 << 20;
+// Rows from this size on are a block of their own: another launch shape replaces them
+// (5,000 submap factors at the default shape: 110 MB that a tuned batch would keep).
+constexpr size_t kOwnRows = BlockPool::kPooled;
 
 vg_status alloc_batch(vg_batch* b, const std::vector<PointSrc>& points) {
     const size_t F = b->F, L = b->L;
     hipStream_t st = b->ctx->stream;
     size_t tables = 0;   // bytes of the uploaded tables, at the front of the block
+    Carve rc{nullptr};
+    carve_rows(b, rc);
+    const bool own_rows = rc.off >= kOwnRows;
+    if (own_rows) {
+        VG_TRY(pool_alloc(b->pool.get(), (void**)&b->sched, rc.off));
+        rc = Carve{b->sched};
+        carve_rows(b, rc);
+    }
     auto carve = [&](Carve& c) {
         b->d_fac = c.take<FactorDesc>(F);
         carve_schedule(b, c);
@@ -943,7 +954,7 @@ vg_status alloc_batch(vg_batch* b, const std::vector<PointSrc>& points) {
         b->d_inliers = c.take<int64_t>(L * F);
         b->d_e = c.take<double>(F);
         b->d_lm = c.take<double>(32 * F);
-        carve_rows(b, c);
+        if (!own_rows) carve_rows(b, c);
     };
     Carve c{nullptr};
     carve(c);
@@ -1098,7 +1109,7 @@ vg_status linearize_host(vg_batch* b) {
 
 void free_batch(vg_batch* b) {
     b->pool->put(b->dblock);
-    dfree(b->sched);
+    b->pool->put(b->sched);
     dfree(b->d_gslab);
     hfree(b->hblock);
     hfree(b->h_lm);

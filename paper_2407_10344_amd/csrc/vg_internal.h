@@ -300,7 +300,7 @@ struct vg_batch {
     int tile_order = 1;                  // 1 contiguous per XCD, 2 round-robin over XCDs
     // device buffers, carved from one block
     char* dblock = nullptr;
-    char* sched = nullptr;          // tables and rows of a launch shape set after creation
+    char* sched = nullptr;          // large rows, or tables and rows of a launch shape set after creation
     vg::FactorDesc* d_fac = nullptr;
     vg::Tile* d_units = nullptr;
     int32_t* d_tile_first = nullptr;

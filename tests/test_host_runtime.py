@@ -234,3 +234,33 @@ def everything_is_freed(h):
 
 def test_contexts_give_back_what_they_kept(run):
     run("everything_is_freed")
+
+
+def tuned_batches_hold_one_schedule(h):
+    """A batch that was given another launch shape holds the rows of that shape only."""
+    s, m = h.source(1_000_000), h.map(1000)
+
+    def used():   # without what is kept idle: a failing call gives that back
+        h.fake.fake_budget(0)
+        a = (C.c_double * 16)()
+        assert h.call("vg_create_source", h.ctx, a, a, None, 50_000_000, C.byref(C.c_void_p())) == h.OOM
+        h.fake.fake_budget(-1)
+        return h.fake.fake_used()
+
+    for F, tile in ((1, 64), (40, 256), (40, 2048)):
+        base = used()
+        large = h.batch([s] * F, [m] * F, tile_points=16384)
+        lean = used() - base
+        h.check("vg_batch_destroy", large)
+        b = h.batch([s] * F, [m] * F, tile_points=tile)
+        chosen = (C.c_int32 * 4)()
+        h.check("vg_batch_tune", b, h.poses(F), 1, chosen)
+        # rows of 320 bytes a tile and less than 32 of tables, those of the first shape too
+        tiles, first = (F * -(-1_000_000 // t) for t in (chosen[1], tile))
+        assert used() - base <= lean + 1.125 * (tiles * 352 + 4096) + first * 32, (F, tile, chosen[1])
+        h.check("vg_batch_destroy", b)
+        assert used() == base
+
+
+def test_tuned_batches_hold_one_schedule(run):
+    run("tuned_batches_hold_one_schedule")
