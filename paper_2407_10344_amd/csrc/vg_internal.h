@@ -362,15 +362,20 @@ constexpr int kSmallWords = 8192;                    // pinned words of a contex
 struct Scratch {
     vg_context* ctx;
     char* ws;
-    size_t ws_bytes = 0, off = 0, need = 0;
+    size_t ws_bytes = 0, off = 0, need = 0, parts = 0;   // parts: the most that one part of the call needed
+    Scratch* whole = nullptr;
     std::vector<void*> ptrs;
     explicit Scratch(vg_context* c) : ctx(c), ws((char*)c->pool->workspace(&ws_bytes)) {}
+    // temporaries of a part of a call, behind those of the call
+    explicit Scratch(Scratch* of) : ctx(of->ctx), ws(of->ws), ws_bytes(of->ws_bytes), off(of->off), whole(of) {}
     Scratch(const Scratch&) = delete;
     Scratch& operator=(const Scratch&) = delete;
     ~Scratch() {
         if (!ptrs.empty()) (void)hipStreamSynchronize(ctx->stream);   // also on early error returns
         for (void* p : ptrs) (void)hipFree(p);
-        ctx->pool->end_workspace(need <= kKeepWorkspace ? need : 0);
+        need += parts;
+        if (whole) whole->parts = need > whole->parts ? need : whole->parts;
+        else ctx->pool->end_workspace(need <= kKeepWorkspace ? need : 0);
     }
     template <typename T>
     hipError_t get(T** p, size_t count) {
@@ -384,7 +389,7 @@ struct Scratch {
         }
         void* q = nullptr;
         hipError_t e = device_alloc(&q, bytes);
-        if (e != hipSuccess && ws && off == 0) {   // too small for this call, and in its way
+        if (e != hipSuccess && ws && off == 0 && !whole) {   // too small for this call, and in its way
             ctx->pool->drop_workspace();
             ws = nullptr;
             e = device_alloc(&q, bytes);

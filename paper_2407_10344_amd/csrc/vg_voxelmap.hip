@@ -386,10 +386,19 @@ vg_status build_map(vg_context* ctx, Scratch& sc, const double* d_xyz, const dou
         }
         return VG_OK;
     }
-    // all levels in one go; clouds too large for the library's 32-bit item counts level by level
-    if (n * L < (int64_t)1 << 30) return build_levels(ctx, sc, d_xyz, d_cov, n, box, m->lv, L, &m->blocks[0]);
+    // all levels in one go; clouds too large for the library's 32-bit item counts, or
+    // whose temporaries for all levels (50 B a point and level) do not fit, level by level
+    if (n * L < (int64_t)1 << 30) {
+        vg_status rc;
+        {
+            Scratch all(&sc);
+            rc = build_levels(ctx, all, d_xyz, d_cov, n, box, m->lv, L, &m->blocks[0]);
+        }
+        if (rc != VG_ERR_OOM || L == 1) return rc;
+        set_error("");
+    }
     for (int l = 0; l < L; ++l) {
-        Scratch one(ctx);
+        Scratch one(&sc);
         const vg_status rc = build_levels(ctx, one, d_xyz, d_cov, n, box, m->lv + l, 1, &m->blocks[l]);
         if (rc != VG_OK) return rc;
     }

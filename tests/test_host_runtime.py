@@ -264,3 +264,41 @@ def tuned_batches_hold_one_schedule(h):
 
 def test_tuned_batches_hold_one_schedule(run):
     run("tuned_batches_hold_one_schedule")
+
+
+def maps_build_level_by_level_when_short_of_memory(h):
+    """The levels of a map are built together, with the temporaries of all of them; where these
+    do not fit, one after the other, with those of one."""
+    n, res = 20_000_000, (0.25, 0.5, 1.0, 2.0)
+
+    def peak(resolutions, budget=-1):
+        h.check("vg_context_destroy", h.ctx)
+        h.ctx = h.make("vg_context_create", 0, None)
+        h.fake.fake_reset()
+        base = h.fake.fake_used()
+        h.fake.fake_budget(base + budget if budget >= 0 else -1)
+        m = h.map(n, resolutions)
+        assert h.lib.vg_last_error() == b""
+        top = h.fake.fake_peak() - base
+        h.fake.fake_budget(-1)
+        for level in range(len(resolutions)):
+            v, cap = C.c_int64(), C.c_int64()
+            h.check("vg_voxelmap_info", m, level, C.byref(v), C.byref(cap))
+            assert (v.value, cap.value) == (100, 64)
+        assert len(h.launches("k_map_stats")) == (1 if budget < 0 else len(resolutions))
+        h.check("vg_voxelmap_destroy", m)
+        return top
+
+    one, together = peak(res[:1]), peak(res)
+    assert together > 2 * one
+    for budget in (one + 100_000, (one + together) // 2):
+        assert peak(res, budget) <= budget
+    h.fake.fake_budget(h.fake.fake_used() + one // 2)
+    out = C.c_void_p()
+    a, r = (C.c_double * 16)(), (C.c_double * 4)(*res)
+    assert h.call("vg_build_voxelmap", h.ctx, a, a, n, r, 4, C.byref(out)) == h.OOM
+    assert h.fake.fake_bad_frees() == 0
+
+
+def test_maps_build_level_by_level_when_short_of_memory(run):
+    run("maps_build_level_by_level_when_short_of_memory")
