@@ -6,10 +6,10 @@ Default workload: the global submap batch -- 500 synthetic submaps of
 one full linearization of the whole batch with everything resident in HBM:
 the poses are a device buffer before timing starts and the device-pointer
 entry point leaves e/H/b and the inlier counts on the device (pose staging,
-tile kernel, factor reduction).  The host-buffer entry point (one captured
-hipGraph: upload poses, the same kernels, download results) is timed beside
-it and reported as ``host_buffers``; the plain per-factor path is compared
-with that one, since both hand over host buffers.
+tile kernel, factor reduction).  The host-buffer entry point (poses read from
+pinned memory, the same kernels, results written or copied to pinned memory,
+one wait) is timed beside it and reported as ``host_buffers``; the plain
+per-factor path is compared with that one, since both hand over host buffers.
 
 Roofline: the algorithmic bytes are charged for the work the kernel does --
 36 B per walked source point (chunks whose bounds cannot reach a target voxel

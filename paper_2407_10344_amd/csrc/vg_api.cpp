@@ -1,5 +1,5 @@
-// C ABI of the VGICP library: validation, handle lifetime, batch scheduling
-// (tile list, plain per-factor loop, batched launch, captured hipGraph),
+// C ABI of the VGICP library: validation, handle lifetime, device memory, batch
+// scheduling (tiles and units, batched launch, plain per-factor loop),
 // Levenberg-Marquardt driver and the launch-shape autotuner.
 #include <algorithm>
 #include <chrono>
@@ -921,8 +921,10 @@ vg_status set_shape(vg_batch* b, int block, int tile_points, int blocks_per_cu, 
 // from pageable memory: 101 us to create and 97 us to close with its frame's other
 // objects, 48 us and 65 us with the two blocks (21 factors).  The tables are written
 // to the pinned block, which later holds poses and results, and copied by one
-// launch; a batch whose tables exceed kStagedTables is uploaded by a copy from
-// ordinary memory (pinning pages costs more than it saves there).
+// launch, which saves 6 us for 20 factors and nothing measurable from 200 to 2,000.
+// Tables of more than kStagedTables (1 KB a factor) are copied from ordinary memory:
+// staged they would more than double the pinned memory that a batch holds (5,000
+// factors: 470 us to create and close staged, 550 us copied).
 constexpr size_t kStagedTables = (size_t)1 << 20;
 // Rows from this size on are a block of their own: another launch shape replaces them
 // (5,000 submap factors at the default shape: 110 MB that a tuned batch would keep).
@@ -1059,7 +1061,14 @@ vg_status run_evaluate_device(vg_batch* b, const double* d_poses, double* d_e) {
 // of 5,000 points: 45 us a call with the copies in a replayed graph, 39 us with
 // the results copied, 35 us without).  Beyond kDirectFactors factors the rows go
 // through one copy (1,000 factors: 68 us direct, 76 us copied; 4,000: 203 and 199).
+// The poses are read by the kernel at every size: evaluating 20 factors of 200 points
+// takes 24.5 us either way, 2,000 take 51 us (56 us with a copy), 5,000 take 101 us
+// (105), 100,000 take 1.52 ms either way.
 constexpr int64_t kDirectFactors = 2048;
+// Histories of a Levenberg-Marquardt run: written to pinned memory that the batch
+// keeps, up to this size (20 factors, 10 iterations: 300 us, 375 us through device
+// memory; 1,000 factors, 10 iterations: 410 and 525 us).  From 1 MB on the two are
+// within 5 % of each other, either one ahead; the line bounds what a batch keeps.
 constexpr size_t kDirectHistory = (size_t)4 << 20;
 
 double* host_out(vg_batch* b, double* device) { return b->F <= kDirectFactors ? b->h_out : device; }

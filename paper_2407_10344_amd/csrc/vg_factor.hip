@@ -235,8 +235,10 @@ struct ProbeLevel {
           kboxw{lv.kboxw[0], lv.kboxw[1], lv.kboxw[2]}, rec32(lv.rec32), r64(lv.r64) {}
 };
 
-// Per-tile chunk data in LDS.  At 4 waves per SIMD a CU holds at most 16
-// waves, so even one-wave workgroups need at most 16 x 9 KB of the 160 KB.
+// Per-tile chunk data in LDS.  With the queues, lists and row sums a linearizing
+// workgroup takes 14.0 KB at 64 threads, 18.7 KB at 128, 27.9 KB at 256 and 46.3 KB
+// at 512: of the 160 KB a compute unit holds 11, 8, 5 and 3 of them, 11 to 24 waves
+// (the registers of the FP32 kernels allow 16).
 // The FP32 data of one chunk, read together from one LDS address.
 struct ChunkLds {
     float frac32[3];   // anchor position inside its coarse voxel, FP32 (voxel keys; in voxel units in one-level
@@ -546,9 +548,12 @@ __device__ __forceinline__ void drain_hit(A& acc, const FactorDesc* __restrict__
 // Register budget, in waves per SIMD.  The FP32 linearize and backward kernels are
 // held at exactly four (<= 128 VGPRs): the scheduler then keeps loads in flight
 // instead of saving registers for a fifth (five spill: 580 us against 395 us for
-// 575 submap factors).  Evaluate and the counts have few live sums and wait
-// on probe loads, so they run more waves (the same batch: evaluate 331 us at six
-// against 364 us at four; overlap 153 us at eight, 166 us at six, 231 us at four).
+// the 590 factors of 64 submaps).  Evaluate and the counts have few live sums and
+// wait on probe loads, so their registers are held for more waves (the same batch:
+// evaluate 331 us at six against 364 us at four; overlap 153 us at eight, 166 us at
+// six, 231 us at four).  LDS lets the compensated evaluate have five of its six at
+// 256 threads, four at 128 and six at 512, and the counts all eight at 256 threads
+// (15.6 KB a workgroup), six at 128.
 // FP64 and Kahan kernels take what their register count allows (FP64: three; four
 // spill and take 150 us against 128 us over the factors of 20 submaps).
 template <int MODE, int PREC, bool KH>
@@ -663,7 +668,7 @@ __global__ void k_grad_combine(const SharedSrc* __restrict__ ss, int32_t S, int6
 // about 12 ns per atomic, serialised across the XCDs on the counters' one cache
 // line, with one atomic per tile and eight more per workgroup to find every
 // partition empty: that was all of the kernel's time below ~8,192-point tiles
-// (575 submap factors, 81M points, 39,900 tiles of 2,048 points: 675 us with the
+// (590 submap factors, 81M points, 39,900 tiles of 2,048 points: 675 us with the
 // counters, 446 us without; 1,954 FP64 tiles: 237 us, 90 us).
 __device__ __forceinline__ int32_t work_item(int32_t n, int32_t interleave) {
     const int32_t span = (n + kParts - 1) / kParts;
@@ -700,7 +705,7 @@ __global__ void k_copy_words(const uint64_t* __restrict__ in, uint64_t* __restri
 // culled in a submap batch, so what a tile costs besides its points (descriptors,
 // anchors, barriers: 43 % of a wave's time there) was as much as the points.  Each
 // wave picks its chunks from the ballots of the whole unit, without a list that one
-// wave writes and a barrier around it.  575 submap factors: linearize 439 -> 364
+// wave writes and a barrier around it.  590 submap factors: linearize 439 -> 364
 // us, overlap 278 -> 232 us (with one tile per unit 447 and 297 us).  The rows stay
 // one per tile and a wave's share of a tile is the same in any unit, so results do
 // not depend on it.

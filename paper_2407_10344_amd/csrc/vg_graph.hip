@@ -95,7 +95,7 @@ __global__ __launch_bounds__(64 * kAsmWaves) void k_graph_assemble(
                         __builtin_amdgcn_wave_barrier();
                         if (lane < 36) {   // H A
                             double x = 0.0;
-    #pragma unroll
+#pragma unroll
                             for (int q = 0; q < 6; ++q) x += sH[wave][6 * r + q] * sA[wave][6 * q + c];
                             sHA[wave][lane] = x;
                         }
@@ -103,14 +103,14 @@ __global__ __launch_bounds__(64 * kAsmWaves) void k_graph_assemble(
                         if (lane < 36) {
                             if (kind == 3) {          // A^T (H A)
                                 v = 0.0;
-    #pragma unroll
+#pragma unroll
                                 for (int p = 0; p < 6; ++p) v += sA[wave][6 * p + r] * sHA[wave][6 * p + c];
                             } else {                  // -H A or its transpose
                                 v = -sHA[wave][kind == 1 ? lane : 6 * c + r];
                             }
                         } else if (lane < 42) {       // -A^T b (used for kind 3)
                             double x = 0.0;
-    #pragma unroll
+#pragma unroll
                             for (int q = 0; q < 6; ++q) x += sA[wave][6 * q + c] * sB[wave][q];
                             v = -x;
                         }
@@ -231,8 +231,9 @@ extern "C" vg_status vg_graph_assemble_async(vg_graph* g, const double* d_poses,
         return g_invalid("NULL device pointer");
     VG_HIP(hipSetDevice(g->ctx->device));
     hipStream_t st = g->ctx->stream;
-    k_graph_assemble<<<(int)std::min<int64_t>(g->nnzb, 1 << 22), 64 * kAsmWaves, 0, st>>>(g->d_blk_ptr, g->d_blk_item, g->d_blk_node, d_poses, d_lin,
-                                                              d_values, d_rhs, g->nnzb);
+    const int grid = (int)std::min<int64_t>(g->nnzb, 1 << 22);
+    k_graph_assemble<<<grid, 64 * kAsmWaves, 0, st>>>(g->d_blk_ptr, g->d_blk_item, g->d_blk_node, d_poses, d_lin,
+                                                      d_values, d_rhs, g->nnzb);
     VG_HIP(hipGetLastError());
     return VG_OK;
 }

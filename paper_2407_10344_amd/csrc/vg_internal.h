@@ -293,7 +293,6 @@ struct vg_batch {
     std::vector<int32_t> h_tile_first;   // F + 1
     std::vector<vg::Tile> h_units;       // units: runs of whole tiles of one factor
     std::vector<int32_t> h_unit_first;   // F + 1
-    std::vector<int64_t> grad_offsets;   // per unique source
     int64_t total_points = 0;
     int64_t grad_rows = 0;               // rows of the concatenated point gradient
     int block = 256, tile_points = 2048, blocks_per_cu = 0;

@@ -28,7 +28,7 @@ struct BuildLevel {
     int64_t K0[3];        // absolute key of the map origin
     int32_t bmin[3];      // first block per axis (biased block coordinates)
     int32_t wy, wz;       // bits of the block's y and z offsets in a code
-    int32_t v0, b0;       // first voxel / block of the level among all levels'
+    int32_t v0;           // first voxel of the level among all levels'
     uint32_t log2cap;
     uint64_t* slots;
     float* rec32;
@@ -325,7 +325,6 @@ static vg_status build_levels(vg_context* ctx, Scratch& sc, const double* d_xyz,
             return VG_ERR_CAPACITY;
         }
         B.lv[l].v0 = info[2 * l];
-        B.lv[l].b0 = info[2 * l + 1];
         // block table: power of two >= 4 x blocks (load factor <= 1/4)
         uint32_t lg = 6;
         while ((1ull << lg) < 4ull * (uint64_t)q.n_blocks) ++lg;
