@@ -360,13 +360,14 @@ constexpr int kSmallWords = 8192;                    // pinned words of a contex
 // similar size allocate nothing.
 struct Scratch {
     vg_context* ctx;
+    size_t ws_bytes = 0;   // (initialised before ws, whose initialiser sets it)
     char* ws;
-    size_t ws_bytes = 0, off = 0, need = 0, parts = 0;   // parts: the most that one part of the call needed
+    size_t off = 0, need = 0, parts = 0;   // parts: the most that one part of the call needed
     Scratch* whole = nullptr;
     std::vector<void*> ptrs;
     explicit Scratch(vg_context* c) : ctx(c), ws((char*)c->pool->workspace(&ws_bytes)) {}
     // temporaries of a part of a call, behind those of the call
-    explicit Scratch(Scratch* of) : ctx(of->ctx), ws(of->ws), ws_bytes(of->ws_bytes), off(of->off), whole(of) {}
+    explicit Scratch(Scratch* of) : ctx(of->ctx), ws_bytes(of->ws_bytes), ws(of->ws), off(of->off), whole(of) {}
     Scratch(const Scratch&) = delete;
     Scratch& operator=(const Scratch&) = delete;
     ~Scratch() {

@@ -28,7 +28,7 @@ std::map<std::string, int64_t> g_values;   // results stood in for
 std::map<uintptr_t, size_t> g_live;
 uintptr_t g_next = (uintptr_t)1 << 44;
 size_t g_used = 0, g_peak = 0, g_budget = ~(size_t)0;
-int64_t g_failed = 0, g_bad_frees = 0, g_fail_at = -1, g_mallocs = 0;
+int64_t g_failed = 0, g_bad_frees = 0, g_fail_at = -1, g_mallocs = 0, g_allocations = 0;
 hipError_t g_last = hipSuccess;
 hipError_t fail(hipError_t e) { return g_last = e; }
 
@@ -84,7 +84,7 @@ extern "C" {
 // ---------------------------------------------------------------- controls
 void fake_reset() {
     g_launches.clear();
-    g_failed = g_bad_frees = g_mallocs = 0;
+    g_failed = g_bad_frees = g_mallocs = g_allocations = 0;
     g_peak = g_used;
 }
 void fake_budget(int64_t bytes) { g_budget = bytes < 0 ? ~(size_t)0 : (size_t)bytes; }
@@ -96,6 +96,7 @@ void fake_watch(const char* name, int n) { g_watch[name] = n; }
 void fake_set(const char* key, int64_t v) { g_values[key] = v; }
 int64_t fake_used() { return (int64_t)g_used; }
 int64_t fake_peak() { return (int64_t)g_peak; }
+int64_t fake_allocations() { return g_allocations; }
 int64_t fake_failed() { return g_failed; }
 int64_t fake_bad_frees() { return g_bad_frees; }
 int64_t fake_last_error() { return (int64_t)g_last; }
@@ -150,6 +151,7 @@ hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3 block, void** args, si
 // ---------------------------------------------------------------- memory
 hipError_t hipMalloc(void** p, size_t bytes) {
     *p = nullptr;
+    ++g_allocations;
     if ((g_fail_at >= 0 && g_mallocs++ >= g_fail_at) || bytes > g_budget || g_used > g_budget - bytes) {
         ++g_failed;
         return fail(hipErrorOutOfMemory);

@@ -51,7 +51,7 @@ class Host:
         self.fake = C.CDLL(runtime, mode=C.RTLD_GLOBAL)
         self.lib = C.CDLL(LIB)
         f = self.fake
-        for name in ("used", "peak", "failed", "bad_frees", "last_error", "launches"):
+        for name in ("used", "peak", "failed", "bad_frees", "last_error", "launches", "allocations"):
             getattr(f, "fake_" + name).restype = C.c_int64
         f.fake_name.restype, f.fake_name.argtypes = C.c_char_p, [C.c_int64]
         f.fake_grid.restype, f.fake_grid.argtypes = C.c_uint32, [C.c_int64]

@@ -302,3 +302,30 @@ def maps_build_level_by_level_when_short_of_memory(h):
 
 def test_maps_build_level_by_level_when_short_of_memory(run):
     run("maps_build_level_by_level_when_short_of_memory")
+
+
+def repeated_calls_allocate_nothing(h):
+    """Temporaries come from the workspace and large objects from kept blocks once a call of
+    that size has been made."""
+    xyz, sensor, res = (C.c_double * 16)(), (C.c_double * 3)(), (C.c_double * 2)(0.5, 1.0)
+    h.set("voxels", 20_000)
+    h.set("blocks", 5000)
+
+    def frame():
+        h.set("downsampled", 40_000)
+        cloud = h.make("vg_preprocess", h.ctx, xyz, 100_000, C.c_double(0.5), 10, sensor)
+        objects = [("vg_source_destroy", h.make("vg_create_source_from_cloud", h.ctx, cloud)),
+                   ("vg_voxelmap_destroy", h.make("vg_build_voxelmap_from_cloud", h.ctx, cloud, res, 2)),
+                   ("vg_voxelmap_destroy", h.map(150_000, (0.25, 0.5, 1.0))), ("vg_source_destroy", h.source(150_000)),
+                   ("vg_cloud_destroy", cloud)]
+        for name, handle in objects:
+            h.check(name, handle)
+
+    for call in range(4):
+        h.fake.fake_reset()
+        frame()
+        assert call == 0 or h.fake.fake_allocations() == 0, (call, h.fake.fake_allocations())
+
+
+def test_repeated_calls_allocate_nothing(run):
+    run("repeated_calls_allocate_nothing")
