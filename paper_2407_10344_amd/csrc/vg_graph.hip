@@ -20,6 +20,7 @@
 struct vg_graph {
     vg_context* ctx = nullptr;
     int64_t N = 0, F = 0, nnzb = 0;
+    int64_t longest = 0;                     // contributions of a block at most
     std::vector<int64_t> row_ptr, col_idx;   // BSR structure (host copy)
     // contributions: per block slot, a list of (factor, kind); kind 0 ii, 1 ij, 2 ji, 3 jj
     int32_t* d_blk_ptr = nullptr;   // nnzb + 1
@@ -29,8 +30,6 @@ struct vg_graph {
 };
 
 namespace vg {
-
-constexpr int kAsmWaves = 4;
 
 // Entry (i, j) of A = Ad(T^-1) for T = (R, t): T^-1 = (R', t') = (R^T, -R^T t) and
 // Ad = [[R', 0], [(t')x R', R']].  P (uniform): R row-major, t.
@@ -52,20 +51,29 @@ __device__ __forceinline__ double adjoint_entry(const double* __restrict__ P, in
 }
 
 // One workgroup per BSR block: its contributions are dealt to the waves in rounds of
-// kAsmWaves, lane k < 36 of a wave making entry (k / 6, k % 6) of one contribution
+// WAVES, lane k < 36 of a wave making entry (k / 6, k % 6) of one contribution
 // and, for a diagonal block, lanes 36..41 the node's right-hand side; the workgroup
 // adds a round's contributions in list order.  Bound by the chain of dependent
 // loads (list, factor row, pose) of the longest list, so the list is read once by
-// the lanes and the rounds are few: a node of 20 factors takes five.  Making A in
-// place (a few selects and nine multiply-adds per lane) leaves no launch and no
-// buffer for it.  500 nodes, 5,000 factors: 55 us a call
-// with separate kernels for A, blocks and right-hand side, 45 us so, most of it the
-// host ordering the two streams.
-__global__ __launch_bounds__(64 * kAsmWaves) void k_graph_assemble(
+// the lanes and, with four waves, the rounds are few: a node of 20 factors takes
+// five.  Making A in place (a few selects and nine multiply-adds per lane) leaves no
+// launch and no buffer for it.  500 nodes, 5,000 factors: 55 us a call with separate
+// kernels for A, blocks and right-hand side, 45 us so, most of it the host ordering
+// the two streams.
+// A graph of many blocks fills the device however long a chain takes, and most of its
+// blocks have one contribution, which leaves three of four waves idle: a block costs
+// 0.75 ns with one wave and 1.6 ns with four, a contribution of the longest list 0.73
+// and 0.22 us.  So one wave from 600 blocks per contribution on: 20,000 nodes and
+// 200,000 factors (248,000 blocks, lists of 42) 184 us (four waves 406), 25,000 blocks
+// with lists of 34 41 us (49); four waves for 12,000 blocks with lists of 34, 23 us
+// (one 25), and for 600 nodes all to all (360,000 blocks, lists of 599), 641 us (755).
+constexpr int64_t kBlocksPerContribution = 600;
+template <int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void k_graph_assemble(
     const int32_t* __restrict__ blk_ptr, const int32_t* __restrict__ blk_item, const int32_t* __restrict__ blk_node,
     const double* __restrict__ poses, const double* __restrict__ lin, double* __restrict__ values,
     double* __restrict__ rhs, int64_t n_blocks) {
-    __shared__ double sH[kAsmWaves][36], sA[kAsmWaves][36], sHA[kAsmWaves][36], sB[kAsmWaves][6], sV[2][kAsmWaves][42];
+    __shared__ double sH[WAVES][36], sA[WAVES][36], sHA[WAVES][36], sB[WAVES][6], sV[2][WAVES][42];
     for (int64_t s = blockIdx.x; s < n_blocks; s += gridDim.x) {
         const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
         const int r = lane / 6, c = lane % 6;   // of lanes 0..35; r == 6: the right-hand side
@@ -76,7 +84,7 @@ __global__ __launch_bounds__(64 * kAsmWaves) void k_graph_assemble(
         for (int32_t base = i0; base < i1; base += 64) {
             const int32_t mine = base + lane < i1 ? blk_item[base + lane] : 0;
             const int cnt = min(64, i1 - base);
-            for (int k0 = 0; k0 < cnt; k0 += kAsmWaves, buf ^= 1) {
+            for (int k0 = 0; k0 < cnt; k0 += WAVES, buf ^= 1) {
                 const int k = k0 + wave;
                 if (k < cnt) {   // uniform per wave
                     const int32_t item = __builtin_amdgcn_readlane(mine, k);
@@ -119,7 +127,7 @@ __global__ __launch_bounds__(64 * kAsmWaves) void k_graph_assemble(
                 }
                 __syncthreads();   // (the sums of the round before last are done with this half of sV)
                 if (threadIdx.x < 42) {
-                    for (int w = 0; w < min(kAsmWaves, cnt - k0); ++w) acc += sV[buf][w][threadIdx.x];
+                    for (int w = 0; w < min(WAVES, cnt - k0); ++w) acc += sV[buf][w][threadIdx.x];
                 }
             }
         }
@@ -188,6 +196,7 @@ extern "C" vg_status vg_create_graph(vg_context* ctx, int64_t N, int64_t F, cons
         g->row_ptr[kv.first.first + 1] += 1;
         g->col_idx.push_back(kv.first.second);
         for (int32_t it : kv.second) bitem.push_back(it);
+        g->longest = std::max<int64_t>(g->longest, (int64_t)bitem.size() - bptr.back());
         bptr.push_back((int32_t)bitem.size());
         bnode.push_back(kv.first.first == kv.first.second ? (int32_t)kv.first.first : -1);
     }
@@ -232,8 +241,12 @@ extern "C" vg_status vg_graph_assemble_async(vg_graph* g, const double* d_poses,
     VG_HIP(hipSetDevice(g->ctx->device));
     hipStream_t st = g->ctx->stream;
     const int grid = (int)std::min<int64_t>(g->nnzb, 1 << 22);
-    k_graph_assemble<<<grid, 64 * kAsmWaves, 0, st>>>(g->d_blk_ptr, g->d_blk_item, g->d_blk_node, d_poses, d_lin,
-                                                      d_values, d_rhs, g->nnzb);
+    if (g->nnzb > kBlocksPerContribution * g->longest)
+        k_graph_assemble<1><<<grid, 64, 0, st>>>(g->d_blk_ptr, g->d_blk_item, g->d_blk_node, d_poses, d_lin, d_values,
+                                                 d_rhs, g->nnzb);
+    else
+        k_graph_assemble<4><<<grid, 256, 0, st>>>(g->d_blk_ptr, g->d_blk_item, g->d_blk_node, d_poses, d_lin, d_values,
+                                                  d_rhs, g->nnzb);
     VG_HIP(hipGetLastError());
     return VG_OK;
 }

@@ -56,3 +56,44 @@ def test_graph_assembly_matches_oracle():
     g.close()
     batch.close()
     ctx.close()
+
+
+def test_graphs_of_many_blocks():
+    """5,000 nodes, 30,000 factors, 42,760 blocks of at most 30 contributions (a wave a block):
+    the rows of the first nodes equal, bit for bit, those of the graph of their factors alone
+    (four waves a block), and the oracle's dense assembly of these within 1e-13 of the largest
+    entries (36 products a contribution, FP64)."""
+    from paper_2407_10344_amd import vgicp
+    ctx = vgicp.Context(0)
+    rng = np.random.default_rng(11)
+    N, F, few = 5000, 30_000, 20
+    ni = rng.integers(0, N, F)
+    nj = (ni + rng.integers(1, 7, F)) % N
+    T = np.stack([synth.configs.random_pose(rng, 40.0, 3.0) for _ in range(F)])
+    H = rng.normal(size=(F, 6, 6))
+    H = H @ H.transpose(0, 2, 1)
+    b = rng.normal(size=(F, 6))
+    lin = torch.tensor(np.concatenate([np.zeros((F, 1)), H.reshape(F, 36), b], axis=1), device="cuda")
+    poses = torch.tensor(vgicp.poses12(T), device="cuda")
+    g = vgicp.Graph(ctx, N, ni, nj)
+    assert g.nnzb > 40_000
+    values, rhs = g.assemble(poses, lin)
+    own = np.flatnonzero((ni < few) | (nj < few))       # every factor of the first nodes
+    sub = vgicp.Graph(ctx, N, ni[own], nj[own])
+    sv, sr = sub.assemble(poses[own], lin[own])
+    torch.cuda.synchronize()
+    n = g.row_ptr[few]
+    assert sub.nnzb < 16_384 and n == sub.row_ptr[few] and np.array_equal(g.col_idx[:n], sub.col_idx[:n])
+    assert torch.equal(values[:n], sv[:n]) and torch.equal(rhs[:few], sr[:few])
+    ids = np.unique(np.concatenate([ni[own], nj[own], np.arange(few)]))
+    Hd, bd = assemble_dense(len(ids), np.searchsorted(ids, ni[own]), np.searchsorted(ids, nj[own]), H[own], b[own],
+                            list(T[own]))
+    v = sv.cpu().numpy()
+    for r in range(few):
+        for k in range(sub.row_ptr[r], sub.row_ptr[r + 1]):
+            i, j = np.searchsorted(ids, (r, sub.col_idx[k]))
+            assert np.abs(v[k] - Hd[6 * i:6 * i + 6, 6 * j:6 * j + 6]).max() <= 1e-13 * np.abs(Hd).max()
+        assert np.abs(sr[r].cpu().numpy() - bd[6 * r:6 * r + 6]).max() <= 1e-13 * np.abs(bd).max()
+    g.close()
+    sub.close()
+    ctx.close()

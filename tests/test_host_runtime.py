@@ -329,3 +329,26 @@ def repeated_calls_allocate_nothing(h):
 
 def test_repeated_calls_allocate_nothing(run):
     run("repeated_calls_allocate_nothing")
+
+
+def waves_follow_the_blocks_of_a_graph(h):
+    """A graph of many blocks for the length of its lists is assembled by one wave a block (most
+    blocks have one contribution), another by four."""
+    d = C.c_void_p(1 << 45)
+    path = [(i, i + 1) for i in range(7999)]            # 24,000 blocks
+    for N, edges, waves in ((100, [(0, i) for i in range(1, 100)], 4), (8000, path, 1),
+                            (8000, path + [(0, 9)] * 36, 1), (8000, path + [(0, 9)] * 40, 4)):
+        F = len(edges)
+        ni, nj = (C.c_int64 * F)(*[e[0] for e in edges]), (C.c_int64 * F)(*[e[1] for e in edges])
+        g = h.make("vg_create_graph", h.ctx, N, F, ni, nj)
+        blocks = C.c_int64()
+        h.check("vg_graph_structure", g, C.byref(blocks), None, None)
+        h.fake.fake_reset()
+        h.check("vg_graph_assemble_async", g, d, d, d, d)
+        (_, grid, block, _), = h.launches("k_graph_assemble")
+        assert (grid, block) == (blocks.value, 64 * waves), (N, F, grid, block)
+        h.check("vg_graph_destroy", g)
+
+
+def test_waves_follow_the_blocks_of_a_graph(run):
+    run("waves_follow_the_blocks_of_a_graph")
