@@ -201,3 +201,18 @@ def test_differentiation_batch_full_size(vg):
         print("factor", f, "near-face choices", n_face, "rel err xi %.3g points %.3g" % (ex, ep), flush=True)
         assert ex <= 1e-5 and ep <= 1e-5
     batch.close()
+
+
+@pytest.mark.parametrize("F", [1, 63, 64, 65, 1000])
+def test_poses_alone_equal_poses_with_jacobians(vg, F):
+    """Retractions without Jacobians (a thread per factor) have the bits of those with them (a
+    wave per factor), from zero to large tangents."""
+    vgicp, ctx = vg
+    rng = np.random.default_rng(F)
+    T0 = np.stack([expm(twist(rng.normal(size=6))) for _ in range(F)])
+    xi = rng.normal(size=(F, 6)) * 10.0 ** rng.uniform(-8, 1, size=(F, 1))
+    xi[0] = 0.0
+    d_T0, d_xi = torch.tensor(vgicp.poses12(T0), device="cuda"), torch.tensor(xi, device="cuda")
+    T, _ = ctx.se3_retract(d_T0, d_xi)
+    alone, none = ctx.se3_retract(d_T0, d_xi, jacobian=False)
+    assert none is None and torch.equal(T, alone)

@@ -352,3 +352,18 @@ def waves_follow_the_blocks_of_a_graph(h):
 
 def test_waves_follow_the_blocks_of_a_graph(run):
     run("waves_follow_the_blocks_of_a_graph")
+
+
+def poses_alone_take_a_thread_each(h):
+    """Retractions without their Jacobians: a thread per factor; with them a wave."""
+    d = C.c_void_p(1 << 45)
+    for F in (1, 64, 65, 1_000_000):
+        for jr, threads in ((None, -(-F // 64) * 64), (d, 64 * F)):
+            h.fake.fake_reset()
+            h.check("vg_se3_retract_async", h.ctx, F, d, d, d, jr)
+            (_, grid, block, _), = h.launches("k_se3")
+            assert grid * block == threads
+
+
+def test_poses_alone_take_a_thread_each(run):
+    run("poses_alone_take_a_thread_each")
