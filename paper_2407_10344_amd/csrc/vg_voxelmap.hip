@@ -404,39 +404,81 @@ vg_status build_map(vg_context* ctx, Scratch& sc, const double* d_xyz, const dou
     return VG_OK;
 }
 
+// Order of a small level's records by key, on the host: the key's offset in the level's
+// key box, sorted by digits from the lowest.
+static void order_on_host(const Level& lv, const std::vector<uint64_t>& keys, std::vector<int32_t>& order) {
+    const size_t V = keys.size();
+    const int by = bits_for((uint64_t)(lv.kmax[1] - lv.kmin[1])), bz = bits_for((uint64_t)(lv.kmax[2] - lv.kmin[2]));
+    const int bits = bits_for((uint64_t)(lv.kmax[0] - lv.kmin[0])) + by + bz;
+    std::vector<uint64_t> code(V), code2(V);
+    std::vector<int32_t> order2(V);
+    for (size_t v = 0; v < V; ++v) {
+        int64_t q[3];
+        unpack_key(keys[v], q);
+        code[v] = ((((uint64_t)(q[0] - lv.kmin[0]) << by) | (uint64_t)(q[1] - lv.kmin[1])) << bz) |
+                  (uint64_t)(q[2] - lv.kmin[2]);
+        order[v] = (int32_t)v;
+    }
+    constexpr int kDigit = 10;
+    for (int s = 0; s < bits; s += kDigit) {
+        uint32_t at[1 << kDigit] = {};
+        for (size_t v = 0; v < V; ++v) ++at[(code[v] >> s) & ((1u << kDigit) - 1)];
+        uint32_t sum = 0;
+        for (uint32_t& n : at) {
+            const uint32_t k = n;
+            n = sum;
+            sum += k;
+        }
+        for (size_t v = 0; v < V; ++v) {
+            const uint32_t to = at[(code[v] >> s) & ((1u << kDigit) - 1)]++;
+            code2[to] = code[v];
+            order2[to] = order[v];
+        }
+        code.swap(code2);
+        order.swap(order2);
+    }
+}
+
 // A level in canonical order (ascending lexicographic key): its records are in
-// block order, and no kernel needs the canonical one, so the rows are ordered here.
+// block order, and no kernel needs the canonical one, so the rows are ordered here:
+// levels of up to kHostOrder voxels on the host, where a sort's launches on the
+// device take longer (2,000 voxels: 66 us a call, 130 us on the device; 15,500: 362
+// and 414; 31,000: 696 and 691).
+constexpr int64_t kHostOrder = 1 << 14;
 vg_status export_level(vg_context* ctx, const Level& lv, int64_t* keys, double* means, double* covs,
                        int64_t* counts) {
     hipStream_t st = ctx->stream;
     const int64_t V = lv.V;
     if (V == 0) return VG_OK;
-    Scratch sc(ctx);
-    uint64_t* ks = nullptr;
-    int32_t *id = nullptr, *order = nullptr;
-    char* tmp = nullptr;
-    size_t tb = 0;
-    (void)hipcub::DeviceRadixSort::SortPairs(nullptr, tb, lv.keys, ks, id, order, (int)V, 0, 3 * kKeyBits);
-    VG_HIP(sc.get(&ks, V));
-    VG_HIP(sc.get(&id, V));
-    VG_HIP(sc.get(&order, V));
-    VG_HIP(sc.get(&tmp, tb + 256));
-    k_iota<<<grid_of(V), 256, 0, st>>>(id, V);
-    VG_HIP(hipGetLastError());
-    tb += 256;
-    VG_HIP(hipcub::DeviceRadixSort::SortPairs(tmp, tb, lv.keys, ks, id, order, (int)V, 0, 3 * kKeyBits, st));
     std::vector<uint64_t> k((size_t)V);
     std::vector<int32_t> c((size_t)V), l2r((size_t)V);
     std::vector<double> r((size_t)V * kRec64);
-    VG_HIP(hipMemcpyAsync(k.data(), ks, sizeof(uint64_t) * V, hipMemcpyDeviceToHost, st));
+    Scratch sc(ctx);
+    if (V > kHostOrder) {
+        uint64_t* ks = nullptr;
+        int32_t *id = nullptr, *order = nullptr;
+        char* tmp = nullptr;
+        size_t tb = 0;
+        (void)hipcub::DeviceRadixSort::SortPairs(nullptr, tb, lv.keys, ks, id, order, (int)V, 0, 3 * kKeyBits);
+        VG_HIP(sc.get(&ks, V));
+        VG_HIP(sc.get(&id, V));
+        VG_HIP(sc.get(&order, V));
+        VG_HIP(sc.get(&tmp, tb + 256));
+        k_iota<<<grid_of(V), 256, 0, st>>>(id, V);
+        VG_HIP(hipGetLastError());
+        tb += 256;
+        VG_HIP(hipcub::DeviceRadixSort::SortPairs(tmp, tb, lv.keys, ks, id, order, (int)V, 0, 3 * kKeyBits, st));
+        VG_HIP(hipMemcpyAsync(l2r.data(), order, sizeof(int32_t) * V, hipMemcpyDeviceToHost, st));
+    }
+    VG_HIP(hipMemcpyAsync(k.data(), lv.keys, sizeof(uint64_t) * V, hipMemcpyDeviceToHost, st));
     VG_HIP(hipMemcpyAsync(c.data(), lv.counts, sizeof(int32_t) * V, hipMemcpyDeviceToHost, st));
-    VG_HIP(hipMemcpyAsync(l2r.data(), order, sizeof(int32_t) * V, hipMemcpyDeviceToHost, st));
     VG_HIP(hipMemcpyAsync(r.data(), lv.rec64, sizeof(double) * kRec64 * V, hipMemcpyDeviceToHost, st));
     VG_HIP(hipStreamSynchronize(st));
+    if (V <= kHostOrder) order_on_host(lv, k, l2r);
     for (int64_t v = 0; v < V; ++v) {
         int64_t q[3];
-        unpack_key(k[v], q);
         const int64_t w = l2r[v];
+        unpack_key(k[w], q);
         if (keys)
             for (int a = 0; a < 3; ++a) keys[3 * v + a] = q[a] + lv.K0[a];
         if (means)

@@ -248,3 +248,21 @@ def test_bad_values_are_refused_wherever_they_are(vg, n):
     with pytest.raises(VGError, match="xyz"):
         vgicp.Cloud(ctx, bad["xyz"], 0.5)
     vgicp.Source(ctx, xyz, cov, nrm).close()
+
+
+@pytest.mark.parametrize("V", [1, 2, 1023, 1025, 16_384, 16_385, 40_000])
+def test_exported_order_on_host_and_device(vg, V):
+    """Levels on both sides of the size up to which the rows are ordered on the host: keys
+    ascending, each voxel's point and covariance with its key, bit for bit."""
+    vgicp, ctx = vg
+    rng = np.random.default_rng(V)
+    cells = rng.choice(200 * 90 * 31, size=V, replace=False)
+    key = np.stack([cells // (90 * 31) - 150, cells // 31 % 90 - 3, cells % 31 + 700], axis=1)
+    xyz = key + rng.uniform(0.01, 0.99, size=(V, 3))
+    cov = np.tile([1.0, 0.0, 0.0, 1.0, 0.0, 1.0], (V, 1)) * rng.uniform(0.5, 2.0, size=(V, 1))
+    m = vgicp.VoxelMap(ctx, xyz, cov, (1.0,))
+    keys, means, covs, counts = m.export(0)
+    o = np.lexsort(key.T[::-1])
+    assert np.array_equal(keys, key[o]) and np.array_equal(means, xyz[o]) and np.array_equal(covs, cov[o])
+    assert np.all(counts == 1)
+    m.close()

@@ -367,3 +367,20 @@ def poses_alone_take_a_thread_each(h):
 
 def test_poses_alone_take_a_thread_each(run):
     run("poses_alone_take_a_thread_each")
+
+
+def small_levels_are_ordered_on_the_host(h):
+    """Exporting a level launches nothing up to 16,384 voxels."""
+    for voxels, launches in ((1, 0), (16_384, 0), (16_385, 2)):
+        h.set("voxels", voxels)
+        m = h.map(20_000)
+        h.fake.fake_reset()
+        n = C.c_int64(voxels)
+        k, f, c = (C.c_int64 * (3 * voxels))(), (C.c_double * (6 * voxels))(), (C.c_int64 * voxels)()
+        h.check("vg_voxelmap_export", m, 0, C.byref(n), k, f, f, c)
+        assert n.value == voxels and min(len(h.launches()), 2) == launches
+        h.check("vg_voxelmap_destroy", m)
+
+
+def test_small_levels_are_ordered_on_the_host(run):
+    run("small_levels_are_ordered_on_the_host")
