@@ -58,7 +58,7 @@ typedef enum {
     VG_OK = 0,
     VG_ERR_INVALID_ARG = -1, /* a pointer, size, pose or option is invalid */
     VG_ERR_HIP = -2,         /* a HIP runtime call failed (message has the HIP string) */
-    VG_ERR_OOM = -3,         /* device or pinned host allocation failed */
+    VG_ERR_OOM = -3,         /* an allocation on the device or the host failed */
     VG_ERR_KEY_RANGE = -4,   /* a target voxel key lies outside the packable range */
     VG_ERR_CAPACITY = -5,    /* too many voxels in one level, downsampled points in a frame or
                                 tiles for the fixed scratch */

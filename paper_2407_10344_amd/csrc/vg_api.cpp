@@ -315,6 +315,11 @@ namespace vg {
 void set_error(const std::string& msg) { g_err = msg; }
 bool context_ok(const vg_context* c) { return ctx_ok(c); }
 
+vg_status out_of_host_memory() {
+    set_error("out of memory");
+    return VG_ERR_OOM;
+}
+
 vg_status hip_fail(hipError_t e, const char* what) {
     (void)hipGetLastError();
     g_err = std::string("HIP error in ") + what + ": " + hipGetErrorString(e);
@@ -331,7 +336,7 @@ extern "C" const char* vg_last_error(void) { return g_err.c_str(); }
 
 extern "C" int32_t vg_version(void) { return 10000; }
 
-extern "C" vg_status vg_context_create(int32_t device, void* hip_stream, vg_context** out) {
+extern "C" vg_status vg_context_create(int32_t device, void* hip_stream, vg_context** out) try {
     g_err.clear();
     if (out == nullptr) return invalid("out is NULL");
     *out = nullptr;
@@ -351,7 +356,8 @@ extern "C" vg_status vg_context_create(int32_t device, void* hip_stream, vg_cont
         set_error("device " + std::to_string(device) + " is " + arch + "; this library is built for gfx950 only");
         return VG_ERR_HIP;
     }
-    auto* c = new vg_context();
+    auto own = std::make_unique<vg_context>();
+    vg_context* c = own.get();
     c->device = device;
     c->pool = std::make_shared<BlockPool>(device);
     c->num_cu = prop.multiProcessorCount;
@@ -372,27 +378,23 @@ extern "C" vg_status vg_context_create(int32_t device, void* hip_stream, vg_cont
     c->arch = arch;
     c->name = prop.name;
     e = hipHostMalloc((void**)&c->h_small, sizeof(int32_t) * kSmallWords, hipHostMallocDefault);
-    if (e != hipSuccess) {
-        delete c;
-        return hip_fail(e, "hipHostMalloc");
-    }
+    if (e != hipSuccess) return hip_fail(e, "hipHostMalloc");
     if (hip_stream != nullptr) {
         c->stream = (hipStream_t)hip_stream;
     } else {
         e = hipStreamCreateWithFlags(&c->stream, hipStreamNonBlocking);
         if (e != hipSuccess) {
             (void)hipHostFree(c->h_small);
-            delete c;
             return hip_fail(e, "hipStreamCreateWithFlags");
         }
         c->own_stream = true;
     }
     c->magic = kCtxMagic;
-    *out = c;
+    *out = own.release();
     return VG_OK;
-}
+} VG_NO_THROW
 
-extern "C" vg_status vg_context_destroy(vg_context* ctx) {
+extern "C" vg_status vg_context_destroy(vg_context* ctx) try {
     g_err.clear();
     if (!ctx_ok(ctx)) return state_err("invalid context");
     (void)hipSetDevice(ctx->device);
@@ -403,7 +405,7 @@ extern "C" vg_status vg_context_destroy(vg_context* ctx) {
     ctx->magic = 0;
     delete ctx;
     return VG_OK;
-}
+} VG_NO_THROW
 
 // Upload of a caller's cloud (covariances and normals may be NULL) and its check
 // on the device: every value finite, every covariance SPD.  box: its bounding box.
@@ -440,18 +442,18 @@ static vg_status make_voxelmap(vg_context* ctx, Scratch& sc, const double* d_xyz
                                const double* resolutions, int32_t L, const double* first, const double box[6],
                                vg_voxelmap** out) {
     auto* m = new vg_voxelmap();
+    AtExit drop([&] {
+        (void)hipStreamSynchronize(ctx->stream);
+        if (m->pool) free_map(m);
+        delete m;
+    });
     m->ctx = ctx;
     m->pool = ctx->pool;
     m->L = L;
     const double rmax = resolutions[L - 1];
     for (int a = 0; a < 3; ++a) m->origin[a] = (n > 0) ? rmax * std::nearbyint(first[a] / rmax) : 0.0;
-    const vg_status st = build_map(ctx, sc, d_xyz, d_cov, n, box, resolutions, L, m);
-    if (st != VG_OK) {
-        (void)hipStreamSynchronize(ctx->stream);
-        free_map(m);
-        delete m;
-        return st;
-    }
+    VG_TRY(build_map(ctx, sc, d_xyz, d_cov, n, box, resolutions, L, m));
+    drop.armed = false;
     m->magic = kMapMagic;
     *out = m;
     return VG_OK;
@@ -469,7 +471,7 @@ static vg_status check_resolutions(const double* resolutions, int32_t L) {
 }
 
 extern "C" vg_status vg_build_voxelmap(vg_context* ctx, const double* xyz, const double* cov, int64_t n,
-                                       const double* resolutions, int32_t L, vg_voxelmap** out) {
+                                       const double* resolutions, int32_t L, vg_voxelmap** out) try {
     g_err.clear();
     const TimelineRange range_("vg_build_voxelmap");
     if (!ctx_ok(ctx)) return state_err("invalid context");
@@ -484,19 +486,19 @@ extern "C" vg_status vg_build_voxelmap(vg_context* ctx, const double* xyz, const
     double box[6], *d_xyz = nullptr, *d_cov = nullptr;
     VG_TRY(upload_cloud(ctx, sc, xyz, cov, nullptr, n, &d_xyz, &d_cov, nullptr, box));
     return make_voxelmap(ctx, sc, d_xyz, d_cov, n, resolutions, L, xyz, box, out);
-}
+} VG_NO_THROW
 
-extern "C" vg_status vg_voxelmap_info(const vg_voxelmap* map, int32_t level, int64_t* n_voxels, int64_t* capacity) {
+extern "C" vg_status vg_voxelmap_info(const vg_voxelmap* map, int32_t level, int64_t* n_voxels, int64_t* capacity) try {
     g_err.clear();
     if (!map_ok(map)) return state_err("invalid voxel map");
     if (level < 0 || level >= map->L) return invalid("level out of range");
     if (n_voxels) *n_voxels = map->lv[level].V;
     if (capacity) *capacity = (int64_t)1 << map->lv[level].log2cap;
     return VG_OK;
-}
+} VG_NO_THROW
 
 extern "C" vg_status vg_voxelmap_export(const vg_voxelmap* map, int32_t level, int64_t* n_voxels, int64_t* keys,
-                                        double* means, double* covs, int64_t* counts) {
+                                        double* means, double* covs, int64_t* counts) try {
     g_err.clear();
     if (!map_ok(map)) return state_err("invalid voxel map");
     if (level < 0 || level >= map->L) return invalid("level out of range");
@@ -509,9 +511,9 @@ extern "C" vg_status vg_voxelmap_export(const vg_voxelmap* map, int32_t level, i
     *n_voxels = V;
     VG_HIP(hipSetDevice(map->ctx->device));
     return export_level(map->ctx, map->lv[level], keys, means, covs, counts);
-}
+} VG_NO_THROW
 
-extern "C" vg_status vg_voxelmap_destroy(vg_voxelmap* map) {
+extern "C" vg_status vg_voxelmap_destroy(vg_voxelmap* map) try {
     g_err.clear();
     if (!map_ok(map)) return state_err("invalid voxel map");
     if (map->users > 0) return state_err("voxel map is used by a live batch");
@@ -521,7 +523,7 @@ extern "C" vg_status vg_voxelmap_destroy(vg_voxelmap* map) {
     map->magic = 0;
     delete map;
     return VG_OK;
-}
+} VG_NO_THROW
 
 // ============================================================================ sources
 
@@ -562,6 +564,11 @@ static vg_status make_source(vg_context* ctx, Scratch& sc, const double* d_xyz, 
                              const double* d_nrm, bool has_normals, int64_t n, const double* first,
                              const double box[6], vg_source** out) {
     auto* s = new vg_source();
+    AtExit drop([&] {
+        (void)hipStreamSynchronize(ctx->stream);
+        if (s->pool) s->pool->put(s->block);
+        delete s;
+    });
     s->ctx = ctx;
     s->pool = ctx->pool;
     s->n = n;
@@ -569,21 +576,16 @@ static vg_status make_source(vg_context* ctx, Scratch& sc, const double* d_xyz, 
     s->n_chunks = s->n_pad / kChunk;
     s->has_normals = has_normals;
     for (int a = 0; a < 3; ++a) s->origin[a] = (n > 0) ? std::nearbyint(first[a]) : 0.0;
-    vg_status st = alloc_source(s);
-    if (st == VG_OK && n > 0) st = layout_source(ctx, sc, s, d_xyz, d_cov, d_nrm, box);
-    if (st != VG_OK) {
-        (void)hipStreamSynchronize(ctx->stream);
-        s->pool->put(s->block);
-        delete s;
-        return st;
-    }
+    VG_TRY(alloc_source(s));
+    if (n > 0) VG_TRY(layout_source(ctx, sc, s, d_xyz, d_cov, d_nrm, box));
+    drop.armed = false;
     s->magic = kSrcMagic;
     *out = s;
     return VG_OK;
 }
 
 extern "C" vg_status vg_create_source(vg_context* ctx, const double* xyz, const double* cov, const double* normals,
-                                      int64_t n, vg_source** out) {
+                                      int64_t n, vg_source** out) try {
     g_err.clear();
     const TimelineRange range_("vg_create_source");
     if (!ctx_ok(ctx)) return state_err("invalid context");
@@ -597,9 +599,9 @@ extern "C" vg_status vg_create_source(vg_context* ctx, const double* xyz, const 
     double box[6], *d_xyz = nullptr, *d_cov = nullptr, *d_nrm = nullptr;
     VG_TRY(upload_cloud(ctx, sc, xyz, cov, normals, n, &d_xyz, &d_cov, &d_nrm, box));
     return make_source(ctx, sc, d_xyz, d_cov, d_nrm, normals != nullptr, n, xyz, box, out);
-}
+} VG_NO_THROW
 
-extern "C" vg_status vg_source_set_points_async(vg_source* src, const void* d_xyz, int32_t dtype) {
+extern "C" vg_status vg_source_set_points_async(vg_source* src, const void* d_xyz, int32_t dtype) try {
     g_err.clear();
     const TimelineRange range_("vg_source_set_points_async");
     if (!src_ok(src)) return state_err("invalid source");
@@ -607,9 +609,9 @@ extern "C" vg_status vg_source_set_points_async(vg_source* src, const void* d_xy
     if (src->n > 0 && d_xyz == nullptr) return invalid("d_xyz is NULL");
     VG_HIP(hipSetDevice(src->ctx->device));
     return set_points(src->ctx, src->self, 1, src->n_chunks, d_xyz, dtype);
-}
+} VG_NO_THROW
 
-extern "C" vg_status vg_source_destroy(vg_source* src) {
+extern "C" vg_status vg_source_destroy(vg_source* src) try {
     g_err.clear();
     if (!src_ok(src)) return state_err("invalid source");
     if (src->users > 0) return state_err("source is used by a live batch");
@@ -619,7 +621,7 @@ extern "C" vg_status vg_source_destroy(vg_source* src) {
     src->magic = 0;
     delete src;
     return VG_OK;
-}
+} VG_NO_THROW
 
 // ============================================================================ preprocessed clouds
 
@@ -627,7 +629,7 @@ static constexpr uint32_t kCloudMagic = 0xC10D0001u;
 static bool cloud_ok(const vg_cloud* c) { return c != nullptr && c->magic == kCloudMagic; }
 
 extern "C" vg_status vg_preprocess(vg_context* ctx, const double* xyz, int64_t n, double r, int32_t k,
-                                   const double* sensor, vg_cloud** out) {
+                                   const double* sensor, vg_cloud** out) try {
     g_err.clear();
     const TimelineRange range_("vg_preprocess");
     if (!ctx_ok(ctx)) return state_err("invalid context");
@@ -646,28 +648,28 @@ extern "C" vg_status vg_preprocess(vg_context* ctx, const double* xyz, int64_t n
     auto* c = new vg_cloud();
     c->ctx = ctx;
     c->pool = ctx->pool;
-    const vg_status st = preprocess_frame(ctx, sc, d_xyz, n, box, r, k, sensor, c);
-    if (st != VG_OK) {
+    AtExit drop([&] {
         (void)hipStreamSynchronize(ctx->stream);
         free_cloud(c);
         delete c;
-        return st;
-    }
+    });
+    VG_TRY(preprocess_frame(ctx, sc, d_xyz, n, box, r, k, sensor, c));
+    drop.armed = false;
     c->magic = kCloudMagic;
     *out = c;
     return VG_OK;
-}
+} VG_NO_THROW
 
-extern "C" vg_status vg_cloud_info(const vg_cloud* cloud, int64_t* n_points, int32_t* k) {
+extern "C" vg_status vg_cloud_info(const vg_cloud* cloud, int64_t* n_points, int32_t* k) try {
     g_err.clear();
     if (!cloud_ok(cloud)) return state_err("invalid cloud");
     if (n_points) *n_points = cloud->m;
     if (k) *k = cloud->k;
     return VG_OK;
-}
+} VG_NO_THROW
 
 extern "C" vg_status vg_cloud_export(const vg_cloud* cloud, double* xyz, double* cov, double* cov_raw,
-                                     double* normals, int64_t* counts, int32_t* nbr, double* nbr_d2) {
+                                     double* normals, int64_t* counts, int32_t* nbr, double* nbr_d2) try {
     g_err.clear();
     if (!cloud_ok(cloud)) return state_err("invalid cloud");
     VG_HIP(hipSetDevice(cloud->ctx->device));
@@ -689,9 +691,9 @@ extern "C" vg_status vg_cloud_export(const vg_cloud* cloud, double* xyz, double*
     if (counts)
         for (int64_t i = 0; i < m; ++i) counts[i] = c32[i];
     return VG_OK;
-}
+} VG_NO_THROW
 
-extern "C" vg_status vg_create_source_from_cloud(vg_context* ctx, const vg_cloud* cloud, vg_source** out) {
+extern "C" vg_status vg_create_source_from_cloud(vg_context* ctx, const vg_cloud* cloud, vg_source** out) try {
     g_err.clear();
     const TimelineRange range_("vg_create_source_from_cloud");
     if (!ctx_ok(ctx)) return state_err("invalid context");
@@ -703,10 +705,10 @@ extern "C" vg_status vg_create_source_from_cloud(vg_context* ctx, const vg_cloud
     if (cloud->m >= (int64_t)1 << 27) return invalid("a source holds fewer than 2^27 points");
     Scratch sc(ctx);
     return make_source(ctx, sc, cloud->xyz, cloud->cov, cloud->nrm, true, cloud->m, cloud->first, cloud->box, out);
-}
+} VG_NO_THROW
 
 extern "C" vg_status vg_build_voxelmap_from_cloud(vg_context* ctx, const vg_cloud* cloud, const double* resolutions,
-                                                  int32_t L, vg_voxelmap** out) {
+                                                  int32_t L, vg_voxelmap** out) try {
     g_err.clear();
     const TimelineRange range_("vg_build_voxelmap_from_cloud");
     if (!ctx_ok(ctx)) return state_err("invalid context");
@@ -718,9 +720,9 @@ extern "C" vg_status vg_build_voxelmap_from_cloud(vg_context* ctx, const vg_clou
     VG_HIP(hipSetDevice(ctx->device));
     Scratch sc(ctx);
     return make_voxelmap(ctx, sc, cloud->xyz, cloud->cov, cloud->m, resolutions, L, cloud->first, cloud->box, out);
-}
+} VG_NO_THROW
 
-extern "C" vg_status vg_cloud_destroy(vg_cloud* cloud) {
+extern "C" vg_status vg_cloud_destroy(vg_cloud* cloud) try {
     g_err.clear();
     if (!cloud_ok(cloud)) return state_err("invalid cloud");
     (void)hipSetDevice(cloud->ctx->device);
@@ -729,7 +731,7 @@ extern "C" vg_status vg_cloud_destroy(vg_cloud* cloud) {
     cloud->magic = 0;
     delete cloud;
     return VG_OK;
-}
+} VG_NO_THROW
 
 // ============================================================================ batches
 
@@ -896,13 +898,7 @@ vg_status set_shape(vg_batch* b, int block, int tile_points, int blocks_per_cu, 
     std::vector<Tile> tiles = b->h_tiles, units = b->h_units;
     std::vector<int32_t> tile_first = b->h_tile_first, unit_first = b->h_unit_first;
     const int was[4] = {b->block, b->tile_points, b->blocks_per_cu, b->tile_order};
-    b->block = block;
-    b->tile_points = tile_points;
-    b->blocks_per_cu = blocks_per_cu;
-    b->tile_order = tile_order;
-    build_tiles(b);
-    const vg_status rc = upload_schedule(b);
-    if (rc != VG_OK) {
+    AtExit restore([&] {
         b->h_tiles.swap(tiles);
         b->h_units.swap(units);
         b->h_tile_first.swap(tile_first);
@@ -911,8 +907,15 @@ vg_status set_shape(vg_batch* b, int block, int tile_points, int blocks_per_cu, 
         b->tile_points = was[1];
         b->blocks_per_cu = was[2];
         b->tile_order = was[3];
-    }
-    return rc;
+    });
+    b->block = block;
+    b->tile_points = tile_points;
+    b->blocks_per_cu = blocks_per_cu;
+    b->tile_order = tile_order;
+    build_tiles(b);
+    VG_TRY(upload_schedule(b));
+    restore.armed = false;
+    return VG_OK;
 }
 
 // A batch's device memory is one block and its pinned memory another: an allocation
@@ -1128,7 +1131,7 @@ void free_batch(vg_batch* b) {
 
 extern "C" vg_status vg_create_factor_batch(vg_context* ctx, int64_t F, vg_source* const* src,
                                             vg_voxelmap* const* tgt, const double* target_viewpoints,
-                                            const vg_batch_options* opts, vg_batch** out) {
+                                            const vg_batch_options* opts, vg_batch** out) try {
     g_err.clear();
     const TimelineRange range_("vg_create_factor_batch");
     if (!ctx_ok(ctx)) return state_err("invalid context");
@@ -1173,6 +1176,12 @@ extern "C" vg_status vg_create_factor_batch(vg_context* ctx, int64_t F, vg_sourc
     auto* b = new vg_batch();
     b->ctx = ctx;
     b->pool = ctx->pool;
+    AtExit drop([&] {
+        (void)hipStreamSynchronize(ctx->stream);
+        free_batch(b);
+        free((void*)b->opt.tune_cache);
+        delete b;
+    });
     b->F = F;
     b->L = L;
     b->opt = o;
@@ -1247,13 +1256,8 @@ extern "C" vg_status vg_create_factor_batch(vg_context* ctx, int64_t F, vg_sourc
         }
     }
     build_tiles(b);
-    const vg_status st = alloc_batch(b, points);
-    if (st != VG_OK) {
-        free_batch(b);
-        if (b->opt.tune_cache) free((void*)b->opt.tune_cache);
-        delete b;
-        return st;
-    }
+    VG_TRY(alloc_batch(b, points));
+    drop.armed = false;
     for (int64_t f = 0; f < F; ++f) {
         src[f]->users += 1;
         tgt[f]->users += 1;
@@ -1261,10 +1265,10 @@ extern "C" vg_status vg_create_factor_batch(vg_context* ctx, int64_t F, vg_sourc
     b->magic = kBatMagic;
     *out = b;
     return VG_OK;
-}
+} VG_NO_THROW
 
 extern "C" vg_status vg_batch_info(const vg_batch* b, int64_t* total_points, int64_t* n_tiles, int32_t* block_threads,
-                                   int32_t* tile_points, int32_t* grid_blocks, int32_t* tile_order) {
+                                   int32_t* tile_points, int32_t* grid_blocks, int32_t* tile_order) try {
     g_err.clear();
     if (!bat_ok(b)) return state_err("invalid batch");
     if (total_points) *total_points = b->total_points;
@@ -1274,9 +1278,9 @@ extern "C" vg_status vg_batch_info(const vg_batch* b, int64_t* total_points, int
     if (grid_blocks) *grid_blocks = kParts * (int32_t)((b->h_units.size() + kParts - 1) / kParts);
     if (tile_order) *tile_order = b->tile_order;
     return VG_OK;
-}
+} VG_NO_THROW
 
-extern "C" vg_status vg_batch_destroy(vg_batch* b) {
+extern "C" vg_status vg_batch_destroy(vg_batch* b) try {
     g_err.clear();
     if (!bat_ok(b)) return state_err("invalid batch");
     (void)hipSetDevice(b->ctx->device);
@@ -1290,10 +1294,10 @@ extern "C" vg_status vg_batch_destroy(vg_batch* b) {
     b->magic = 0;
     delete b;
     return VG_OK;
-}
+} VG_NO_THROW
 
 extern "C" vg_status vg_linearize(vg_batch* b, const double* poses, double* e, double* H, double* bv,
-                                  int64_t* inliers) {
+                                  int64_t* inliers) try {
     g_err.clear();
     const TimelineRange range_("vg_linearize");
     if (!bat_ok(b)) return state_err("invalid batch");
@@ -1310,9 +1314,9 @@ extern "C" vg_status vg_linearize(vg_batch* b, const double* poses, double* e, d
     }
     if (inliers) std::memcpy(inliers, b->h_inliers, sizeof(int64_t) * b->L * b->F);
     return VG_OK;
-}
+} VG_NO_THROW
 
-extern "C" vg_status vg_evaluate(vg_batch* b, const double* poses, double* e) {
+extern "C" vg_status vg_evaluate(vg_batch* b, const double* poses, double* e) try {
     g_err.clear();
     const TimelineRange range_("vg_evaluate");
     if (!bat_ok(b)) return state_err("invalid batch");
@@ -1324,9 +1328,9 @@ extern "C" vg_status vg_evaluate(vg_batch* b, const double* poses, double* e) {
     VG_TRY(finish_host(b, b->d_e, (size_t)b->F));
     std::memcpy(e, b->h_out, sizeof(double) * b->F);
     return VG_OK;
-}
+} VG_NO_THROW
 
-extern "C" vg_status vg_overlap(vg_batch* b, const double* poses, double* overlap) {
+extern "C" vg_status vg_overlap(vg_batch* b, const double* poses, double* overlap) try {
     g_err.clear();
     const TimelineRange range_("vg_overlap");
     if (!bat_ok(b)) return state_err("invalid batch");
@@ -1339,18 +1343,18 @@ extern "C" vg_status vg_overlap(vg_batch* b, const double* poses, double* overla
     VG_TRY(finish_host(b, b->d_out, (size_t)b->L * b->F));
     std::memcpy(overlap, b->h_out, sizeof(double) * b->L * b->F);
     return VG_OK;
-}
+} VG_NO_THROW
 
-extern "C" vg_status vg_linearize_async(vg_batch* b, const double* d_poses, double* d_out, int64_t* d_inliers) {
+extern "C" vg_status vg_linearize_async(vg_batch* b, const double* d_poses, double* d_out, int64_t* d_inliers) try {
     g_err.clear();
     const TimelineRange range_("vg_linearize_async");
     if (!bat_ok(b)) return state_err("invalid batch");
     if (d_poses == nullptr || d_out == nullptr) return invalid("d_poses or d_out is NULL");
     VG_HIP(hipSetDevice(b->ctx->device));
     return run_linearize_device(b, d_poses, d_out, d_inliers);
-}
+} VG_NO_THROW
 
-extern "C" vg_status vg_linearize_noalloc(vg_batch* b, const double* d_poses, double* d_out, int64_t* d_inliers) {
+extern "C" vg_status vg_linearize_noalloc(vg_batch* b, const double* d_poses, double* d_out, int64_t* d_inliers) try {
     g_err.clear();
     const TimelineRange range_("vg_linearize_noalloc");
     if (!bat_ok(b)) return state_err("invalid batch");
@@ -1379,19 +1383,19 @@ extern "C" vg_status vg_linearize_noalloc(vg_batch* b, const double* d_poses, do
     unsigned char* base = static_cast<unsigned char*>(b->ctx->scratch);
     const Workspace ws{reinterpret_cast<double*>(base + off_rows), reinterpret_cast<float*>(base + off_posef), nullptr};
     return run_linearize_device(b, ws, d_poses, d_out, d_inliers);
-}
+} VG_NO_THROW
 
-extern "C" vg_status vg_evaluate_async(vg_batch* b, const double* d_poses, double* d_e) {
+extern "C" vg_status vg_evaluate_async(vg_batch* b, const double* d_poses, double* d_e) try {
     g_err.clear();
     const TimelineRange range_("vg_evaluate_async");
     if (!bat_ok(b)) return state_err("invalid batch");
     if (d_poses == nullptr || d_e == nullptr) return invalid("d_poses or d_e is NULL");
     VG_HIP(hipSetDevice(b->ctx->device));
     return run_evaluate_device(b, d_poses, d_e);
-}
+} VG_NO_THROW
 
 extern "C" vg_status vg_backward_async(vg_batch* b, const double* d_poses, const double* d_grad_e, const double* d_jr,
-                                       double* d_grad_xi, void* d_grad_points, int32_t points_dtype) {
+                                       double* d_grad_xi, void* d_grad_points, int32_t points_dtype) try {
     g_err.clear();
     const TimelineRange range_("vg_backward_async");
     if (!bat_ok(b)) return state_err("invalid batch");
@@ -1426,9 +1430,9 @@ extern "C" vg_status vg_backward_async(vg_batch* b, const double* d_poses, const
     VG_TRY(launch_tiles(b, ws, kBwd, d_poses, d_grad_e, d_grad_points, points_dtype, 0, b->F));
     VG_TRY(launch_grad_combine(b, d_grad_points, points_dtype));
     return launch_reduce(b, ws, kBwd, d_poses, 0, (int32_t)b->F, nullptr, nullptr, d_grad_e, d_jr, d_grad_xi);
-}
+} VG_NO_THROW
 
-extern "C" vg_status vg_batch_set_points_async(vg_batch* b, const void* d_points, int32_t dtype) {
+extern "C" vg_status vg_batch_set_points_async(vg_batch* b, const void* d_points, int32_t dtype) try {
     g_err.clear();
     const TimelineRange range_("vg_batch_set_points_async");
     if (!bat_ok(b)) return state_err("invalid batch");
@@ -1436,10 +1440,10 @@ extern "C" vg_status vg_batch_set_points_async(vg_batch* b, const void* d_points
     if (b->grad_rows > 0 && d_points == nullptr) return invalid("d_points is NULL");
     VG_HIP(hipSetDevice(b->ctx->device));
     return set_points(b->ctx, b->d_points, b->n_sources, b->max_chunks, d_points, dtype);
-}
+} VG_NO_THROW
 
 extern "C" vg_status vg_se3_retract_async(vg_context* ctx, int64_t F, const double* d_T0, const double* d_xi,
-                                          double* d_T, double* d_jr) {
+                                          double* d_T, double* d_jr) try {
     g_err.clear();
     const TimelineRange range_("vg_se3_retract_async");
     if (!ctx_ok(ctx)) return state_err("invalid context");
@@ -1447,7 +1451,7 @@ extern "C" vg_status vg_se3_retract_async(vg_context* ctx, int64_t F, const doub
     if (F > 0 && (d_T0 == nullptr || d_xi == nullptr || d_T == nullptr)) return invalid("NULL pointer");
     VG_HIP(hipSetDevice(ctx->device));
     return launch_se3_retract(ctx, F, d_T0, d_xi, d_T, d_jr);
-}
+} VG_NO_THROW
 
 namespace {
 
@@ -1481,17 +1485,17 @@ vg_status lm_step(vg_batch* b, double* d_poses, double* d_lambda, double* d_e, i
 }  // namespace
 
 extern "C" vg_status vg_lm_step_async(vg_batch* b, double* d_poses, double* d_lambda, double* d_e,
-                                      int32_t* d_accepted) {
+                                      int32_t* d_accepted) try {
     g_err.clear();
     const TimelineRange range_("vg_lm_step_async");
     if (!bat_ok(b)) return state_err("invalid batch");
     if (d_poses == nullptr || d_lambda == nullptr) return invalid("d_poses or d_lambda is NULL");
     VG_HIP(hipSetDevice(b->ctx->device));
     return lm_step(b, d_poses, d_lambda, d_e, d_accepted, 1, 0, false);
-}
+} VG_NO_THROW
 
 extern "C" vg_status vg_lm_run(vg_batch* b, const double* poses_in, int32_t iters, double lambda0, double* poses_out,
-                               int32_t* accepted, double* e_hist) {
+                               int32_t* accepted, double* e_hist) try {
     g_err.clear();
     const TimelineRange range_("vg_lm_run");
     if (!bat_ok(b)) return state_err("invalid batch");
@@ -1521,6 +1525,11 @@ extern "C" vg_status vg_lm_run(vg_batch* b, const double* poses_in, int32_t iter
     } else {
         VG_TRY(dev_alloc(&hist, bytes));
     }
+    AtExit drop([&] {
+        if (direct) return;
+        (void)hipStreamSynchronize(st);
+        dfree(hist);
+    });
     double* eh = reinterpret_cast<double*>(hist);
     int32_t* acc = reinterpret_cast<int32_t*>(hist + items * sizeof(double));
     std::vector<unsigned char> copy;
@@ -1548,14 +1557,10 @@ extern "C" vg_status vg_lm_run(vg_batch* b, const double* poses_in, int32_t iter
         if (e_hist && iters > 0) std::memcpy(e_hist, h, sizeof(double) * items);
         if (accepted && iters > 0) std::memcpy(accepted, h + sizeof(double) * items, sizeof(int32_t) * items);
     } while (0);
-    if (!direct) {
-        if (rc != VG_OK) (void)hipStreamSynchronize(st);
-        dfree(hist);
-    }
     return rc;
-}
+} VG_NO_THROW
 
-extern "C" vg_status vg_batch_work(vg_batch* b, int64_t* walked_points, int64_t* walked_chunks, int64_t* lookups) {
+extern "C" vg_status vg_batch_work(vg_batch* b, int64_t* walked_points, int64_t* walked_chunks, int64_t* lookups) try {
     g_err.clear();
     if (!bat_ok(b)) return state_err("invalid batch");
     VG_HIP(hipSetDevice(b->ctx->device));
@@ -1570,10 +1575,10 @@ extern "C" vg_status vg_batch_work(vg_batch* b, int64_t* walked_points, int64_t*
             for (int l = 0; l < b->L; ++l) lookups[(int64_t)b->L * f + l] = r[2 + l];
     }
     return VG_OK;
-}
+} VG_NO_THROW
 
 extern "C" vg_status vg_correspondences(vg_batch* b, const double* pose, int64_t factor, int64_t* keys,
-                                        int32_t* found) {
+                                        int32_t* found) try {
     g_err.clear();
     const TimelineRange range_("vg_correspondences");
     if (!bat_ok(b)) return state_err("invalid batch");
@@ -1607,7 +1612,7 @@ extern "C" vg_status vg_correspondences(vg_batch* b, const double* pose, int64_t
     dfree(d_keys);
     dfree(d_found);
     return rc;
-}
+} VG_NO_THROW
 
 namespace {
 
@@ -1647,7 +1652,7 @@ vg_status time_device(vg_batch* b, int reps, float* ms_tiles, float* ms_reduce) 
 
 }  // namespace
 
-extern "C" vg_status vg_batch_time_kernels(vg_batch* b, const double* poses, int32_t reps, float* ms) {
+extern "C" vg_status vg_batch_time_kernels(vg_batch* b, const double* poses, int32_t reps, float* ms) try {
     g_err.clear();
     if (!bat_ok(b)) return state_err("invalid batch");
     if (ms == nullptr) return invalid("ms is NULL");
@@ -1664,9 +1669,9 @@ extern "C" vg_status vg_batch_time_kernels(vg_batch* b, const double* poses, int
     const auto t1 = std::chrono::steady_clock::now();
     ms[2] = (float)(std::chrono::duration<double, std::milli>(t1 - t0).count() / reps);
     return VG_OK;
-}
+} VG_NO_THROW
 
-extern "C" vg_status vg_batch_tune(vg_batch* b, const double* poses, int32_t reps, int32_t* chosen) {
+extern "C" vg_status vg_batch_tune(vg_batch* b, const double* poses, int32_t reps, int32_t* chosen) try {
     g_err.clear();
     const TimelineRange range_("vg_batch_tune");
     if (!bat_ok(b)) return state_err("invalid batch");
@@ -1801,4 +1806,4 @@ extern "C" vg_status vg_batch_tune(vg_batch* b, const double* poses, int32_t rep
         }
     }
     return VG_OK;
-}
+} VG_NO_THROW

@@ -162,7 +162,7 @@ hipError_t up(T** d, const std::vector<T>& h) {
 }  // namespace
 
 extern "C" vg_status vg_create_graph(vg_context* ctx, int64_t N, int64_t F, const int64_t* node_i,
-                                     const int64_t* node_j, vg_graph** out) {
+                                     const int64_t* node_j, vg_graph** out) try {
     set_error("");
     if (!context_ok(ctx)) {
         set_error("invalid context");
@@ -186,6 +186,10 @@ extern "C" vg_status vg_create_graph(vg_context* ctx, int64_t N, int64_t F, cons
     }
     for (int64_t n = 0; n < N; ++n) blocks[{n, n}];   // every node has a diagonal block
     auto* g = new vg_graph();
+    AtExit drop([&] {
+        graph_free(g);
+        delete g;
+    });
     g->ctx = ctx;
     g->N = N;
     g->F = F;
@@ -206,17 +210,14 @@ extern "C" vg_status vg_create_graph(vg_context* ctx, int64_t N, int64_t F, cons
     if (e == hipSuccess) e = up(&g->d_blk_ptr, bptr);
     if (e == hipSuccess) e = up(&g->d_blk_item, bitem);
     if (e == hipSuccess) e = up(&g->d_blk_node, bnode);
-    if (e != hipSuccess) {
-        graph_free(g);
-        delete g;
-        return hip_fail(e, "graph upload");
-    }
+    if (e != hipSuccess) return hip_fail(e, "graph upload");
+    drop.armed = false;
     g->magic = kGraphMagic;
     *out = g;
     return VG_OK;
-}
+} VG_NO_THROW
 
-extern "C" vg_status vg_graph_structure(const vg_graph* g, int64_t* nnz_blocks, int64_t* row_ptr, int64_t* col_idx) {
+extern "C" vg_status vg_graph_structure(const vg_graph* g, int64_t* nnz_blocks, int64_t* row_ptr, int64_t* col_idx) try {
     set_error("");
     if (!graph_ok(g)) {
         set_error("invalid graph");
@@ -226,10 +227,10 @@ extern "C" vg_status vg_graph_structure(const vg_graph* g, int64_t* nnz_blocks, 
     if (row_ptr) std::copy(g->row_ptr.begin(), g->row_ptr.end(), row_ptr);
     if (col_idx) std::copy(g->col_idx.begin(), g->col_idx.end(), col_idx);
     return VG_OK;
-}
+} VG_NO_THROW
 
 extern "C" vg_status vg_graph_assemble_async(vg_graph* g, const double* d_poses, const double* d_lin,
-                                             double* d_values, double* d_rhs) {
+                                             double* d_values, double* d_rhs) try {
     const vg::TimelineRange range_("vg_graph_assemble_async");
     set_error("");
     if (!graph_ok(g)) {
@@ -249,9 +250,9 @@ extern "C" vg_status vg_graph_assemble_async(vg_graph* g, const double* d_poses,
                                                   d_rhs, g->nnzb);
     VG_HIP(hipGetLastError());
     return VG_OK;
-}
+} VG_NO_THROW
 
-extern "C" vg_status vg_graph_destroy(vg_graph* g) {
+extern "C" vg_status vg_graph_destroy(vg_graph* g) try {
     set_error("");
     if (!graph_ok(g)) {
         set_error("invalid graph");
@@ -263,4 +264,4 @@ extern "C" vg_status vg_graph_destroy(vg_graph* g) {
     g->magic = 0;
     delete g;
     return VG_OK;
-}
+} VG_NO_THROW

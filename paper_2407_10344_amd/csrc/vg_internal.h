@@ -347,6 +347,28 @@ vg_status hip_fail(hipError_t e, const char* what);
         if (_e != hipSuccess) return vg::hip_fail(_e, #call);\
     } while (0)
 
+// Ends every entry point of the ABI (a function-try-block): an exception, which is the
+// host's memory running out, becomes a status.  The message is short enough for the
+// string to hold it without allocating.
+vg_status out_of_host_memory();
+#define VG_NO_THROW                         \
+    catch (...) {                           \
+        return vg::out_of_host_memory();    \
+    }
+
+// Runs f at the end of its scope, also on exceptions, unless disarmed.
+template <typename F>
+struct AtExit {
+    F f;
+    bool armed = true;
+    explicit AtExit(F g) : f(g) {}
+    AtExit(const AtExit&) = delete;
+    AtExit& operator=(const AtExit&) = delete;
+    ~AtExit() {
+        if (armed) f();
+    }
+};
+
 // ---------------------------------------------------------------- scratch
 
 constexpr size_t kKeepWorkspace = (size_t)1 << 30;   // a larger call's temporaries are freed with it

@@ -27,13 +27,15 @@ def build(folder):
 
 
 def run(folder, module, function):
-    """Output lines of ``module.function(Host())`` in a process of its own."""
+    """``module.function(Host())`` in a process of its own."""
     if not os.path.exists(LIB):
         from paper_2407_10344_amd import build as b
         b.build()
     code = ("import sys; sys.path[:0] = [%r, %r]; import host_runtime, %s as m; m.%s(host_runtime.Host(%r)); print('done')"
             % (HERE, ROOT, module, function, build(str(folder))))
-    r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=300)
+    # large allocations of the host are mapped, and unmapped when they are freed
+    env = dict(os.environ, MALLOC_MMAP_THRESHOLD_="131072")
+    r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=300, env=env)
     assert r.returncode == 0 and r.stdout.strip().endswith("done"), (r.returncode, r.stdout[-3000:], r.stderr[-6000:])
 
 

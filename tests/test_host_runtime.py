@@ -384,3 +384,63 @@ def small_levels_are_ordered_on_the_host(h):
 
 def test_small_levels_are_ordered_on_the_host(run):
     run("small_levels_are_ordered_on_the_host")
+
+
+def host_memory_runs_out(h):
+    """Calls that run out of host memory return VG_ERR_OOM, hold nothing afterwards and leave
+    their handles usable; no exception leaves the library."""
+    import resource
+
+    s, m = h.source(1000), h.map(1000)
+    F, n = 60_000, 60_000
+    src, tgt = (C.c_void_p * F)(*[s.value] * F), (C.c_void_p * F)(*[m.value] * F)
+    o = host_runtime.Options()
+    nodes = [(C.c_int64 * n)(*range(k, n + k)) for k in (0, 1)]
+    keep = h.batch([s] * 4000, [s_ for s_ in [m] * 4000], tile_points=64)
+    poses = h.poses(4000)
+    iters = 200
+    out, acc, eh = (C.c_double * (12 * 4000))(), (C.c_int32 * (iters * 4000))(), (C.c_double * (iters * 4000))()
+    h.set("voxels", 400_000)
+    big = h.map(600_000)
+    voxels = C.c_int64(400_000)
+    rows = [(C.c_int64 * (3 * 400_000))(), (C.c_double * (3 * 400_000))(), (C.c_double * (6 * 400_000))(),
+            (C.c_int64 * 400_000)()]
+    made = C.c_void_p()
+    # (in this order: the small pieces of a graph's lists stay with the host's allocator)
+    calls = {"lm": ("vg_lm_run", keep, poses, iters, C.c_double(1e-4), out, acc, eh),
+             "tuner": ("vg_batch_tune", keep, poses, 1, None),
+             "export": ("vg_voxelmap_export", big, 0, C.byref(voxels), *rows),
+             "batch": ("vg_create_factor_batch", h.ctx, F, src, tgt, None, C.byref(o), C.byref(made)),
+             "graph": ("vg_create_graph", h.ctx, n + 1, n, *nodes, C.byref(made))}
+    undo = {"batch": "vg_batch_destroy", "graph": "vg_graph_destroy"}
+    soft, hard = resource.getrlimit(resource.RLIMIT_AS)
+    refused = dict.fromkeys(calls, 0)
+    for name, call in calls.items():
+        for _ in range(2):   # shapes and kept blocks as after a call
+            assert h.call(*call) == 0
+            if name in undo:
+                h.check(undo[name], made)
+        for step in range(24):
+            base, shape = h.fake.fake_used(), h.info(keep)
+            with open("/proc/self/statm") as f:
+                now = int(f.read().split()[0]) * 4096
+            resource.setrlimit(resource.RLIMIT_AS, (now + (step * step << 18), hard))
+            rc = h.call(*call)
+            resource.setrlimit(resource.RLIMIT_AS, (soft, hard))
+            assert rc in (0, h.OOM), (name, step, rc)
+            if rc == 0 and name in undo:
+                h.check(undo[name], made)
+            if rc != 0:
+                refused[name] += 1
+                assert h.lib.vg_last_error()
+            if name != "tuner":
+                assert h.fake.fake_used() == base, (name, step, base, h.fake.fake_used())
+            d = C.c_void_p(1 << 45)
+            h.check("vg_linearize_async", keep, d, d, None)
+            assert h.info(keep)["tile"] == shape["tile"] or name == "tuner"
+    assert all(refused.values()), refused
+    assert h.fake.fake_bad_frees() == 0
+
+
+def test_host_memory_running_out(run):
+    run("host_memory_runs_out")
